@@ -205,7 +205,8 @@ MlpWs mlp_layout(const stl_problem_t *up, const Dims &d1, const Dims &d2, int va
     off += align256((size_t)d2.r * d2.Mp() * d2.N * d2.es);
     w.one_pass = variant == STL_FLAG_AUTO && stl::recode_eligible(up->dtype, d1.N);
     w.hidden = off;
-    if (!w.one_pass) off += align256((size_t)up->m * up->n * d1.es);
+    // the declared size holds the hidden activation for every n1 / 4 that is no multiple of 8, as the header's rule for H does
+    if (!w.one_pass || d1.N % 8) off += align256((size_t)up->m * up->n * d1.es);
     w.total = off;
     return w;
 }
@@ -694,7 +695,7 @@ stl_status_t stl_recode(const stl_problem_t *up, const stl_problem_t *down, cons
     if (any_misaligned(Yhat1, D1, E_X2, Xhat2, H)) return fail(STL_ERR_INVALID_ARG, "stl_recode: pointer not 16-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     const bool gelu = (flags & STL_FLAG_GELU) != 0;
-    if (variant == STL_FLAG_AUTO && stl::recode_eligible(up->dtype, d1.N)) {
+    if (variant == STL_FLAG_AUTO && stl::recode_eligible(up->dtype, d1.N) && (H || d1.N % 8 == 0)) {
         STL_HIP(stl::launch_recode(Yhat1, D1, E_X2, Xhat2, d1.M, d1.N, d1.r, d2.r, gelu, PG, s), "recode");
         return STL_OK;
     }

@@ -41,6 +41,57 @@ __device__ __forceinline__ void store16(void *p, u32x4_t v)
     }
 }
 
+// Eight bf16 of a plane row, n of them left in the row from p on (n <= 0: none).  ANY = false: rows are whole 16-byte chunks
+// (column count a multiple of 8, n then too).  ANY = true: any column count of at least 8, so that a row starts at any
+// even address and its last chunk may be incomplete; gfx950 loads and stores 16 bytes at any address, and such a chunk is
+// read as the eight elements that end with the row, shifted down (zeros move in), and written in pieces of 4, 2 and 1.
+typedef u32x4_t u32x4_any_t __attribute__((aligned(2)));
+typedef u32x2_t u32x2_any_t __attribute__((aligned(2)));
+typedef uint32_t u32_any_t __attribute__((aligned(2)));
+
+template <bool ANY>
+__device__ __forceinline__ u32x4_t load8(const bf16_t *p, int n)
+{
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if constexpr (!ANY) {
+        if (n > 0) v = *reinterpret_cast<const u32x4_t *>(p);
+    } else {
+        const int miss = n < 8 ? 8 - n : 0;                  // elements of the chunk beyond the row's end
+        if (n > 0) v = *reinterpret_cast<const u32x4_any_t *>(p - miss);
+        if (n > 0 && miss) {
+            uint64_t lo = v[0] | ((uint64_t)v[1] << 32), hi = v[2] | ((uint64_t)v[3] << 32);
+            const int sh = 16 * miss;                        // 16 ... 112
+            lo = sh < 64 ? (lo >> (sh & 63)) | (hi << ((64 - sh) & 63)) : hi >> (sh & 63);
+            hi = sh < 64 ? hi >> (sh & 63) : 0;
+            v = u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+        }
+    }
+    return v;
+}
+
+template <bool ANY>
+__device__ __forceinline__ void store8(bf16_t *p, int n, u32x4_t v)
+{
+    if constexpr (!ANY) {
+        if (n > 0) *reinterpret_cast<u32x4_t *>(p) = v;
+    } else if (n >= 8) {
+        *reinterpret_cast<u32x4_any_t *>(p) = v;
+    } else if (n > 0) {
+        if (n & 4) {
+            *reinterpret_cast<u32x2_any_t *>(p) = u32x2_t{v[0], v[1]};
+            p += 4;
+            v[0] = v[2];
+            v[1] = v[3];
+        }
+        if (n & 2) {
+            *reinterpret_cast<u32_any_t *>(p) = v[0];
+            p += 2;
+            v[0] = v[1];
+        }
+        if (n & 1) *p = (bf16_t)(v[0] & 0xffffu);
+    }
+}
+
 // storage-type traits: load as fp32, store from fp32
 template <typename T> struct Elem;
 template <> struct Elem<float> {

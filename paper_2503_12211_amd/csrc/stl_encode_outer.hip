@@ -24,7 +24,8 @@
 namespace stl {
 
 // OUTER = false: the encode alone (Qp, part unused) -- the same whole-line stores through the slab, used for plain encodes
-template <int KC, bool OUTER>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
+// ANY: column counts that are no multiple of 8 (see load8)
+template <int KC, bool OUTER, bool ANY>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
 __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E,
                                                              bf16_t *__restrict__ P, const bf16_t *__restrict__ Qp,
                                                              float *__restrict__ part, int R, int Cc, int r, int chunks, int pg,
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
 #pragma unroll
     for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // wavefront w of block b takes items 4b + w, 4b + w + 4 * gridDim.x, ...
-    encode_items<KC, OUTER>(A, E, P, Qp, R, Cc, r, chunks, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
+    encode_items<KC, OUTER, false, 1, ANY>(A, E, P, Qp, R, Cc, r, chunks, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
                             (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], dacc, lane);
 
     if (!OUTER) return;
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
             ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
 }
 
-bool encode_outer_eligible(int dtype, int Cc) { return dtype == 1 && (Cc % 8) == 0; }
+bool encode_outer_eligible(int dtype, int Cc) { return dtype == 1 && Cc >= 8; }
 
 int encode_outer_blocks(int R, int Cc)
 {
@@ -73,18 +74,19 @@ hipError_t launch_encode_outer(const void *A, const void *E, void *P, const void
     if (R <= 0) return hipErrorInvalidValue;
     const int chunks = (Cc + 63) / 64;
     const int nb = encode_outer_blocks(R, Cc);
-    if (r <= 32)
-        hipLaunchKernelGGL((encode_outer16_kernel<1, true>), dim3(nb), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E,
-                           (bf16_t *)P, (const bf16_t *)Qp, part, R, Cc, r, chunks, pg, rm);
-    else
-        hipLaunchKernelGGL((encode_outer16_kernel<2, true>), dim3(nb), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E,
-                           (bf16_t *)P, (const bf16_t *)Qp, part, R, Cc, r, chunks, pg, rm);
+    const dim3 grid(nb), block(256);
+    const bf16_t *a = (const bf16_t *)A, *en = (const bf16_t *)E, *q = (const bf16_t *)Qp;
+    bf16_t *out = (bf16_t *)P;
+    const bool any = Cc % 8 != 0;
+    auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, true, true> : encode_outer16_kernel<1, true, false>)
+                        : (any ? encode_outer16_kernel<2, true, true> : encode_outer16_kernel<2, true, false>);
+    hipLaunchKernelGGL(kern, grid, block, 0, s, a, en, out, q, part, R, Cc, r, chunks, pg, rm);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !final_sum) return e;
     return launch_outer_final(part, G, nb, r * 16, accumulate, s);
 }
 
-// the encode alone through the same kernel (bf16, Cc % 8 == 0): grid-stride over (tile row, 64-tile chunk) items
+// the encode alone through the same kernel (bf16, Cc >= 8): grid-stride over (tile row, 64-tile chunk) items
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm)
 {
     if (pg <= 0) pg = R;
@@ -94,12 +96,11 @@ hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int
     const long items = (long)R * chunks;
     long blocks = (items + 3) / 4;
     if (blocks > 8192) blocks = 8192;
-    if (r <= 32)
-        hipLaunchKernelGGL((encode_outer16_kernel<1, false>), dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)A,
-                           (const bf16_t *)E, (bf16_t *)P, (const bf16_t *)nullptr, (float *)nullptr, R, Cc, r, chunks, pg, rm);
-    else
-        hipLaunchKernelGGL((encode_outer16_kernel<2, false>), dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)A,
-                           (const bf16_t *)E, (bf16_t *)P, (const bf16_t *)nullptr, (float *)nullptr, R, Cc, r, chunks, pg, rm);
+    const bool any = Cc % 8 != 0;
+    auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, false, true> : encode_outer16_kernel<1, false, false>)
+                        : (any ? encode_outer16_kernel<2, false, true> : encode_outer16_kernel<2, false, false>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E, (bf16_t *)P,
+                       (const bf16_t *)nullptr, (float *)nullptr, R, Cc, r, chunks, pg, rm);
     return hipGetLastError();
 }
 

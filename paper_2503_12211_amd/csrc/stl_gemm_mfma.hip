@@ -7,6 +7,10 @@
 // spread over all banks.  An operand whose contiguous memory dimension is not the contraction
 // index is transposed in registers on its way from HBM to LDS, so the MFMA loop is the same
 // for the forward product and the two backward products.
+// A contiguous dimension that is no multiple of 8 (250 tile columns of a 1000-class head, 50 tile rows of 200 tokens) leaves
+// rows at any even address: the ANY forms load and store them with unaligned 16-byte accesses.  Before, such shapes went
+// element by element through the fp32 kernel: attention scores 96 x (200 x 64 x 200), r = 32, 73 -> 23, 153 -> 23 and 182 -> 21 us
+// for the three products; 2048 x 768 x 1000, r = 32: 86 -> 15, 119 -> 13, 238 -> 28 us.
 // Wavefronts compute 32x32x16 MFMA fragments; accumulators stay in registers for the whole
 // contraction.  Block ids are remapped so that consecutive blocks of one plane land on the
 // same XCD (and share its L2).
@@ -36,7 +40,8 @@ struct Lay {
 
 // ---- HBM -> registers ------------------------------------------------------------------
 // Direct operand: stored [row][l], l contiguous (leading dimension ld elements).
-template <int ROWS, int NT>
+// ANY: contiguous dimensions that are no multiple of 8 (see load8; at least 8), here and below.
+template <int ROWS, int NT, bool ANY>
 struct DirectLoader {
     static constexpr int CH = ROWS * 8 / NT;  // 16-byte chunks per thread
     u32x4_t v[CH];
@@ -47,9 +52,7 @@ struct DirectLoader {
         for (int j = 0; j < CH; ++j) {
             const int id = tid + j * NT, row = id >> 3, c = id & 7;
             const int gr = row0 + row, gk = k0 + c * 8;
-            u32x4_t z = {0u, 0u, 0u, 0u};
-            if (gr < rows_total && gk < Kl) z = *reinterpret_cast<const u32x4_t *>(base + lay.off(gr) + gk);
-            v[j] = z;
+            v[j] = load8<ANY>(base + lay.off(gr) + gk, gr < rows_total ? Kl - gk : 0);
         }
     }
     __device__ __forceinline__ void store(char *lds, int tid) const
@@ -65,10 +68,11 @@ struct DirectLoader {
 // Transposing operand: stored [l][row], row contiguous (leading dimension ld elements).
 // A thread takes units of 4 l-values x 8 rows, swaps them in registers and writes 8 bytes
 // (4 consecutive k) to each of 8 LDS rows.
-template <int ROWS, int NT>
+template <int ROWS, int NT, bool ANY>
 struct TransLoader {
     static constexpr int RG = ROWS / 8;                // row groups
     static constexpr int UNITS = (BK / 4) * RG / NT;   // units per thread
+    static_assert(UNITS >= 1, "more threads than units");
     u32x4_t v[UNITS][4];
     __device__ __forceinline__ void load(const bf16_t *__restrict__ base, const Lay &lay, int row0, int rows_total, int k0,
                                          int Kl, int tid)
@@ -80,9 +84,7 @@ struct TransLoader {
 #pragma unroll
             for (int kk = 0; kk < 4; ++kk) {
                 const int gk = k0 + kq * 4 + kk;
-                u32x4_t z = {0u, 0u, 0u, 0u};
-                if (gr < rows_total && gk < Kl) z = *reinterpret_cast<const u32x4_t *>(base + lay.off(gk) + gr);
-                v[u][kk] = z;
+                v[u][kk] = load8<ANY>(base + lay.off(gk) + gr, gk < Kl ? rows_total - gr : 0);
             }
         }
     }
@@ -105,14 +107,14 @@ struct TransLoader {
     }
 };
 
-template <bool KMAJOR, int ROWS, int NT>
-struct LoaderSel { typedef DirectLoader<ROWS, NT> type; };
-template <int ROWS, int NT>
-struct LoaderSel<true, ROWS, NT> { typedef TransLoader<ROWS, NT> type; };
+template <bool KMAJOR, int ROWS, int NT, bool ANY>
+struct LoaderSel { typedef DirectLoader<ROWS, NT, ANY> type; };
+template <int ROWS, int NT, bool ANY>
+struct LoaderSel<true, ROWS, NT, ANY> { typedef TransLoader<ROWS, NT, ANY> type; };
 
 // ---- kernel ----------------------------------------------------------------------------
 // A_T: A stored [l][i];  B_T: B stored [l][j].  (false: stored [i][l] resp. [j][l].)
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(const bf16_t *__restrict__ A,
                                                                           const bf16_t *__restrict__ B,
                                                                           TO *__restrict__ Out, int Mi, int Nj, int Kl,
@@ -140,8 +142,8 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(const 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
 
-    typename LoaderSel<A_T, BM, NT>::type la;
-    typename LoaderSel<B_T, BN, NT>::type lb;
+    typename LoaderSel<A_T, BM, NT, ANY>::type la;
+    typename LoaderSel<B_T, BN, NT, ANY>::type lb;
 
     f32x16_t acc[FM][FN];
 #pragma unroll
@@ -169,6 +171,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(const 
         }
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
+            if (ANY && kt * BK + ks * 16 >= Kl) break;      // steps beyond the contraction hold zeros only
             bf16x8_t fa[FM], fb[FN];
 #pragma unroll
             for (int a = 0; a < FM; ++a)
@@ -219,7 +222,14 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(const 
             if (gi < Mi && gj < Nj) {
                 u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + rr * PITCH + (lane % LPR) * 16);
                 TO *o = Out + ldo.off(gi) + gj;
-                if (ACC) {
+                if (ANY && ES == 2) {
+                    store8<true>(reinterpret_cast<bf16_t *>(o), Nj - gj, w);
+                } else if (ANY && Nj % 4) {                 // fp32 rows at any multiple of 4 bytes
+                    const f32x4_t nw = __builtin_bit_cast(f32x4_t, w);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (gj + e < Nj) Elem<TO>::st(o + e, ACC ? Elem<TO>::ld(o + e) + nw[e] : nw[e]);
+                } else if (ACC) {
                     const f32x4_t old = *reinterpret_cast<const f32x4_t *>(o);
                     f32x4_t nw = __builtin_bit_cast(f32x4_t, w);
                     nw += old;
@@ -240,15 +250,14 @@ bool plane_gemm_mfma_eligible(const GemmDesc &g)
     // instantiated operand forms: forward [i][l]x[l][j], input gradient [i][l]x[j][l] (storage out),
     // weight gradient [l][i]x[l][j] (fp32 out, or storage out for a run-time encoded second operand)
     if (g.a_kmajor ? !g.b_kmajor : g.out_f32) return false;
-    // 16-byte global loads along each operand's contiguous dimension
-    if (g.Mi % 8 || g.Nj % 8 || g.Kl % 8) return false;
-    return true;
+    // 16-byte global loads along each operand's contiguous dimension, at any even address
+    return g.Mi >= 8 && g.Nj >= 8 && g.Kl >= 8;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
 static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, A_T, B_T, TO, ACC>;
+    auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, A_T, B_T, TO, ACC, ANY>;
     constexpr int smem = 2 * (BM + BN) * BK * 2;
     // once per instantiation (initialisation of a function-local static is thread-safe)
     static const hipError_t attr_err =
@@ -263,13 +272,30 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
     return hipGetLastError();
 }
 
+template <bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
+static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+{
+    if constexpr (!ANY) {
+        // large planes: 256 x 256 blocks, 8 wavefronts of 128 x 64; small ones: 128 x 128 blocks, 4 wavefronts of 64 x 64
+        if (g.Mi > 128 && g.Nj > 128) return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+        return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    }
+    // The largest block that still fills the chip (256 CUs): a bigger block moves fewer bytes per product, but these kernels
+    // prefetch a single stage, so idle CUs and short contractions cost more.  Forward form, us at 256 / 128 / 64:
+    //   M x K x N, r = 512 x 1024 x 1024, 32: 48 / 69 / 116 (256 blocks of 256);  256 x 1024 x 1024, 32: 44 / 38 / 63 (128, 512
+    //   blocks);  1024 x 192 x 250, 32: 21 / 17 / 26 (512 blocks of 128);  512 x 192 x 250, 32: 19 / 14 / 13 (256 blocks of
+    //   128);  128 x 192 x 250, 8: 17 / 13 / 10
+    auto blocks = [&](int b) { return (double)((g.Mi + b - 1) / b) * ((g.Nj + b - 1) / b) * g.batch * g.nb; };
+    if (g.Mi > 128 && g.Nj > 128 && blocks(256) >= 256) return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    if (g.Mi > 64 && g.Nj > 64 && blocks(128) >= 384) return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    return launch_cfg<64, 64, 1, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+}
+
 template <bool A_T, bool B_T, typename TO, bool ACC>
 static hipError_t launch_shape(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    // large planes: 256 x 256 blocks, 8 wavefronts of 128 x 64; small ones: 128 x 128 blocks, 4 wavefronts of 64 x 64
-    // (256x256 with 4 wavefronts of 128x128, 256x128 and 128x256 were measured and are not faster at any shape)
-    if (g.Mi > 128 && g.Nj > 128) return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC>(g, A, B, Out, s);
-    return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+    const bool any = g.Mi % 8 || g.Nj % 8 || g.Kl % 8;
+    return any ? launch_block<A_T, B_T, TO, ACC, true>(g, A, B, Out, s) : launch_block<A_T, B_T, TO, ACC, false>(g, A, B, Out, s);
 }
 
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const 
 
 bool plane_gemm_pipe_eligible(const GemmDesc &g)
 {
-    if (!plane_gemm_mfma_eligible(g)) return false;
+    if (!plane_gemm_mfma_eligible(g) || g.Mi % 8 || g.Nj % 8) return false;     // whole, aligned 16-byte chunks
     if (g.Kl % pipe::BKS) return false;
     // a stage's 32 stored rows of an [l][row] operand stay inside one group; so do the rows of an epilogue pass
     if (g.a_kmajor && g.a_rows_per_group() % pipe::BKS) return false;

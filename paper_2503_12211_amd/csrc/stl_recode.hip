@@ -19,7 +19,8 @@ namespace stl {
 
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 
-template <bool GELU, int KC>   // KC = number of 32-plane groups of the larger of the two ranks (1: <= 32, 2: <= 64)
+// ANY: column counts that are no multiple of 8 (see load8)
+template <bool GELU, int KC, bool ANY>   // KC = number of 32-plane groups of the larger of the two ranks (1: <= 32, 2: <= 64)
 __global__ __launch_bounds__(256) void recode_mfma_kernel(const bf16_t *__restrict__ P, const bf16_t *__restrict__ Dm,
                                                           const bf16_t *__restrict__ E2, bf16_t *__restrict__ Q, int R,
                                                           int Cc, int r1, int r2, int chunks, int pg)
@@ -75,9 +76,7 @@ __global__ __launch_bounds__(256) void recode_mfma_kernel(const bf16_t *__restri
 #pragma unroll
         for (int g8 = 0; g8 < KC * 4; ++g8) {
             const int pl = 8 * g8 + pr;
-            u32x4_t v = {0u, 0u, 0u, 0u};
-            if (Ii < R && pl < r1 && Jl < Cc) v = *reinterpret_cast<const u32x4_t *>(P + rowb + (size_t)pl * plane + Jl);
-            pre[g8] = v;
+            pre[g8] = load8<ANY>(P + rowb + (size_t)pl * plane + Jl, Ii < R && pl < r1 ? Cc - Jl : 0);
         }
     };
     fetch(In, ckn);
@@ -155,13 +154,20 @@ __global__ __launch_bounds__(256) void recode_mfma_kernel(const bf16_t *__restri
             const int pl = 8 * g8 + pr;
             if (pl < r2 && J0 + 8 * ch < Cc) {
                 const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swo(pl)) << 4));
-                *reinterpret_cast<u32x4_t *>(Q + rowb_out + (size_t)pl * plane + J0 + 8 * ch) = w;
+                store8<ANY>(Q + rowb_out + (size_t)pl * plane + J0 + 8 * ch, Cc - J0 - 8 * ch, w);
             }
         }
     }
 }
 
-bool recode_eligible(int dtype, int Cc) { return dtype == 1 && (Cc % 8) == 0; }
+bool recode_eligible(int dtype, int Cc) { return dtype == 1 && Cc >= 8; }
+
+template <bool ANY>
+static auto pick_recode(bool one_group, bool gelu)
+{
+    if (one_group) return gelu ? recode_mfma_kernel<true, 1, ANY> : recode_mfma_kernel<false, 1, ANY>;
+    return gelu ? recode_mfma_kernel<true, 2, ANY> : recode_mfma_kernel<false, 2, ANY>;
+}
 
 hipError_t launch_recode(const void *P, const void *Dm, const void *E2, void *Q, int R, int Cc, int r1, int r2, bool gelu,
                          int pg, hipStream_t s)
@@ -174,13 +180,8 @@ hipError_t launch_recode(const void *P, const void *Dm, const void *E2, void *Q,
     const dim3 grid((unsigned)blocks), block(256);
     const bf16_t *p = (const bf16_t *)P, *d = (const bf16_t *)Dm, *e = (const bf16_t *)E2;
     bf16_t *q = (bf16_t *)Q;
-    if (r1 <= 32 && r2 <= 32) {
-        if (gelu) hipLaunchKernelGGL((recode_mfma_kernel<true, 1>), grid, block, 0, s, p, d, e, q, R, Cc, r1, r2, chunks, pg);
-        else hipLaunchKernelGGL((recode_mfma_kernel<false, 1>), grid, block, 0, s, p, d, e, q, R, Cc, r1, r2, chunks, pg);
-    } else {
-        if (gelu) hipLaunchKernelGGL((recode_mfma_kernel<true, 2>), grid, block, 0, s, p, d, e, q, R, Cc, r1, r2, chunks, pg);
-        else hipLaunchKernelGGL((recode_mfma_kernel<false, 2>), grid, block, 0, s, p, d, e, q, R, Cc, r1, r2, chunks, pg);
-    }
+    auto kern = Cc % 8 ? pick_recode<true>(r1 <= 32 && r2 <= 32, gelu) : pick_recode<false>(r1 <= 32 && r2 <= 32, gelu);
+    hipLaunchKernelGGL(kern, grid, block, 0, s, p, d, e, q, R, Cc, r1, r2, chunks, pg);
     return hipGetLastError();
 }
 

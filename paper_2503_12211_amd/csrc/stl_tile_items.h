@@ -16,7 +16,10 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 // different numbers of items.
 // THROUGH: the plane stores are written through to memory (see store16).  DEPTH: items whose operands are in flight
 // at once (in registers) -- 1 where dozens of wavefronts per CU hide the latency, more where only eight run.
-template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1>
+// ANY: any column count of at least 8 (see load8); otherwise a multiple of 8.  Bound by HBM and, for small matrices, by the
+// launch; one pass over a row's planes whatever the width: with one thread per tile and a separate scalar sum, dYhat + dD of
+// 512 x 250 tiles, r = 32, took 10 + 285 us, now 8; dYhat + dD of 4800 x 50 tiles 13 + 577 us, now 14.
+template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false>
 __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E, bf16_t *__restrict__ P,
                                              const bf16_t *__restrict__ Qp, int R, int Cc, int r, int chunks, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane)
@@ -68,9 +71,7 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 #pragma unroll
             for (int g8 = 0; g8 < KC * 4; ++g8) {
                 const int pl = 8 * g8 + pr, tk = J0 + 8 * ch;
-                u32x4_t v = {0u, 0u, 0u, 0u};
-                if (Ii < R && pl < r && tk < Cc) v = *reinterpret_cast<const u32x4_t *>(Qp + rowb + (size_t)pl * plane + tk);
-                qa[d][g8] = v;
+                qa[d][g8] = load8<ANY>(Qp + rowb + (size_t)pl * plane + tk, Ii < R && pl < r ? Cc - tk : 0);
             }
         }
     };
@@ -157,7 +158,9 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
             const int pl = 8 * g8 + pr;
             if (pl < r && J0 + 8 * ch < Cc) {
                 const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4));
-                store16<THROUGH>(P + rowb_out + (size_t)pl * plane + J0 + 8 * ch, w);
+                bf16_t *o = P + rowb_out + (size_t)pl * plane + J0 + 8 * ch;
+                if constexpr (ANY) store8<true>(o, Cc - J0 - 8 * ch, w);
+                else store16<THROUGH>(o, w);
             }
         }
     }
@@ -166,7 +169,8 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 
 // The item loop of one wavefront, items as in encode_items.  slab: KC * 32 * 128 bytes of LDS private to the
 // wavefront; sT: 64 x 32 bytes (OUTER only); oacc accumulates the basis gradient (OUTER).  No workgroup barrier inside.
-template <bool GELU, int KC, bool OUTER, int DEPTH = 1>   // DEPTH as in encode_items
+// DECODE = false: the basis gradient alone (Dm and Cmat unused).
+template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true>   // DEPTH, ANY as in encode_items
 __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
                                              int R, int Cc, int r, int chunks, const bf16_t *__restrict__ V, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane)
@@ -181,7 +185,7 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
     // A fragments: lane (entry q = j, kq) holds D[32g + 8kq + e][q], e = 0..7
     bf16x8_t fa[KC];
 #pragma unroll
-    for (int g = 0; g < KC; ++g) {
+    for (int g = 0; g < (DECODE ? KC : 0); ++g) {
         uint32_t w[4];
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
@@ -212,9 +216,8 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
 #pragma unroll
         for (int g8 = 0; g8 < KC * 4; ++g8) {
             const int pl = 8 * g8 + pr;
-            u32x4_t v = {0u, 0u, 0u, 0u};       // planes >= r stay zero (they meet zero D entries, but must be finite)
-            if (Ii < R && pl < r && Jl < Cc) v = *reinterpret_cast<const u32x4_t *>(P + rowb + (size_t)pl * plane + Jl);
-            pre[d][g8] = v;
+            // planes >= r stay zero (they meet zero D entries, but must be finite)
+            pre[d][g8] = load8<ANY>(P + rowb + (size_t)pl * plane + Jl, Ii < R && pl < r ? Cc - Jl : 0);
         }
         if (OUTER) {
             const int Jt = cki * 64 + lane, nv = rm.valid(Ia);
@@ -280,7 +283,7 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
                 }
             }
         }
-        if (live) {
+        if (live && DECODE) {
             const int nv_out = rm.valid(I);
             const size_t r0_out = rm.row0(I);
 #pragma unroll

@@ -158,166 +158,6 @@ __global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restri
 }
 
 // ---------------------------------------------------------------------------------------
-// bf16 encode on the matrix cores.  The map "16 tile entries -> r planes" is a small dense
-// contraction (K = 16); on the vector ALUs it costs as many cycles as the HBM transfer, on
-// MFMA it is free and the kernel is bound by the stream through HBM alone.
-//   v_mfma_f32_32x32x16_bf16:  rows = planes (E, 32 x 16), columns = tiles (tile entries, 16 x 32).
-// A wavefront takes 128 consecutive tiles of one tile row: lane (j, h) loads rows 2h and 2h+1 of
-// tiles 4j..4j+3 (32 contiguous bytes each); MFMA u works on tiles 4j+u, so that afterwards a lane
-// holds 4 consecutive tiles of a plane and writes them with one 8-byte store.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void encode_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E,
-                                                          bf16_t *__restrict__ P, int R, int Cc, int r, int chunks, int pg,
-                                                          RowMap rm)
-{
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long item = (long)blockIdx.x * 4 + wave;          // (tile row, chunk of 128 tile columns)
-    if (item >= (long)R * chunks) return;
-    const int I = rm.tile_row((int)(item / chunks)), J0 = (int)(item % chunks) * 128;
-    const int nv = rm.valid(I);
-    const size_t r0 = rm.row0(I);
-    const int j = lane & 31, h = lane >> 5;
-    const size_t ld = (size_t)Cc * 4;
-    const int Jl = J0 + 4 * j;                               // first of this lane's 4 tiles
-
-    u32x4_t row[2][2];                                       // [row 2h / 2h+1][tiles (0,1) / (2,3)]
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            u32x4_t z = {0u, 0u, 0u, 0u};
-            if (Jl + 2 * c < Cc && 2 * h + a < nv)
-                z = *reinterpret_cast<const u32x4_t *>(A + (r0 + 2 * h + a) * ld + (size_t)(Jl + 2 * c) * 4);
-            row[a][c] = z;
-        }
-
-    const size_t plane = (size_t)pg * Cc, rowb = plane_row_base(I, pg, r, Cc);
-    for (int g = 0; g < r; g += 32) {
-        const int pl = g + j;
-        u32x4_t ev = {0u, 0u, 0u, 0u};
-        if (pl < r) ev = *reinterpret_cast<const u32x4_t *>(E + pl * 16 + 8 * h);
-        const bf16x8_t ea = __builtin_bit_cast(bf16x8_t, ev);
-        f32x16_t acc[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const u32x4_t bv = {row[0][u >> 1][2 * (u & 1)], row[0][u >> 1][2 * (u & 1) + 1],
-                                row[1][u >> 1][2 * (u & 1)], row[1][u >> 1][2 * (u & 1) + 1]};
-            f32x16_t zero;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) zero[v] = 0.f;
-            acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ea, __builtin_bit_cast(bf16x8_t, bv), zero, 0, 0, 0);
-        }
-        if (Jl < Cc) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int po = g + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (po < r) {
-                    u32x2_t w = {pack_bf16x2(acc[0][v], acc[1][v]), pack_bf16x2(acc[2][v], acc[3][v])};
-                    *reinterpret_cast<u32x2_t *>(P + rowb + (size_t)po * plane + Jl) = w;
-                }
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// bf16 basis gradients on the matrix cores:  G (r x 16) = P (r x T) . tileview(V) (T x 16),
-// contraction over all T = R*Cc tiles, v_mfma_f32_16x16x32_bf16 (rows = planes, columns = the 16
-// tile entries, K = 32 tiles).  P fragments come straight from HBM (8 consecutive tiles of a plane
-// = 16 bytes); V is read coalesced and turned into "entry x tile" form through LDS.
-// Stage 1 writes one partial per block in a fixed order; stage 2 adds them in block order.
-// ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void outer_mfma_kernel(const bf16_t *__restrict__ P, const bf16_t *__restrict__ V,
-                                                         float *__restrict__ part, int R, int Cc, int r,
-                                                         int tiles_per_block, int pg, RowMap rm)
-{
-    constexpr int PITCH = 64 + 8;                       // bf16 elements per LDS row (16-byte aligned rows)
-    __shared__ __align__(16) bf16_t sV[4][16][PITCH];
-    __shared__ float red[4][64 * 16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const long T = (long)R * Cc;
-    const long t0 = (long)blockIdx.x * tiles_per_block;
-    long t1 = t0 + tiles_per_block;
-    if (t1 > T) t1 = T;
-    const size_t ld = (size_t)Cc * 4;
-    const int q = lane & 15, kq = lane >> 4;
-    const int ngroups = (r + 15) >> 4;
-
-    f32x4_t acc[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) acc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // operands of one 256-tile step of the block: this wavefront's 64 tiles of V (4 rows x 8 bytes per lane) and the
-    // P fragments (8 consecutive tiles of a plane per lane).  The next step's operands are in flight while the
-    // current step runs on the matrix cores.
-    u32x2_t v[4];
-    u32x4_t pa[2][4];
-    auto fetch = [&](long base) {
-        const long tb = base + wave * 64;
-        const long tile = tb + lane;
-        if (tile < t1) {
-            const long idx = tile / Cc, J = tile - idx * Cc;
-            const int I = rm.tile_row((int)idx), nv = rm.valid(I);
-            const size_t r0 = rm.row0(I);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-                v[a] = a < nv ? *reinterpret_cast<const u32x2_t *>(V + (r0 + a) * ld + (size_t)J * 4) : u32x2_t{0u, 0u};
-        } else {
-#pragma unroll
-            for (int a = 0; a < 4; ++a) v[a] = u32x2_t{0u, 0u};
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const long tk = tb + 32 * s + 8 * kq;        // 8 consecutive tiles of one tile row (Cc % 8 == 0): all in or all out
-            const int Ik = (int)(tk / Cc);
-            const size_t off = tk < t1 ? plane_row_base(rm.tile_row(Ik), pg, r, Cc) + (size_t)(tk - (long)Ik * Cc) : 0;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int pl = 16 * g + q;
-                u32x4_t av = {0u, 0u, 0u, 0u};
-                if (g < ngroups && pl < r && tk < t1) av = *reinterpret_cast<const u32x4_t *>(P + off + (size_t)pl * pg * Cc);
-                pa[s][g] = av;
-            }
-        }
-    };
-
-    fetch(t0);
-    for (long base = t0; base < t1; base += 256) {       // uniform trip count over the block
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            sV[wave][4 * a + 0][lane] = (bf16_t)(v[a][0] & 0xffffu);
-            sV[wave][4 * a + 1][lane] = (bf16_t)(v[a][0] >> 16);
-            sV[wave][4 * a + 2][lane] = (bf16_t)(v[a][1] & 0xffffu);
-            sV[wave][4 * a + 3][lane] = (bf16_t)(v[a][1] >> 16);
-        }
-        u32x4_t pc[2][4];
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) pc[s][g] = pa[s][g];
-        // sV[wave] is private to the wavefront and a wavefront's LDS operations execute in order: no workgroup barrier
-        // (a barrier would also make the wavefront wait for the loads it is about to put in flight)
-        if (base + 256 < t1) fetch(base + 256);
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const bf16x8_t fb = *reinterpret_cast<const bf16x8_t *>(&sV[wave][q][32 * s + 8 * kq]);
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (g < ngroups)
-                    acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, pc[s][g]), fb, acc[g], 0, 0, 0);
-        }
-    }
-    // accumulator element e of group g: plane 16g + 4*(lane/16) + e, tile entry lane%16
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave][(16 * g + 4 * kq + e) * 16 + q] = acc[g][e];
-    __syncthreads();
-    for (int i = threadIdx.x; i < r * 16; i += 256)
-        part[(size_t)blockIdx.x * r * 16 + i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
-}
-
-// ---------------------------------------------------------------------------------------
 // bf16 decode on the matrix cores:  tile entries (16) x tiles = D^T (16 x r) . Yhat (r x tiles),
 // v_mfma_f32_16x16x32_bf16 with rows = tile entries, columns = 16 tiles, K = planes.
 // A wavefront takes 64 consecutive tiles of one tile row: the r plane segments (128 bytes each) are
@@ -327,8 +167,9 @@ __global__ __launch_bounds__(256) void outer_mfma_kernel(const bf16_t *__restric
 // ---------------------------------------------------------------------------------------
 // OUTER: the same pass also accumulates the basis gradient G (r x 16) += P (r x tiles) . tileview(V) (tiles x 16)
 // (dE_X with P = dXhat, V = X while dX is decoded), so that the planes are read from HBM once for both results;
-// every block writes one partial to `part`, added up in block order by outer_final_kernel.
-template <bool GELU, int KC, bool OUTER>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
+// every block writes one partial to `part`, added up in block order by outer_final_kernel.  DECODE = false: G alone.
+// ANY: column counts that are no multiple of 8 (see load8).
+template <bool GELU, int KC, bool OUTER, bool ANY = false, bool DECODE = true>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
 __global__ __launch_bounds__(256) void decode_mfma_kernel(const bf16_t *__restrict__ P, const bf16_t *__restrict__ Dm,
                                                           bf16_t *__restrict__ Cmat, int R, int Cc, int r, int chunks,
                                                           const bf16_t *__restrict__ V, float *__restrict__ part, int pg,
@@ -344,7 +185,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(const bf16_t *__restri
 #pragma unroll
     for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // wavefront w of block b takes items 4b + w, 4b + w + 4 * gridDim.x, ...
-    decode_items<GELU, KC, OUTER>(P, Dm, Cmat, R, Cc, r, chunks, V, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
+    decode_items<GELU, KC, OUTER, 1, ANY, DECODE>(P, Dm, Cmat, R, Cc, r, chunks, V, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
                                   (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], oacc, lane);
     if (OUTER) {
         // accumulator e of group g: plane 16g + 4*kq + e, tile entry j; fixed-order sum over the four wavefronts
@@ -490,14 +331,7 @@ hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R
     if (pg <= 0) pg = R;
     const int Rs = rm.count(R);                             // tile rows this launch walks over
     if (Rs <= 0) return hipSuccess;
-    if (dtype == 1 && (Cc % 8) == 0 && !basis_f32) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
-    if (dtype == 1 && (Cc % 4) == 0 && !basis_f32) {
-        const int chunks = (Cc + 127) / 128;
-        const long items = (long)Rs * chunks;
-        hipLaunchKernelGGL(encode_mfma_kernel, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, (const bf16_t *)A,
-                           (const bf16_t *)E, (bf16_t *)P, Rs, Cc, r, chunks, pg, rm);
-        return hipGetLastError();
-    }
+    if (dtype == 1 && Cc >= 8 && !basis_f32) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
     if (dtype == 0) return launch_encode_t<float, float>(A, E, P, Rs, Cc, r, pg, rm, s);
     return basis_f32 ? launch_encode_t<bf16_t, float>(A, E, P, Rs, Cc, r, pg, rm, s)
                      : launch_encode_t<bf16_t, bf16_t>(A, E, P, Rs, Cc, r, pg, rm, s);
@@ -517,27 +351,27 @@ static hipError_t launch_decode_t(const void *P, const void *Dm, void *Cmat, int
     return hipGetLastError();
 }
 
+template <bool ANY>
+static auto pick_decode(int r, bool gelu)
+{
+    if (r <= 32) return gelu ? decode_mfma_kernel<true, 1, false, ANY> : decode_mfma_kernel<false, 1, false, ANY>;
+    return gelu ? decode_mfma_kernel<true, 2, false, ANY> : decode_mfma_kernel<false, 2, false, ANY>;
+}
+
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R_all, int Cc, int r, bool gelu, int pg,
                          hipStream_t s, RowMap rm, bool basis_f32)
 {
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);                          // tile rows this launch walks over
     if (R <= 0) return hipSuccess;
-    if (dtype == 1 && (Cc % 8) == 0 && !basis_f32) {
+    if (dtype == 1 && Cc >= 8 && !basis_f32) {
         const int chunks = (Cc + 63) / 64;
         const long items = (long)R * chunks;
         long blocks = (items + 3) / 4;
         if (blocks > 8192) blocks = 8192;                   // grid-stride over (tile row, 64-tile chunk) items
-        const dim3 grid((unsigned)blocks), block(256);
-        const bf16_t *p = (const bf16_t *)P, *d = (const bf16_t *)Dm;
-        bf16_t *c = (bf16_t *)Cmat;
-        if (r <= 32) {
-            if (gelu) hipLaunchKernelGGL((decode_mfma_kernel<true, 1, false>), grid, block, 0, s, p, d, c, R, Cc, r, chunks, nullptr, nullptr, pg, rm);
-            else hipLaunchKernelGGL((decode_mfma_kernel<false, 1, false>), grid, block, 0, s, p, d, c, R, Cc, r, chunks, nullptr, nullptr, pg, rm);
-        } else {
-            if (gelu) hipLaunchKernelGGL((decode_mfma_kernel<true, 2, false>), grid, block, 0, s, p, d, c, R, Cc, r, chunks, nullptr, nullptr, pg, rm);
-            else hipLaunchKernelGGL((decode_mfma_kernel<false, 2, false>), grid, block, 0, s, p, d, c, R, Cc, r, chunks, nullptr, nullptr, pg, rm);
-        }
+        auto kern = Cc % 8 ? pick_decode<true>(r, gelu) : pick_decode<false>(r, gelu);
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)P, (const bf16_t *)Dm, (bf16_t *)Cmat, R, Cc,
+                           r, chunks, (const bf16_t *)nullptr, (float *)nullptr, pg, rm);
         return hipGetLastError();
     }
     if (dtype == 0) return launch_decode_t<float, float>(P, Dm, Cmat, R, Cc, r, gelu, pg, rm, s);
@@ -560,7 +394,7 @@ hipError_t launch_outer_final_pair(const float *part0, float *G0, int nb0, const
     return hipGetLastError();
 }
 
-bool decode_outer_eligible(int dtype, int Cc) { return dtype == 1 && (Cc % 8) == 0; }
+bool decode_outer_eligible(int dtype, int Cc) { return dtype == 1 && Cc >= 8; }
 
 int decode_outer_blocks(int R, int Cc)
 {
@@ -569,6 +403,14 @@ int decode_outer_blocks(int R, int Cc)
     return (int)(blocks > 1024 ? 1024 : blocks);
 }
 
+template <bool ANY>
+static auto pick_decode_outer(int r, const void *Cmat)
+{
+    if (r <= 32) return Cmat ? decode_mfma_kernel<false, 1, true, ANY, true> : decode_mfma_kernel<false, 1, true, ANY, false>;
+    return Cmat ? decode_mfma_kernel<false, 2, true, ANY, true> : decode_mfma_kernel<false, 2, true, ANY, false>;
+}
+
+// Cmat == nullptr: the basis gradient alone
 hipError_t launch_decode_outer(const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R_all,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm, bool final_sum)
 {
@@ -579,10 +421,8 @@ hipError_t launch_decode_outer(const void *P, const void *Dm, void *Cmat, const 
     const int nb = decode_outer_blocks(R, Cc);
     const bf16_t *p = (const bf16_t *)P, *d = (const bf16_t *)Dm, *v = (const bf16_t *)V;
     bf16_t *c = (bf16_t *)Cmat;
-    if (r <= 32)
-        hipLaunchKernelGGL((decode_mfma_kernel<false, 1, true>), dim3(nb), dim3(256), 0, s, p, d, c, R, Cc, r, chunks, v, part, pg, rm);
-    else
-        hipLaunchKernelGGL((decode_mfma_kernel<false, 2, true>), dim3(nb), dim3(256), 0, s, p, d, c, R, Cc, r, chunks, v, part, pg, rm);
+    auto kern = Cc % 8 ? pick_decode_outer<true>(r, Cmat) : pick_decode_outer<false>(r, Cmat);
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, p, d, c, R, Cc, r, chunks, v, part, pg, rm);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !final_sum) return e;
     const int n_out = r * 16;
@@ -606,6 +446,8 @@ int outer_reduce_blocks(int64_t tiles)
 hipError_t launch_outer_reduce(int dtype, const void *P, const void *V, float *G, float *part, int R_all, int Cc, int r,
                                int accumulate, int pg, hipStream_t s, RowMap rm)
 {
+    if (decode_outer_eligible(dtype, Cc))
+        return launch_decode_outer(P, nullptr, nullptr, V, G, part, R_all, Cc, r, accumulate, pg, s, rm);
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);
     if (R <= 0) return hipErrorInvalidValue;
@@ -615,9 +457,6 @@ hipError_t launch_outer_reduce(int dtype, const void *P, const void *V, float *G
     if (dtype == 0)
         hipLaunchKernelGGL(outer_partial_kernel<float>, dim3(nb), dim3(256), 0, s, (const float *)P, (const float *)V,
                            part, R, Cc, r, tpb, pg, rm);
-    else if (Cc % 8 == 0)
-        hipLaunchKernelGGL(outer_mfma_kernel, dim3(nb), dim3(256), 0, s, (const bf16_t *)P, (const bf16_t *)V, part, R,
-                           Cc, r, tpb, pg, rm);
     else
         hipLaunchKernelGGL(outer_partial_kernel<bf16_t>, dim3(nb), dim3(256), 0, s, (const bf16_t *)P,
                            (const bf16_t *)V, part, R, Cc, r, tpb, pg, rm);

@@ -1,0 +1,66 @@
+"""bf16 layers whose tile counts are no multiple of 8: rows at any even address, incomplete last chunks.  Every output of the
+saved-plane step (and of the calls that take a basis gradient alone) against the plane oracle, at the edges of the chunks
+(8 tiles), items (64 tile columns) and blocks (64, 128, 256) of the kernels and with contractions that end inside a step.
+
+Bars: gpu_util.check -- relative Frobenius error 1e-2 overall, per block and per tile row, every entry within 0.05 rms: the
+three roundings to bf16 that an output passes through (2.9e-3 rms, derived there)."""
+import numpy as np
+import pytest
+
+import stl_synth
+from oracle import planes
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("dX", "dWhat", "dE_X", "dD")
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import gpu_util
+    return gpu_util
+
+
+# M, K, N tile counts and r: 8 is the smallest width of these kernels, 7 the largest that stays with the others
+SHAPES = [(9, 8, 9, 32), (8, 15, 8, 5), (33, 63, 65, 17), (65, 9, 127, 49), (50, 16, 50, 32), (129, 129, 66, 24),
+          (257, 40, 250, 8), (512, 192, 250, 32), (70, 250, 262, 64), (300, 65, 1001, 16), (16, 7, 9, 8), (7, 12, 10, 8)]
+
+
+@pytest.mark.parametrize("M,K,N,r", SHAPES)
+def test_step_any_width(gu, M, K, N, r):
+    p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=300 + M + K + N + r, dtype="bf16", with_dC=True)
+    got = gu.step(p, "bf16")
+    C, Y = planes.forward(p["X"], p["What"], p["E_X"], p["D"], return_yhat=True)
+    gu.check(got["C"], C, "bf16", "C")
+    gu.check(got["Yhat"], Y, "bf16", "Yhat", slab=1)
+    gu.check(got["Xhat"], planes.encode(p["X"], p["E_X"]), "bf16", "Xhat", slab=1)
+    ref = dict(zip(NAMES, planes.backward(p["X"], p["What"], p["E_X"], p["D"], p["dC"])))
+    for name in NAMES:
+        gu.check(got[name], ref[name], "bf16", name)
+    # accumulation into fp32 gradients, and a basis gradient without the matrix gradient it usually comes with
+    init = [np.ones_like(ref[nm], dtype=np.float32) for nm in NAMES[1:]]
+    acc = gu.backward(p, "bf16", accumulate=1, init=init)
+    for nm in NAMES[1:]:
+        assert gu.rel(acc[nm] - 1.0, ref[nm]) <= gu.TOL["bf16"], nm
+    alone = gu.backward(p, "bf16", skip=("dX", "dWhat"))
+    for nm in ("dE_X", "dD"):
+        assert gu.rel(alone[nm], ref[nm]) <= gu.TOL["bf16"], nm
+
+
+@pytest.mark.parametrize("r1,R,N1,r2", [(24, 5, 9, 24), (49, 3, 66, 17), (8, 2, 250, 64)])
+def test_recode_any_width(gu, r1, R, N1, r2):
+    """Inter-layer step in one pass and in two launches: the same planes, bit for bit."""
+    import torch
+
+    import paper_2503_12211_amd as stl
+    rng = np.random.default_rng(r1 + N1)
+    up, down = stl.Problem(4 * R, 32, 4 * N1, r1), stl.Problem(4 * R, 4 * N1, 32, r2)
+    Y = gu.planes_to_dev(stl_synth.round_to(rng.standard_normal((r1, R, N1)), "bf16"), "bf16")
+    D, E = (gu.dev(stl_synth.round_to(rng.standard_normal((r, 16)) / 4, "bf16"), "bf16") for r in (r1, r2))
+    out = []
+    for flags in (stl.STL_FLAG_GELU, stl.STL_FLAG_GELU | stl.STL_FLAG_UNFUSED):
+        Q = gu.planes_buffer(r2, R, N1, "bf16")
+        H = torch.empty((4 * R, 4 * N1), dtype=torch.bfloat16, device="cuda")
+        stl.stl_recode(up, down, Y, D, E, Q, H, flags)
+        out.append(gu.planes_to_host(Q, r2, R, N1))
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
