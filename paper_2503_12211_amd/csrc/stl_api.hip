@@ -476,14 +476,11 @@ stl_status_t stl_encode_weight_backward(const stl_problem_t *prob, const void *W
         STL_HIP(stl::launch_cast_bf16(dWhat, base + w.planes, (size_t)d.r * d.K * d.N, s), "encode_weight_backward/round dWhat");
         planes = base + w.planes;
     }
-    if (dW && dE_W && stl::decode_outer_eligible(dt, d.N)) {
-        STL_HIP(stl::launch_decode_outer(planes, E_W, dW, W, dE_W, part, d.K, d.N, d.r, accumulate, 0, s),
-                "encode_weight_backward/dW + dE_W");
-        return STL_OK;
-    }
-    if (dW) STL_HIP(stl::launch_decode(dt, planes, E_W, dW, d.K, d.N, d.r, false, 0, s), "encode_weight_backward/dW");
     if (dE_W)
-        STL_HIP(stl::launch_outer_reduce(dt, planes, W, dE_W, part, d.K, d.N, d.r, accumulate, 0, s), "encode_weight_backward/dE_W");
+        STL_HIP(stl::launch_decode_outer(dt, planes, E_W, dW, W, dE_W, part, d.K, d.N, d.r, accumulate, 0, s),
+                "encode_weight_backward/dW + dE_W");
+    else if (dW)
+        STL_HIP(stl::launch_decode(dt, planes, E_W, dW, d.K, d.N, d.r, false, 0, s), "encode_weight_backward/dW");
     return STL_OK;
 }
 
@@ -633,16 +630,15 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
         STL_HIP(stl::launch_plane_gemm(dt, g, xhat, What, base + w.yhat, s), "backward/recompute Yhat");
         yhat = base + w.yhat;
     }
-    // when both fused gradient passes run, their block partials are added up by one launch at the end
-    const bool pair = dD && stl::encode_outer_eligible(dt, d.N) && dX && dE_X && stl::decode_outer_eligible(dt, d.K);
+    // when both basis gradients are asked for, their block partials are added up by one launch at the end
+    const bool pair = dD && dE_X;
     float *part2 = (float *)(base + w.part2);
-    if (dD && stl::encode_outer_eligible(dt, d.N)) {
+    if (dD) {
         // one pass over dC: dYhat = encode with D, dD = sum over tiles of Yhat (x) dc
-        STL_HIP(stl::launch_encode_outer(dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, stl::RowMap(), !pair),
+        STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, stl::RowMap(), !pair),
                 "backward/dYhat + dD");
     } else {
         STL_HIP(stl::launch_encode(dt, dC, D, dyhat, d.M, d.N, d.r, PG, s), "backward/encode dC");
-        if (dD) STL_HIP(stl::launch_outer_reduce(dt, yhat, dC, dD, part, d.M, d.N, d.r, accumulate, PG, s), "backward/dD");
     }
     // The weight gradient goes first: the pass that follows the second product (decode of dXhat) is bound by HBM and
     // finds the freshly written dXhat in the last-level cache, which a product in between would have flushed; the
@@ -657,19 +653,17 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
         stl::GemmDesc g{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG};
         STL_HIP(stl::launch_plane_gemm(dt, g, dyhat, What, dxhat, s), "backward/dXhat");
     }
-    if (dX && dE_X && stl::decode_outer_eligible(dt, d.K)) {
-        // one pass over dXhat: dX = decode with E_X, dE_X = sum over tiles of dXhat (x) x
-        STL_HIP(stl::launch_decode_outer(dxhat, E_X, dX, X, dE_X, pair ? part2 : part, d.M, d.K, d.r, accumulate, PG, s,
+    if (dE_X) {
+        // one pass over dXhat: dX = decode with E_X (if asked for), dE_X = sum over tiles of dXhat (x) x
+        STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, pair ? part2 : part, d.M, d.K, d.r, accumulate, PG, s,
                                          stl::RowMap(), !pair),
                 "backward/dX + dE_X");
         if (pair)
             STL_HIP(stl::launch_outer_final_pair(part, dD, stl::encode_outer_blocks(d.M, d.N), part2, dE_X,
                                                  stl::decode_outer_blocks(d.M, d.K), d.r * 16, accumulate, s),
                     "backward/dD and dE_X sums");
-    } else {
-        if (dX) STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s), "backward/decode dX");
-        if (dE_X)
-            STL_HIP(stl::launch_outer_reduce(dt, dxhat, X, dE_X, part, d.M, d.K, d.r, accumulate, PG, s), "backward/dE_X");
+    } else if (dX) {
+        STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s), "backward/decode dX");
     }
     return STL_OK;
 }
@@ -843,23 +837,19 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
         STL_HIP(stl::launch_plane_gemm(dt, g, ahat, bhat, base + w.yhat, s), "aa_backward/recompute Yhat");
         yhat = base + w.yhat;
     }
-    if (dD && stl::encode_outer_eligible(dt, d.N)) {
-        STL_HIP(stl::launch_encode_outer(dC, D, dyhat, yhat, dD, part, RA, d.N, d.r, accumulate, PG, s), "aa_backward/dYhat + dD");
-    } else {
+    if (dD)
+        STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, yhat, dD, part, RA, d.N, d.r, accumulate, PG, s), "aa_backward/dYhat + dD");
+    else
         STL_HIP(stl::launch_encode(dt, dC, D, dyhat, RA, d.N, d.r, PG, s), "aa_backward/encode dC");
-        if (dD) STL_HIP(stl::launch_outer_reduce(dt, yhat, dC, dD, part, RA, d.N, d.r, accumulate, PG, s), "aa_backward/dD");
-    }
     if (want_a) {
         // dAhat[b][p] = dYhat[b][p] * Bhat[b][p]^T, then back through the encoding of A
         // (with B stored transposed Bhat is [p][J][L]: the contraction index J is then its row index)
         stl::GemmDesc g{d.M, d.K, d.N, d.r, false, bt, false, false, PG, PG, PG, nb};
         STL_HIP(stl::launch_plane_gemm(dt, g, dyhat, bhat, dahat, s), "aa_backward/dAhat");
-        if (dA && dE_A && stl::decode_outer_eligible(dt, d.K)) {
-            STL_HIP(stl::launch_decode_outer(dahat, E_A, dA, A, dE_A, part, RA, d.K, d.r, accumulate, PG, s), "aa_backward/dA + dE_A");
-        } else {
-            if (dA) STL_HIP(stl::launch_decode(dt, dahat, E_A, dA, RA, d.K, d.r, false, PG, s), "aa_backward/decode dA");
-            if (dE_A) STL_HIP(stl::launch_outer_reduce(dt, dahat, A, dE_A, part, RA, d.K, d.r, accumulate, PG, s), "aa_backward/dE_A");
-        }
+        if (dE_A)
+            STL_HIP(stl::launch_decode_outer(dt, dahat, E_A, dA, A, dE_A, part, RA, d.K, d.r, accumulate, PG, s), "aa_backward/dA + dE_A");
+        else
+            STL_HIP(stl::launch_decode(dt, dahat, E_A, dA, RA, d.K, d.r, false, PG, s), "aa_backward/decode dA");
     }
     if (want_b) {
         // dBhat[b][p] = Ahat[b][p]^T * dYhat[b][p] in the storage type (one problem each, nothing accumulates over the
@@ -872,12 +862,10 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
             stl::GemmDesc g{d.K, d.N, d.M, d.r, true, true, false, false, PG, PG, PG, nb};
             STL_HIP(stl::launch_plane_gemm(dt, g, ahat, dyhat, dbhat, s), "aa_backward/dBhat");
         }
-        if (dB && dE_B && stl::decode_outer_eligible(dt, CB)) {
-            STL_HIP(stl::launch_decode_outer(dbhat, e_b, dB, B, ge_b, part, RB, CB, d.r, acc_b, PG, s), "aa_backward/dB + dE_B");
-        } else {
-            if (dB) STL_HIP(stl::launch_decode(dt, dbhat, e_b, dB, RB, CB, d.r, false, PG, s), "aa_backward/decode dB");
-            if (dE_B) STL_HIP(stl::launch_outer_reduce(dt, dbhat, B, ge_b, part, RB, CB, d.r, acc_b, PG, s), "aa_backward/dE_B");
-        }
+        if (dE_B)
+            STL_HIP(stl::launch_decode_outer(dt, dbhat, e_b, dB, B, ge_b, part, RB, CB, d.r, acc_b, PG, s), "aa_backward/dB + dE_B");
+        else
+            STL_HIP(stl::launch_decode(dt, dbhat, e_b, dB, RB, CB, d.r, false, PG, s), "aa_backward/decode dB");
         if (bt && dE_B) STL_HIP(stl::launch_transpose_basis_grad(ge_b, dE_B, d.r, accumulate, s), "aa_backward/dE_B of the stored basis");
     }
     return STL_OK;
@@ -965,12 +953,10 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
     }
     // dYhat and dD from the complete tile rows (all of them when nothing is ragged) ...
     const stl::RowMap body = g.map(1);
-    if (dD && stl::encode_outer_eligible(dt, d.N)) {
-        STL_HIP(stl::launch_encode_outer(dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, body), "ragged_backward/dYhat + dD");
-    } else {
+    if (dD)
+        STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, body), "ragged_backward/dYhat + dD");
+    else
         STL_HIP(stl::launch_encode(dt, dC, D, dyhat, d.M, d.N, d.r, PG, s, body), "ragged_backward/encode dC");
-        if (dD) STL_HIP(stl::launch_outer_reduce(dt, yhat, dC, dD, part, d.M, d.N, d.r, accumulate, PG, s, body), "ragged_backward/dD");
-    }
     if (g.nrho) {
         // ... and from each image's last tile row through the fold: its adjoint is an encode with the composed decoder;
         // one product Yhat (x) dC over those tile rows feeds both dD and dfold
@@ -978,7 +964,7 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
         STL_HIP(stl::launch_fold_decoder(dt, D, fold, dprime, d.r, g.nrho, s), "ragged_backward/compose fold");
         STL_HIP(stl::launch_encode(dt, dC, dprime, dyhat, d.M, d.N, d.r, PG, s, tail, true), "ragged_backward/encode folded dC");
         if (dD || want_fold) {
-            STL_HIP(stl::launch_outer_reduce(dt, yhat, dC, gtail, part, d.M, d.N, d.r, 0, PG, s, tail), "ragged_backward/last tile rows");
+            STL_HIP(stl::launch_decode_outer(dt, yhat, nullptr, nullptr, dC, gtail, part, d.M, d.N, d.r, 0, PG, s, tail), "ragged_backward/last tile rows");
             STL_HIP(stl::launch_fold_grads(dt, gtail, D, fold, dD, dfold, d.r, g.nrho, accumulate, s), "ragged_backward/dD + dfold");
         }
     }
@@ -992,13 +978,10 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
     }
     // gradients of null rows are dropped (never written); null rows of X count as zeros in dE_X
     const stl::RowMap all = g.map(0);
-    if (dX && dE_X && stl::decode_outer_eligible(dt, d.K)) {
-        STL_HIP(stl::launch_decode_outer(dxhat, E_X, dX, X, dE_X, part, d.M, d.K, d.r, accumulate, PG, s, all), "ragged_backward/dX + dE_X");
-    } else {
-        if (dX) STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s, all), "ragged_backward/decode dX");
-        if (dE_X)
-            STL_HIP(stl::launch_outer_reduce(dt, dxhat, X, dE_X, part, d.M, d.K, d.r, accumulate, PG, s, all), "ragged_backward/dE_X");
-    }
+    if (dE_X)
+        STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, part, d.M, d.K, d.r, accumulate, PG, s, all), "ragged_backward/dX + dE_X");
+    else if (dX)
+        STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s, all), "ragged_backward/decode dX");
     return STL_OK;
 }
 

@@ -103,6 +103,36 @@ template <> struct Elem<bf16_t> {
     static __device__ __forceinline__ void st(bf16_t *p, float v) { *p = f32_to_bf16(v); }
 };
 
+// Four consecutive elements as fp32, n of them left in the row from p on (zeros for the others); p at any element.
+typedef f32x4_t f32x4_any_t __attribute__((aligned(4)));
+
+template <typename T>
+__device__ __forceinline__ f32x4_t load4(const T *p, int n)
+{
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (n >= 4) {
+        if constexpr (sizeof(T) == 4) {
+            v = *reinterpret_cast<const f32x4_any_t *>(p);
+        } else {
+            const u32x2_t w = *reinterpret_cast<const u32x2_any_t *>(p);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = bf16_to_f32((bf16_t)(w[e >> 1] >> (16 * (e & 1))));
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < n) v[e] = Elem<T>::ld(p + e);
+    }
+    return v;
+}
+
+// one row of a tile (4 elements, aligned to their size)
+__device__ __forceinline__ void store4(float *p, f32x4_t v) { *reinterpret_cast<f32x4_t *>(p) = v; }
+__device__ __forceinline__ void store4(bf16_t *p, f32x4_t v)
+{
+    *reinterpret_cast<u32x2_t *>(p) = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+}
+
 // Plane tensors [p][tile row][tile column] are stored in groups of `pg` tile rows: element (p, I, J) of an
 // r x R x Cc tensor lives at ((I / pg) * r + p) * pg * Cc + (I % pg) * Cc + J.  pg = R is the plain plane-major
 // layout (weights and their gradients); the activation-side tensors use groups of 64 tile rows, which keeps the r

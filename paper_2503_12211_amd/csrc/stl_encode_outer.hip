@@ -57,8 +57,6 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
             ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
 }
 
-bool encode_outer_eligible(int dtype, int Cc) { return dtype == 1 && Cc >= 8; }
-
 int encode_outer_blocks(int R, int Cc)
 {
     const long items = (long)R * ((Cc + 63) / 64);
@@ -66,24 +64,16 @@ int encode_outer_blocks(int R, int Cc)
     return (int)(blocks > 1024 ? 1024 : blocks);
 }
 
-hipError_t launch_encode_outer(const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R, int Cc,
-                               int r, int accumulate, int pg, hipStream_t s, RowMap rm, bool final_sum)
+// both maps on the matrix cores (bf16, Cc >= 8), nb blocks that leave one partial each; R counts the rows of this launch
+hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
+                                     int nb, hipStream_t s, RowMap rm)
 {
-    if (pg <= 0) pg = R;
-    R = rm.count(R);                                        // tile rows this launch walks over
-    if (R <= 0) return hipErrorInvalidValue;
-    const int chunks = (Cc + 63) / 64;
-    const int nb = encode_outer_blocks(R, Cc);
-    const dim3 grid(nb), block(256);
-    const bf16_t *a = (const bf16_t *)A, *en = (const bf16_t *)E, *q = (const bf16_t *)Qp;
-    bf16_t *out = (bf16_t *)P;
     const bool any = Cc % 8 != 0;
     auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, true, true> : encode_outer16_kernel<1, true, false>)
                         : (any ? encode_outer16_kernel<2, true, true> : encode_outer16_kernel<2, true, false>);
-    hipLaunchKernelGGL(kern, grid, block, 0, s, a, en, out, q, part, R, Cc, r, chunks, pg, rm);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !final_sum) return e;
-    return launch_outer_final(part, G, nb, r * 16, accumulate, s);
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E, (bf16_t *)P, (const bf16_t *)Qp, part, R,
+                       Cc, r, (Cc + 63) / 64, pg, rm);
+    return hipGetLastError();
 }
 
 // the encode alone through the same kernel (bf16, Cc >= 8): grid-stride over (tile row, 64-tile chunk) items

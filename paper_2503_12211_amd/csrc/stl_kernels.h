@@ -55,17 +55,12 @@ hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R, int Cc, int r, bool gelu, int pg,
                          hipStream_t s, RowMap rm = RowMap(), bool basis_f32 = false);
 
-// G[p][q] (+)= sum_tiles P[p][tile] * tileview(V)[tile][q]; `part` holds outer_reduce_blocks(R*Cc) * r * 16 floats
-int outer_reduce_blocks(int64_t tiles);
-hipError_t launch_outer_reduce(int dtype, const void *P, const void *V, float *G, float *part, int R, int Cc, int r,
-                               int accumulate, int pg, hipStream_t s, RowMap rm = RowMap());
-
-// decode and basis gradient in one pass over the planes (bf16): Cmat <- decode(P, Dm), G (+)= P . tileview(V);
-// `part` holds decode_outer_blocks(R, Cc) * r * 16 floats
-bool decode_outer_eligible(int dtype, int Cc);
+// Basis gradient G[p][q] (+)= sum_tiles P[p][tile] * tileview(V)[tile][q], in one pass with the decode of the same planes
+// (Cmat <- decode(P, Dm)), or alone when Cmat is NULL (Dm is not read then); `part` holds decode_outer_blocks(R, Cc) * r * 16 floats
 int decode_outer_blocks(int R, int Cc);
-hipError_t launch_decode_outer(const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
+hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
+int outer_reduce_blocks(int64_t tiles);     // a further bound on the partials, for the declared workspace sizes
 
 // G[i] (+)= sum over nb partials part[b][i], i < n_out, in block order (second stage of the basis-gradient sums)
 hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s);
@@ -73,12 +68,14 @@ hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, in
 hipError_t launch_outer_final_pair(const float *part0, float *G0, int nb0, const float *part1, float *G1, int nb1, int n_out,
                                    int accumulate, hipStream_t s);
 
-// encode and basis gradient in one pass over the matrix (bf16): P <- encode(A, E), G (+)= Qp . tileview(A);
+// encode and basis gradient in one pass over the matrix: P <- encode(A, E), G (+)= Qp . tileview(A);
 // `part` holds encode_outer_blocks(R, Cc) * r * 16 floats
-bool encode_outer_eligible(int dtype, int Cc);
 int encode_outer_blocks(int R, int Cc);
-hipError_t launch_encode_outer(const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R, int Cc,
+hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R, int Cc,
                                int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
+// its bf16 kernel (Cc >= 8); launch_encode_outer picks it
+hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
+                                     int nb, hipStream_t s, RowMap rm);
 
 // fold of an image's last tile row (row counts not divisible by 4): composed decoder Dp (r x 16 fp32) from Dm and the
 // nrho x 4 fold coefficients; and the gradients that come from those tile rows, given Gt = Yhat (x) dC over them

@@ -1,6 +1,6 @@
 // Tile-level linear maps of the STL operator: encode (step (i) of Algorithm 1), decode
 // (step (iii)) and the two basis-gradient reductions.  All of these stream a matrix once
-// through HBM; arithmetic is fp32.
+// through HBM; sums are fp32.
 #include "stl_kernels.h"
 #include "stl_device.h"
 #include "stl_tile_items.h"
@@ -9,125 +9,157 @@
 namespace stl {
 
 // ---------------------------------------------------------------------------------------
-// encode:  P[p][I][L] = sum_q E[p][q] * A[4I + q/4][4L + q%4]        (planes of encoded tiles)
-// One thread per tile; lanes run along L so that every row segment and every plane row is
-// read / written contiguously by a wavefront.
+// The tile maps in fp32 arithmetic on the vector ALUs, for fp32 storage, for bf16 rows of fewer than 8 tiles and for bases
+// kept in fp32 (the folded decoder):
+//   ENC    Pout[p][I][J]  = sum_q B[p][q] V[4I + q/4][4J + q%4]                  (planes of encoded tiles)
+//   DEC    Cmat[4I + q/4][4J + q%4] = sum_p B[p][q] Pin[p][I][J]                 (+ optional GELU)
+//   OUTER  G[p][q] = sum_{I,J} Pin[p][I][J] V[4I + q/4][4J + q%4]                (basis gradient; with ENC or DEC or alone)
+// A group of 256 threads takes items of 64 tiles: 64 tile columns of one tile row, or 64 >> lw tile rows of at most
+// 1 << lw columns where the matrix is narrow.  The item's planes (float4 per thread, 256 bytes per plane) and tiles are
+// staged through LDS, the next item's loads in flight meanwhile, and every thread then plays a role per map: ENC (tile, every
+// fourth plane), DEC (tile, tile row), OUTER (entry q, every 16th plane; the 64 tiles of an item are summed on their own
+// before they join the running sum).  Bound by HBM on large matrices and by latency on small ones, which is what the
+// grouping is for: with one thread per tile, planes one after the other, 64 x 64 tiles at r = 49 took 9 us to encode,
+// 19 to decode and 332 for a basis gradient (16 workgroups); now 5, 5 and 11 (with the decode).
+// OUTER blocks leave one partial each, added up in block order by outer_final_kernel: no floating-point atomics, so the
+// results are bitwise reproducible.
 // ---------------------------------------------------------------------------------------
-// TB: type the basis is stored in (the storage type, or fp32 for a basis composed on the device).  R counts the tile
-// rows this launch walks over (see RowMap).
-template <typename T, typename TB>
-__global__ __launch_bounds__(256) void encode_kernel(const T *__restrict__ A, const TB *__restrict__ E,
-                                                     T *__restrict__ P, int R, int Cc, int r, int pg, RowMap rm)
+// T: storage type; TB: type the basis is stored in (the storage type, or fp32 for a basis composed on the device).
+// R counts the tile rows this launch walks over (see RowMap).
+constexpr int kTilePitch = 64 + 4;          // floats per LDS row of 64 tiles
+
+template <typename T, typename TB, bool ENC, bool DEC, bool OUTER, bool GELU, int GROUPS>
+__global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restrict__ V, const T *__restrict__ Pin,
+                                                                const TB *__restrict__ B, T *__restrict__ Pout,
+                                                                T *__restrict__ Cmat, float *__restrict__ part, int R, int Cc, int r,
+                                                                int lw, int pg, RowMap rm)
 {
-    __shared__ float sE[64 * 16];
-    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-    for (int i = tid; i < r * 16; i += 256) sE[i] = Elem<TB>::ld(E + i);
-    __syncthreads();
+    constexpr bool PLANES = DEC || OUTER, TILES = ENC || OUTER;
+    constexpr int TP = kTilePitch;
+    extern __shared__ __align__(16) char smem[];
+    const int ng = (r + 15) >> 4;                            // plane rows are staged in whole groups of 16, zeros beyond r
+    float *sB = reinterpret_cast<float *>(smem);             // [r][16]
+    const int gt = threadIdx.x & 255, grp = threadIdx.x >> 8;
+    float *sP = sB + r * 16 + grp * ((PLANES ? ng * 16 * TP : 0) + (TILES ? 16 * TP : 0));     // [p][tile]
+    float *sX = sP + (PLANES ? ng * 16 * TP : 0);            // [q][tile]
+    if (ENC || DEC)
+        for (int i = threadIdx.x; i < r * 16; i += GROUPS * 256) sB[i] = Elem<TB>::ld(B + i);
 
-    const int L = blockIdx.x * blockDim.x + threadIdx.x;
-    if (L >= Cc) return;
-    const size_t ld = (size_t)Cc * 4;
-    const size_t plane = (size_t)pg * Cc;
-    // grid-stride over the tile rows: the grid's second extent is capped, any row count is covered
-    for (int idx = blockIdx.y * blockDim.y + threadIdx.y; idx < R; idx += gridDim.y * blockDim.y) {
-        const int I = rm.tile_row(idx), nv = rm.valid(I);
-        const size_t r0 = rm.row0(I);
-        float x[16];
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) x[a * 4 + b] = a < nv ? Elem<T>::ld(A + (r0 + a) * ld + (size_t)L * 4 + b) : 0.f;
+    const int W = 1 << lw, rows = 64 >> lw, chunks = (Cc + W - 1) >> lw;
+    const long items = (long)((R + rows - 1) / rows) * chunks;
+    const size_t ld = (size_t)Cc * 4, plane = (size_t)pg * Cc;
 
-        T *out = P + plane_row_base(I, pg, r, Cc) + L;
-        for (int p = 0; p < r; ++p) {
-            float s = 0.f;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) s = fmaf(sE[p * 16 + q], x[q], s);
-            Elem<T>::st(out + (size_t)p * plane, s);
-        }
-    }
-}
+    // tile t of an item: index of its tile row among the rows of this launch, its tile column
+    struct Pos { int idx, J; };
+    auto locate = [&](long item, int t) {
+        const int rb = (int)(item / chunks), ck = (int)(item - (long)rb * chunks);
+        return Pos{rb * rows + (t >> lw), (ck << lw) + (t & (W - 1))};
+    };
+    const int t = gt & 63, a = gt >> 6;                      // roles: tile, tile row (ENC: planes a, a + 4, ...)
+    const int c4 = gt & 15, p16 = gt >> 4;                   // loader of planes: tiles 4 c4 ..; planes p16, p16 + 16, ...
 
-// ---------------------------------------------------------------------------------------
-// decode:  Cmat[4I + q/4][4J + q%4] = sum_p Dm[p][q] * P[p][I][J]     (+ optional GELU)
-// ---------------------------------------------------------------------------------------
-template <typename T, typename TB, bool GELU>
-__global__ __launch_bounds__(256) void decode_kernel(const T *__restrict__ P, const TB *__restrict__ Dm,
-                                                     T *__restrict__ Cmat, int R, int Cc, int r, int pg, RowMap rm)
-{
-    __shared__ float sD[64 * 16];
-    const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-    for (int i = tid; i < r * 16; i += 256) sD[i] = Elem<TB>::ld(Dm + i);
-    __syncthreads();
-
-    const int J = blockIdx.x * blockDim.x + threadIdx.x;
-    if (J >= Cc) return;
-    const size_t plane = (size_t)pg * Cc;
-    const size_t ld = (size_t)Cc * 4;
-    // grid-stride over the tile rows, as in the encode
-    for (int idx = blockIdx.y * blockDim.y + threadIdx.y; idx < R; idx += gridDim.y * blockDim.y) {
-        const int I = rm.tile_row(idx), nv = rm.valid(I);
-        const size_t r0 = rm.row0(I);
-        const T *in = P + plane_row_base(I, pg, r, Cc) + J;
-        float c[16];
+    f32x4_t pre[PLANES ? 4 : 1], xpre = {0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](long item) {
+        if (PLANES) {
+            const Pos at = locate(item, 4 * c4);
+            const bool in = item < items && at.idx < R;
+            const size_t off = in ? plane_row_base(rm.tile_row(at.idx), pg, r, Cc) + at.J : 0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) c[q] = 0.f;
-        for (int p = 0; p < r; ++p) {
-            const float y = Elem<T>::ld(in + (size_t)p * plane);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) c[q] = fmaf(sD[p * 16 + q], y, c[q]);
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                float v = c[a * 4 + b];
-                if (GELU) v = gelu_erf(v);
-                if (a < nv) Elem<T>::st(Cmat + (r0 + a) * ld + (size_t)J * 4 + b, v);
+            for (int i = 0; i < 4; ++i) {
+                const int p = p16 + 16 * i;
+                pre[i] = i < ng ? load4<T>(Pin + off + (size_t)p * plane, in && p < r ? Cc - at.J : 0) : f32x4_t{0.f, 0.f, 0.f, 0.f};
             }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// basis gradients:  G[p][q] (+)= sum_{I,J} P[p][I][J] * V[4I + q/4][4J + q%4]
-// (dD with P=Yhat, V=dC;  dE_X with P=dXhat, V=X).  Two deterministic stages: every block
-// sums a fixed range of tiles in a fixed order into part[block][p][q]; the second stage
-// adds the partials in block order.  No atomics, so results are bitwise reproducible.
-// ---------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void outer_partial_kernel(const T *__restrict__ P, const T *__restrict__ V,
-                                                            float *__restrict__ part, int R, int Cc, int r,
-                                                            int tiles_per_block, int pg, RowMap rm)
-{
-    // 256 threads: q = tid & 15, tile lane = tid >> 4 (16 tiles in flight); loop over planes.
-    __shared__ float red[16][16];
-    const int q = threadIdx.x & 15, tl = threadIdx.x >> 4;
-    const size_t T_total = (size_t)R * Cc;
-    const size_t t0 = (size_t)blockIdx.x * tiles_per_block;
-    size_t t1 = t0 + tiles_per_block;
-    if (t1 > T_total) t1 = T_total;
-    const size_t ld = (size_t)Cc * 4;
-    for (int p = 0; p < r; ++p) {
-        float s = 0.f;
-        for (size_t tile = t0 + tl; tile < t1; tile += 16) {
-            const size_t J = tile % Cc;
-            const int I = rm.tile_row((int)(tile / Cc));
-            const float v = (q >> 2) < rm.valid(I) ? Elem<T>::ld(V + (rm.row0(I) + (q >> 2)) * ld + J * 4 + (q & 3)) : 0.f;
-            const float y = Elem<T>::ld(P + plane_row_base(I, pg, r, Cc) + (size_t)p * pg * Cc + J);
-            s = fmaf(y, v, s);
         }
-        red[tl][q] = s;
-        __syncthreads();
-        if (tl == 0) {
-            float tot = 0.f;
+        if (TILES) {
+            const Pos at = locate(item, t);
+            const int I = item < items && at.idx < R && at.J < Cc ? rm.tile_row(at.idx) : -1;
+            xpre = I >= 0 && a < rm.valid(I) ? load4<T>(V + (rm.row0(I) + a) * ld + (size_t)at.J * 4, 4) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};                     // OUTER: entry q = c4, planes p16 + 16 i
+    const long stride = (long)gridDim.x * GROUPS;
+    fetch((long)blockIdx.x * GROUPS + grp);
+    for (long base = (long)blockIdx.x * GROUPS; base < items; base += stride) {      // same trip count for all groups
+        const long item = base + grp;
+        __syncthreads();                                     // previous item's readers are done (first: nothing to wait for)
+        if (PLANES)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) tot += red[i][q];
-            part[((size_t)blockIdx.x * r + p) * 16 + q] = tot;
-        }
+            for (int i = 0; i < 4; ++i)
+                if (i < ng) *reinterpret_cast<f32x4_t *>(sP + (p16 + 16 * i) * TP + 4 * c4) = pre[i];
+        if (TILES)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) sX[(4 * a + b) * TP + t] = xpre[b];
         __syncthreads();
+        fetch(item + stride);
+
+        const Pos at = locate(item, t);
+        const bool in = item < items && at.idx < R && at.J < Cc;
+        const int I = in ? rm.tile_row(at.idx) : 0;
+        if (OUTER) {
+            f32x4_t s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+            for (int u = 0; u < 16; ++u) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t *>(sX + c4 * TP + 4 * u);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (i < ng) {
+                        const f32x4_t y = *reinterpret_cast<const f32x4_t *>(sP + (p16 + 16 * i) * TP + 4 * u);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) s[i][e] = fmaf(y[e], v[e], s[i][e]);
+                    }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += (s[i][0] + s[i][1]) + (s[i][2] + s[i][3]);
+        }
+        if (ENC) {
+            float x[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) x[q] = sX[q * TP + t];
+            T *out = Pout + (in ? plane_row_base(I, pg, r, Cc) + at.J : 0);
+#pragma unroll 4
+            for (int p = a; p < r; p += 4) {
+                float s = 0.f;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) s = fmaf(sB[p * 16 + q], x[q], s);
+                if (in) Elem<T>::st(out + (size_t)p * plane, s);
+            }
+        }
+        if (DEC) {
+            f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+            for (int p = 0; p < r; ++p) {
+                const float y = sP[p * TP + t];
+                const f32x4_t d = *reinterpret_cast<const f32x4_t *>(sB + p * 16 + 4 * a);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c[e] = fmaf(d[e], y, c[e]);
+            }
+            if (GELU)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) c[e] = gelu_erf(c[e]);
+            if (in && a < rm.valid(I)) store4(Cmat + (rm.row0(I) + a) * ld + (size_t)at.J * 4, c);
+        }
+    }
+    if (OUTER) {
+        // fixed-order sum over the groups, then this block's partial
+        __syncthreads();
+        float *red = sB + r * 16;                            // [group][p][16] over the staging areas, all read by now
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < ng) red[(grp * ng * 16 + p16 + 16 * i) * 16 + c4] = acc[i];
+        __syncthreads();
+        for (int i = threadIdx.x; i < r * 16; i += GROUPS * 256) {
+            float tot = red[i];
+#pragma unroll
+            for (int g = 1; g < GROUPS; ++g) tot += red[g * ng * 256 + i];
+            part[(size_t)blockIdx.x * r * 16 + i] = tot;
+        }
     }
 }
 
+// second stage of the basis-gradient sums: the blocks' partials in block order
 __global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restrict__ part, float *__restrict__ G,
                                                            int nblocks, int n_out, int accumulate,
                                                            const float *__restrict__ part1 = nullptr,
@@ -316,12 +348,33 @@ hipError_t launch_cast_bf16(const float *in, void *out, size_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-template <typename T, typename TB>
-static hipError_t launch_encode_t(const void *A, const void *E, void *P, int Rs, int Cc, int r, int pg, const RowMap &rm,
-                                  hipStream_t s)
+// lw: log2 of the tile columns an item takes per tile row (see tile_map_kernel), for rows of Cc tiles
+static int tile_item_log2(int Cc)
 {
-    dim3 block(64, 4), grid((Cc + 63) / 64, (Rs + 3) / 4 > 32768 ? 32768 : (Rs + 3) / 4);   // the kernel strides over the rows
-    hipLaunchKernelGGL((encode_kernel<T, TB>), grid, block, 0, s, (const T *)A, (const TB *)E, (T *)P, Rs, Cc, r, pg, rm);
+    int lw = 2;                                             // at least the 4 tiles of a float4
+    while (lw < 6 && (1 << lw) < Cc) ++lw;
+    return lw;
+}
+
+// blocks > 0: exactly that many (one partial each); 0: as many as there are items, up to 8192
+template <typename T, typename TB, bool ENC, bool DEC, bool OUTER, bool GELU>
+static hipError_t launch_tile_map(const void *V, const void *Pin, const void *B, void *Pout, void *Cmat, float *part, int R, int Cc,
+                                  int r, int pg, const RowMap &rm, int blocks, hipStream_t s)
+{
+    constexpr int GROUPS = OUTER ? 4 : 1;                   // a partial per four groups, as many blocks as the workspace has room for
+    auto kern = tile_map_kernel<T, TB, ENC, DEC, OUTER, GELU, GROUPS>;
+    constexpr int most = 64 * 16 * 4 + GROUPS * (64 + 16) * kTilePitch * 4;
+    static_assert(most <= 160 * 1024, "LDS budget");
+    // once per instantiation (initialisation of a function-local static is thread-safe)
+    static const hipError_t attr_err =
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (attr_err != hipSuccess) return attr_err;
+    const int ng = (r + 15) / 16, lw = tile_item_log2(Cc), rows = 64 >> lw;
+    const int smem = r * 64 + GROUPS * ((DEC || OUTER ? ng * 16 : 0) + (ENC || OUTER ? 16 : 0)) * kTilePitch * 4;
+    const long items = (long)((R + rows - 1) / rows) * ((Cc + (1 << lw) - 1) >> lw);
+    if (blocks <= 0) blocks = (int)(items > 8192 ? 8192 : items);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(GROUPS * 256), smem, s, (const T *)V, (const T *)Pin, (const TB *)B, (T *)Pout,
+                       (T *)Cmat, part, R, Cc, r, lw, pg, rm);
     return hipGetLastError();
 }
 
@@ -332,23 +385,10 @@ hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R
     const int Rs = rm.count(R);                             // tile rows this launch walks over
     if (Rs <= 0) return hipSuccess;
     if (dtype == 1 && Cc >= 8 && !basis_f32) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
-    if (dtype == 0) return launch_encode_t<float, float>(A, E, P, Rs, Cc, r, pg, rm, s);
-    return basis_f32 ? launch_encode_t<bf16_t, float>(A, E, P, Rs, Cc, r, pg, rm, s)
-                     : launch_encode_t<bf16_t, bf16_t>(A, E, P, Rs, Cc, r, pg, rm, s);
-}
-
-template <typename T, typename TB>
-static hipError_t launch_decode_t(const void *P, const void *Dm, void *Cmat, int Rs, int Cc, int r, bool gelu, int pg,
-                                  const RowMap &rm, hipStream_t s)
-{
-    dim3 block(64, 4), grid((Cc + 63) / 64, (Rs + 3) / 4 > 32768 ? 32768 : (Rs + 3) / 4);   // the kernel strides over the rows
-    if (gelu)
-        hipLaunchKernelGGL((decode_kernel<T, TB, true>), grid, block, 0, s, (const T *)P, (const TB *)Dm, (T *)Cmat, Rs, Cc, r,
-                           pg, rm);
-    else
-        hipLaunchKernelGGL((decode_kernel<T, TB, false>), grid, block, 0, s, (const T *)P, (const TB *)Dm, (T *)Cmat, Rs, Cc, r,
-                           pg, rm);
-    return hipGetLastError();
+    auto run = dtype == 0     ? launch_tile_map<float, float, true, false, false, false>
+               : basis_f32 ? launch_tile_map<bf16_t, float, true, false, false, false>
+                           : launch_tile_map<bf16_t, bf16_t, true, false, false, false>;
+    return run(A, nullptr, E, P, nullptr, nullptr, Rs, Cc, r, pg, rm, 0, s);
 }
 
 template <bool ANY>
@@ -374,9 +414,10 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
                            r, chunks, (const bf16_t *)nullptr, (float *)nullptr, pg, rm);
         return hipGetLastError();
     }
-    if (dtype == 0) return launch_decode_t<float, float>(P, Dm, Cmat, R, Cc, r, gelu, pg, rm, s);
-    return basis_f32 ? launch_decode_t<bf16_t, float>(P, Dm, Cmat, R, Cc, r, gelu, pg, rm, s)
-                     : launch_decode_t<bf16_t, bf16_t>(P, Dm, Cmat, R, Cc, r, gelu, pg, rm, s);
+    auto run = dtype == 0     ? (gelu ? launch_tile_map<float, float, false, true, false, true> : launch_tile_map<float, float, false, true, false, false>)
+               : basis_f32 ? (gelu ? launch_tile_map<bf16_t, float, false, true, false, true> : launch_tile_map<bf16_t, float, false, true, false, false>)
+                           : (gelu ? launch_tile_map<bf16_t, bf16_t, false, true, false, true> : launch_tile_map<bf16_t, bf16_t, false, true, false, false>);
+    return run(nullptr, P, Dm, nullptr, Cmat, nullptr, R, Cc, r, pg, rm, 0, s);
 }
 
 hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s)
@@ -394,8 +435,6 @@ hipError_t launch_outer_final_pair(const float *part0, float *G0, int nb0, const
     return hipGetLastError();
 }
 
-bool decode_outer_eligible(int dtype, int Cc) { return dtype == 1 && Cc >= 8; }
-
 int decode_outer_blocks(int R, int Cc)
 {
     const long items = (long)R * ((Cc + 63) / 64);
@@ -411,59 +450,53 @@ static auto pick_decode_outer(int r, const void *Cmat)
 }
 
 // Cmat == nullptr: the basis gradient alone
-hipError_t launch_decode_outer(const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R_all,
+hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R_all,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm, bool final_sum)
 {
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);
     if (R <= 0) return hipErrorInvalidValue;
-    const int chunks = (Cc + 63) / 64;
     const int nb = decode_outer_blocks(R, Cc);
-    const bf16_t *p = (const bf16_t *)P, *d = (const bf16_t *)Dm, *v = (const bf16_t *)V;
-    bf16_t *c = (bf16_t *)Cmat;
-    auto kern = Cc % 8 ? pick_decode_outer<true>(r, Cmat) : pick_decode_outer<false>(r, Cmat);
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, p, d, c, R, Cc, r, chunks, v, part, pg, rm);
-    hipError_t e = hipGetLastError();
+    hipError_t e;
+    if (dtype == 1 && Cc >= 8) {
+        auto kern = Cc % 8 ? pick_decode_outer<true>(r, Cmat) : pick_decode_outer<false>(r, Cmat);
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, (const bf16_t *)P, (const bf16_t *)Dm, (bf16_t *)Cmat, R, Cc, r, (Cc + 63) / 64,
+                           (const bf16_t *)V, part, pg, rm);
+        e = hipGetLastError();
+    } else {
+        auto run = dtype == 0 ? (Cmat ? launch_tile_map<float, float, false, true, true, false> : launch_tile_map<float, float, false, false, true, false>)
+                              : (Cmat ? launch_tile_map<bf16_t, bf16_t, false, true, true, false> : launch_tile_map<bf16_t, bf16_t, false, false, true, false>);
+        e = run(V, P, Dm, nullptr, Cmat, part, R, Cc, r, pg, rm, nb, s);
+    }
     if (e != hipSuccess || !final_sum) return e;
-    const int n_out = r * 16;
-    return launch_outer_final(part, G, nb, n_out, accumulate, s);
+    return launch_outer_final(part, G, nb, r * 16, accumulate, s);
 }
 
-static int outer_tiles_per_block(int64_t tiles)
+hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R_all, int Cc,
+                               int r, int accumulate, int pg, hipStream_t s, RowMap rm, bool final_sum)
 {
-    // at most 512 partials; blocks take whole 256-tile steps (4 wavefronts x 64 tiles)
-    int64_t tpb = (tiles + 511) / 512;
-    tpb = (tpb + 255) / 256 * 256;
-    return (int)(tpb < 256 ? 256 : tpb);
-}
-
-int outer_reduce_blocks(int64_t tiles)
-{
-    const int tpb = outer_tiles_per_block(tiles);
-    return (int)((tiles + tpb - 1) / tpb);
-}
-
-hipError_t launch_outer_reduce(int dtype, const void *P, const void *V, float *G, float *part, int R_all, int Cc, int r,
-                               int accumulate, int pg, hipStream_t s, RowMap rm)
-{
-    if (decode_outer_eligible(dtype, Cc))
-        return launch_decode_outer(P, nullptr, nullptr, V, G, part, R_all, Cc, r, accumulate, pg, s, rm);
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);
     if (R <= 0) return hipErrorInvalidValue;
-    const int64_t tiles = (int64_t)R * Cc;
-    const int tpb = outer_tiles_per_block(tiles);
-    const int nb = outer_reduce_blocks(tiles);
-    if (dtype == 0)
-        hipLaunchKernelGGL(outer_partial_kernel<float>, dim3(nb), dim3(256), 0, s, (const float *)P, (const float *)V,
-                           part, R, Cc, r, tpb, pg, rm);
-    else
-        hipLaunchKernelGGL(outer_partial_kernel<bf16_t>, dim3(nb), dim3(256), 0, s, (const bf16_t *)P,
-                           (const bf16_t *)V, part, R, Cc, r, tpb, pg, rm);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int n_out = r * 16;
-    return launch_outer_final(part, G, nb, n_out, accumulate, s);
+    const int nb = encode_outer_blocks(R, Cc);
+    hipError_t e;
+    if (dtype == 1 && Cc >= 8) {
+        e = launch_encode_outer_lines(A, E, P, Qp, part, R, Cc, r, pg, nb, s, rm);
+    } else {
+        auto run = dtype == 0 ? launch_tile_map<float, float, true, false, true, false> : launch_tile_map<bf16_t, bf16_t, true, false, true, false>;
+        e = run(A, Qp, E, P, nullptr, part, R, Cc, r, pg, rm, nb, s);
+    }
+    if (e != hipSuccess || !final_sum) return e;
+    return launch_outer_final(part, G, nb, r * 16, accumulate, s);
+}
+
+// Partials the workspaces have room for, besides decode_outer_blocks and encode_outer_blocks: their declared sizes stand.
+int outer_reduce_blocks(int64_t tiles)
+{
+    int64_t tpb = (tiles + 511) / 512;
+    tpb = (tpb + 255) / 256 * 256;
+    if (tpb < 256) tpb = 256;
+    return (int)((tiles + tpb - 1) / tpb);
 }
 
 }  // namespace stl
