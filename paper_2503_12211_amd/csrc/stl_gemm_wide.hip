@@ -1,7 +1,7 @@
 // Pipelined plane products whose first operand is stored [row][l] (the forward products Yhat[p] = Xhat[p] What[p] and
 // the input-gradient products dXhat[p] = dYhat[p] What[p]^T), with that operand fetched as whole 128-byte lines.
 //
-// Same kernel as gemm_pipe_kernel in every other respect (256 x 256 block, eight wavefronts of 128 x 64, 32x32x16
+// Same kernel as gemm_pipe_kernel in every other respect (256 x 256 block, eight wavefronts of 128 x 64, 16x16x32
 // MFMA, persistent block list, next block's first loads in flight during the epilogue, wavefront-private epilogue
 // slab), and the same products in the same order: results are bit-identical.  What differs is the path of the first
 // operand into LDS (SrcWide / FragWide in stl_gemm_pipe.h): slots of 64 contraction elements that serve two stages
@@ -20,9 +20,9 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
                                                              int tiles_n, int total, int a_pg, int b_pg, int o_pg, int batch)
 {
     using namespace pipe;
-    constexpr int BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = 4, FN = 2, SWZ = 2, NSB = 4;
+    constexpr int BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = WM / 16, FN = WN / 16, NSB = 4;
     constexpr int A_SLOT = BM * 128, B_STAGE = BN * BKS * 2, B_BASE = 3 * A_SLOT;
-    constexpr int RP = 16, PITCH = WN * 2 + 16, SLAB = RP * PITCH;
+    constexpr int SLAB = slab_bytes<FM, FN, bf16_t>();
     static_assert(B_BASE + NSB * B_STAGE == 160 * 1024 && NW * SLAB <= A_SLOT, "LDS map");
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: LDS-DMA destinations stay in SGPRs
@@ -33,21 +33,19 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
     const uint32_t smem_lds = (uint32_t)(uintptr_t)STL_LDS(smem);
 
     FragWide<BM> fa;
-    Frag<B_T, SWZ, BN> fb;
+    Frag<B_T, BN> fb;
     fa.init(wm * WM, lane);
     fb.init(wn * WN, lane);
 
     auto locate = [&](int v, int &p, int &i0, int &j0) {
-        int lid = v;
-        if ((total & 7) == 0 && (gridDim.x & 7) == 0) lid = (v & 7) * (total >> 3) + (v >> 3);
-        p = lid / per_plane;
-        const int rem = lid - p * per_plane;
+        p = v / per_plane;
+        const int rem = v - p * per_plane;
         i0 = (rem / tiles_n) * BM;
         j0 = (rem % tiles_n) * BN;
     };
 
     SrcWide<BM, NW> sa;
-    Src<B_T, SWZ, BN, NW> sb;
+    Src<B_T, BN, NW, false> sb;
     // LDS addresses: first-operand slot of pair j, second-operand stage s
     auto a_slot = [&](int pair) { return (pair % 3) * A_SLOT; };
     auto b_slot = [&](int s) { return B_BASE + (s % NSB) * B_STAGE; };
@@ -55,35 +53,34 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
     // the second): H0 B0 H1 B1 H2 B2 H3 before the loop, then H(s+4) B(s+3) in iteration s -- four instructions per
     // iteration as long as both exist.
     auto start_block = [&](int v) {
+        // the lane id as an opaque value: what the sources derive from it is computed per block and occupies no registers while
+        // the products run (spilled values would be reloaded between the loads issued here, and waited for with them)
+        int sl = lane;
+        asm volatile("" : "+v"(sl));
         int p, i0, j0;
         locate(v, p, i0, j0);
-        sa.init(A, Kl, i0, Mi, wave, lane, p, batch, a_pg, 0);
-        sb.init(B, B_T ? Nj : Kl, j0, Nj, wave, lane, p, batch, b_pg, 0);
+        sa.init(A, Kl, i0, Mi, wave, sl, p, batch, a_pg, 0);
+        sb.init(B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, b_pg, 0, Kl);
         sa.template issue_half<0>(smem_lds + a_slot(0), wave);
-        sb.issue(smem_lds + b_slot(0), wave);
+        sb.issue(smem_lds + b_slot(0), wave, sl);
         sa.template issue_half<1>(smem_lds + a_slot(0), wave);
-        sb.issue(smem_lds + b_slot(1), wave);
+        sb.issue(smem_lds + b_slot(1), wave, sl);
         if (nks > 2) {
             sa.template issue_half<0>(smem_lds + a_slot(1), wave);
-            sb.issue(smem_lds + b_slot(2), wave);
+            sb.issue(smem_lds + b_slot(2), wave, sl);
             sa.template issue_half<1>(smem_lds + a_slot(1), wave);
         }
     };
 
-    int v = blockIdx.x;
-    if (v < total) start_block(v);
+    const int step = block_step(), end = end_block(total);
+    int v = first_block(total);
+    if (v < end) start_block(v);
 
-    for (; v < total; v += gridDim.x) {
+    WaveTile<FM, FN> w;
+    for (; v < end; v += step) {
         int p, i0, j0;
         locate(v, p, i0, j0);
-
-        f32x16_t acc[FM][FN];
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+        w.clear();
 
         // Loads complete in the order they were issued.  Before the first fragments are read H0, B0, H1 must have
         // landed: everything but the last eight instructions (B1 H2 B2 H3) when the contraction has more than one
@@ -92,16 +89,15 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
         if (nks > 2) wait_vmcnt<8>();
         else wait_vmcnt<2>();
         block_barrier();
-
-        bf16x8_t va[2][FM], vb[2][FN];      // fragment double buffer: [k16-step parity]
 #pragma unroll
-        for (int a = 0; a < FM; ++a) va[0][a] = fa.read(smem + a_slot(0), a, 0, 0);
+        for (int a = 0; a < FM; ++a) w.va[a] = fa.read(smem + a_slot(0), a, 0);
 #pragma unroll
-        for (int b = 0; b < FN; ++b) vb[0][b] = fb.read(smem + b_slot(0), b, 0);
+        for (int b = 0; b < FN; ++b) w.vb[0][b] = fb.read(smem + b_slot(0), b);
 
-        // One stage s = 2 * pair + SP (two k16-steps).  RA: half slot s + 4 of the first operand is fetched; RB: stage
-        // s + 3 of the second.  At the top of iteration s everything issued up to iteration s - 2 must have landed
-        // (stage s + 1 of both operands); what iteration s - 1 issued may still be in flight: WAIT instructions.
+        // One stage s = 2 * pair + SP.  RA: half slot s + 4 of the first operand is fetched; RB: stage s + 3 of the second.
+        // At the top of iteration s everything issued up to iteration s - 2 must have landed (stage s + 1 of both
+        // operands, whose fragments are fetched meanwhile; it lies in the same slot of the first operand when s is even); what
+        // iteration s - 1 issued may still be in flight: WAIT instructions.
         auto stage = [&](int s, auto sp_c, auto ra_c, auto rb_c, auto wait_c) {
             constexpr int SP = decltype(sp_c)::value, WAIT = decltype(wait_c)::value;
             constexpr bool RA = decltype(ra_c)::value, RB = decltype(rb_c)::value;
@@ -109,42 +105,20 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
             block_barrier();   // stage s+1 visible to all; nobody reads stage s-1 any more
             const int pair = s >> 1;
             const uint32_t dst_a = smem_lds + a_slot(pair + 2), dst_b = smem_lds + b_slot(s + NSB - 1);
-            const char *cur_a = smem + a_slot(pair), *nxt_a = smem + a_slot(pair + SP);
-            const char *nxt_b = smem + b_slot(s + 1), *cur_b = smem + b_slot(s);
-            auto step = [&](auto par_c, const char *src_a, int sp_src, const char *src_b, int ks, auto a_side_c) {
-                constexpr int par = decltype(par_c)::value;
-                constexpr bool a_side = decltype(a_side_c)::value;
-                static_for<0, FM * FN>([&](auto i_c) {
-                    constexpr int i = decltype(i_c)::value, a = i / FN, b = i % FN;
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[par][b], va[par][a], acc[a][b], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    // one fragment fetch per MFMA slot, in the order the next step consumes them: B0, A0, B1, A1, A2, A3
-                    if constexpr (i < FM + FN) {
-                        if constexpr (i < 2 * FN) {
-                            if constexpr ((i % 2) == 0) vb[par ^ 1][i / 2] = fb.read(src_b, i / 2, ks);
-                            else va[par ^ 1][i / 2] = fa.read(src_a, i / 2, ks, sp_src);
-                        } else {
-                            va[par ^ 1][i - FN] = fa.read(src_a, i - FN, ks, sp_src);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if constexpr (i >= 2 && (i % 2) == 0) {
-                        constexpr int j = (i - 2) / 2;       // DMA slot inside this step
-                        if constexpr (a_side) {
-                            if constexpr (RA && j < decltype(sa)::NI) sa.template issue_one<SP>(dst_a, wave, j);
-                        } else {
-                            if constexpr (RB && j < decltype(sb)::NI) sb.issue_one(dst_b, wave, j);
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                });
-            };
-            // step 0 (fetch k16-step 1 of stage s; refill the first operand), step 1 (fetch k16-step 0 of stage s+1;
-            // refill the second operand).  Stage s+1 lies in the same slot of the first operand when s is even.
-            step(std::integral_constant<int, 0>{}, cur_a, SP, cur_b, 1, std::true_type{});
-            step(std::integral_constant<int, 1>{}, nxt_a, SP ^ 1, nxt_b, 0, std::false_type{});
+            const char *nxt_a = smem + a_slot(pair + SP), *nxt_b = smem + b_slot(s + 1);
+            w.template stage<SP>([&](int f) { return fa.read(nxt_a, f, SP ^ 1); }, [&](int f) { return fb.read(nxt_b, f); },
+                                 [&](auto a_c) {
+                                     constexpr int a = decltype(a_c)::value, NA = decltype(sa)::NI, NB = decltype(sb)::NI;
+                                     static_for<0, NA + NB>([&](auto j_c) {
+                                         constexpr int j = decltype(j_c)::value;
+                                         if constexpr (j * FM / (NA + NB) == a) {
+                                             if constexpr (RA && j < NA) sa.template issue_one<SP>(dst_a, wave, j);
+                                             if constexpr (RB && j >= NA) sb.issue_one(dst_b, wave, j - NA);
+                                         }
+                                     });
+                                 });
             if constexpr (RA) sa.template next_pair<SP>();
-            if constexpr (RB) sb.next_stage();
+            if constexpr (RB) sb.next_stage(wave, lane);
         };
         using T_ = std::true_type;
         using F_ = std::false_type;
@@ -170,49 +144,17 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
 
         // every wavefront is done with the ring: refill it for the next block before storing this one
         block_barrier();
-        if (v + (int)gridDim.x < total) start_block(v + gridDim.x);
-
-        // Epilogue, as in gemm_pipe_kernel: accumulator e of fragment (a, b) is
-        //   Out[row = 32a + lane%32][column = 32b + 8*(e/4) + 4*(lane/32) + e%4]
-        bf16_t *outp = Out + (size_t)p * o_pg * Nj;
-        const int frow = lane & 31, fhalf = lane >> 5;
-        constexpr int LPR = WN * 2 / 16, RPI = 64 / LPR;
-        static_for<0, FM>([&](auto a_c) {
-            constexpr int a = decltype(a_c)::value;
-            static_for<0, 32 / RP>([&](auto pass_c) {
-                constexpr int pass = decltype(pass_c)::value;
-                if ((frow / RP) == pass) {
-                    char *rowp = slab + (frow % RP) * PITCH;
-#pragma unroll
-                    for (int b = 0; b < FN; ++b)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            const int cc = b * 32 + 8 * g + 4 * fhalf;
-                            const u32x2_t w = {pack_bf16x2(acc[a][b][4 * g], acc[a][b][4 * g + 1]),
-                                               pack_bf16x2(acc[a][b][4 * g + 2], acc[a][b][4 * g + 3])};
-                            *reinterpret_cast<u32x2_t *>(rowp + cc * 2) = w;
-                        }
-                }
-                asm volatile("" ::: "memory");
-                const int gi_base = i0 + wm * WM + a * 32 + pass * RP;
-                const size_t row_off = plane_row_base(gi_base < Mi ? gi_base : 0, o_pg, batch, Nj);
-                const int gj = j0 + wn * WN + (lane % LPR) * 8;
-#pragma unroll
-                for (int it = 0; it < RP / RPI; ++it) {
-                    const int rr = it * RPI + lane / LPR;
-                    const int gi = gi_base + rr;
-                    const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + rr * PITCH + (lane % LPR) * 16);
-                    if (gi < Mi && gj < Nj) *reinterpret_cast<u32x4_t *>(outp + row_off + (size_t)rr * Nj + gj) = w;
-                }
-                asm volatile("" ::: "memory");
-            });
-        });
+        if (v + step < end) start_block(v + step);
+        int el = lane;                                   // opaque, as above
+        asm volatile("" : "+v"(el));
+        w.template store<bf16_t, false, false>(slab, Out + (size_t)p * o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, o_pg, batch,
+                                                   el);
     }
 }
 
 bool plane_gemm_wide_eligible(const GemmDesc &g)
 {
-    return plane_gemm_pipe_eligible(g) && !g.a_kmajor && !g.out_f32 && !g.accumulate && g.nb == 1 && g.Kl % 64 == 0;
+    return plane_gemm_pipe_eligible(g) && !g.a_kmajor && !g.out_f32 && !g.accumulate && g.nb == 1 && g.Kl % 64 == 0 && pipe_block(g) == PipeBlock::b256;
 }
 
 static int wide_cu_count()
@@ -237,8 +179,7 @@ static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, v
     const int tiles_m = (g.Mi + 255) / 256, tiles_n = (g.Nj + 255) / 256;
     const long total = (long)tiles_m * tiles_n * g.batch;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
-    const int cus = wide_cu_count();
-    const unsigned grid = (unsigned)(total > cus ? cus : total);
+    const unsigned grid = pipe::list_grid(total, wide_cu_count());
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, (const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl,
                        tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
     return hipGetLastError();

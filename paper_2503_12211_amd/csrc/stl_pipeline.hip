@@ -70,10 +70,10 @@ template <bool GELU>
 __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
 {
     using namespace pipe;
-    constexpr int NS = 4, SWZ = 2, BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = 4, FN = 2;
+    constexpr int NS = 4, BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = WM / 16, FN = WN / 16;
     constexpr int OPER_BYTES = BM * BKS * 2, STAGE_BYTES = (BM + BN) * BKS * 2;
     constexpr int DMA_PER_STAGE = (BM + BN) / 16 / NW;
-    constexpr int RP = 16, PITCH = WN * 2 + 16, SLAB = RP * PITCH;     // epilogue staging per wavefront
+    constexpr int SLAB = 16 * WN * 2;                    // epilogue staging per wavefront: one fragment row
     constexpr int PG = kPlaneGroup;
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -89,12 +89,12 @@ __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
     const int chunks_k = Kl / 64, chunks_n = (Nj + 63) / 64;
     const RowMap rm;
 
-    Frag<false, SWZ, BM> fa;
-    Frag<true, SWZ, BN> fb;
+    Frag<false, BM> fa;
+    Frag<true, BN> fb;
     fa.init(wm * WM, lane);
     fb.init(wn * WN, lane);
-    Src<false, SWZ, BM, NW> sa;
-    Src<true, SWZ, BN, NW> sb;
+    Src<false, BM, NW, false> sa;
+    Src<true, BN, NW, false> sb;
 
     // ---- the list -------------------------------------------------------------------------------------------------
     enum { K_NONE = 0, K_GEMM = 1, K_GEMM_EMPTY = 2, K_ENC = 3, K_DEC = 4 };
@@ -161,13 +161,13 @@ __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
     const unsigned enc_target = 8u * (unsigned)a.nT, gemm_target = 8u * (unsigned)a.nG;
 
     auto start_block = [&](const Item &it) {   // point the DMA sources at the block and put its first NS-1 stages in flight
-        sa.init(a.Xhat, Kl, it.rb * BM, Mi, wave, lane, it.p, batch, PG, 0);
-        sb.init(a.What, Nj, it.bj * BN, Nj, wave, lane, it.p, batch, Kl, 0);
+        sa.init(a.Xhat, Kl, it.rb * BM, Mi, wave, lane, it.p, batch, PG, 0, Kl);
+        sb.init(a.What, Nj, it.bj * BN, Nj, wave, lane, it.p, batch, Kl, 0, Kl);
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) {
             if (s < nks) {
-                sa.issue(smem_lds + s * STAGE_BYTES, wave);
-                sb.issue(smem_lds + s * STAGE_BYTES + OPER_BYTES, wave);
+                sa.issue(smem_lds + s * STAGE_BYTES, wave, lane);
+                sb.issue(smem_lds + s * STAGE_BYTES + OPER_BYTES, wave, lane);
             }
         }
     };
@@ -182,26 +182,20 @@ __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
                 start_block(it);
             }
             const int i0 = it.rb * BM, j0 = it.bj * BN;
-            f32x16_t acc[FM][FN];
-#pragma unroll
-            for (int x = 0; x < FM; ++x)
-#pragma unroll
-                for (int y = 0; y < FN; ++y)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+            WaveTile<FM, FN> w;
+            w.clear();
 
             if (nks > NS - 2) wait_vmcnt<DMA_PER_STAGE * (NS - 2)>();
             else wait_vmcnt<0>();
             block_barrier();
-
-            bf16x8_t va[2][FM], vb[2][FN];      // fragment double buffer: [k16-step parity]
 #pragma unroll
-            for (int x = 0; x < FM; ++x) va[0][x] = fa.read(smem, x, 0);
+            for (int x = 0; x < FM; ++x) w.va[x] = fa.read(smem, x);
 #pragma unroll
-            for (int y = 0; y < FN; ++y) vb[0][y] = fb.read(smem + OPER_BYTES, y, 0);
+            for (int y = 0; y < FN; ++y) w.vb[0][y] = fb.read(smem + OPER_BYTES, y);
 
-            // one stage = two k16-steps; the same instruction order as the stand-alone plane-product kernel
-            auto stage = [&](int s, auto refill_c) {
+            // one stage; the same products in the same order as the stand-alone plane-product kernels
+            auto stage = [&](int s, auto par_c, auto refill_c) {
+                constexpr int PAR = decltype(par_c)::value;
                 constexpr bool REFILL = decltype(refill_c)::value;
                 if (s + 1 < nks) {
                     if (REFILL || s + NS - 2 < nks) wait_vmcnt<DMA_PER_STAGE * (NS - 3)>();
@@ -209,46 +203,40 @@ __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
                 }
                 block_barrier();
                 const uint32_t dst = smem_lds + ((s + NS - 1) % NS) * STAGE_BYTES;
-                const char *cur = smem + (s % NS) * STAGE_BYTES;
                 const char *nxt = smem + ((s + 1) % NS) * STAGE_BYTES;
-                auto step = [&](auto par_c, const char *src, int ks, auto a_side_c) {
-                    constexpr int par = decltype(par_c)::value;
-                    constexpr bool a_side = decltype(a_side_c)::value;
-                    static_for<0, FM * FN>([&](auto i_c) {
-                        constexpr int i = decltype(i_c)::value, x = i / FN, y = i % FN;
-                        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vb[par][y], va[par][x], acc[x][y], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (i < FM + FN) {
-                            constexpr int pairs = FM < FN ? FM : FN;
-                            if constexpr (i < 2 * pairs) {
-                                if constexpr ((i % 2) == 0) vb[par ^ 1][i / 2] = fb.read(src + OPER_BYTES, i / 2, ks);
-                                else va[par ^ 1][i / 2] = fa.read(src, i / 2, ks);
-                            } else {
-                                va[par ^ 1][i - pairs] = fa.read(src, i - pairs, ks);
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                        if constexpr (REFILL && i >= 2 && (i % 2) == 0) {
-                            constexpr int j = (i - 2) / 2;
-                            if constexpr (a_side) {
-                                if constexpr (j < decltype(sa)::NI) sa.issue_one(dst, wave, j);
-                            } else {
-                                if constexpr (j < decltype(sb)::NI) sb.issue_one(dst + OPER_BYTES, wave, j);
-                            }
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                    });
-                };
-                step(std::integral_constant<int, 0>{}, cur, 1, std::true_type{});
-                step(std::integral_constant<int, 1>{}, nxt, 0, std::false_type{});
+                w.template stage<PAR>([&](int f) { return fa.read(nxt, f); }, [&](int f) { return fb.read(nxt + OPER_BYTES, f); },
+                                      [&](auto a_c) {
+                                          constexpr int x = decltype(a_c)::value, NA = decltype(sa)::NI, NB = decltype(sb)::NI;
+                                          static_for<0, NA + NB>([&](auto j_c) {
+                                              constexpr int j = decltype(j_c)::value;
+                                              if constexpr (REFILL && j * FM / (NA + NB) == x) {
+                                                  if constexpr (j < NA) sa.issue_one(dst, wave, j);
+                                                  else sb.issue_one(dst + OPER_BYTES, wave, j - NA);
+                                              }
+                                          });
+                                      });
                 if constexpr (REFILL) {
-                    sa.next_stage();
-                    sb.next_stage();
+                    sa.next_stage(wave, lane);
+                    sb.next_stage(wave, lane);
                 }
             };
-            const int n_refill = nks > NS - 1 ? nks - (NS - 1) : 0;
-            for (int s = 0; s < n_refill; ++s) stage(s, std::true_type{});
-            for (int s = n_refill; s < nks; ++s) stage(s, std::false_type{});
+            using I0 = std::integral_constant<int, 0>;
+            using I1 = std::integral_constant<int, 1>;
+            // nks is even (K is a multiple of 64 tiles), the last three stages refill nothing
+            int s = 0;
+            for (; s + 4 < nks; s += 2) {
+                stage(s, I0{}, std::true_type{});
+                stage(s + 1, I1{}, std::true_type{});
+            }
+            if (s + 3 < nks) {
+                stage(s, I0{}, std::true_type{});
+                stage(s + 1, I1{}, std::false_type{});
+                s += 2;
+            }
+            for (; s < nks; s += 2) {
+                stage(s, I0{}, std::false_type{});
+                stage(s + 1, I1{}, std::false_type{});
+            }
 
             // every wavefront is done with the ring.  Take the next ticket now: if it is a product block whose rows are
             // already encoded, its first stages go in flight before this block is stored.
@@ -260,40 +248,7 @@ __global__ __launch_bounds__(512) void forward_pipeline_kernel(const FwdPipe a)
                 prefetched = true;
             }
 
-            // Epilogue: accumulator e of fragment (x, y) is Out[row 32x + lane%32][column 32y + 8(e/4) + 4(lane/32) + e%4]
-            bf16_t *outp = a.Yhat + (size_t)it.p * PG * Nj;
-            const int frow = lane & 31, fhalf = lane >> 5;
-            constexpr int LPR = WN * 2 / 16, RPI = 64 / LPR;
-            static_for<0, FM>([&](auto x_c) {
-                constexpr int x = decltype(x_c)::value;
-                static_for<0, 32 / RP>([&](auto pass_c) {
-                    constexpr int pass = decltype(pass_c)::value;
-                    if ((frow / RP) == pass) {
-                        char *rowp = slab + (frow % RP) * PITCH;
-#pragma unroll
-                        for (int y = 0; y < FN; ++y)
-#pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                const int cc = y * 32 + 8 * g + 4 * fhalf;
-                                const u32x2_t w = {pack_bf16x2(acc[x][y][4 * g], acc[x][y][4 * g + 1]),
-                                                   pack_bf16x2(acc[x][y][4 * g + 2], acc[x][y][4 * g + 3])};
-                                *reinterpret_cast<u32x2_t *>(rowp + cc * 2) = w;
-                            }
-                    }
-                    asm volatile("" ::: "memory");
-                    const int gi_base = i0 + wm * WM + x * 32 + pass * RP;
-                    const size_t row_off = plane_row_base(gi_base < Mi ? gi_base : 0, PG, batch, Nj);
-                    const int gj = j0 + wn * WN + (lane % LPR) * 8;
-#pragma unroll
-                    for (int k = 0; k < RP / RPI; ++k) {
-                        const int rr = k * RPI + lane / LPR;
-                        const int gi = gi_base + rr;
-                        const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + rr * PITCH + (lane % LPR) * 16);
-                        if (gi < Mi && gj < Nj) store16<true>(outp + row_off + (size_t)rr * Nj + gj, w);
-                    }
-                    asm volatile("" ::: "memory");
-                });
-            });
+            w.template store<bf16_t, false, true, 1>(slab, a.Yhat + (size_t)it.p * PG * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, PG, batch, lane);
             signal(kCtrBase + a.nrb + it.rb);
             t = tn;
             continue;
