@@ -472,6 +472,10 @@ stl_status_t stl_encode_weight_backward(const stl_problem_t *prob, const void *W
     char *base = (char *)ws;
     float *part = (float *)(base + w.part);
     const void *planes = dWhat;
+    if (dt == STL_BF16 && d.N >= 8 && (dW || dE_W)) {
+        STL_HIP(stl::launch_decode_outer_f32(dWhat, E_W, dW, W, dE_W, part, d.K, d.N, d.r, accumulate, s), "encode_weight_backward/dW + dE_W");
+        return STL_OK;
+    }
     if (dt == STL_BF16 && (dW || dE_W)) {
         STL_HIP(stl::launch_cast_bf16(dWhat, base + w.planes, (size_t)d.r * d.K * d.N, s), "encode_weight_backward/round dWhat");
         planes = base + w.planes;

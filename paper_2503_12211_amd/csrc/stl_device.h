@@ -132,6 +132,36 @@ __device__ __forceinline__ f32x4_t load4(const T *p, int n)
     return v;
 }
 
+// Eight consecutive plane elements on their way from memory to LDS as bf16: held as loaded, so that a prefetch does not wait
+// for its data, and rounded (fp32 planes) when they are taken.
+template <typename T, bool ANY>
+struct Raw8 {
+    u32x4_t v;
+    __device__ __forceinline__ void load(const T *p, int n) { v = load8<ANY>(p, n); }
+    __device__ __forceinline__ u32x4_t take() const { return v; }
+};
+template <bool ANY>
+struct Raw8<float, ANY> {
+    f32x4_t a, b;
+    __device__ __forceinline__ void load(const float *p, int n)
+    {
+        if constexpr (ANY) {
+            a = load4<float>(p, n);
+            b = load4<float>(p + 4, n - 4);
+        } else {
+            a = b = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (n > 0) {
+                a = *reinterpret_cast<const f32x4_t *>(p);
+                b = *reinterpret_cast<const f32x4_t *>(p + 4);
+            }
+        }
+    }
+    __device__ __forceinline__ u32x4_t take() const
+    {
+        return u32x4_t{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(b[0], b[1]), pack_bf16x2(b[2], b[3])};
+    }
+};
+
 // one row of a tile (4 elements, aligned to their size)
 __device__ __forceinline__ void store4(float *p, f32x4_t v) { *reinterpret_cast<f32x4_t *>(p) = v; }
 __device__ __forceinline__ void store4(bf16_t *p, f32x4_t v)

@@ -60,6 +60,9 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
 int decode_outer_blocks(int R, int Cc);
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
+// the same from fp32 planes into a bf16 matrix (plane-major, Cc >= 8); W or G may be NULL
+hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const void *V, float *G, float *part, int R, int Cc, int r,
+                                   int accumulate, hipStream_t s);
 int outer_reduce_blocks(int64_t tiles);     // a further bound on the partials, for the declared workspace sizes
 
 // G[i] (+)= sum over nb partials part[b][i], i < n_out, in block order (second stage of the basis-gradient sums)

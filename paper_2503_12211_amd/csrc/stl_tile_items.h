@@ -169,9 +169,10 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 
 // The item loop of one wavefront, items as in encode_items.  slab: KC * 32 * 128 bytes of LDS private to the
 // wavefront; sT: 64 x 32 bytes (OUTER only); oacc accumulates the basis gradient (OUTER).  No workgroup barrier inside.
-// DECODE = false: the basis gradient alone (Dm and Cmat unused).
-template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true>   // DEPTH, ANY as in encode_items
-__device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
+// DECODE = false: the basis gradient alone (Dm and Cmat unused).  TP: storage type of the planes; fp32 planes (the gradient of
+// an encoded weight) are rounded to bf16 on their way into LDS.
+template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t>   // DEPTH, ANY as in encode_items
+__device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
                                              int R, int Cc, int r, int chunks, const bf16_t *__restrict__ V, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane)
 {
@@ -206,7 +207,7 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
     // instruction; with OUTER also tile J0 + lane of V (4 rows x 8 bytes).  The NEXT item's operands are fetched into
     // registers while the current item is computed and stored.
     const int pr = lane >> 3, ch = lane & 7;
-    u32x4_t pre[DEPTH][KC * 4];
+    Raw8<TP, ANY> pre[DEPTH][KC * 4];
     u32x2_t xpre[DEPTH][OUTER ? 4 : 1];
     auto fetch = [&](int d, long item) {
         const int Ii = (int)(item / chunks), cki = (int)(item - (long)Ii * chunks);
@@ -217,7 +218,7 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
         for (int g8 = 0; g8 < KC * 4; ++g8) {
             const int pl = 8 * g8 + pr;
             // planes >= r stay zero (they meet zero D entries, but must be finite)
-            pre[d][g8] = load8<ANY>(P + rowb + (size_t)pl * plane + Jl, Ii < R && pl < r ? Cc - Jl : 0);
+            pre[d][g8].load(P + rowb + (size_t)pl * plane + Jl, Ii < R && pl < r ? Cc - Jl : 0);
         }
         if (OUTER) {
             const int Jt = cki * 64 + lane, nv = rm.valid(Ia);
@@ -248,7 +249,7 @@ __device__ __forceinline__ void decode_items(const bf16_t *__restrict__ P, const
 #pragma unroll
         for (int g8 = 0; g8 < KC * 4; ++g8) {
             const int pl = 8 * g8 + pr;
-            *reinterpret_cast<u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4)) = pre[d][g8];
+            *reinterpret_cast<u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4)) = pre[d][g8].take();
         }
         if (OUTER) {
             // lane = tile J0 + lane: its 16 entries (4 rows x 8 bytes) as two 16-byte writes, tile-major; they come back

@@ -200,9 +200,9 @@ __global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restri
 // OUTER: the same pass also accumulates the basis gradient G (r x 16) += P (r x tiles) . tileview(V) (tiles x 16)
 // (dE_X with P = dXhat, V = X while dX is decoded), so that the planes are read from HBM once for both results;
 // every block writes one partial to `part`, added up in block order by outer_final_kernel.  DECODE = false: G alone.
-// ANY: column counts that are no multiple of 8 (see load8).
-template <bool GELU, int KC, bool OUTER, bool ANY = false, bool DECODE = true>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
-__global__ __launch_bounds__(256) void decode_mfma_kernel(const bf16_t *__restrict__ P, const bf16_t *__restrict__ Dm,
+// ANY: column counts that are no multiple of 8 (see load8).  TP: storage type of the planes.
+template <bool GELU, int KC, bool OUTER, bool ANY = false, bool DECODE = true, typename TP = bf16_t>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
+__global__ __launch_bounds__(256) void decode_mfma_kernel(const TP *__restrict__ P, const bf16_t *__restrict__ Dm,
                                                           bf16_t *__restrict__ Cmat, int R, int Cc, int r, int chunks,
                                                           const bf16_t *__restrict__ V, float *__restrict__ part, int pg,
                                                           RowMap rm)
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(const bf16_t *__restri
 #pragma unroll
     for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // wavefront w of block b takes items 4b + w, 4b + w + 4 * gridDim.x, ...
-    decode_items<GELU, KC, OUTER, 1, ANY, DECODE>(P, Dm, Cmat, R, Cc, r, chunks, V, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
+    decode_items<GELU, KC, OUTER, 1, ANY, DECODE, TP>(P, Dm, Cmat, R, Cc, r, chunks, V, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
                                   (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], oacc, lane);
     if (OUTER) {
         // accumulator e of group g: plane 16g + 4*kq + e, tile entry j; fixed-order sum over the four wavefronts
@@ -447,6 +447,34 @@ static auto pick_decode_outer(int r, const void *Cmat)
 {
     if (r <= 32) return Cmat ? decode_mfma_kernel<false, 1, true, ANY, true> : decode_mfma_kernel<false, 1, true, ANY, false>;
     return Cmat ? decode_mfma_kernel<false, 2, true, ANY, true> : decode_mfma_kernel<false, 2, true, ANY, false>;
+}
+
+// bf16 matrix from fp32 planes (plane-major): W <- decode(P, E) and, unless G is NULL, G (+)= P . tileview(V), the planes rounded to
+// bf16 once.  Reading them as they are saves the pass that stored a rounded copy: 4096 x 4096, r = 32 (134 MB of planes), 40 + 28 us
+// as rounding pass + decode, now 43 (4.7 TB/s).
+hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const void *V, float *G, float *part, int R, int Cc, int r,
+                                   int accumulate, hipStream_t s)
+{
+    if (R <= 0 || Cc < 8) return hipErrorInvalidValue;
+    const RowMap rm;
+    const int chunks = (Cc + 63) / 64;
+    const bf16_t *e = (const bf16_t *)E, *v = (const bf16_t *)V;
+    bf16_t *w = (bf16_t *)W;
+    if (!G) {
+        const long items = (long)R * chunks, blocks = (items + 3) / 4;
+        auto kern = r <= 32 ? (Cc % 8 ? decode_mfma_kernel<false, 1, false, true, true, float> : decode_mfma_kernel<false, 1, false, false, true, float>)
+                            : (Cc % 8 ? decode_mfma_kernel<false, 2, false, true, true, float> : decode_mfma_kernel<false, 2, false, false, true, float>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks)), dim3(256), 0, s, P, e, w, R, Cc, r, chunks, v, part, R, rm);
+        return hipGetLastError();
+    }
+    const int nb = decode_outer_blocks(R, Cc);
+    auto kern = W ? (r <= 32 ? (Cc % 8 ? decode_mfma_kernel<false, 1, true, true, true, float> : decode_mfma_kernel<false, 1, true, false, true, float>)
+                             : (Cc % 8 ? decode_mfma_kernel<false, 2, true, true, true, float> : decode_mfma_kernel<false, 2, true, false, true, float>))
+                  : (r <= 32 ? (Cc % 8 ? decode_mfma_kernel<false, 1, true, true, false, float> : decode_mfma_kernel<false, 1, true, false, false, float>)
+                             : (Cc % 8 ? decode_mfma_kernel<false, 2, true, true, false, float> : decode_mfma_kernel<false, 2, true, false, false, float>));
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, P, e, w, R, Cc, r, chunks, v, part, R, rm);
+    const hipError_t err = hipGetLastError();
+    return err != hipSuccess ? err : launch_outer_final(part, G, nb, r * 16, accumulate, s);
 }
 
 // Cmat == nullptr: the basis gradient alone

@@ -64,3 +64,30 @@ def test_recode_any_width(gu, r1, R, N1, r2):
         stl.stl_recode(up, down, Y, D, E, Q, H, flags)
         out.append(gu.planes_to_host(Q, r2, R, N1))
     assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("K,N,r", [(3, 8, 32), (9, 65, 24), (16, 72, 49), (5, 250, 64)])
+def test_encode_weight_backward_from_f32_planes(gu, K, N, r):
+    """Gradients through the weight encoding with the fp32 planes read directly, each output alone and both together: dW
+    sees the planes' rounding to bf16 and its own (2.3e-3 rms), dE_W the planes' alone."""
+    import torch
+
+    import paper_2503_12211_amd as stl
+    rng = np.random.default_rng(K + N + r)
+    W = stl_synth.round_to(rng.standard_normal((4 * K, 4 * N)), "bf16")
+    E = stl_synth.round_to(rng.standard_normal((r, 16)) / 4, "bf16")
+    dWh = rng.standard_normal((r, K, N)).astype(np.float32)
+    ref = dict(zip(("dW", "dE"), planes.encode_weight_backward(W, E, dWh)))
+    prob = stl.Problem(4, 4 * K, 4 * N, r)
+    nb = stl.stl_workspace_bytes(prob, stl.STL_OP_ENCODE_WEIGHT_BACKWARD)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    first = None
+    for want in (("dW", "dE"), ("dW",), ("dE",)):
+        dW = torch.full((4 * K, 4 * N), float("nan"), dtype=torch.bfloat16, device="cuda") if "dW" in want else None
+        dE = torch.full((r, 16), float("nan"), device="cuda") if "dE" in want else None
+        stl.stl_encode_weight_backward(prob, gu.dev(W, "bf16"), gu.dev(E, "bf16"), torch.from_numpy(dWh).cuda(), dW, dE, 0, ws, nb)
+        got = {"dW": dW, "dE": dE}
+        for name in want:
+            assert gu.rel(gu.host(got[name]), ref[name]) <= gu.TOL["bf16"], (want, name)
+        first = first or {n: t.clone() for n, t in got.items()}
+        assert all(torch.equal(got[n], first[n]) for n in want)
