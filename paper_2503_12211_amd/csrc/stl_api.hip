@@ -536,12 +536,14 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
     if (!X || !What || !E_X || !D || !C) return fail(STL_ERR_INVALID_ARG, "stl_forward: NULL pointer");
     if (any_misaligned(X, What, E_X, D, C, Xhat_save, Yhat_save))
         return fail(STL_ERR_INVALID_ARG, "stl_forward: pointer not 16-byte aligned");
-    // Automatic choice: the single-launch variant where the whole operator is launch-bound (measured: it wins up to
-    // about four million tile products per plane set, e.g. m = 128, k = n = 512, r = 8: one launch of ~10 us against
-    // three of ~5 us), the three-launch path everywhere else.
+    // Automatic choice: the single-launch variant where the whole operator is launch-bound -- up to about four million tile
+    // products per plane set, and at r <= 8 wherever every CU has at most one block and the chain of contraction steps is short
+    // (m = 128 / 256 / 1024 / 4096, k = n = 512, r = 8: 10.5 / 10.6 / 10.7 / 11.1 us a call against 13.2 / 13.1 / 13.0 / 13.1 of three launches; at
+    // m = 32, k = 1024, n = 512 16.8 against 14.7) -- the three-launch path everywhere else.
     const FwdWs w_declared = fwd_layout(d, variant);     // the workspace is checked against what the caller asked for
     if (variant == STL_FLAG_AUTO && !Xhat_save && stl::block_forward_eligible(prob->dtype, d.M, d.K, d.N, d.r) &&
-        (double)d.M * d.K * d.N * d.r <= 4.2e6)
+        ((double)d.M * d.K * d.N * d.r <= 4.2e6 ||
+         (d.r <= 8 && d.K <= 128 && (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) <= 256)))
         variant = STL_FLAG_FUSED;
     if (variant == STL_FLAG_PIPELINED && !stl::forward_pipeline_eligible(prob->dtype, d.M, d.K, d.N, d.r))
         return fail(STL_ERR_UNSUPPORTED,

@@ -17,14 +17,14 @@
 // kernel moves 26 GB through L2 at 20 TB/s, the rate the L2 -> LDS path gives).  It wins only where the whole
 // operator is bound by launch latency: one launch instead of three for problems of a few microseconds, which is
 // where the automatic variant choice uses it.
-#include "stl_kernels.h"
-#include "stl_device.h"
+#include "stl_gemm_pipe.h"
 
 namespace stl {
 namespace fused {
 
-typedef short v4i16_t __attribute__((ext_vector_type(4)));
-#define STL_LDS_PTR(p) ((__attribute__((address_space(3))) char *)(p))
+using pipe::block_barrier;
+using pipe::dma16;
+using pipe::v4i16_t;
 
 constexpr int BI = 32, BJ = 32, KC = 16;          // block: 32 x 32 tiles, 16 tile columns of X per step
 constexpr int SX_BYTES = 4 * BI * KC * 4 * 2;     // X sub-block: 128 rows x 64 entries  = 16 KB
@@ -38,16 +38,7 @@ constexpr int smem_bytes()
     return (loop > exch ? loop : exch) + SD_BYTES;
 }
 
-__device__ __forceinline__ void dma16(const bf16_t *g, uint32_t lds_wave_base)
-{
-    // LDS-DMA, 16 bytes per lane, lane L lands at lds_wave_base + 16 L.  Inline assembly so that the loop below
-    // orders these loads itself (vmcnt + barrier) instead of the compiler draining them before every LDS read.
-    const uint32_t l = __builtin_amdgcn_readfirstlane(lds_wave_base);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");
-}
-__device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // ENCODE: true = FUSED (reads X), false = EPILOGUE (reads Xhat).  RP: planes padded to 8, 16 or 32 (sizes the LDS
 // stages and the accumulators, so that small r leaves room for several workgroups per CU).
@@ -67,7 +58,7 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
     char *sXh = smem + 2 * A_STAGE;                   // FUSED only: encoded stage, single buffer
     char *sW = sXh + (ENCODE ? SXH_BYTES : 0);        // 2 stages
     float *sD = reinterpret_cast<float *>(smem + smem_bytes<RP, ENCODE>() - SD_BYTES);
-    const uint32_t lds0 = (uint32_t)(uintptr_t)STL_LDS_PTR(smem);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)STL_LDS(smem);
     const uint32_t ldsA = lds0, ldsW = lds0 + (uint32_t)(sW - smem);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -159,8 +150,8 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
     const int nch = K / KC;
     issue(0);
     for (int c = 0; c < nch; ++c) {
-        wait_dma();
-        barrier();                                    // stage c landed for all; stage c+1's buffers are free
+        pipe::wait_vmcnt<0>();
+        block_barrier();                                    // stage c landed for all; stage c+1's buffers are free
         if (c + 1 < nch) issue((c + 1) & 1);
         const char *stA = sA + (c & 1) * A_STAGE;
         const char *stW = sW + (c & 1) * SW_BYTES;
@@ -195,7 +186,7 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
                 }
             }
             wait_lds();
-            barrier();                                // encoded stage visible to all wavefronts
+            block_barrier();                                // encoded stage visible to all wavefronts
         }
 #pragma unroll
         for (int t = 0; t < PW; ++t) {
@@ -203,9 +194,9 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
             if (p < r) {
                 const bf16x8_t a = *reinterpret_cast<const bf16x8_t *>(stXh + p * 1024 + offA);
                 const v4i16_t b0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) v4i16_t *)STL_LDS_PTR(stW + p * 1024 + offB[0]));
+                    (__attribute__((address_space(3))) v4i16_t *)STL_LDS(stW + p * 1024 + offB[0]));
                 const v4i16_t b1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) v4i16_t *)STL_LDS_PTR(stW + p * 1024 + offB[1]));
+                    (__attribute__((address_space(3))) v4i16_t *)STL_LDS(stW + p * 1024 + offB[1]));
                 struct { v4i16_t lo, hi; } both = {b0, b1};
                 acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8_t, both), acc[t], 0, 0, 0);
             }
@@ -213,7 +204,7 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
     }
 
     // ---- exchange: accumulator e of plane p is Yhat[p][I = 8*(e/4) + 4h + e%4][J = lane%32] ---------------------
-    barrier();
+    block_barrier();
     float *sY = reinterpret_cast<float *>(smem);      // [p][I][J]
 #pragma unroll
     for (int t = 0; t < PW; ++t) {
@@ -225,28 +216,41 @@ __global__ __launch_bounds__(256) void stl_block_kernel(const bf16_t *__restrict
     }
     __syncthreads();
 
-    // ---- decode: 4 tiles per thread ---------------------------------------------------------------------------
-#pragma unroll 1
-    for (int it = 0; it < 4; ++it) {
-        const int id = tid + 256 * it, I = id >> 5, J = id & 31;
-        const int gi = I0 + I, gj = J0 + J;
-        float cq[16];
+    // ---- decode: 4 tiles per thread, all four per plane so that the decoder's row is read from LDS once (tile after tile, with
+    // a chain of dependent LDS reads per plane, the decode was most of the time of a small problem at larger ranks) ------------
+    float cq[4][16];
 #pragma unroll
-        for (int q = 0; q < 16; ++q) cq[q] = 0.f;
-        for (int p = 0; p < r; ++p) {
-            const float y = sY[(p * BI + I) * BJ + J];
-            if (Ysave != nullptr && gi < M && gj < N) Ysave[plane_row_base(gi, pg, r, N) + (size_t)p * pg * N + gj] = f32_to_bf16(y);
+    for (int it = 0; it < 4; ++it)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) cq[q] = fmaf(sD[p * 16 + q], y, cq[q]);
+        for (int q = 0; q < 16; ++q) cq[it][q] = 0.f;
+    const int I = tid >> 5, J = tid & 31, gj = J0 + J;        // tile rows I, I + 8, I + 16, I + 24
+#pragma unroll 2
+    for (int p = 0; p < r; ++p) {
+        float y[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) y[it] = sY[(p * BI + I + 8 * it) * BJ + J];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4_t d = *reinterpret_cast<const f32x4_t *>(sD + p * 16 + 4 * q4);
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cq[it][4 * q4 + e] = fmaf(d[e], y[it], cq[it][4 * q4 + e]);
         }
-        if (gi < M && gj < N) {
+    }
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                float c0 = cq[4 * a], c1 = cq[4 * a + 1], c2 = cq[4 * a + 2], c3 = cq[4 * a + 3];
-                if (GELU) { c0 = gelu_erf(c0); c1 = gelu_erf(c1); c2 = gelu_erf(c2); c3 = gelu_erf(c3); }
-                const u32x2_t w = {pack_bf16x2(c0, c1), pack_bf16x2(c2, c3)};
-                *reinterpret_cast<u32x2_t *>(C + ((size_t)gi * 4 + a) * n_elems + (size_t)gj * 4) = w;
-            }
+    for (int it = 0; it < 4; ++it) {
+        const int gi = I0 + I + 8 * it;
+        if (gi >= M || gj >= N) continue;
+        if (Ysave != nullptr)
+            for (int p = 0; p < r; ++p)
+                Ysave[plane_row_base(gi, pg, r, N) + (size_t)p * pg * N + gj] = f32_to_bf16(sY[(p * BI + I + 8 * it) * BJ + J]);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            float c0 = cq[it][4 * a], c1 = cq[it][4 * a + 1], c2 = cq[it][4 * a + 2], c3 = cq[it][4 * a + 3];
+            if (GELU) { c0 = gelu_erf(c0); c1 = gelu_erf(c1); c2 = gelu_erf(c2); c3 = gelu_erf(c3); }
+            const u32x2_t w = {pack_bf16x2(c0, c1), pack_bf16x2(c2, c3)};
+            *reinterpret_cast<u32x2_t *>(C + ((size_t)gi * 4 + a) * n_elems + (size_t)gj * 4) = w;
         }
     }
 }

@@ -1,0 +1,26 @@
+"""Automatic choice of the forward variant at r <= 8: the single-launch variant's bits wherever the rule takes it, and right
+against the oracle on either side of the rule's edges (128 tile columns of X, 256 blocks of 32 x 32 tiles, r = 8)."""
+import numpy as np
+import pytest
+
+import stl_synth
+from oracle import planes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("m,k,n,r,single", [(1024, 512, 512, 8, True), (4096, 256, 1024, 5, True), (2052, 512, 992, 8, False),
+                                            (1024, 576, 512, 8, False), (1024, 512, 512, 9, False), (1020, 448, 1056, 7, True)])
+def test_auto_forward(gu, m, k, n, r, single):
+    import paper_2503_12211_amd as stl
+    p = stl_synth.stl_problem(m, k, n, r, seed=600 + m + k + n + r, dtype="bf16")
+    got = gu.forward(p, "bf16")
+    gu.check(got, planes.forward(p["X"], p["What"], p["E_X"], p["D"]), "bf16", "C")
+    flag = stl.STL_FLAG_FUSED if single else stl.STL_FLAG_UNFUSED
+    assert np.array_equal(got, gu.forward(p, "bf16", flags=flag))
