@@ -258,10 +258,13 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename
 static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
     auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, A_T, B_T, TO, ACC, ANY>;
-    constexpr int smem = 2 * (BM + BN) * BK * 2;
+    constexpr int stage = (BM + BN) * BK * 2, most = 2 * stage;
+    // a contraction of one stage needs one: twice the workgroups per CU to hide its loads (96 x (50 x 50 x 50), r = 32: 23 -> 15 us)
+    constexpr int slabs = 32 * (BN / WAVES_N * (int)sizeof(TO) + 16) * WAVES_M * WAVES_N;      // of the epilogue
+    const int smem = g.Kl > BK ? most : stage > slabs ? stage : slabs;
     // once per instantiation (initialisation of a function-local static is thread-safe)
     static const hipError_t attr_err =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (attr_err != hipSuccess) return attr_err;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
