@@ -15,7 +15,7 @@ def gu():
     return gpu_util
 
 
-@pytest.mark.parametrize("m,k,n,r,single", [(1024, 512, 512, 8, True), (4096, 256, 1024, 5, True), (2052, 512, 992, 8, False),
+@pytest.mark.parametrize("m,k,n,r,single", [(1024, 512, 512, 8, True), (4096, 256, 1024, 5, True), (4100, 512, 992, 8, False),
                                             (1024, 576, 512, 8, False), (1024, 512, 512, 9, False), (1020, 448, 1056, 7, True)])
 def test_auto_forward(gu, m, k, n, r, single):
     import paper_2503_12211_amd as stl
