@@ -192,7 +192,7 @@ stl_status_t stl_decode(const stl_problem_t *prob, const void *Yhat, const void 
  * flags: STL_FLAG_GELU applies the exact-erf GELU between the layers (evaluated in fp32, rounded to
  *   the storage dtype before the second encode); without it the step is the paper's linear map
  *   Yhat1 (D1 E_X2^T) per tile.  Variant STL_FLAG_AUTO uses the one-pass step where its kernel
- *   applies (bf16, n1/4 a multiple of 8); STL_FLAG_UNFUSED always runs decode and encode as two
+ *   applies (bf16, n1/4 at least 8); STL_FLAG_UNFUSED always runs decode and encode as two
  *   launches through a hidden-activation buffer in the workspace.  Other variant values: UNSUPPORTED.
  * X: m x k1 (in).  What1: r1 x K1 x N1, What2: r2 x N1 x N2 (in).  E_X1, D1: r1 x 16; E_X2, D2: r2 x 16 (in).
  * C: m x n2 (out).  ws / ws_bytes: at least stl_mlp_workspace_bytes(up, down, flags).
