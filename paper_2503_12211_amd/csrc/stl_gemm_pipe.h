@@ -297,16 +297,16 @@ inline unsigned list_grid(long total, int workgroups)
     return (unsigned)(wanted < 8 ? 8 : wanted);
 }
 
-// the lane offsets of a block's DMA sources fit 32 bits: at most 256 rows of a [row][l] operand, which may lie in several
-// groups, or 32 rows of an [l][row] one
+// The lane offsets of a block's DMA sources fit 32 bits: 32 rows of an [l][row] operand, 256 of a [row][l] one.  Those lie
+// side by side in a plane-major operand; in a grouped one every group border among them adds the group's other planes.
 inline bool offsets_fit(const GemmDesc &g)
 {
-    auto span = [&](bool kmajor, int rows_per_group, int ld) {
-        const double rows = kmajor ? 32 : 256 + (256.0 / rows_per_group + 1) * (g.batch - 1) * rows_per_group;
+    auto span = [&](bool kmajor, int pg, int ld) {
+        const double rows = kmajor ? 32 : pg <= 0 ? 256 : 256 + (256.0 / pg + 1) * (g.batch - 1) * pg;
         return (rows + 1) * ld * 2;
     };
-    return span(g.a_kmajor, g.a_rows_per_group(), g.a_kmajor ? g.Mi : g.Kl) < 4294967296.0 &&
-           span(g.b_kmajor, g.b_rows_per_group(), g.b_kmajor ? g.Nj : g.Kl) < 4294967296.0;
+    return span(g.a_kmajor, g.a_pg, g.a_kmajor ? g.Mi : g.Kl) < 4294967296.0 &&
+           span(g.b_kmajor, g.b_pg, g.b_kmajor ? g.Nj : g.Kl) < 4294967296.0;
 }
 
 // compile-time loop: the body sees its index as a constant, so register arrays are never indexed dynamically

@@ -124,6 +124,9 @@ struct GemmDesc {
     int o_rows_per_group() const { return o_pg > 0 ? o_pg : nb * Mi; }
 };
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
+// the kernel that launch_plane_gemm takes: stl_gemm_wide.hip, stl_gemm_pipe.hip, stl_gemm_mfma.hip, stl_gemm_generic.hip
+enum class GemmPath { wide, pipe, staged, generic };
+GemmPath plane_gemm_path(int dtype, const GemmDesc &g);
 // the any-shape path (fp32 MFMA), also used directly for fp32 storage
 hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out,
                                      hipStream_t s);

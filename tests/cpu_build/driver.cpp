@@ -1,9 +1,11 @@
 // Driver of the CPU address check (test infrastructure only): calls the C ABI entry points on host buffers whose end
 // coincides with the end of their allocation, under AddressSanitizer.  Each command-line argument is one case:
 //   fwd:m:k:n:r:flags   bwd:m:k:n:r   mlp:m:k:h:r   ewb:k:n:r   aa:nb:m:k:n:r   ragged:nimg:rows:k:n:r
+//   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (prints which plane-product kernel and block a product takes)
 //   plant   (a planted mistake -- an output buffer 32 bytes short -- that the sanitizer must report)
 // A leading "f32," selects fp32 storage (default bf16).
 #include "stl.h"
+#include "stl_kernels.h"
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -44,6 +46,11 @@ int main(int argc, char **argv)
             void *A = exact(3 * 256 * 128 * 2), *B = exact(3 * 128 * 256 * 2), *C = exact(3 * 256 * 256 * 2 - 32), *E = exact(1024);
             const size_t wf = stl_aa_workspace_bytes(&p, 3, STL_OP_FORWARD);
             CHECK(stl_aa_forward(&p, 3, A, B, E, E, E, C, nullptr, nullptr, nullptr, exact(wf), wf, 0, nullptr));
+        } else if (op == "route") {
+            stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, false, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
+            const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
+            const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
+            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::wide || path == stl::GemmPath::pipe ? blocks[(int)stl::pipe_block(g)] : "-");
         } else if (op == "fwd" || op == "bwd") {
             const long m = v[0], k = v[1], n = v[2];
             const int r = (int)v[3], flags = op == "fwd" ? (int)v[4] : 0;
