@@ -55,6 +55,9 @@ hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R, int Cc, int r, bool gelu, int pg,
                          hipStream_t s, RowMap rm = RowMap(), bool basis_f32 = false);
 
+// whether a plain encode or decode of R x Cc tiles goes one tile per thread (fp32 arithmetic)
+bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r);
+
 // Basis gradient G[p][q] (+)= sum_tiles P[p][tile] * tileview(V)[tile][q], in one pass with the decode of the same planes
 // (Cmat <- decode(P, Dm)), or alone when Cmat is NULL (Dm is not read then); `part` holds decode_outer_blocks(R, Cc) * r * 16 floats
 int decode_outer_blocks(int R, int Cc);

@@ -9,8 +9,8 @@
 namespace stl {
 
 // ---------------------------------------------------------------------------------------
-// The tile maps in fp32 arithmetic on the vector ALUs, for fp32 storage, for bf16 rows of fewer than 8 tiles and for bases
-// kept in fp32 (the folded decoder):
+// The tile maps in fp32 arithmetic on the vector ALUs, for fp32 storage (plain encodes and decodes of large matrices: one tile
+// per thread, below), for bf16 rows of fewer than 8 tiles and for bases kept in fp32 (the folded decoder):
 //   ENC    Pout[p][I][J]  = sum_q B[p][q] V[4I + q/4][4J + q%4]                  (planes of encoded tiles)
 //   DEC    Cmat[4I + q/4][4J + q%4] = sum_p B[p][q] Pin[p][I][J]                 (+ optional GELU)
 //   OUTER  G[p][q] = sum_{I,J} Pin[p][I][J] V[4I + q/4][4J + q%4]                (basis gradient; with ENC or DEC or alone)
@@ -158,6 +158,101 @@ __global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restr
         }
     }
 }
+
+// ---------------------------------------------------------------------------------------
+// Encode and decode of large fp32 matrices, one tile per thread: the tile stays in registers, nothing but the basis goes through
+// LDS, and a wavefront reads and writes whole cache lines of 64 neighbouring tiles.  The decode has eight planes' loads in
+// flight.  Bound by HBM; the items of tile_map_kernel pay two barriers and an LDS round trip per 64 tiles, which only their
+// fusions are worth, and help where one tile per thread leaves CUs idle.  us as items / one tile per thread:
+//   encode 1024 x 1024 tiles, r = 4 / 16 / 49: 20 / 27 / 55 -> 13 / 22 / 46;  4096 x 1000, r = 16: 133 -> 104 (3.6 TB/s of 5.4 copied)
+//   decode 1024 x 1024 tiles, r = 4 / 16 / 49: 27 / 31 / 62 -> 14 / 22 / 47;  4096 x 1000, r = 16: 131 -> 97;  16384 x 9, r = 16: 11.7 -> 7.6
+// ---------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void encode_tiles_kernel(const float *__restrict__ A, const float *__restrict__ E, float *__restrict__ P,
+                                                           int R, int Cc, int r, int pg, RowMap rm)
+{
+    __shared__ __align__(16) float sE[64 * 16];
+    for (int i = threadIdx.y * blockDim.x + threadIdx.x; i < r * 16; i += 256) sE[i] = E[i];
+    __syncthreads();
+    const int J = blockIdx.x * blockDim.x + threadIdx.x;
+    if (J >= Cc) return;
+    const size_t ld = (size_t)Cc * 4, plane = (size_t)pg * Cc;
+    for (int idx = blockIdx.y * blockDim.y + threadIdx.y; idx < R; idx += gridDim.y * blockDim.y) {
+        const int I = rm.tile_row(idx), nv = rm.valid(I);
+        const size_t r0 = rm.row0(I);
+        f32x4_t x[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) x[a] = a < nv ? load4<float>(A + (r0 + a) * ld + (size_t)J * 4, 4) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        float *out = P + plane_row_base(I, pg, r, Cc) + J;
+        for (int p = 0; p < r; ++p) {
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s = fmaf(sE[p * 16 + q], x[q >> 2][q & 3], s);
+            out[(size_t)p * plane] = s;
+        }
+    }
+}
+
+template <typename T, bool GELU>
+__global__ __launch_bounds__(256) void decode_tiles_kernel(const T *__restrict__ P, const T *__restrict__ Dm, T *__restrict__ Cmat, int R,
+                                                           int Cc, int r, int pg, RowMap rm)
+{
+    __shared__ __align__(16) float sD[64 * 16];
+    for (int i = threadIdx.y * blockDim.x + threadIdx.x; i < r * 16; i += 256) sD[i] = Elem<T>::ld(Dm + i);
+    __syncthreads();
+    const int J = blockIdx.x * blockDim.x + threadIdx.x;
+    if (J >= Cc) return;
+    const size_t ld = (size_t)Cc * 4, plane = (size_t)pg * Cc;
+    for (int idx = blockIdx.y * blockDim.y + threadIdx.y; idx < R; idx += gridDim.y * blockDim.y) {
+        const int I = rm.tile_row(idx), nv = rm.valid(I);
+        const size_t r0 = rm.row0(I);
+        const T *in = P + plane_row_base(I, pg, r, Cc) + J;
+        float c[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) c[q] = 0.f;
+        for (int p0 = 0; p0 < r; p0 += 8) {
+            float y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] = p0 + u < r ? Elem<T>::ld(in + (size_t)(p0 + u) * plane) : 0.f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p0 + u < r)
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) c[q] = fmaf(sD[(p0 + u) * 16 + q], y[u], c[q]);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            f32x4_t v;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) v[b] = GELU ? gelu_erf(c[4 * a + b]) : c[4 * a + b];
+            if (a < nv) store4(Cmat + (r0 + a) * ld + (size_t)J * 4, v);
+        }
+    }
+}
+
+// From 2^17 tiles on one tile per thread fills the chip (two wavefronts per SIMD; at 2^16 tiles and r = 64 the items are still ahead, 8.4
+// against 10.7 us).  Rows of fewer than 8 tiles stay with the items at any rank (100000 x 3, r = 49: 20 against 25 us to
+// encode), and so does the encode of bf16.  bf16 rows of 9 to 15 tiles fill a quarter of the matrix-core decode's chunk:
+// at small ranks one tile per thread decodes 16384 x 9 tiles, r = 8, in 7.7 us against 10.3 (at r = 32 of 65536 rows it takes 39 against 36).
+bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r)
+{
+    if ((int64_t)R * Cc < 131072) return false;
+    return dtype == 0 ? Cc >= 8 : decode && Cc % 8 && Cc >= 8 && Cc < 16 && r <= 8;
+}
+
+struct TileGrid {
+    dim3 grid, block;
+    // 64 tile columns where rows are whole lines of 64, otherwise as many as a row takes, up to 256: a line that two blocks
+    // share costs (4096 x 1000 tiles, r = 32, encode: 176 us at 256 columns, 232 at 64), and so do planes 4 MB apart whose rows
+    // all blocks walk in step (16 x 16384, r = 32: 14.0 us at 256, 8.6 at 64)
+    TileGrid(int R, int Cc)
+    {
+        int bx = Cc % 64 == 0 ? 64 : 256;
+        while (bx > 8 && bx / 2 >= Cc) bx /= 2;
+        const int by = 256 / bx, rows = (R + by - 1) / by;
+        grid = dim3((Cc + bx - 1) / bx, rows > 32768 ? 32768 : rows);      // the kernels stride over the rows
+        block = dim3(bx, by);
+    }
+};
 
 // second stage of the basis-gradient sums: the blocks' partials in block order
 __global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restrict__ part, float *__restrict__ G,
@@ -385,10 +480,25 @@ hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R
     const int Rs = rm.count(R);                             // tile rows this launch walks over
     if (Rs <= 0) return hipSuccess;
     if (dtype == 1 && Cc >= 8 && !basis_f32) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
+    if (tile_per_thread(dtype, false, Rs, Cc, r)) {
+        const TileGrid t(Rs, Cc);
+        hipLaunchKernelGGL(encode_tiles_kernel, t.grid, t.block, 0, s, (const float *)A, (const float *)E, (float *)P, Rs, Cc, r, pg, rm);
+        return hipGetLastError();
+    }
     auto run = dtype == 0     ? launch_tile_map<float, float, true, false, false, false>
                : basis_f32 ? launch_tile_map<bf16_t, float, true, false, false, false>
                            : launch_tile_map<bf16_t, bf16_t, true, false, false, false>;
     return run(A, nullptr, E, P, nullptr, nullptr, Rs, Cc, r, pg, rm, 0, s);
+}
+
+template <typename T>
+static hipError_t launch_decode_tiles(const void *P, const void *Dm, void *Cmat, int R, int Cc, int r, bool gelu, int pg, hipStream_t s,
+                                      const RowMap &rm)
+{
+    const TileGrid t(R, Cc);
+    auto kern = gelu ? decode_tiles_kernel<T, true> : decode_tiles_kernel<T, false>;
+    hipLaunchKernelGGL(kern, t.grid, t.block, 0, s, (const T *)P, (const T *)Dm, (T *)Cmat, R, Cc, r, pg, rm);
+    return hipGetLastError();
 }
 
 template <bool ANY>
@@ -404,6 +514,9 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);                          // tile rows this launch walks over
     if (R <= 0) return hipSuccess;
+    if ((dtype == 0 || !basis_f32) && tile_per_thread(dtype, true, R, Cc, r))
+        return dtype == 0 ? launch_decode_tiles<float>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm)
+                          : launch_decode_tiles<bf16_t>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm);
     if (dtype == 1 && Cc >= 8 && !basis_f32) {
         const int chunks = (Cc + 63) / 64;
         const long items = (long)R * chunks;

@@ -2,6 +2,7 @@
 // coincides with the end of their allocation, under AddressSanitizer.  Each command-line argument is one case:
 //   fwd:m:k:n:r:flags   bwd:m:k:n:r   mlp:m:k:h:r   ewb:k:n:r   aa:nb:m:k:n:r   ragged:nimg:rows:k:n:r
 //   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (prints which plane-product kernel and block a product takes)
+//   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   plant   (a planted mistake -- an output buffer 32 bytes short -- that the sanitizer must report)
 // A leading "f32," selects fp32 storage (default bf16).
 #include "stl.h"
@@ -51,6 +52,18 @@ int main(int argc, char **argv)
             const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
             const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
             printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::wide || path == stl::GemmPath::pipe ? blocks[(int)stl::pipe_block(g)] : "-");
+        } else if (op == "tiles") {
+            printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
+        } else if (op == "stages") {
+            const long m = 4 * v[0], n = 4 * v[1];
+            const int r = (int)v[2];
+            stl_problem_t p{m, n, n, 4, r, dt};
+            void *X = exact(m * n * es), *E = exact(r * 16 * es), *P = exact(stl_plane_elems(v[0], v[1], r) * es);
+            CHECK(stl_encode_activation(&p, X, E, P, nullptr));
+            CHECK(stl_decode(&p, P, E, X, 0, nullptr));
+            CHECK(stl_decode(&p, P, E, X, STL_FLAG_GELU, nullptr));
+            stl_problem_t w{4, m, n, 4, r, dt};
+            CHECK(stl_encode_weight(&w, X, E, exact((size_t)r * v[0] * v[1] * es), nullptr));
         } else if (op == "fwd" || op == "bwd") {
             const long m = v[0], k = v[1], n = v[2];
             const int r = (int)v[3], flags = op == "fwd" ? (int)v[4] : 0;

@@ -29,3 +29,16 @@ def test_large_weights_stay_on_the_pipelined_kernels(checker):  # noqa: F811
     # rows of a grouped operand lie further apart: here the offsets of 256 of them pass 32 bits and the product is staged
     # through registers
     assert routes(checker, [desc("dXhat", 2048, 1024, 131072, 64)]) == [("staged", "-")]
+
+
+def test_large_fp32_tile_maps_go_one_tile_per_thread(checker):  # noqa: F811
+    cases = {"f32,tiles:1:1024:1024:4": 1, "f32,tiles:1:2048:64:49": 1, "f32,tiles:0:16384:8:16": 1, "f32,tiles:0:2047:64:16": 0,
+             "f32,tiles:1:64:64:49": 0, "f32,tiles:0:100000:7:16": 0, "tiles:1:16384:9:8": 1, "tiles:1:16384:9:9": 0,
+             "tiles:1:16384:16:8": 0, "tiles:0:16384:9:8": 0, "tiles:1:16384:8:8": 0}
+    _, text = checker(*cases)
+    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
+
+
+def test_large_fp32_tile_maps_addresses(checker):  # noqa: F811
+    checker("f32,stages:1025:128:17", "f32,stages:16390:8:5", "f32,stages:2100:65:9", "f32,stages:130:1013:33", "stages:14570:9:8",
+            "stages:8740:15:3", "f32,ragged:2800:197:32:36:5", "f32,ewb:520:4096:9")
