@@ -55,6 +55,16 @@ typedef u32x4_t u32x4_any_t __attribute__((aligned(2)));
 typedef u32x2_t u32x2_any_t __attribute__((aligned(2)));
 typedef uint32_t u32_any_t __attribute__((aligned(2)));
 
+// eight elements moved h places towards the first, 0 < h < 8, zeros behind them
+__device__ __forceinline__ u32x4_t shift_down(u32x4_t v, int h)
+{
+    uint64_t lo = v[0] | ((uint64_t)v[1] << 32), hi = v[2] | ((uint64_t)v[3] << 32);
+    const int sh = 16 * h;                                   // 16 ... 112
+    lo = sh < 64 ? (lo >> (sh & 63)) | (hi << ((64 - sh) & 63)) : hi >> (sh & 63);
+    hi = sh < 64 ? hi >> (sh & 63) : 0;
+    return u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+}
+
 template <bool ANY>
 __device__ __forceinline__ u32x4_t load8(const bf16_t *p, int n)
 {
@@ -64,13 +74,7 @@ __device__ __forceinline__ u32x4_t load8(const bf16_t *p, int n)
     } else {
         const int miss = n < 8 ? 8 - n : 0;                  // elements of the chunk beyond the row's end
         if (n > 0) v = *reinterpret_cast<const u32x4_any_t *>(p - miss);
-        if (n > 0 && miss) {
-            uint64_t lo = v[0] | ((uint64_t)v[1] << 32), hi = v[2] | ((uint64_t)v[3] << 32);
-            const int sh = 16 * miss;                        // 16 ... 112
-            lo = sh < 64 ? (lo >> (sh & 63)) | (hi << ((64 - sh) & 63)) : hi >> (sh & 63);
-            hi = sh < 64 ? hi >> (sh & 63) : 0;
-            v = u32x4_t{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
-        }
+        if (n > 0 && miss) v = shift_down(v, miss);
     }
     return v;
 }
@@ -96,6 +100,14 @@ __device__ __forceinline__ void store8(bf16_t *p, int n, u32x4_t v)
         }
         if (n & 1) *p = (bf16_t)(v[0] & 0xffffu);
     }
+}
+
+// elements h .. min(n, 8) - 1 of the chunk at p, which may begin before its row (h > 0)
+__device__ __forceinline__ void store8_between(bf16_t *p, int h, int n, u32x4_t v)
+{
+    if (h >= 8) return;
+    if (h > 0) v = shift_down(v, h);
+    store8<true>(p + h, (h > 0 && n > 8 ? 8 : n) - h, v);
 }
 
 // storage-type traits: load as fp32, store from fp32

@@ -24,8 +24,8 @@
 namespace stl {
 
 // OUTER = false: the encode alone (Qp, part unused) -- the same whole-line stores through the slab, used for plain encodes
-// ANY: column counts that are no multiple of 8 (see load8)
-template <int KC, bool OUTER, bool ANY>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
+// ANY: column counts that are no multiple of 8 (see load8); SHIFT: with items that begin on cache lines (see encode_items)
+template <int KC, bool OUTER, bool ANY, bool SHIFT = false>   // KC = number of 32-plane groups (1: r <= 32, 2: r <= 64)
 __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E,
                                                              bf16_t *__restrict__ P, const bf16_t *__restrict__ Qp,
                                                              float *__restrict__ part, int R, int Cc, int r, int chunks, int pg,
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
 #pragma unroll
     for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // wavefront w of block b takes items 4b + w, 4b + w + 4 * gridDim.x, ...
-    encode_items<KC, OUTER, false, 1, ANY>(A, E, P, Qp, R, Cc, r, chunks, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
+    encode_items<KC, OUTER, false, 1, ANY, SHIFT>(A, E, P, Qp, R, Cc, r, chunks, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
                             (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], dacc, lane);
 
     if (!OUTER) return;
@@ -76,18 +76,26 @@ hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, cons
     return hipGetLastError();
 }
 
+// A plane row of a width that is no multiple of 8 begins anywhere in a cache line, so that items of 64 columns counted from its
+// beginning write two incomplete lines per plane.  Once the planes no longer fit the caches beside the matrix that is most of the
+// time (8192 x 508 tiles, r = 32: 116 us; with 32-column fragments of 256 bytes per plane 90; lines written whole 84), and
+// narrower rows pay for an item more per row (16384 x 132, r = 49: 78 -> 95 us; 4096 x 252, r = 49: 25 both ways).  r R Cc = 3.3e7:
+// 4096 x 508, r = 16: 30 -> 24, 4096 x 1004, r = 8: 34 both ways; below, 1024 x 1004, r = 16: 12.6 -> 13.1.
+bool encode_line_starts(int R, int Cc, int r) { return Cc % 8 && Cc > 192 && (double)r * R * Cc >= 3.2e7; }
+
 // the encode alone through the same kernel (bf16, Cc >= 8): grid-stride over (tile row, 64-tile chunk) items
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm)
 {
     if (pg <= 0) pg = R;
     R = rm.count(R);
     if (R <= 0) return hipSuccess;
-    const int chunks = (Cc + 63) / 64;
+    const bool any = Cc % 8 != 0, starts = encode_line_starts(R, Cc, r);
+    const int chunks = starts ? (Cc + 126) / 64 : (Cc + 63) / 64;
     const long items = (long)R * chunks;
     long blocks = (items + 3) / 4;
     if (blocks > 8192) blocks = 8192;
-    const bool any = Cc % 8 != 0;
-    auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, false, true> : encode_outer16_kernel<1, false, false>)
+    auto kern = starts  ? (r <= 32 ? encode_outer16_kernel<1, false, true, true> : encode_outer16_kernel<2, false, true, true>)
+                : r <= 32 ? (any ? encode_outer16_kernel<1, false, true> : encode_outer16_kernel<1, false, false>)
                         : (any ? encode_outer16_kernel<2, false, true> : encode_outer16_kernel<2, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E, (bf16_t *)P,
                        (const bf16_t *)nullptr, (float *)nullptr, R, Cc, r, chunks, pg, rm);

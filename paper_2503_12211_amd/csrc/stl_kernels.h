@@ -95,6 +95,7 @@ hipError_t launch_transpose_basis(int dtype, const void *E, void *Et, int r, hip
 hipError_t launch_transpose_basis_grad(const float *Gt, float *G, int r, int accumulate, hipStream_t s);
 
 // bf16 encode with whole-line plane stores (Cc >= 8); launch_encode picks it
+bool encode_line_starts(int R, int Cc, int r);      // whether its items begin on cache lines
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm);
 
 // out[i] = bf16(in[i]), round to nearest even

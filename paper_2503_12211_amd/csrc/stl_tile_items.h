@@ -19,7 +19,9 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 // ANY: any column count of at least 8 (see load8); otherwise a multiple of 8.  Bound by HBM and, for small matrices, by the
 // launch; one pass over a row's planes whatever the width: with one thread per tile and a separate scalar sum, dYhat + dD of
 // 512 x 250 tiles, r = 32, took 10 + 285 us, now 8; dYhat + dD of 4800 x 50 tiles 13 + 577 us, now 14.
-template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false>
+// SHIFT (with ANY, without OUTER): an item's 64 tile columns begin where the plane rows' cache lines do, up to 63 columns to the
+// left of its multiple of 64; `chunks` then counts (Cc + 126) / 64 items per row (see encode_line_starts).
+template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false>
 __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E, bf16_t *__restrict__ P,
                                              const bf16_t *__restrict__ Qp, int R, int Cc, int r, int chunks, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane)
@@ -52,19 +54,23 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
         srow[u] = trel[u] ^ (((trel[u] >> 3) & 1) << 2);
     }
 
+    // Row I of a plane begins (I % pg) Cc elements behind the group's beginning, and the planes of a group lie pg Cc apart: a
+    // multiple of a line in the grouped layout, so that one shift serves all planes.
+    auto shift = [&](int I) { return SHIFT ? (int)(((size_t)(I % pg) * Cc) & 63) : 0; };
+
     u32x2_t xa[DEPTH][4];                   // this lane's tile rows, one per product
     u32x4_t qa[DEPTH][OUTER ? KC * 4 : 1];  // plane segments, loader role: plane 8*g8 + pr, tiles 8ch .. 8ch+7
     auto fetch = [&](int d, long item) {
         const int Ii = (int)(item / chunks), cki = (int)(item - (long)Ii * chunks);
-        const int J0 = cki * 64;
         const int Ia = Ii < R ? rm.tile_row(Ii) : 0;        // Ii counts the tile rows of this launch, Ia is the tile row itself
+        const int J0 = cki * 64 - shift(Ia);
         const size_t rowb = plane_row_base(Ia, pg, r, Cc);
         const bool row_ok = Ii < R && kq < rm.valid(Ia);    // a null row reads as zero
         const size_t r0 = rm.row0(Ia);
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             u32x2_t v = {0u, 0u};
-            if (row_ok && J0 + trel[u] < Cc) v = *reinterpret_cast<const u32x2_t *>(A + (r0 + kq) * ld + (size_t)(J0 + trel[u]) * 4);
+            if (row_ok && J0 + trel[u] < Cc && (!SHIFT || J0 + trel[u] >= 0)) v = *reinterpret_cast<const u32x2_t *>(A + (r0 + kq) * ld + (size_t)(J0 + trel[u]) * 4);
             xa[d][u] = v;
         }
         if (OUTER) {
@@ -84,7 +90,7 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
     for (int d = 0; d < DEPTH; ++d) {
         const long item0 = base + d * stride;
         if (item0 >= end) break;
-        const int Iidx = (int)(item0 / chunks), J0 = (int)(item0 - (long)Iidx * chunks) * 64;
+        const int Iidx = (int)(item0 / chunks), cki = (int)(item0 - (long)Iidx * chunks);
         u32x2_t x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) x[u] = xa[d][u];
@@ -98,7 +104,7 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
         }
         if (item0 + DEPTH * stride < end) fetch(d, item0 + DEPTH * stride);
         if (Iidx >= R) continue;
-        const int I = rm.tile_row(Iidx);
+        const int I = rm.tile_row(Iidx), J0 = cki * 64 - shift(I);
 
         // tile rows -> second slab
         if (OUTER) {
@@ -159,7 +165,8 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
             if (pl < r && J0 + 8 * ch < Cc) {
                 const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4));
                 bf16_t *o = P + rowb_out + (size_t)pl * plane + J0 + 8 * ch;
-                if constexpr (ANY) store8<true>(o, Cc - J0 - 8 * ch, w);
+                if constexpr (SHIFT) store8_between(o, J0 + 8 * ch < 0 ? -(J0 + 8 * ch) : 0, Cc - J0 - 8 * ch, w);
+                else if constexpr (ANY) store8<true>(o, Cc - J0 - 8 * ch, w);
                 else store16<THROUGH>(o, w);
             }
         }

@@ -42,3 +42,10 @@ def test_large_fp32_tile_maps_go_one_tile_per_thread(checker):  # noqa: F811
 def test_large_fp32_tile_maps_addresses(checker):  # noqa: F811
     checker("f32,stages:1025:128:17", "f32,stages:16390:8:5", "f32,stages:2100:65:9", "f32,stages:130:1013:33", "stages:14570:9:8",
             "stages:8740:15:3", "f32,ragged:2800:197:32:36:5", "f32,ewb:520:4096:9")
+
+
+def test_wide_bf16_encodes_of_odd_widths_write_whole_lines(checker):  # noqa: F811
+    cases = {"lines:8192:508:32": 1, "lines:4096:1001:49": 1, "lines:8192:512:32": 0, "lines:16384:132:49": 0, "lines:1024:1004:16": 0}
+    _, text = checker(*cases)
+    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
+    checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "ragged:52:197:1000:32:64")
