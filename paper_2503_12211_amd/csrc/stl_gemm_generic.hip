@@ -15,8 +15,11 @@ namespace stl {
 
 // MFMA accumulator layout of v_mfma_f32_32x32x2_f32: lane (j = lane % 32, h = lane / 32) supplies A[row j][k = h] and
 // B[k = h][column j]; accumulator e of the lane is C[row 8 (e / 4) + 4 h + e % 4][column j].
+// Three wavefronts per SIMD for the 128 x 128 blocks (at the price of eleven spilled registers; left alone the compiler takes
+// registers for two): 1024-cube, r = 32, 770 -> 695 us, bf16 dWhat of 1024 x 1024 from four tile rows 57 -> 53.  With a sum into the
+// output it helps some sizes and costs others (r = 32 of the latter 123 -> 100, r = 8 31 -> 36) and stays at two.
 template <typename T, typename TO, bool ACC, int BT>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
+__global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                            TO *__restrict__ Out, int Mi, int Nj, int Kl, int a_km,
                                                            int b_km, int a_pg, int b_pg, int o_pg, int batch, int nb)
 {
