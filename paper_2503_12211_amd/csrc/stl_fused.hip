@@ -269,10 +269,8 @@ static hipError_t launch_block_t(const void *Xin, const void *What, const void *
     auto kern = fused::stl_block_kernel<RP, ENCODE, GELU>;
     constexpr int smem = fused::smem_bytes<RP, ENCODE>();
     static_assert(smem <= 160 * 1024, "LDS budget");
-    // once per instantiation (initialisation of a function-local static is thread-safe)
-    static const hipError_t attr_err =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (attr_err != hipSuccess) return attr_err;
+    static std::atomic<uint64_t> granted{0};               // of this instantiation
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted); e != hipSuccess) return e;
     const int bi = (M + fused::BI - 1) / fused::BI, bj = (N + fused::BJ - 1) / fused::BJ;
     const long total = (long)bi * bj;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

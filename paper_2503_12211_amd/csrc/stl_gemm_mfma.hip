@@ -262,10 +262,8 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
     // a contraction of one stage needs one: twice the workgroups per CU to hide its loads (96 x (50 x 50 x 50), r = 32: 23 -> 15 us)
     constexpr int slabs = 32 * (BN / WAVES_N * (int)sizeof(TO) + 16) * WAVES_M * WAVES_N;      // of the epilogue
     const int smem = g.Kl > BK ? most : stage > slabs ? stage : slabs;
-    // once per instantiation (initialisation of a function-local static is thread-safe)
-    static const hipError_t attr_err =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (attr_err != hipSuccess) return attr_err;
+    static std::atomic<uint64_t> granted{0};               // of this instantiation
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), most, granted); e != hipSuccess) return e;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

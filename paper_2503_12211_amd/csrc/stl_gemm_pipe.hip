@@ -222,10 +222,8 @@ static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *
     constexpr int smem = NS * (BM + BN) * pipe::BKS * 2 + NW * pipe::slab_bytes<BM / WAVES_M / 16, BN / WAVES_N / 16, TO>();
     static_assert(smem <= 160 * 1024, "LDS budget");
     constexpr int per_cu = 160 * 1024 / smem > 2 ? 2 : 160 * 1024 / smem;
-    // once per instantiation (initialisation of a function-local static is thread-safe)
-    static const hipError_t attr_err =
-        hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (attr_err != hipSuccess) return attr_err;
+    static std::atomic<uint64_t> granted{0};               // of this instantiation
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted); e != hipSuccess) return e;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

@@ -2,8 +2,23 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 
 namespace stl {
+
+// Lets `kern` be launched with up to `bytes` of dynamic LDS (more than 64 KB has to be asked for) on the current device.  `done`
+// belongs to that kernel alone and holds the devices it has been granted on, a bit each; devices beyond 64 are asked every time.
+inline hipError_t allow_lds(const void *kern, int bytes, std::atomic<uint64_t> &done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
+}
 
 // dtype: 0 = fp32 storage, 1 = bf16 storage (matches stl_dtype_t)
 // pg: rows per group of the plane tensor's layout (see plane_row_base); 0 = plane-major (one group of all rows)

@@ -333,14 +333,12 @@ hipError_t launch_forward_pipeline(const void *X, const void *E, const void *Wha
     if (e != hipSuccess) return e;
     constexpr int smem = 4 * 512 * pipe::BKS * 2 + 8 * 16 * (64 * 2 + 16) + 64;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto launch = [&](auto kern) {
-        static const hipError_t attr_err =
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        if (attr_err != hipSuccess) return attr_err;
-        hipLaunchKernelGGL(kern, dim3(pipeline_cus()), dim3(512), smem, s, a);
-        return hipGetLastError();
-    };
-    return gelu ? launch(forward_pipeline_kernel<true>) : launch(forward_pipeline_kernel<false>);
+    static std::atomic<uint64_t> granted[2] = {};           // the two kernels are of one type
+    auto kern = gelu ? forward_pipeline_kernel<true> : forward_pipeline_kernel<false>;
+    e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted[gelu]);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(pipeline_cus()), dim3(512), smem, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace stl

@@ -4,6 +4,7 @@
 //   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (prints which plane-product kernel and block a product takes)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   lines:R:Cc:r   (prints whether a bf16 encode starts its items on cache lines)
+//   device:N   (the device that is current for the following cases)
 //   plant   (a planted mistake -- an output buffer 32 bytes short -- that the sanitizer must report)
 // A leading "f32," selects fp32 storage (default bf16).
 #include "stl.h"
@@ -48,6 +49,8 @@ int main(int argc, char **argv)
             void *A = exact(3 * 256 * 128 * 2), *B = exact(3 * 128 * 256 * 2), *C = exact(3 * 256 * 256 * 2 - 32), *E = exact(1024);
             const size_t wf = stl_aa_workspace_bytes(&p, 3, STL_OP_FORWARD);
             CHECK(stl_aa_forward(&p, 3, A, B, E, E, E, C, nullptr, nullptr, nullptr, exact(wf), wf, 0, nullptr));
+        } else if (op == "device") {
+            (void)hipSetDevice((int)v[0]);
         } else if (op == "route") {
             stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, false, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
             const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};

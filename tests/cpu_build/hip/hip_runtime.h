@@ -11,6 +11,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
+#include <utility>
 #define __global__
 #define __device__
 #define __host__
@@ -26,8 +28,12 @@ enum { hipSuccess = 0, hipErrorInvalidValue = 1 };
 enum { hipFuncAttributeMaxDynamicSharedMemorySize = 0, hipDeviceAttributeMultiprocessorCount = 1 };
 inline hipError_t hipGetLastError() { return 0; }
 inline const char *hipGetErrorString(hipError_t) { return "cpu"; }
-inline hipError_t hipFuncSetAttribute(const void *, int, int) { return 0; }
-inline hipError_t hipGetDevice(int *d) { *d = 0; return 0; }
+// the dynamic LDS a kernel may ask for beyond 64 KB, granted per device and kernel
+inline int g_cpu_device = 0;
+inline std::map<std::pair<int, const void *>, int> g_cpu_lds_granted;
+inline hipError_t hipFuncSetAttribute(const void *f, int, int bytes) { g_cpu_lds_granted[{g_cpu_device, f}] = bytes; return 0; }
+inline hipError_t hipSetDevice(int d) { g_cpu_device = d; return 0; }
+inline hipError_t hipGetDevice(int *d) { *d = g_cpu_device; return 0; }
 inline hipError_t hipDeviceGetAttribute(int *v, int, int) { *v = 256; return 0; }
 #define HIP_SYMBOL(x) (&(x))
 inline hipError_t hipGetSymbolAddress(void **p, const void *sym) { *p = const_cast<void *>(sym); return 0; }
@@ -47,8 +53,12 @@ inline void cpu_check_launch(const char *name, dim3 grid, dim3 block, size_t sme
     }
 }
 template <typename F>
-inline void cpu_launch(const char *name, dim3 grid, dim3 block, size_t smem, F f)
+inline void cpu_launch(const char *name, const void *kern, dim3 grid, dim3 block, size_t smem, F f)
 {
+    if (smem > 64 * 1024 && g_cpu_lds_granted[{g_cpu_device, kern}] < (int)smem) {
+        fprintf(stderr, "runtime error: launch of %s with %zu bytes of dynamic LDS not granted on device %d\n", name, smem, g_cpu_device);
+        abort();
+    }
     g_kernel_name = name;
     g_dyn_lds = smem;
     cpu_check_launch(name, grid, block, smem);
@@ -74,7 +84,7 @@ inline void cpu_launch(const char *name, dim3 grid, dim3 block, size_t smem, F f
     g_dyn_lds_buf = nullptr;
     free(lds_block);
 }
-#define hipLaunchKernelGGL(kern, grid, block, smem, stream, ...) cpu_launch(#kern, grid, block, (size_t)(smem), [&]() { kern(__VA_ARGS__); })
+#define hipLaunchKernelGGL(kern, grid, block, smem, stream, ...) cpu_launch(#kern, (const void *)(kern), grid, block, (size_t)(smem), [&]() { kern(__VA_ARGS__); })
 inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f; }
 #define __syncthreads() ((void)0)
 #define __builtin_amdgcn_readfirstlane(x) (x)

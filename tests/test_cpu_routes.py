@@ -49,3 +49,11 @@ def test_wide_bf16_encodes_of_odd_widths_write_whole_lines(checker):  # noqa: F8
     _, text = checker(*cases)
     assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
     checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "ragged:52:197:1000:32:64")
+
+
+def test_second_device_of_a_process(checker):  # noqa: F811
+    """Dynamic LDS beyond 64 KB is granted per device and kernel: calls that ran on one device run on the next one too, and a kernel
+    runs whether or not one of the same type ran before (the pipelined forward without and with GELU)."""
+    cases = ("f32,bwd:64:32:48:49", "bwd:1024:512:512:32", "bwd:300:260:300:32", "fwd:64:64:64:32:3", "fwd:2048:256:1024:32:4",
+             "fwd:2048:256:1024:32:260", "aa:2:256:128:256:32")
+    checker(*cases, "device:1", *cases, "device:0", *cases)
