@@ -273,30 +273,41 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
     return hipGetLastError();
 }
 
-template <bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
-static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+static bool any_width(const GemmDesc &g) { return g.Mi % 8 || g.Nj % 8 || g.Kl % 8; }
+
+// Edge of the (square) block.
+int staged_block(const GemmDesc &g)
 {
-    if constexpr (!ANY) {
-        // large planes: 256 x 256 blocks, 8 wavefronts of 128 x 64; small ones: 128 x 128 blocks, 4 wavefronts of 64 x 64
-        if (g.Mi > 128 && g.Nj > 128) return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-        return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-    }
+    // multiples of 8, stacked problems: 256 x 256 blocks, 8 wavefronts of 128 x 64, for large planes, 128 x 128, 4 of 64 x 64, for others
+    if (!any_width(g)) return g.Mi > 128 && g.Nj > 128 ? 256 : 128;
     // The largest block that still fills the chip (256 CUs): a bigger block moves fewer bytes per product, but these kernels
     // prefetch a single stage, so idle CUs and short contractions cost more.  Forward form, us at 256 / 128 / 64:
     //   M x K x N, r = 512 x 1024 x 1024, 32: 48 / 69 / 116 (256 blocks of 256);  256 x 1024 x 1024, 32: 44 / 38 / 63 (128, 512
     //   blocks);  1024 x 192 x 250, 32: 21 / 17 / 26 (512 blocks of 128);  512 x 192 x 250, 32: 19 / 14 / 13 (256 blocks of
     //   128);  128 x 192 x 250, 8: 17 / 13 / 10
     auto blocks = [&](int b) { return (double)((g.Mi + b - 1) / b) * ((g.Nj + b - 1) / b) * g.batch * g.nb; };
-    if (g.Mi > 128 && g.Nj > 128 && blocks(256) >= 256) return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-    if (g.Mi > 64 && g.Nj > 64 && blocks(128) >= 384) return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-    return launch_cfg<64, 64, 1, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    if (g.Mi > 128 && g.Nj > 128 && blocks(256) >= 256) return 256;
+    return g.Mi > 64 && g.Nj > 64 && blocks(128) >= 384 ? 128 : 64;
+}
+
+template <bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
+static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+{
+    switch (staged_block(g)) {
+        case 256: return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+        case 128: return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    }
+    if constexpr (ANY) return launch_cfg<64, 64, 1, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
+    return hipErrorInvalidValue;
 }
 
 template <bool A_T, bool B_T, typename TO, bool ACC>
 static hipError_t launch_shape(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    const bool any = g.Mi % 8 || g.Nj % 8 || g.Kl % 8;
-    return any ? launch_block<A_T, B_T, TO, ACC, true>(g, A, B, Out, s) : launch_block<A_T, B_T, TO, ACC, false>(g, A, B, Out, s);
+    if (any_width(g)) return launch_block<A_T, B_T, TO, ACC, true>(g, A, B, Out, s);
+    // weight gradients of widths that are multiples of 8 go to the LDS-DMA kernel at any contraction length
+    if constexpr (sizeof(TO) == 4) return hipErrorInvalidValue;
+    else return launch_block<A_T, B_T, TO, ACC, false>(g, A, B, Out, s);
 }
 
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)

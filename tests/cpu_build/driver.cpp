@@ -55,7 +55,8 @@ int main(int argc, char **argv)
             stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, false, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
             const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
             const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
-            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::wide || path == stl::GemmPath::pipe ? blocks[(int)stl::pipe_block(g)] : "-");
+            const char *staged = stl::staged_block(g) == 256 ? "256x256" : stl::staged_block(g) == 128 ? "128x128" : "64x64";
+            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::generic ? "-" : path == stl::GemmPath::staged ? staged : blocks[(int)stl::pipe_block(g)]);
         } else if (op == "tiles") {
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "lines") {
