@@ -2,15 +2,23 @@
 test_cpu_address_check.py prints them)."""
 from test_cpu_address_check import checker, pytestmark  # noqa: F401
 
+from test_gpu_blocks import AA_SHAPES, SHAPES
+
 PG = 64
+BLOCKS = ("64x64", "128x128", "128x256", "256x256")
 
 
-def desc(form, M, K, N, r, nb=1):
-    """The product descriptors of stl_api.hip, tile counts: the forward product Yhat, the input gradient dXhat and the weight
-    gradient dWhat; `aa`: the same three of nb stacked pairs of activations (both operands and dBhat in the grouped layout)."""
-    b = 0 if not form.startswith("aa_") else PG
-    return {"Yhat": (M, N, K, r, 0, 1, 0, PG, b, PG, nb), "dXhat": (M, K, N, r, 0, 0, 0, PG, b, PG, nb),
-            "dWhat": (K, N, M, r, 1, 1, 0 if b else 1, PG, PG, b, nb)}[form.removeprefix("aa_")]
+def desc(form, M, K, N, r):
+    """The products of one layer as stl_api.hip describes them, tile counts: forward, input gradient, weight gradient."""
+    return {"Yhat": (M, N, K, r, 0, 1, 0, PG, 0, PG, 1), "dXhat": (M, K, N, r, 0, 0, 0, PG, 0, PG, 1),
+            "dWhat": (K, N, M, r, 1, 1, 1, PG, PG, 0, 1)}[form]
+
+
+def aa_descs(nb, M, K, N, r, bt):
+    """The three products of stacked pairs of activations."""
+    grads_b = (N, K, M) if bt else (K, N, M)
+    return [(M, N, K, r, 0, 0 if bt else 1, 0, PG, PG, PG, nb), (M, K, N, r, 0, 1 if bt else 0, 0, PG, PG, PG, nb),
+            grads_b + (r, 1, 1, 0, PG, PG, PG, nb)]
 
 
 def routes(run, descs):
@@ -28,7 +36,7 @@ def test_large_weights_stay_on_the_pipelined_kernels(checker):  # noqa: F811
         assert path in ("wide", "pipe"), s
     # rows of a grouped operand lie further apart: here the offsets of 256 of them pass 32 bits and the product is staged
     # through registers
-    assert routes(checker, [desc("dXhat", 2048, 1024, 131072, 64)]) == [("staged", "-")]
+    assert routes(checker, [desc("dXhat", 2048, 1024, 131072, 64)]) == [("staged", "256x256")]
 
 
 def test_large_fp32_tile_maps_go_one_tile_per_thread(checker):  # noqa: F811
@@ -57,3 +65,39 @@ def test_second_device_of_a_process(checker):  # noqa: F811
     cases = ("f32,bwd:64:32:48:49", "bwd:1024:512:512:32", "bwd:300:260:300:32", "fwd:64:64:64:32:3", "fwd:2048:256:1024:32:4",
              "fwd:2048:256:1024:32:260", "aa:2:256:128:256:32")
     checker(*cases, "device:1", *cases, "device:0", *cases)
+
+
+def _covered(run, descs):
+    """{(operand forms, fp32 output, stacked, kernel, block, ends inside a stage or any width)} that these products reach."""
+    out = set()
+    for d, (path, block) in zip(descs, routes(run, descs)):
+        Mi, Nj, Kl, akm, bkm, f32, nb = d[0], d[1], d[2], d[4], d[5], d[6], d[10]
+        odd = bool(Kl % 32) if path == "pipe" else bool(Mi % 8 or Nj % 8 or Kl % 8)
+        out.add((akm, bkm, f32, nb > 1, path, block, odd))
+    return out
+
+
+def test_gpu_shapes_reach_every_kernel_form_and_block(checker):  # noqa: F811
+    layer = _covered(checker, [desc(f, *s) for s in SHAPES for f in ("Yhat", "dXhat", "dWhat")])
+    want = {(a, b, f, False, "pipe", blk, tail) for a, b, f in ((0, 1, 0), (0, 0, 0), (1, 1, 1)) for blk in BLOCKS for tail in (False, True)}
+    want |= {(0, b, 0, False, "wide", "256x256", False) for b in (0, 1)}
+    want |= {(a, b, f, False, "staged", blk, True) for a, b, f in ((0, 1, 0), (0, 0, 0), (1, 1, 1)) for blk in ("64x64", "128x128", "256x256")}
+    assert want - layer == set() and layer - want == set()
+    aa = _covered(checker, [d for s in AA_SHAPES for d in aa_descs(*s)])
+    want = {(1, 1, 0, False, "pipe", blk, tail) for blk in BLOCKS for tail in (False, True)}
+    want |= {(1, 1, 0, False, "staged", blk, True) for blk in ("64x64", "128x128", "256x256")}
+    for a, b in ((0, 1), (0, 0), (1, 1)):
+        # stacked problems: the LDS-DMA kernel at one stage (where 64 x 64 is never the fastest block), otherwise staged
+        want |= {(a, b, 0, True, "pipe", blk, False) for blk in BLOCKS[1:]}
+        want |= {(a, b, 0, True, "staged", blk, False) for blk in ("128x128", "256x256")}
+        want |= {(a, b, 0, True, "staged", blk, True) for blk in ("64x64", "128x128", "256x256")}
+    assert want - aa == set(), want - aa
+    assert {k for k in aa if k[3]} - want == set()
+
+
+def test_listed_layers_of_the_any_width_tests(checker):  # noqa: F811
+    """The shapes of test_gpu_any_width.py take the kernels they are meant for."""
+    from test_gpu_any_width import SHAPES as ANY
+    for s in ANY:
+        want = "generic" if min(s[:3]) < 8 else "staged"
+        assert {path for path, _ in routes(checker, [desc(f, *s) for f in ("Yhat", "dXhat", "dWhat")])} == {want}, s

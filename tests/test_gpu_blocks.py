@@ -1,5 +1,7 @@
-"""bf16 plane products over all their block sizes (256 x 256, 128 x 256, 128 x 128, 64 x 64), with blocks that hang over the edge
-and contractions that end inside a stage of 32 (and, in the weight gradient, at any tile row).
+"""bf16 plane products over all their block sizes -- LDS-DMA kernels: 256 x 256, 128 x 256, 128 x 128, 64 x 64, whole-line form; products
+staged through registers: 256 x 256, 128 x 128, 64 x 64 -- with blocks that hang over the edge and contractions that end inside a
+stage of 32 (and, in the weight gradient, at any tile row).  test_cpu_routes.py asserts that the shapes below reach every
+combination that exists.
 
 Bars: gpu_util.check (see test_gpu_any_width.py)."""
 import numpy as np
@@ -20,14 +22,50 @@ def gu():
 
 
 # M, K, N tile counts, r -- blocks of the three products Yhat, dXhat, dWhat
-SHAPES = [(16, 40, 64, 8),          # 64 or 128, 128, 128; fewer rows than a block
+SHAPES = [(16, 40, 64, 8),          # 128, 128, 128: fewer rows than a block
           (300, 200, 264, 3),       # 64, 64, 64
-          (130, 72, 136, 49),       # 128, 64, 128
+          (130, 72, 136, 49),       # 128, 64, 64
           (257, 488, 520, 40),      # 128, 128 x 256, 128; the weight gradient contracts over an odd number of rows
           (640, 320, 512, 24),      # 128 x 256, 128, 128
           (520, 264, 776, 32),      # 128, 128, 256
           (1030, 72, 520, 64),      # 128, 128, 128 x 256
-          (2040, 232, 2040, 4)]     # 256 with a contraction of 232; 128 for the others
+          (2040, 232, 2040, 4),     # 256 with a contraction of 232; 64, 64
+          # contractions of whole stages, more of them than a ring holds
+          (192, 160, 160, 3),       # 64, 64, 64
+          (160, 160, 160, 48),      # 128, 128, 128
+          (160, 400, 264, 64),      # 128 x 256, 128 x 256 (both end inside a stage), 256
+          (387, 160, 320, 64),      # 256, 128 x 256, 128 x 256 (from an odd number of rows)
+          (288, 480, 160, 64),      # 128 x 256, 256, 128 x 256
+          (421, 400, 272, 64),      # 256, 256, 256, all ending inside a stage
+          (864, 192, 192, 64),      # whole-line 256, whole-line 256, 64
+          # staged through registers, odd widths
+          (100, 106, 111, 3),       # 64, 64, 64
+          (305, 261, 134, 64),      # 128, 256, 128
+          (288, 153, 271, 64),      # 256, 128, 128
+          (128, 270, 265, 64)]      # 64, 64, 256
+
+# stacked problems, M, K, N, r, second operand stored transposed -- blocks of Yhat, dAhat, dBhat
+AA_SHAPES = [(1, 192, 160, 160, 3, False),        # one problem: the bf16 product of two [l][row] operands (dBhat) on
+             (1, 154, 152, 152, 3, True),         #   64, with whole stages and without
+             (1, 160, 160, 160, 48, True),        #   128
+             (1, 164, 200, 216, 40, False),       #   128, ending inside a stage
+             (1, 288, 480, 160, 64, False),       #   128 x 256
+             (1, 387, 160, 320, 64, False),       #   128 x 256, ending inside a stage
+             (1, 160, 400, 264, 64, False),       #   256
+             (1, 421, 400, 272, 64, True),        #   256, ending inside a stage
+             (1, 100, 106, 111, 3, False),        #   staged 64
+             (1, 288, 153, 271, 64, True),        #   staged 128
+             (1, 128, 270, 265, 64, False),       #   staged 256
+             (2, 32, 32, 32, 3, False),           # stacked: 128, one stage
+             (4, 32, 32, 32, 64, False),          #   128 x 256
+             (8, 272, 32, 144, 16, False),        #   256, staged 128, 128
+             (2, 32, 272, 144, 64, True),         #   staged 128, 128, 256
+             (8, 288, 144, 32, 16, False),        #   staged 128, 256, staged 128
+             (2, 80, 112, 80, 3, True),           #   staged 128, multiples of 8
+             (2, 160, 192, 160, 3, True),         #   staged 256, multiples of 8
+             (2, 73, 75, 119, 3, True),           #   staged 64, odd widths
+             (8, 77, 96, 93, 49, False),          #   staged 128
+             (4, 194, 147, 145, 64, False)]       #   staged 256
 
 
 @pytest.mark.parametrize("M,K,N,r", SHAPES)
@@ -44,6 +82,22 @@ def test_step_blocks(gu, M, K, N, r):
     acc = gu.backward(p, "bf16", accumulate=1, init=init)
     # one rounding of (1 + gradient) on top of the same sums
     assert np.abs(acc["dWhat"] - 1.0 - got["dWhat"]).max() <= 2.0 ** -22 * max(1.0, np.abs(got["dWhat"]).max())
+
+
+@pytest.mark.parametrize("nb,M,K,N,r,bt", AA_SHAPES)
+def test_two_activation_blocks(gu, nb, M, K, N, r, bt):
+    import paper_2503_12211_amd as stl
+    FL = stl.STL_FLAG_B_TRANSPOSED if bt else 0
+    p = stl_synth.aa_problem(nb, 4 * M, 4 * K, 4 * N, r, seed=900 + M + K + N + r, dtype="bf16", with_dC=True)
+    B = p["B"]
+    if bt:
+        B = np.ascontiguousarray(np.concatenate([B[b * 4 * K:(b + 1) * 4 * K].T for b in range(nb)], axis=0))
+    args = (p["A"], B, p["E_A"], p["E_B"], p["D"])
+    gu.check(gu.aa_forward(*args, nb, "bf16", flags=FL), planes.aa_forward(*args, nbatch=nb, b_transposed=bt), "bf16", "C")
+    got = gu.aa_backward(*args, p["dC"], nb, "bf16", flags=FL)
+    ref = dict(zip(("dA", "dB", "dE_A", "dE_B", "dD"), planes.aa_backward(*args, p["dC"], nbatch=nb, b_transposed=bt)))
+    for name in ref:
+        gu.check(got[name], ref[name], "bf16", name)
 
 
 @pytest.mark.parametrize("M,K,N,r", [(130, 72, 136, 9), (300, 40, 264, 5), (70, 250, 262, 4)])
