@@ -35,13 +35,9 @@ template <bool THROUGH>
 __device__ __forceinline__ void store16(void *p, u32x4_t v)
 {
     if constexpr (THROUGH) {
-#if defined(__HIP_DEVICE_COMPILE__)
         // a wide store's data registers may be overwritten one wait state after it at the earliest (the compiler does
         // not look into the statement)
-        __asm__ volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
-#else   // passes that generate no device code
-        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");
-#endif
+        asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
     } else {
         *reinterpret_cast<u32x4_t *>(p) = v;
     }

@@ -44,13 +44,9 @@ __device__ __forceinline__ int gswz(int k)                                      
 __device__ __forceinline__ void dma16(const bf16_t *g, uint32_t lds_wave_base)
 {
     const uint32_t l = __builtin_amdgcn_readfirstlane(lds_wave_base);
-#if defined(__HIP_DEVICE_COMPILE__)
     // a write of M0 by the scalar unit and the LDS-DMA load that reads it must be one wait state apart (the compiler, which
     // sees to that elsewhere, does not look into the statement)
-    __asm__ volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");
-#else   // passes that generate no device code
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");
-#endif
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");
 }
 
 __device__ __forceinline__ const bf16_t *at_bytes(const bf16_t *base, uint32_t off)

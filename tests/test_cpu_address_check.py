@@ -22,7 +22,10 @@ CLANG = Path(os.environ.get("STL_HOST_CLANG", "/opt/rocm/llvm/bin/clang++"))
 
 pytestmark = pytest.mark.skipif(not CLANG.exists(), reason=f"{CLANG} not found")
 
-DMA = ('asm volatile("s_mov_b32 m0, %1\\n\\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");')
+# The two memory instructions that the kernels write themselves, each with the wait state it needs: between the write of M0 and
+# the LDS-DMA load that reads it, and behind a wide store whose data registers the compiler may reuse.
+DMA = ('asm volatile("s_mov_b32 m0, %1\\n\\ts_nop 0\\n\\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(l) : "memory", "m0");')
+THROUGH = ('asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\\n\\ts_nop 0" ::"v"(p), "v"(v) : "memory");')
 
 
 def _host_source(text: str) -> str:
@@ -30,7 +33,6 @@ def _host_source(text: str) -> str:
     16-byte read the sanitizer can see whose LDS destination is checked against the dynamic LDS size of the launch, hardware
     waits and barriers nothing."""
     text = text.replace("extern __shared__ __align__(16) char smem[];", "char *smem = cpu_dyn_lds_ptr();")
-    assert "global_load_lds_dwordx4 %0" not in text or DMA in text, "LDS-DMA statement changed: update the host form"
     text = text.replace(DMA, "cpu_touch16(g, l);")
     # LDS addresses count from the start of the dynamic array in the host form
     for macro in ("STL_LDS", "STL_LDS_PTR"):
@@ -38,9 +40,9 @@ def _host_source(text: str) -> str:
     text = re.sub(r'asm volatile\("s_barrier" ::: "memory"\);', ";", text)
     text = re.sub(r'asm volatile\("s_waitcnt [^;]*;', ";", text)
     text = re.sub(r'asm volatile\("" : "\+v"\(\w+\)\);', ";", text)      # opaque-value fences
-    text = text.replace('asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(p), "v"(v) : "memory");',
-                        "*reinterpret_cast<u32x4_t *>(p) = v;")               # write-through store: a plain store on the host
-    left = [ln for ln in text.splitlines() if "asm volatile" in ln and 'asm volatile("" :::' not in ln]
+    text = text.replace(THROUGH, "*reinterpret_cast<u32x4_t *>(p) = v;")               # write-through store: a plain store on the host
+    # any other statement, in any spelling, is one that this host form does not know
+    left = [ln for ln in text.splitlines() if re.search(r"\b(__)?asm(__)?\b", ln) and 'asm volatile("" :::' not in ln]
     assert not left, f"unhandled inline assembly: {left}"
     if "STL_PIPELINE_STATIC_TICKETS" in text:
         text = "#define STL_PIPELINE_STATIC_TICKETS 1\n" + text

@@ -102,8 +102,8 @@ def test_two_activation_blocks(gu, nb, M, K, N, r, bt):
 
 @pytest.mark.parametrize("M,K,N,r", [(130, 72, 136, 9), (300, 40, 264, 5), (70, 250, 262, 4)])
 def test_non_finite_rows_stay_where_they_are(gu, M, K, N, r):
-    """Infinities and NaN in one tile row of X reach that tile row of C and no other: nothing of a neighbouring row, or of
-    what lies beyond the contraction's end, enters a product."""
+    """Infinities and NaN in one tile row of X reach that tile row of C and no other: nothing of a neighbouring row enters a
+    product."""
     p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=800 + M, dtype="bf16")
     clean = gu.forward(p, "bf16")
     q = dict(p, X=p["X"].copy())
@@ -114,3 +114,29 @@ def test_non_finite_rows_stay_where_they_are(gu, M, K, N, r):
     others = np.r_[0:4 * row, 4 * row + 4:4 * M]
     assert np.array_equal(got[others], clean[others])
     assert not np.isfinite(got[4 * row:4 * row + 4]).all()
+
+
+@pytest.mark.parametrize("dtype,M,K,N,r", [("bf16", 130, 72, 136, 9), ("bf16", 257, 488, 520, 40), ("bf16", 45, 272, 416, 64),
+                                           ("bf16", 70, 250, 262, 4), ("bf16", 100, 130, 67, 3), ("f32", 50, 33, 70, 7)])
+def test_weight_gradient_ends_with_the_rows(gu, dtype, M, K, N, r):
+    """The weight gradient contracts over the tile rows: what lies behind them in the last group of a plane -- here NaN in the
+    saved planes and in all of the workspace -- takes no part, not even multiplied by zero."""
+    import torch
+
+    import paper_2503_12211_amd as stl
+    p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=950 + M, dtype=dtype, with_dC=True)
+    prob = stl.Problem(4 * M, 4 * K, 4 * N, r, gu.STL_DT[dtype])
+    X, What, E_X, D, dC = (gu.dev(p[s], dtype) for s in ("X", "What", "E_X", "D", "dC"))
+    nb = stl.stl_workspace_bytes(prob, stl.STL_OP_BACKWARD)
+    got = []
+    for fill in (0, 0xff):                                   # bytes 0xff: NaN in either type
+        Xh, Y = (torch.full((stl.stl_plane_elems(M, w, r) * (4 if dtype == "f32" else 2),), fill, dtype=torch.uint8, device="cuda")
+                 .view(gu.TORCH_DT[dtype]) for w in (K, N))
+        ws = torch.full((nb,), fill, dtype=torch.uint8, device="cuda")
+        stl.stl_forward(prob, X, What, E_X, D, torch.empty_like(dC), Xh, Y, ws, nb, stl.STL_FLAG_UNFUSED)
+        assert bool(torch.isnan(Xh).any()) == bool(fill and M % gu.PG)         # the padding is untouched
+        ws.fill_(fill)
+        dWhat = torch.full((r, K, N), float("nan"), device="cuda")
+        stl.stl_backward(prob, X, What, E_X, D, dC, Xh, Y, None, dWhat, None, None, 0, ws, nb)
+        got.append(dWhat)
+    assert bool(torch.isfinite(got[0]).all()) and torch.equal(got[0], got[1])
