@@ -175,32 +175,48 @@ bool plane_gemm_pipe_eligible(const GemmDesc &g)
     return pipe::offsets_fit(g);
 }
 
-// The block that takes the least time, from what each was seen to take (us, forward form, K = 32 .. 1024): a single round of
-// blocks on the chip lasts a latency plus a time per stage, more where all CUs fetch and store at once; many rounds of the
-// large blocks last a time per round, many small blocks a time per block.  M x K x N, r: us at 256 x 256 / 128 x 128 / 64 x 64:
-//     16 x 1024 x 1024, 32: 24 / 17 / 16      256 x 256 x 256, 32: 11 / 7.8 / 7.6      512 x 512 x 512, 32: 18 / 16 / 27
-//    512 x 192 x 768,  32: 13 / 13 / 28      512 x 768 x 192, 24: 21 / 14 / 14       1024 x 512 x 512, 32: 22 / 27 / 49
-//   1024 x 1024 x 1024, 8: 26 / 25 / 37     2048 x 256 x 1024, 8: 16 / 18 / 38       4096 x 256 x 1024, 24: 69 / 89 / 209
-// (before, every plane above 128 x 128 took 256 x 256 blocks, smaller ones register-staged 128 x 128 blocks: 24 us for
-// the first of these and 10.7 for the second).
+// The block that takes the least time, predicted from rounds of blocks over the workgroups that the chip holds (one per CU, two of
+// the smaller blocks): a full round costs a time per stage and per byte stored, the last one a latency, a time per stage and
+// more of both the more CUs it occupies.  Coefficients are least squares over 187 shapes (M from 16 to 4096 tiles, K and N from 32 to
+// 1280, 8 to 64 planes, all product forms, 749 points); over shapes left out of the fit the block taken was 0.9 % slower than the
+// fastest on average and at most 25 % (2.3 and 29 % with a rule of fewer terms that knew no rounds of the smaller blocks and
+// no output type, which had 62 of 503 large planes more than 3 % slower than 256 x 256).  Some of them, us at
+// 256 x 256 / 128 x 256 / 128 x 128 / 64 x 64:
+//   Yhat   16 x 1024 x 1024, 32: 25 / 18 / 18 / 16    256 x 256 x 256, 32: 11 / 9.4 / 8.1 / 8.1    512 x 512 x 512, 32: 18 / 16 / 16 / 27
+//        1024 x 256 x 256,  49: 15 / 18 / 19 / 31   1024 x 1024 x 1024, 8: 26 / 22 / 24 / 38     4096 x 256 x 1024, 24: 81 / 96 / 103 / 211
+//   dXhat  208 x 128 x 624,  24: 17 / 13 / 12 / 7.8  3064 x 352 x 688, 12: 42 / 45 / 37 / 55
+//   dWhat 1024 x 1024 x 1024, 8: 30 / 26 / 26 / 45   1024 x 1024 x 1024, 32: 77 / 101 / 116 / 189  2048 x 256 x 256, 49: 49 / 38 / 35 / 40
+//   added to what is there  256 x 512 x 512, 49: 26 / 30 / 29 / 41   1024 x 1024 x 1024, 8: 39 / 31 / 31 / 50
+namespace {
+struct BlockCost {
+    int m, n, workgroups;
+    double round, round_stage, round_out;              // a full round: base, per stage of 32, per output size (2 bytes)
+    double last, last_stage, last_out;                 // a last one that is not full
+    double load_stage, load_out;                       // times the share of workgroups that it occupies
+    double time(const GemmDesc &g) const
+    {
+        const double st = (g.Kl + pipe::BKS - 1) / pipe::BKS, out = g.out_f32 ? (g.accumulate ? 4 : 2) : 1;
+        const double x = (double)((g.Mi + m - 1) / m) * ((g.Nj + n - 1) / n) * g.batch * g.nb / workgroups;
+        const double full = std::floor(x), rem = x - full;
+        return full * (round + round_stage * st + round_out * out) +
+               (rem > 0 ? last + last_stage * st + last_out * out + rem * (load_stage * st + load_out * out) : 0);
+    }
+};
+constexpr BlockCost kCost[] = {{256, 256, 256, 0.94, 0.80, 4.58, 4.18, 0.60, 1.44, 0.19, 2.10},        // in the order of PipeBlock
+                               {128, 256, 256, 1.34, 0.52, 2.40, 3.94, 0.42, 1.11, 0.12, 1.02},
+                               {128, 128, 512, 1.08, 0.60, 2.13, 3.32, 0.36, 0.57, 0.32, 1.84},
+                               {64, 64, 512, 1.86, 0.26, 0.59, 3.19, 0.14, 0.18, 0.19, 1.23}};
+}  // namespace
+
 PipeBlock pipe_block(const GemmDesc &g)
 {
-    const double st = (g.Kl + pipe::BKS - 1) / pipe::BKS;
-    auto blocks = [&](int bm, int bn) { return (double)((g.Mi + bm - 1) / bm) * ((g.Nj + bn - 1) / bn) * g.batch * g.nb; };
-    // one workgroup per CU: full rounds, then a last round whose length grows with how many CUs it occupies
-    auto rounds = [&](double b, double full, double lat, double load) {
-        const double n = std::floor(b / 256), rem = b / 256 - n;
-        return n > 0 ? n * full + (rem > 0 ? lat + rem * load : 0) : lat + rem * load;
-    };
-    // several workgroups per CU: latency of one block against the time all of them take
-    auto many = [&](double lat, double work) { return std::sqrt(lat * lat + work * work); };
-    const double t256 = rounds(blocks(256, 256), 5.3 + 0.83 * st, 6 + 0.56 * st, 2.5 + 0.2 * st);
-    const double t128x256 = rounds(blocks(128, 256), 3.7 + 0.55 * st, 5 + 0.37 * st, 1.5 + 0.13 * st);
-    const double t128 = many(4.1 + 0.375 * st, blocks(128, 128) * (0.005 + 0.00122 * st));
-    const double t64 = many(4.6 + 0.13 * st, blocks(64, 64) * (0.006 + 0.00047 * st));
-    if (t256 <= t128x256 && t256 <= t128 && t256 <= t64) return PipeBlock::b256;
-    if (t128x256 <= t128 && t128x256 <= t64) return PipeBlock::b128x256;
-    return t128 <= t64 ? PipeBlock::b128 : PipeBlock::b64;
+    int best = 0;
+    double t = kCost[0].time(g);
+    for (int i = 1; i < 4; ++i) {
+        const double ti = kCost[i].time(g);
+        if (ti < t) t = ti, best = i;
+    }
+    return (PipeBlock)best;
 }
 
 static int cu_count()

@@ -1,7 +1,7 @@
 // Driver of the CPU address check (test infrastructure only): calls the C ABI entry points on host buffers whose end
 // coincides with the end of their allocation, under AddressSanitizer.  Each command-line argument is one case:
 //   fwd:m:k:n:r:flags   bwd:m:k:n:r   mlp:m:k:h:r   ewb:k:n:r   aa:nb:m:k:n:r   ragged:nimg:rows:k:n:r
-//   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (prints which plane-product kernel and block a product takes)
+//   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (out_f32 = 2: added to it; prints which plane-product kernel and block a product takes)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   lines:R:Cc:r   (prints whether a bf16 encode starts its items on cache lines)
 //   device:N   (the device that is current for the following cases)
@@ -52,7 +52,7 @@ int main(int argc, char **argv)
         } else if (op == "device") {
             (void)hipSetDevice((int)v[0]);
         } else if (op == "route") {
-            stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, false, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
+            stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, v[6] > 1, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
             const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
             const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
             const char *staged = stl::staged_block(g) == 256 ? "256x256" : stl::staged_block(g) == 128 ? "128x128" : "64x64";

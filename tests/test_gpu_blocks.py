@@ -22,46 +22,50 @@ def gu():
 
 
 # M, K, N tile counts, r -- blocks of the three products Yhat, dXhat, dWhat
-SHAPES = [(16, 40, 64, 8),          # 128, 128, 128: fewer rows than a block
+SHAPES = [(16, 40, 64, 8),          # 64, 64, 64: fewer rows than a block
           (300, 200, 264, 3),       # 64, 64, 64
-          (130, 72, 136, 49),       # 128, 64, 64
-          (257, 488, 520, 40),      # 128, 128 x 256, 128; the weight gradient contracts over an odd number of rows
-          (640, 320, 512, 24),      # 128 x 256, 128, 128
+          (130, 72, 136, 49),       # 64, 64, 64
+          (257, 488, 520, 40),      # 256, 128 x 256, 256; the weight gradient contracts over an odd number of rows
+          (640, 320, 512, 24),      # 128 x 256, 128 x 256, 128 x 256
           (520, 264, 776, 32),      # 128, 128, 256
           (1030, 72, 520, 64),      # 128, 128, 128 x 256
           (2040, 232, 2040, 4),     # 256 with a contraction of 232; 64, 64
-          # contractions of whole stages, more of them than a ring holds
+          # contractions of whole stages, more of them than a ring holds, beside some that end inside one
           (192, 160, 160, 3),       # 64, 64, 64
-          (160, 160, 160, 48),      # 128, 128, 128
-          (160, 400, 264, 64),      # 128 x 256, 128 x 256 (both end inside a stage), 256
-          (387, 160, 320, 64),      # 256, 128 x 256, 128 x 256 (from an odd number of rows)
-          (288, 480, 160, 64),      # 128 x 256, 256, 128 x 256
-          (421, 400, 272, 64),      # 256, 256, 256, all ending inside a stage
-          (864, 192, 192, 64),      # whole-line 256, whole-line 256, 64
+          (206, 160, 224, 49),      # 128, 128, 128
+          (416, 264, 208, 48),      # 128 x 256, 256, 128
+          (160, 832, 160, 40),      # 64, 256, 256
+          (928, 160, 192, 33),      # 256, whole-line 256, 64
+          (131, 192, 712, 48),      # whole-line 256, 64, 256
           # staged through registers, odd widths
           (100, 106, 111, 3),       # 64, 64, 64
           (305, 261, 134, 64),      # 128, 256, 128
           (288, 153, 271, 64),      # 256, 128, 128
           (128, 270, 265, 64)]      # 64, 64, 256
 
-# stacked problems, M, K, N, r, second operand stored transposed -- blocks of Yhat, dAhat, dBhat
+# stacked problems, M, K, N, r, second operand stored transposed -- the blocks that count
 AA_SHAPES = [(1, 192, 160, 160, 3, False),        # one problem: the bf16 product of two [l][row] operands (dBhat) on
              (1, 154, 152, 152, 3, True),         #   64, with whole stages and without
-             (1, 160, 160, 160, 48, True),        #   128
+             (1, 160, 672, 16, 49, False),        #   128
              (1, 164, 200, 216, 40, False),       #   128, ending inside a stage
              (1, 288, 480, 160, 64, False),       #   128 x 256
-             (1, 387, 160, 320, 64, False),       #   128 x 256, ending inside a stage
+             (1, 208, 672, 16, 64, True),         #   128 x 256, ending inside a stage
              (1, 160, 400, 264, 64, False),       #   256
              (1, 421, 400, 272, 64, True),        #   256, ending inside a stage
              (1, 100, 106, 111, 3, False),        #   staged 64
              (1, 288, 153, 271, 64, True),        #   staged 128
              (1, 128, 270, 265, 64, False),       #   staged 256
-             (2, 32, 32, 32, 3, False),           # stacked: 128, one stage
-             (4, 32, 32, 32, 64, False),          #   128 x 256
-             (8, 272, 32, 144, 16, False),        #   256, staged 128, 128
-             (2, 32, 272, 144, 64, True),         #   staged 128, 128, 256
-             (8, 288, 144, 32, 16, False),        #   staged 128, 256, staged 128
-             (2, 80, 112, 80, 3, True),           #   staged 128, multiples of 8
+             (2, 32, 32, 32, 3, False),           # stacked, one stage: 64, all three products
+             (8, 80, 32, 16, 33, False),          #   128: Yhat
+             (8, 16, 32, 80, 33, True),           #        Yhat with [j][l]
+             (8, 32, 80, 16, 33, False),          #        dBhat
+             (8, 144, 32, 16, 16, False),         #   128 x 256: Yhat
+             (8, 144, 16, 32, 16, False),         #              dAhat
+             (8, 32, 144, 16, 16, False),         #              dBhat
+             (8, 272, 32, 144, 16, False),        #   256: Yhat
+             (8, 288, 144, 32, 16, False),        #        dAhat
+             (2, 32, 272, 144, 64, True),         #        dBhat
+             (2, 80, 112, 80, 3, True),           # stacked, more stages: staged 128, multiples of 8
              (2, 160, 192, 160, 3, True),         #   staged 256, multiples of 8
              (2, 73, 75, 119, 3, True),           #   staged 64, odd widths
              (8, 77, 96, 93, 49, False),          #   staged 128
