@@ -80,7 +80,9 @@ enum { STL_OP_ENCODE_WEIGHT = 0, STL_OP_FORWARD = 1, STL_OP_BACKWARD = 2, STL_OP
 
 /* forward variants (low byte of `flags`) and modifiers */
 enum {
-    STL_FLAG_AUTO = 0,      /* library picks the fastest variant for the shape */
+    STL_FLAG_AUTO = 0,      /* the library's choice: FUSED for problems bound by their launches (bf16, r <= 32, k a multiple of 64,
+                               n of 32, no Xhat_save: m k n r / 64 up to 4.2e6, or r <= 8, k <= 512 and at most 256 blocks of
+                               128 x 128 outputs), otherwise UNFUSED */
     STL_FLAG_UNFUSED = 1,   /* Algorithm 1 as three launches: encode -> plane products -> decode   */
     STL_FLAG_EPILOGUE = 2,  /* encode launch, then plane products with D applied in the epilogue   */
     STL_FLAG_FUSED = 3,     /* one launch: encode -> MFMA -> decode, no plane ever written to HBM   */
@@ -205,8 +207,8 @@ stl_status_t stl_mlp_forward(const stl_problem_t *up, const stl_problem_t *down,
 /*
  * The inter-layer step of stl_mlp_forward on its own: Yhat1 r1 x M x N1 (in), D1 r1 x 16, E_X2 r2 x 16
  * (in) -> Xhat2 r2 x M x N1 (out).  H: scratch for the hidden activation, m x n1 elements of the storage
- * dtype; may be NULL when the one-pass kernel applies (bf16 and n1/4 a multiple of 8) and the variant is
- * STL_FLAG_AUTO, required otherwise (INVALID_ARG if missing).  flags as for stl_mlp_forward.
+ * dtype; may be NULL for bf16 with n1/4 a multiple of 8 and the variant STL_FLAG_AUTO, required otherwise
+ * (INVALID_ARG if missing), also where the one-pass kernel applies and does not touch it.  flags as for stl_mlp_forward.
  */
 stl_status_t stl_recode(const stl_problem_t *up, const stl_problem_t *down, const void *Yhat1,
                         const void *D1, const void *E_X2, void *Xhat2, void *H, int flags, void *stream);

@@ -145,7 +145,8 @@ struct EwbWs {
     size_t planes, part, total;
 };
 
-// backward of the weight encoding: a bf16 copy of dWhat (bf16 storage only) and the partial sums of dE_W
+// backward of the weight encoding: a bf16 copy of dWhat (bf16 storage; written for fewer than 8 tile columns only, other widths
+// keep the declared size) and the partial sums of dE_W
 EwbWs ewb_layout(const stl_problem_t *p, const Dims &d)
 {
     EwbWs w{};
@@ -205,7 +206,7 @@ MlpWs mlp_layout(const stl_problem_t *up, const Dims &d1, const Dims &d2, int va
     off += align256((size_t)d2.r * d2.Mp() * d2.N * d2.es);
     w.one_pass = variant == STL_FLAG_AUTO && stl::recode_eligible(up->dtype, d1.N);
     w.hidden = off;
-    // the declared size holds the hidden activation for every n1 / 4 that is no multiple of 8, as the header's rule for H does
+    // a width that is no multiple of 8 keeps the declared size it had before the one-pass kernel took it
     if (!w.one_pass || d1.N % 8) off += align256((size_t)up->m * up->n * d1.es);
     w.total = off;
     return w;
@@ -536,10 +537,14 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
     if (!X || !What || !E_X || !D || !C) return fail(STL_ERR_INVALID_ARG, "stl_forward: NULL pointer");
     if (any_misaligned(X, What, E_X, D, C, Xhat_save, Yhat_save))
         return fail(STL_ERR_INVALID_ARG, "stl_forward: pointer not 16-byte aligned");
-    // Automatic choice: the single-launch variant where the whole operator is launch-bound -- up to about four million tile
-    // products per plane set, and at r <= 8 wherever every CU has at most one block and the chain of contraction steps is short
-    // (m = 128 / 256 / 1024 / 4096, k = n = 512, r = 8: 10.5 / 10.6 / 10.7 / 11.1 us a call against 13.2 / 13.1 / 13.0 / 13.1 of three launches; at
-    // m = 32, k = 1024, n = 512 16.8 against 14.7) -- the three-launch path everywhere else.
+    // Automatic choice.  The single launch decodes the fp32 sums, three launches round Yhat to the storage type in between.  It is taken
+    //  - up to about four million tile products per plane set, where the operator is bound by its launches (m = 128, k = n = 512, r = 8:
+    //    10.5 us against 13.2).  One block walks the whole contraction there, so that few rows and a long contraction take longer
+    //    than three launches would (m = 32, n = 512, r = 8: k = 1024 16.8 against 13.3, k = 2048 29.7 against 13.2); such calls keep
+    //    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other;
+    //  - at r <= 8 also wherever every CU has at most one block and the contraction is short: m = 1024 / 4096 / 8192, k = n = 512, r = 8
+    //    10.8 / 11.2 / 13.8 us against 13.1 / 13.2 / 17.6, and nowhere slower over m = 32 ... 8192, k = 64 ... 512, n = 128 ... 4096.
+    // Three launches everywhere else.
     const FwdWs w_declared = fwd_layout(d, variant);     // the workspace is checked against what the caller asked for
     if (variant == STL_FLAG_AUTO && !Xhat_save && stl::block_forward_eligible(prob->dtype, d.M, d.K, d.N, d.r) &&
         ((double)d.M * d.K * d.N * d.r <= 4.2e6 ||

@@ -1,5 +1,6 @@
-"""Automatic choice of the forward variant at r <= 8: the single-launch variant's bits wherever the rule takes it, and right
-against the oracle on either side of the rule's edges (128 tile columns of X, 256 blocks of 32 x 32 tiles, r = 8)."""
+"""Automatic choice of the forward variant: the single-launch variant's bits wherever the rule takes it, and right against the
+oracle on either side of the rule's edges (at r <= 8 128 tile columns of X and 256 blocks of 32 x 32 tiles; 4.2 million tile products at
+any contraction length and rank)."""
 import numpy as np
 import pytest
 
@@ -16,7 +17,9 @@ def gu():
 
 
 @pytest.mark.parametrize("m,k,n,r,single", [(1024, 512, 512, 8, True), (4096, 256, 1024, 5, True), (4100, 512, 992, 8, False),
-                                            (1024, 576, 512, 8, False), (1024, 512, 512, 9, False), (1020, 448, 1056, 7, True)])
+                                            (1024, 576, 512, 8, False), (1024, 512, 512, 9, False), (1020, 448, 1056, 7, True),
+                                            (32, 1024, 512, 8, True), (32, 2048, 512, 8, True), (32, 2048, 544, 8, False),
+                                            (128, 256, 256, 32, True), (132, 256, 256, 32, False)])
 def test_auto_forward(gu, m, k, n, r, single):
     import paper_2503_12211_amd as stl
     p = stl_synth.stl_problem(m, k, n, r, seed=600 + m + k + n + r, dtype="bf16")
