@@ -281,6 +281,18 @@ __device__ __forceinline__ void mask_tail(bf16x8_t &v, int rem, int lane)
     v = __builtin_bit_cast(bf16x8_t, w);
 }
 
+// CUs of the device (of the first one a process uses: all are of one kind), the workgroups of a persistent launch
+inline int cu_count()
+{
+    static const int n = []() {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 256;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+        return cus;
+    }();
+    return n;
+}
+
 // Block list of a persistent launch.  Hardware deals workgroup ids round-robin over the 8 XCDs; each XCD takes a contiguous
 // eighth of the list (its workgroups side by side in it), so that the blocks an L2 serves at one time are neighbours of
 // one or two planes.  The grid is a multiple of 8.

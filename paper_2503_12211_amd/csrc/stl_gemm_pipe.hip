@@ -219,17 +219,6 @@ PipeBlock pipe_block(const GemmDesc &g)
     return (PipeBlock)best;
 }
 
-static int cu_count()
-{
-    static const int n = []() {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-        return cus;
-    }();
-    return n;
-}
-
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL>
 static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
@@ -243,7 +232,7 @@ static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
-    const int wgs = cu_count() * per_cu;                   // they walk the block list
+    const int wgs = pipe::cu_count() * per_cu;                   // they walk the block list
     const unsigned grid = pipe::list_grid(total, wgs);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), smem, s, (const bf16_t *)A, (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj,
                        g.Kl, tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);

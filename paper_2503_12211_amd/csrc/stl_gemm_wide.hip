@@ -157,17 +157,6 @@ bool plane_gemm_wide_eligible(const GemmDesc &g)
     return plane_gemm_pipe_eligible(g) && !g.a_kmajor && !g.out_f32 && !g.accumulate && g.nb == 1 && g.Kl % 64 == 0 && pipe_block(g) == PipeBlock::b256;
 }
 
-static int wide_cu_count()
-{
-    static const int n = []() {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
-        return cus;
-    }();
-    return n;
-}
-
 template <bool B_T>
 static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
@@ -178,7 +167,7 @@ static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, v
     const int tiles_m = (g.Mi + 255) / 256, tiles_n = (g.Nj + 255) / 256;
     const long total = (long)tiles_m * tiles_n * g.batch;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
-    const unsigned grid = pipe::list_grid(total, wide_cu_count());
+    const unsigned grid = pipe::list_grid(total, pipe::cu_count());
     hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, (const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl,
                        tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
     return hipGetLastError();

@@ -299,17 +299,6 @@ bool forward_pipeline_eligible(int dtype, int M, int K, int N, int r)
 
 size_t forward_pipeline_counter_bytes(int M) { return (size_t)(kCtrBase + 2 * ((M + 255) / 256)) * sizeof(unsigned); }
 
-static int pipeline_cus()
-{
-    static const int n = []() {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8) return 256;
-        return cus / 8 * 8;
-    }();
-    return n;
-}
-
 hipError_t launch_forward_pipeline(const void *X, const void *E, const void *What, const void *Dm, void *Xhat, void *Yhat,
                                    void *C, void *counters, int M, int K, int N, int r, bool gelu, hipStream_t s)
 {
@@ -337,7 +326,7 @@ hipError_t launch_forward_pipeline(const void *X, const void *E, const void *Wha
     auto kern = gelu ? forward_pipeline_kernel<true> : forward_pipeline_kernel<false>;
     e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted[gelu]);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(pipeline_cus()), dim3(512), smem, s, a);
+    hipLaunchKernelGGL(kern, dim3(pipe::cu_count() < 8 ? 256 : pipe::cu_count() / 8 * 8), dim3(512), smem, s, a);
     return hipGetLastError();
 }
 
