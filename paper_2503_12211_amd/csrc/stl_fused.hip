@@ -270,7 +270,7 @@ static hipError_t launch_block_t(const void *Xin, const void *What, const void *
     constexpr int smem = fused::smem_bytes<RP, ENCODE>();
     static_assert(smem <= 160 * 1024, "LDS budget");
     static std::atomic<uint64_t> granted{0};               // of this instantiation
-    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted); e != hipSuccess) return e;
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted); e != hipSuccess) return e;
     const int bi = (M + fused::BI - 1) / fused::BI, bj = (N + fused::BJ - 1) / fused::BJ;
     const long total = (long)bi * bj;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

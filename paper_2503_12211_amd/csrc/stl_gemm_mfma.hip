@@ -263,7 +263,7 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
     constexpr int slabs = 32 * (BN / WAVES_N * (int)sizeof(TO) + 16) * WAVES_M * WAVES_N;      // of the epilogue
     const int smem = g.Kl > BK ? most : stage > slabs ? stage : slabs;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
-    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), most, granted); e != hipSuccess) return e;
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, most, granted); e != hipSuccess) return e;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

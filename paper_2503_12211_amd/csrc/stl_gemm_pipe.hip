@@ -228,7 +228,7 @@ static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *
     static_assert(smem <= 160 * 1024, "LDS budget");
     constexpr int per_cu = 160 * 1024 / smem > 2 ? 2 : 160 * 1024 / smem;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
-    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted); e != hipSuccess) return e;
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted); e != hipSuccess) return e;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

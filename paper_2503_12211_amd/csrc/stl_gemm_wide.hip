@@ -163,7 +163,7 @@ static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, v
     auto kern = gemm_pipe_wide_kernel<B_T>;
     constexpr int smem = 160 * 1024;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
-    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted); e != hipSuccess) return e;
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted); e != hipSuccess) return e;
     const int tiles_m = (g.Mi + 255) / 256, tiles_n = (g.Nj + 255) / 256;
     const long total = (long)tiles_m * tiles_n * g.batch;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;

@@ -6,16 +6,18 @@
 
 namespace stl {
 
-// Lets `kern` be launched with up to `bytes` of dynamic LDS (more than 64 KB has to be asked for) on the current device.  `done`
-// belongs to that kernel alone and holds the devices it has been granted on, a bit each; devices beyond 64 are asked every time.
-inline hipError_t allow_lds(const void *kern, int bytes, std::atomic<uint64_t> &done)
+// Lets `kern` be launched with `bytes` of dynamic LDS, at most `most`, on the current device: more than 64 KB has to be asked for.
+// `done` belongs to that kernel alone and holds the devices it has been granted on, a bit each; devices beyond 64 are asked
+// every time.
+inline hipError_t allow_lds(const void *kern, int bytes, int most, std::atomic<uint64_t> &done)
 {
+    if (bytes <= 64 * 1024) return hipSuccess;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
     if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
-    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, most);
     if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
     return e;
 }

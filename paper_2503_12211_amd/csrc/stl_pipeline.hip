@@ -324,7 +324,7 @@ hipError_t launch_forward_pipeline(const void *X, const void *E, const void *Wha
     static_assert(smem <= 160 * 1024, "LDS budget");
     static std::atomic<uint64_t> granted[2] = {};           // the two kernels are of one type
     auto kern = gelu ? forward_pipeline_kernel<true> : forward_pipeline_kernel<false>;
-    e = allow_lds(reinterpret_cast<const void *>(kern), smem, granted[gelu]);
+    e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted[gelu]);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(pipe::cu_count() < 8 ? 256 : pipe::cu_count() / 8 * 8), dim3(512), smem, s, a);
     return hipGetLastError();

@@ -460,10 +460,10 @@ static hipError_t launch_tile_map(const void *V, const void *Pin, const void *B,
     auto kern = tile_map_kernel<T, TB, ENC, DEC, OUTER, GELU, GROUPS>;
     constexpr int most = 64 * 16 * 4 + GROUPS * (64 + 16) * kTilePitch * 4;
     static_assert(most <= 160 * 1024, "LDS budget");
-    static std::atomic<uint64_t> granted{0};               // of this instantiation
-    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), most, granted); e != hipSuccess) return e;
     const int ng = (r + 15) / 16, lw = tile_item_log2(Cc), rows = 64 >> lw;
     const int smem = r * 64 + GROUPS * ((DEC || OUTER ? ng * 16 : 0) + (ENC || OUTER ? 16 : 0)) * kTilePitch * 4;
+    static std::atomic<uint64_t> granted{0};               // of this instantiation
+    if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, most, granted); e != hipSuccess) return e;
     const long items = (long)((R + rows - 1) / rows) * ((Cc + (1 << lw) - 1) >> lw);
     if (blocks <= 0) blocks = (int)(items > 8192 ? 8192 : items);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(GROUPS * 256), smem, s, (const T *)V, (const T *)Pin, (const TB *)B, (T *)Pout,
