@@ -52,3 +52,32 @@ def test_against_the_oracle_and_the_item_kernels(gu, dtype, M, Cc, r, gelu):
     assert np.array_equal(P[:, :top], Pt)
     if dtype == "f32":                     # the bf16 decode of fewer tiles is the matrix cores', which add in another order
         assert np.array_equal(C[:4 * top], Ct)
+
+
+@pytest.mark.parametrize("rows,K,N,r", [(197, 64, 65, 5), (39, 72, 96, 17)])
+def test_ragged_rows(gu, rows, K, N, r):
+    """Through the row map: null rows read as zeros and never written, the last tile rows decoded apart."""
+    nimg = -(-140000 // ((rows // 4) * min(K, N)))
+    p = stl_synth.ragged_problem(nimg, rows, 4 * K, 4 * N, r, seed=92, dtype="f32")
+    C, Xh, Yh = gu.ragged_forward(p, rows, "f32", save=True)
+    gu.check(Xh, planes.encode(planes.pad_rows(p["X"], rows), p["E_X"]), "f32", "Xhat", slab=1)
+    gu.check(C, planes.ragged_forward(p["X"], p["What"], p["E_X"], p["D"], p["fold"], rows), "f32", "C")
+
+
+def test_plane_major(gu):
+    """The weight's layout: its encode, and dW alone from plane-major gradients."""
+    import torch
+
+    import paper_2503_12211_amd as stl
+    K, N, r = 1031, 129, 9
+    rng = np.random.default_rng(5)
+    W = rng.standard_normal((4 * K, 4 * N)).astype(np.float32)
+    E = (rng.standard_normal((r, 16)) / 4).astype(np.float32)
+    dWh = rng.standard_normal((r, K, N)).astype(np.float32)
+    gd = gu.Guard()
+    What = gd.alloc((r, K, N), torch.float32)
+    stl.stl_encode_weight(stl.Problem(4, 4 * K, 4 * N, r, stl.STL_F32), gu.dev(W, "f32"), gu.dev(E, "f32"), What)
+    gd.check()
+    gu.check(gu.host(What), planes.encode(W, E), "f32", "What", slab=1)
+    got = gu.encode_weight_backward(W, E, dWh, "f32", skip=("dE_W",))
+    gu.check(got["dW"], planes.encode_weight_backward(W, E, dWh)[0], "f32", "dW")
