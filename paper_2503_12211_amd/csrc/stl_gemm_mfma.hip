@@ -1,246 +1,292 @@
 // Batched plane products on the CDNA4 matrix cores (step (ii) of Algorithm 1, Claim 3.4):
-//     Out[p][i][j] (+)= sum_l A[p](i,l) * B[p](l,j)       bf16 x bf16 -> fp32, p < r planes.
+//     Out[p][i][j] (+)= sum_l A[p](i,l) * B[p](l,j)       bf16 x bf16 -> fp32, p < r planes,
+// for what the LDS-DMA kernels do not take: contiguous dimensions that are no multiple of 8 (250 tile columns of a 1000-class head,
+// 50 tile rows of 200 tokens), whose rows begin at any even address, and stacked problems with more than one stage.
 //
-// One workgroup owns a BM x BN block of one plane.  Both operands are staged in LDS in
-// "row x 64 k-values" form (k contiguous), double buffered, 16-byte chunks XOR-swizzled so
-// that fragment reads (ds_read_b128, 32 rows x 2 k-halves per wavefront) and staging writes
-// spread over all banks.  An operand whose contiguous memory dimension is not the contraction
-// index is transposed in registers on its way from HBM to LDS, so the MFMA loop is the same
-// for the forward product and the two backward products.
-// A contiguous dimension that is no multiple of 8 (250 tile columns of a 1000-class head, 50 tile rows of 200 tokens) leaves
-// rows at any even address: the ANY forms load and store them with unaligned 16-byte accesses.  Before, such shapes went
-// element by element through the fp32 kernel: attention scores 96 x (200 x 64 x 200), r = 32, 73 -> 23, 153 -> 23 and 182 -> 21 us
-// for the three products; 2048 x 768 x 1000, r = 32: 86 -> 15, 119 -> 13, 238 -> 28 us.
-// Wavefronts compute 32x32x16 MFMA fragments; accumulators stay in registers for the whole
-// contraction.  Block ids are remapped so that consecutive blocks of one plane land on the
-// same XCD (and share its L2).
-#include "stl_kernels.h"
-#include "stl_device.h"
-
+// One workgroup owns a BM x BN block of one plane, 16x16x32 MFMA.  Operands go from HBM to LDS through registers, 16 bytes at a time
+// from any even address, into the LDS layouts of the LDS-DMA kernels (fragment addressing and swizzles of stl_gemm_pipe.h): an
+// operand whose contiguous dimension is not the contraction keeps its orientation and is read by the transposing
+// ds_read_b64_tr_b16.  A stage is 64 contraction elements, two pieces of 32; LDS is double buffered and the next PF stages are in
+// registers.
+// What bounds it: the latency of a chain of short stages, and before that the instructions around each load, since the products
+// themselves are a few MFMAs.  Hence row addresses are computed once per workgroup (or by two multiply-adds per load where the rows
+// are the contraction; groups of rows by a shift, not a division), the incomplete last chunk of a row costs nothing where a
+// block has none, and accumulators leave as 8-byte pieces through a slab of the wavefront's own.
+// Measured, us, with the operands transposed in registers, addresses and chunk ends computed at every load and one stage in flight ->
+// now: 512 x 192 x 250 tiles, r = 32 (Yhat / dXhat / dWhat) 14.4 / 13.3 / 28 -> 8.6 / 8.9 / 11; 512 x 1023 x 1024, r = 32 (Yhat) 52 -> 40;
+// 96 x (50 x 16 x 50), r = 32 (the three products) 19 / 17.5 / 16 -> 8.5 / 8.4 / 8.3 for 15 MB of output or input planes each.
+#include "stl_gemm_pipe.h"
+#include <cmath>
 
 namespace stl {
+namespace staged {
 
-constexpr int BK = 64;  // contraction elements per LDS stage (one 128-byte LDS row)
+constexpr int BK = 64;      // contraction elements per LDS stage, in two pieces of pipe::BKS
 
-__device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
-
-// byte offset of the 16-byte chunk c (0..7) of `row` inside one staged operand
-__device__ __forceinline__ int lds_off(int row, int c) { return row * (BK * 2) + ((c ^ swz(row)) << 4); }
-
-// where storage row `row` of plane p of an operand begins (rows in groups of pg, see plane_row_base)
+// Where the stored rows of one operand lie (see plane_row_base): row I of plane p begins at (I + (I >> shift) * skip) * ld + p * plane
+// elements.  Groups have a power of two of rows, or there is one group (shift 31).
 struct Lay {
-    int pg, batch, p;
-    long ld;
-    int row0;   // first stored row of this problem inside the stacked operand
-    __device__ __forceinline__ size_t off(int row) const
-    {
-        return plane_row_base(row0 + row, pg, batch, (int)ld) + (size_t)p * pg * ld;
-    }
+    int ld, shift, skip;
+    long plane;
+    __device__ __forceinline__ long row(int I) const { return (long)(I + (I >> shift) * skip) * ld; }
 };
 
-// ---- HBM -> registers ------------------------------------------------------------------
-// Direct operand: stored [row][l], l contiguous (leading dimension ld elements).
-// ANY: contiguous dimensions that are no multiple of 8 (see load8; at least 8), here and below.
-template <int ROWS, int NT, bool ANY>
-struct DirectLoader {
-    static constexpr int CH = ROWS * 8 / NT;  // 16-byte chunks per thread
-    u32x4_t v[CH];
-    __device__ __forceinline__ void load(const bf16_t *__restrict__ base, const Lay &lay, int row0, int rows_total, int k0,
-                                         int Kl, int tid)
-    {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int id = tid + j * NT, row = id >> 3, c = id & 7;
-            const int gr = row0 + row, gk = k0 + c * 8;
-            v[j] = load8<ANY>(base + lay.off(gr) + gk, gr < rows_total ? Kl - gk : 0);
-        }
-    }
-    __device__ __forceinline__ void store(char *lds, int tid) const
-    {
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int id = tid + j * NT, row = id >> 3, c = id & 7;
-            *reinterpret_cast<u32x4_t *>(lds + lds_off(row, c)) = v[j];
-        }
-    }
+// n / d for 0 <= n < 2^31, as one multiplication: mul = ceil(2^(31 + s) / d) with 2^s >= d, so that the error n (mul d - 2^(31 + s)) / d
+// stays below 2^(31 + s) / d
+struct Div {
+    uint32_t mul, shift;
+    __device__ __forceinline__ int of(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
 };
 
-// Transposing operand: stored [l][row], row contiguous (leading dimension ld elements).
-// A thread takes units of 4 l-values x 8 rows, swaps them in registers and writes 8 bytes
-// (4 consecutive k) to each of 8 LDS rows.
-template <int ROWS, int NT, bool ANY>
-struct TransLoader {
-    static constexpr int RG = ROWS / 8;                // row groups
-    static constexpr int UNITS = (BK / 4) * RG / NT;   // units per thread
-    static_assert(UNITS >= 1, "more threads than units");
-    u32x4_t v[UNITS][4];
-    __device__ __forceinline__ void load(const bf16_t *__restrict__ base, const Lay &lay, int row0, int rows_total, int k0,
-                                         int Kl, int tid)
+// eight elements moved h places towards the first, zeros behind them, any h >= 0
+__device__ __forceinline__ u32x4_t settle(u32x4_t v, int h) { return h <= 0 ? v : h >= 8 ? u32x4_t{0u, 0u, 0u, 0u} : shift_down(v, h); }
+
+// One operand's share of a thread: NC 16-byte chunks per piece of 32 contraction elements.
+//   [row][l]: chunk id = tid + j NT is (row id / 4, elements 8 (id % 4) ..);   [l][row]: (l = id / (ROWS / 8), rows 8 (id % (ROWS / 8)) ..)
+// The swizzles repeat over the rows that j steps by, so that a thread's chunks are a fixed distance apart in LDS.  A chunk that
+// reaches beyond its row is read as the eight elements that end with the row and moved into place on its way to LDS, so
+// that no load waits for another; elements beyond the contraction become zeros there.
+template <bool KMAJOR, int ROWS, int NT>
+struct Piece {
+    static constexpr int NC = ROWS * 4 / NT, CPR = ROWS / 8;
+    static constexpr int BYTES = ROWS * 64;                    // of a piece in LDS
+    static constexpr int STEP = KMAJOR ? NT / CPR : NT / 4;    // rows that j steps by
+    static_assert(NC >= 1 && STEP % 16 == 0, "every thread takes chunks whose swizzle does not depend on j");
+    const bf16_t *src[KMAJOR ? 1 : NC];     // [row][l]: the rows; [l][row]: this thread's column of row 0
+    int lds, k, over;                       // LDS offset of chunk 0; contraction offset in a piece; elements beyond the row's end ([l][row])
+    bool edge;                              // the block has rows beyond the operand's ([l][row])
+    __device__ __forceinline__ void init(const bf16_t *base, const Lay &lay, int row0, int total, int roff, int tid)
+    {
+        if constexpr (!KMAJOR) {
+            const int row = tid >> 2, c = tid & 3;
+            lds = row * 64 + ((c ^ pipe::fswz(row)) << 4);
+            k = 8 * c;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                int g = row0 + row + j * STEP;
+                g = g < total ? g : total - 1;                 // rows past the edge feed only discarded outputs
+                src[j] = base + lay.row(roff + g);
+            }
+        } else {
+            const int c = tid % CPR, col = row0 + 8 * c;
+            k = tid / CPR;
+            lds = k * (ROWS * 2) + ((c ^ pipe::gswz<ROWS>(k)) << 4);
+            edge = row0 + ROWS > total;
+            over = col - (total - 8);
+            src[0] = base + (over > 0 ? total - 8 : col);
+        }
+    }
+    // the piece of the contraction elements l0 .. l0 + 31, as it lies in memory
+    __device__ __forceinline__ void load(u32x4_t (&v)[NC], const Lay &lay, int roff, int l0, int Kl) const
     {
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            const int id = tid + u * NT, rg = id % RG, kq = id / RG;
-            const int gr = row0 + rg * 8;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const int gk = k0 + kq * 4 + kk;
-                v[u][kk] = load8<ANY>(base + lay.off(gk) + gr, gk < Kl ? rows_total - gr : 0);
+        for (int j = 0; j < NC; ++j) {
+            if constexpr (!KMAJOR) {
+                const int l = l0 + k;
+                v[j] = *reinterpret_cast<const u32x4_any_t *>(src[j] + (l < Kl - 8 ? l : Kl - 8));
+            } else {
+                const int l = l0 + k + j * STEP;
+                v[j] = *reinterpret_cast<const u32x4_any_t *>(src[0] + lay.row(roff + (l < Kl ? l : Kl - 1)));
             }
         }
     }
-    __device__ __forceinline__ void store(char *lds, int tid) const
+    __device__ __forceinline__ void put(char *piece, u32x4_t (&v)[NC], int l0, int Kl) const
     {
+        const bool tail = l0 + pipe::BKS > Kl;
+        if (tail || (KMAJOR && edge)) {
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) {
-            const int id = tid + u * NT, rg = id % RG, kq = id / RG;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                // element j of each of the four l-rows -> 4 consecutive k of LDS row rg*8+j
-                const int d = j >> 1, sh = (j & 1) * 16;
-                const uint32_t e0 = (v[u][0][d] >> sh) & 0xffffu, e1 = (v[u][1][d] >> sh) & 0xffffu;
-                const uint32_t e2 = (v[u][2][d] >> sh) & 0xffffu, e3 = (v[u][3][d] >> sh) & 0xffffu;
-                u32x2_t w = {e0 | (e1 << 16), e2 | (e3 << 16)};
-                const int row = rg * 8 + j;
-                *reinterpret_cast<u32x2_t *>(lds + lds_off(row, kq >> 1) + (kq & 1) * 8) = w;
-            }
+            for (int j = 0; j < NC; ++j) v[j] = settle(v[j], KMAJOR ? (l0 + k + j * STEP < Kl ? over : 8) : l0 + k - (Kl - 8));
         }
+#pragma unroll
+        for (int j = 0; j < NC; ++j) *reinterpret_cast<u32x4_t *>(piece + lds + j * STEP * (KMAJOR ? ROWS * 2 : 64)) = v[j];
     }
 };
 
-template <bool KMAJOR, int ROWS, int NT, bool ANY>
-struct LoaderSel { typedef DirectLoader<ROWS, NT, ANY> type; };
-template <int ROWS, int NT, bool ANY>
-struct LoaderSel<true, ROWS, NT, ANY> { typedef TransLoader<ROWS, NT, ANY> type; };
-
-// ---- kernel ----------------------------------------------------------------------------
 // A_T: A stored [l][i];  B_T: B stored [l][j].  (false: stored [i][l] resp. [j][l].)
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_mfma_kernel(const bf16_t *__restrict__ A,
-                                                                          const bf16_t *__restrict__ B,
-                                                                          TO *__restrict__ Out, int Mi, int Nj, int Kl,
-                                                                          int tiles_m, int tiles_n, int total, int a_pg,
-                                                                          int b_pg, int o_pg, int batch)
+// PF: stages on their way in registers (1 or 2); 0: the contraction is a single stage.  KS: groups of WAVES_M x WAVES_N wavefronts
+// that take every KS-th stage each, their sums added up in LDS at the end.
+template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
+__global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 : KS == 1 ? 5 : 4) : 2) void gemm_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
+                                                                          TO *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m, int tiles_n,
+                                                                          int total, int batch, Div by_plane, Div by_row, Div by_batch, Lay la,
+                                                                          Lay lb, Lay lo)
 {
-    constexpr int NT = WAVES_M * WAVES_N * 64;
-    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int FM = WM / 32, FN = WN / 32;
-    constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
+    using pipe::static_for;
+    constexpr int NT = WAVES_M * WAVES_N * 64, WM = BM / WAVES_M, WN = BN / WAVES_N, FM = WM / 16, FN = WN / 16;
+    typedef Piece<A_T, BM, NT> PA;
+    typedef Piece<B_T, BN, NT> PB;
+    constexpr int STAGE = 2 * (PA::BYTES + PB::BYTES);
+    // blocks of narrow outputs: fragments that lie beyond the output take no part
+    constexpr bool NARROW = BM == 64;
     extern __shared__ __align__(16) char smem[];
 
-    // XCD-aware block order: hardware deals consecutive block ids round-robin to the 8 XCDs
-    int bid = blockIdx.x;
-    if ((total & 7) == 0) bid = (bid & 7) * (total >> 3) + (bid >> 3);
-    const int per_plane = tiles_m * tiles_n;
-    const int q = bid / per_plane;                    // (stacked problem, plane)
-    const int rem = bid - q * per_plane;
-    const int i0 = (rem / tiles_n) * BM, j0 = (rem % tiles_n) * BN;
-    const int pb = q / batch, p = q - pb * batch;
+    const int bid = pipe::first_block(total);                   // one block per workgroup; each XCD takes a contiguous eighth
+    if (bid >= pipe::end_block(total)) return;
+    const int q = by_plane.of(bid), rem = bid - q * (tiles_m * tiles_n);   // (stacked problem, plane)
+    const int bi = by_row.of(rem), i0 = bi * BM, j0 = (rem - bi * tiles_n) * BN;
+    const int pb = by_batch.of(q), p = q - pb * batch;
 
-    const Lay lda{a_pg, batch, p, A_T ? Mi : Kl, pb * (A_T ? Kl : Mi)}, ldb{b_pg, batch, p, B_T ? Nj : Kl, pb * (B_T ? Kl : Nj)},
-        ldo{o_pg, batch, p, Nj, pb * Mi};
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int group = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    const int tid = KS == 1 ? threadIdx.x : threadIdx.x % NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    char *own = smem + group * (2 * STAGE);                     // this group's two buffers
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const int a_roff = pb * (A_T ? Kl : Mi), b_roff = pb * (B_T ? Kl : Nj);
+    PA pa;
+    PB pbt;
+    pa.init(A + (size_t)p * la.plane, la, i0, Mi, a_roff, tid);
+    pbt.init(B + (size_t)p * lb.plane, lb, j0, Nj, b_roff, tid);
+    pipe::Frag<A_T, BM> fa;
+    pipe::Frag<B_T, BN> fb;
+    fa.init(wm * WM, lane);
+    fb.init(wn * WN, lane);
 
-    typename LoaderSel<A_T, BM, NT, ANY>::type la;
-    typename LoaderSel<B_T, BN, NT, ANY>::type lb;
+    constexpr int SETS = PF ? PF : 1;
+    u32x4_t ra[SETS][2][PA::NC], rb[SETS][2][PB::NC];
+    auto fetch = [&](auto set_c, int st) {
+        constexpr int S = decltype(set_c)::value;
+        static_for<0, 2>([&](auto h_c) {
+            constexpr int h = decltype(h_c)::value;
+            const int l0 = st * BK + h * pipe::BKS;
+            if (h == 0 || l0 < Kl) {
+                pa.load(ra[S][h], la, a_roff, l0, Kl);
+                pbt.load(rb[S][h], lb, b_roff, l0, Kl);
+            }
+        });
+    };
+    auto put = [&](auto set_c, int st, int buf) {
+        constexpr int S = decltype(set_c)::value;
+        char *stage = own + buf * STAGE;
+        static_for<0, 2>([&](auto h_c) {
+            constexpr int h = decltype(h_c)::value;
+            if (h == 0 || st * BK + h * pipe::BKS < Kl) {
+                pa.put(stage + h * PA::BYTES, ra[S][h], st * BK + h * pipe::BKS, Kl);
+                pbt.put(stage + 2 * PA::BYTES + h * PB::BYTES, rb[S][h], st * BK + h * pipe::BKS, Kl);
+            }
+        });
+    };
 
-    f32x16_t acc[FM][FN];
+    pipe::acc4_t acc[FM][FN];
 #pragma unroll
     for (int a = 0; a < FM; ++a)
 #pragma unroll
-        for (int b = 0; b < FN; ++b)
+        for (int b = 0; b < FN; ++b) acc[a][b] = pipe::acc4_t{0.f, 0.f, 0.f, 0.f};
+    const int row0 = i0 + wm * WM, col0 = j0 + wn * WN;         // the wavefront's corner of the output
+    const bool idle = NARROW && row0 >= Mi;
+    auto multiply = [&](int st, int buf) {
+        const char *stage = own + buf * STAGE;
+        static_for<0, 2>([&](auto h_c) {
+            constexpr int h = decltype(h_c)::value;
+            if (idle || (h && st * BK + h * pipe::BKS >= Kl)) return;
+            const char *sa = stage + h * PA::BYTES, *sb = stage + 2 * PA::BYTES + h * PB::BYTES;
+            bf16x8_t va[FM];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+            for (int a = 0; a < FM; ++a) va[a] = fa.read(sa, a);
+            static_for<0, FN>([&](auto b_c) {
+                constexpr int b = decltype(b_c)::value;
+                if (NARROW && b && col0 + 16 * b >= Nj) return;
+                const bf16x8_t vb = fb.read(sb, b);
+                // operands as (second, first): a lane ends with four consecutive output columns
+#pragma unroll
+                for (int a = 0; a < FM; ++a) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vb, va[a], acc[a][b], 0, 0, 0);
+            });
+        });
+    };
 
-    const int nk = (Kl + BK - 1) / BK;
-    la.load(A, lda, i0, Mi, 0, Kl, tid);
-    lb.load(B, ldb, j0, Nj, 0, Kl, tid);
-    la.store(smem, tid);
-    lb.store(smem + A_BYTES, tid);
-    __syncthreads();
-
-    const int frow = lane & 31, fhalf = lane >> 5;
-    for (int kt = 0; kt < nk; ++kt) {
-        char *cur = smem + (kt & 1) * STAGE;
-        char *nxt = smem + ((kt + 1) & 1) * STAGE;
-        const bool more = kt + 1 < nk;
-        if (more) {
-            la.load(A, lda, i0, Mi, (kt + 1) * BK, Kl, tid);
-            lb.load(B, ldb, j0, Nj, (kt + 1) * BK, Kl, tid);
-        }
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            if (ANY && kt * BK + ks * 16 >= Kl) break;      // steps beyond the contraction hold zeros only
-            bf16x8_t fa[FM], fb[FN];
-#pragma unroll
-            for (int a = 0; a < FM; ++a)
-                fa[a] = *reinterpret_cast<const bf16x8_t *>(cur + lds_off(wm * WM + a * 32 + frow, ks * 2 + fhalf));
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-                fb[b] = *reinterpret_cast<const bf16x8_t *>(cur + A_BYTES +
-                                                            lds_off(wn * WN + b * 32 + frow, ks * 2 + fhalf));
-#pragma unroll
-            for (int a = 0; a < FM; ++a)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-        }
-        if (more) {
-            la.store(nxt, tid);
-            lb.store(nxt + A_BYTES, tid);
-        }
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, SETS - 1>;
+    const int nst = (Kl + BK - 1) / BK;
+    if constexpr (PF == 0) {
+        fetch(I0{}, 0);
+        put(I0{}, 0, 0);
         __syncthreads();
+        multiply(0, 0);
+        __syncthreads();
+    } else {
+        // round u: the group's stage st = KS u + group is multiplied, its next one goes from registers to the other buffer (whose
+        // readers passed the barrier one round ago), the one PF rounds on is asked for; cur: register set of stage st
+        const int rounds = (nst + KS - 1) / KS;
+        if (group < nst) fetch(I0{}, group);
+        if (PF == 2 && group + KS < nst) fetch(I1{}, group + KS);
+        if (group < nst) put(I0{}, group, 0);
+        __syncthreads();
+        auto round = [&](int u, auto cur, auto nxt) {
+            const int st = KS * u + group;
+            if (st + PF * KS < nst) fetch(cur, st + PF * KS);
+            if (st < nst) multiply(st, u & 1);
+            if (st + KS < nst) put(nxt, st + KS, (u & 1) ^ 1);
+            __syncthreads();
+        };
+        for (int u = 0; u < rounds; u += 2) {
+            round(u, I0{}, I1{});
+            if (u + 1 < rounds) round(u + 1, I1{}, I0{});
+        }
+    }
+    if constexpr (KS > 1) {
+        constexpr int PER = FM * FN * 16;                       // bytes of a thread's sums
+        static_assert(PER * NT <= 2 * STAGE, "a group's sums fit its buffers");
+        auto at = [&](int g, int i) { return reinterpret_cast<pipe::acc4_t *>(smem + g * (2 * STAGE) + (i * NT + tid) * 16); };
+        if (group > 0)
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b) *at(group, a * FN + b) = acc[a][b];
+        __syncthreads();
+        if (group > 0) return;
+#pragma unroll
+        for (int g = 1; g < KS; ++g)
+#pragma unroll
+            for (int a = 0; a < FM; ++a)
+#pragma unroll
+                for (int b = 0; b < FN; ++b) acc[a][b] += *at(g, a * FN + b);
     }
 
-    // Epilogue.  Accumulator layout of a 32x32 fragment: column = lane % 32,
-    // row = 8*(v/4) + 4*(lane/32) + v%4.  Each wavefront passes 32 rows x WN columns at a time
-    // through its own LDS slab so that HBM sees whole 16-byte, row-contiguous stores.
-    constexpr int ES = sizeof(TO);
-    constexpr int PITCH = WN * ES + 16;                 // bytes per staged row (+16: spreads rows over banks)
-    constexpr int LPR = WN * ES / 16;                   // lanes per row in the store phase
-    constexpr int RPI = 64 / LPR;                       // rows per store instruction
-    char *slab = smem + wave * (32 * PITCH);
-    static_assert(32 * PITCH * WAVES_M * WAVES_N <= 2 * STAGE, "epilogue slab does not fit");
+    // Epilogue: 16 rows at a time through a slab that belongs to the wavefront alone (its LDS operations execute in order: no
+    // barrier), leaving as row-contiguous 16-byte pieces; rows begin at any element.
+    if (idle) return;
+    constexpr int ES = sizeof(TO), RB = WN * ES, CH = RB / 16, LD = 16 * CH / 64;
+    static_assert(16 * RB * WAVES_M * WAVES_N <= STAGE, "epilogue slabs lie in the first stage");
+    auto swz = [](int row) { return CH == 16 ? row & 15 : (row >> 1) & 7; };
+    char *slab = smem + wave * (16 * RB);
+    const int wr = lane & 15, rr = lane / CH, rc = lane % CH, gj = col0 + rc * (16 / ES);
+    TO *outp = Out + (size_t)p * lo.plane + gj;
+    static_for<0, FM>([&](auto a_c) {
+        constexpr int a = decltype(a_c)::value;
+        char *rowp = slab + wr * RB;
+        asm volatile("" ::: "memory");
 #pragma unroll
-    for (int a = 0; a < FM; ++a) {
-        __syncthreads();
+        for (int b = 0; b < FN; ++b) {
+            const pipe::acc4_t v = acc[a][b];
+            if constexpr (ES == 2)
+                *reinterpret_cast<u32x2_t *>(rowp + (((2 * b + (lane >> 5)) ^ swz(wr)) << 4) + ((lane >> 4) & 1) * 8) =
+                    u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            else
+                *reinterpret_cast<f32x4_t *>(rowp + (((4 * b + (lane >> 4)) ^ swz(wr)) << 4)) = v;
+        }
+        asm volatile("" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < FN; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rr = 8 * (v >> 2) + 4 * fhalf + (v & 3), cc = b * 32 + frow;
-                Elem<TO>::st(reinterpret_cast<TO *>(slab + rr * PITCH) + cc, acc[a][b][v]);
-            }
-        __syncthreads();
-        const int gi_base = i0 + wm * WM + a * 32;
-        const int gj = j0 + wn * WN + (lane % LPR) * (16 / ES);
-#pragma unroll
-        for (int it = 0; it < 32 / RPI; ++it) {
-            const int rr = it * RPI + lane / LPR;
-            const int gi = gi_base + rr;
-            if (gi < Mi && gj < Nj) {
-                u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + rr * PITCH + (lane % LPR) * 16);
-                TO *o = Out + ldo.off(gi) + gj;
-                if (ANY && ES == 2) {
-                    store8<true>(reinterpret_cast<bf16_t *>(o), Nj - gj, w);
-                } else if (ANY && Nj % 4) {                 // fp32 rows at any multiple of 4 bytes
-                    const f32x4_t nw = __builtin_bit_cast(f32x4_t, w);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (gj + e < Nj) Elem<TO>::st(o + e, ACC ? Elem<TO>::ld(o + e) + nw[e] : nw[e]);
-                } else if (ACC) {
-                    const f32x4_t old = *reinterpret_cast<const f32x4_t *>(o);
-                    f32x4_t nw = __builtin_bit_cast(f32x4_t, w);
-                    nw += old;
-                    *reinterpret_cast<f32x4_t *>(o) = nw;
+        for (int i = 0; i < LD; ++i) {
+            const int row = i * (64 / CH) + rr, gi = row0 + 16 * a + row;
+            const u32x4_t w = *reinterpret_cast<const u32x4_t *>(slab + row * RB + ((rc ^ swz(row)) << 4));
+            if (gi >= Mi || gj >= Nj) continue;
+            TO *o = outp + lo.row(pb * Mi + gi);
+            if constexpr (ES == 2) {
+                store8<true>(reinterpret_cast<bf16_t *>(o), Nj - gj, w);
+            } else {
+                f32x4_t nw = __builtin_bit_cast(f32x4_t, w);
+                if (gj + 4 <= Nj) {
+                    if constexpr (ACC) nw += *reinterpret_cast<const f32x4_any_t *>(o);
+                    *reinterpret_cast<f32x4_any_t *>(o) = nw;
                 } else {
-                    *reinterpret_cast<u32x4_t *>(o) = w;
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (gj + e < Nj) o[e] = ACC ? o[e] + nw[e] : nw[e];
                 }
             }
         }
-    }
+    });
 }
+
+}  // namespace staged
 
 // ---- host side ---------------------------------------------------------------------------
 bool plane_gemm_mfma_eligible(const GemmDesc &g)
@@ -254,22 +300,47 @@ bool plane_gemm_mfma_eligible(const GemmDesc &g)
     return g.Mi >= 8 && g.Nj >= 8 && g.Kl >= 8;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
+// layout of an operand of `cols` columns in groups of pg rows (0: plane-major, `rows` stored rows per plane); false if the groups
+// have no power of two of rows
+static bool make_lay(staged::Lay &l, int pg, long rows, int cols, int batch)
+{
+    l.ld = cols;
+    l.plane = (pg > 0 ? pg : rows) * cols;
+    l.shift = 31;
+    l.skip = 0;
+    if (pg <= 0 || rows <= pg) return true;              // one group
+    l.skip = (batch - 1) * pg;
+    for (l.shift = 0; (1 << l.shift) < pg; ++l.shift) {}
+    return (1 << l.shift) == pg && (double)rows * batch < 2147483648.0;
+}
+
+static staged::Div make_div(int d)
+{
+    uint32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    return {(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), 31 + s};
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
 static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    auto kern = gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, A_T, B_T, TO, ACC, ANY>;
-    constexpr int stage = (BM + BN) * BK * 2, most = 2 * stage;
-    // a contraction of one stage needs one: twice the workgroups per CU to hide its loads (96 x (50 x 50 x 50), r = 32: 23 -> 15 us)
-    constexpr int slabs = 32 * (BN / WAVES_N * (int)sizeof(TO) + 16) * WAVES_M * WAVES_N;      // of the epilogue
-    const int smem = g.Kl > BK ? most : stage > slabs ? stage : slabs;
+    auto kern = staged::gemm_mfma_kernel<BM, BN, WAVES_M, WAVES_N, PF, KS, A_T, B_T, TO, ACC>;
+    constexpr int stage = (BM + BN) * staged::BK * 2, most = 2 * stage * KS;
+    // a contraction of one stage needs one: more workgroups per CU to hide its loads
+    const int smem = g.Kl > staged::BK ? most : stage;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
     if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, most, granted); e != hipSuccess) return e;
+    staged::Lay la, lb, lo;
+    if (!make_lay(la, g.a_pg, (long)g.nb * g.a_rows(), A_T ? g.Mi : g.Kl, g.batch) ||
+        !make_lay(lb, g.b_pg, (long)g.nb * g.b_rows(), B_T ? g.Nj : g.Kl, g.batch) ||
+        !make_lay(lo, g.o_pg, (long)g.nb * g.Mi, g.Nj, g.batch))
+        return hipErrorInvalidValue;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
-    if (total > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(WAVES_M * WAVES_N * 64), smem, s, (const bf16_t *)A,
-                       (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, tiles_m, tiles_n, (int)total, g.a_rows_per_group(),
-                       g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
+    if (total > 0x7ffffff0L) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WAVES_M * WAVES_N * KS * 64), smem, s, (const bf16_t *)A,
+                       (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, tiles_m, tiles_n, (int)total, g.batch,
+                       make_div(tiles_m * tiles_n), make_div(tiles_n), make_div(g.batch), la, lb, lo);
     return hipGetLastError();
 }
 
@@ -280,48 +351,57 @@ int staged_block(const GemmDesc &g)
 {
     // multiples of 8, stacked problems: 256 x 256 blocks, 8 wavefronts of 128 x 64, for large planes, 128 x 128, 4 of 64 x 64, for others
     if (!any_width(g)) return g.Mi > 128 && g.Nj > 128 ? 256 : 128;
-    // The largest block that still fills the chip (256 CUs): a bigger block moves fewer bytes per product, but these kernels
-    // prefetch a single stage, so idle CUs and short contractions cost more.  Forward form, us at 256 / 128 / 64:
-    //   M x K x N, r = 512 x 1024 x 1024, 32: 48 / 69 / 116 (256 blocks of 256);  256 x 1024 x 1024, 32: 44 / 38 / 63 (128, 512
-    //   blocks);  1024 x 192 x 250, 32: 21 / 17 / 26 (512 blocks of 128);  512 x 192 x 250, 32: 19 / 14 / 13 (256 blocks of
-    //   128);  128 x 192 x 250, 8: 17 / 13 / 10
     auto blocks = [&](int b) { return (double)((g.Mi + b - 1) / b) * ((g.Nj + b - 1) / b) * g.batch * g.nb; };
-    if (g.Mi > 128 && g.Nj > 128 && blocks(256) >= 256) return 256;
-    return g.Mi > 64 && g.Nj > 64 && blocks(128) >= 384 ? 128 : 64;
+    // A bigger block moves fewer bytes per product, idle CUs and the latency of its longer stages cost more; sparse second rounds
+    // of the big ones most of all.  us at 256 / 128 / 64:
+    //   Yhat  512 x 1023 x 1024, 32: 41 / 51 / 79 (256 blocks of 256)    256 x 1023 x 1024, 32: 38 / 28 / 44    128 x 1023 x 1024, 32: 37 / 22 / 27
+    //         2048 x 513 x 513, 32: 74 / 87 / 108                        1000 x 513 x 513, 8: 26 / 21 / 20 (320 blocks of 128)
+    //         1024 x 192 x 250, 32: 14 / 11 / 13                         512 x 192 x 250, 32: 12.1 / 8.5 / 8.3 (256 of 128)
+    //   dWhat and the encode before it: 2048 x 513 x 513, 32: 189 / 136 / 141 (288 of 256)    1023 x 257 x 513, 16: 59 / 42 / 32
+    const double b256 = blocks(256);
+    if (g.Mi > 128 && g.Nj > 128 && b256 >= 192 * std::ceil(b256 / 256)) return 256;
+    return g.Mi > 64 && g.Nj > 64 && blocks(128) >= (g.Kl > 640 ? 256 : 384) ? 128 : 64;
 }
 
-template <bool A_T, bool B_T, typename TO, bool ACC, bool ANY>
-static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+// A product with a single stage, or an output that a 64 x 64 block covers in one dimension, takes 64 x 64 blocks however many there
+// are (us at 64 / 128 / 256: Yhat 2048 x 50 x 513, r = 32 20 / 23 / 22; forward and backward of 96 x (64 x 64 x 20), r = 32 96 / 136 / 242,
+// of 96 x (128 x 16 x 128) 212 / 235 / 370).
+static bool thin(const GemmDesc &g) { return g.Mi <= 64 || g.Nj <= 64 || g.Kl <= staged::BK; }
+
+// Groups of wavefronts that share the contraction of a 64 x 64 block: where the blocks leave CUs idle and the chain of stages is
+// long, each group has loads of its own in flight.  us with 1 / 2 / 4 groups: Yhat 64 x 500 x 500, 32 (256 blocks, 8 stages) 10.0 / 7.5 / 8.0,
+// 512 x 192 x 250, 32 (1024 blocks, 3 stages) 8.5 / 10.4 / 14.8; dWhat and the encode before it 512 x 192 x 250, 32 (384, 8) 18.5 / 16.8 / 20.2,
+// 3000 x 100 x 100, 8 (32, 47) 56 / 35 / 27, 1023 x 257 x 513, 16 (720, 16) 32 / 32 / 38.
+static int staged_groups(const GemmDesc &g)
 {
-    switch (staged_block(g)) {
-        case 256: return launch_cfg<256, 256, 2, 4, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-        case 128: return launch_cfg<128, 128, 2, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-    }
-    if constexpr (ANY) return launch_cfg<64, 64, 1, 2, A_T, B_T, TO, ACC, ANY>(g, A, B, Out, s);
-    return hipErrorInvalidValue;
+    const double blocks = (double)((g.Mi + 63) / 64) * ((g.Nj + 63) / 64) * g.batch * g.nb;
+    const int stages = (g.Kl + staged::BK - 1) / staged::BK;
+    return blocks <= 256 && stages >= 12 ? 4 : blocks <= 512 && stages >= 4 ? 2 : 1;
 }
 
 template <bool A_T, bool B_T, typename TO, bool ACC>
-static hipError_t launch_shape(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    if (any_width(g)) return launch_block<A_T, B_T, TO, ACC, true>(g, A, B, Out, s);
-    // weight gradients of widths that are multiples of 8 go to the LDS-DMA kernel at any contraction length
-    if constexpr (sizeof(TO) == 4) return hipErrorInvalidValue;
-    else return launch_block<A_T, B_T, TO, ACC, false>(g, A, B, Out, s);
+    switch (thin(g) ? 64 : staged_block(g)) {
+        case 256: return launch_cfg<256, 256, 2, 4, 1, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+        case 128: return launch_cfg<128, 128, 2, 2, 2, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+    }
+    if (g.Kl <= staged::BK) return launch_cfg<64, 64, 4, 1, 0, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+    switch (staged_groups(g)) {
+        case 4: return launch_cfg<64, 64, 4, 1, 2, 4, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+        case 2: return launch_cfg<64, 64, 4, 1, 2, 2, A_T, B_T, TO, ACC>(g, A, B, Out, s);
+    }
+    return launch_cfg<64, 64, 4, 1, 2, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
 }
 
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    if (g.out_f32) {
-        if (g.a_kmajor && g.b_kmajor)
-            return g.accumulate ? launch_shape<true, true, float, true>(g, A, B, Out, s)
-                                : launch_shape<true, true, float, false>(g, A, B, Out, s);
-        return hipErrorInvalidValue;  // only the weight-gradient product stores fp32
-    }
-    if (g.a_kmajor && g.b_kmajor) return launch_shape<true, true, bf16_t, false>(g, A, B, Out, s);
-    if (!g.a_kmajor && g.b_kmajor) return launch_shape<false, true, bf16_t, false>(g, A, B, Out, s);
-    if (!g.a_kmajor && !g.b_kmajor) return launch_shape<false, false, bf16_t, false>(g, A, B, Out, s);
-    return hipErrorInvalidValue;
+    if (!plane_gemm_mfma_eligible(g)) return hipErrorInvalidValue;
+    if (g.out_f32)                                       // only the weight-gradient product stores fp32
+        return g.accumulate ? launch_block<true, true, float, true>(g, A, B, Out, s)
+                            : launch_block<true, true, float, false>(g, A, B, Out, s);
+    if (g.a_kmajor) return launch_block<true, true, bf16_t, false>(g, A, B, Out, s);
+    return g.b_kmajor ? launch_block<false, true, bf16_t, false>(g, A, B, Out, s) : launch_block<false, false, bf16_t, false>(g, A, B, Out, s);
 }
 
 }  // namespace stl

@@ -153,7 +153,7 @@ hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A
                                      hipStream_t s);
 // bf16 MFMA path, operands staged through registers (any width of at least 8)
 bool plane_gemm_mfma_eligible(const GemmDesc &g);
-int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes
+int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes (thin products: 64 x 64 whatever this says)
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 // bf16 MFMA path with LDS-DMA loads and a multi-stage LDS ring (contiguous dimensions a multiple of 8)
 enum class PipeBlock { b256, b128x256, b128, b64 };
