@@ -1,12 +1,10 @@
 // Any-shape batched plane product on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32: fp32 operands, fp32
 // accumulation).  This is the path for fp32 storage and for bf16 planes with a dimension below 8 (their values are widened
-// to fp32 on the way into LDS, which is exact).  256 threads = four wavefronts, a BT x BT block of one plane; edges are
-// zero-filled on load and masked on store.
+// to fp32 on the way into LDS, which is exact).  256 threads = four wavefronts; edges are zero-filled on load and masked on store.
 //
-// Large planes are bound by the fp32 matrix cores (157 TFLOP/s), small ones by the latency of a chain of stages, so the
-// operands come in 16-byte pieces, the next stage is in registers while the current one is multiplied out of the other
-// LDS buffer (one barrier per stage), and small problems take 64 x 64 blocks with 32 contraction elements per stage: fewer,
-// longer stages over more workgroups.  49 planes of 64 x 64 x 64: 28 us with element-wise staging of 128 x 128 blocks, now 8.
+// Large planes are bound by the fp32 matrix cores (157 TFLOP/s): 128 x 128 blocks, operands in 16-byte pieces, the next stage in registers
+// while the current one is multiplied out of the other LDS buffer (one barrier per stage).  Small ones are bound by the latency
+// of a chain of stages and by idle CUs: 32 x 32 blocks with the contraction shared (gemm_small_kernel).
 #include "stl_kernels.h"
 #include "stl_device.h"
 
@@ -15,15 +13,15 @@ namespace stl {
 
 // MFMA accumulator layout of v_mfma_f32_32x32x2_f32: lane (j = lane % 32, h = lane / 32) supplies A[row j][k = h] and
 // B[k = h][column j]; accumulator e of the lane is C[row 8 (e / 4) + 4 h + e % 4][column j].
-// Three wavefronts per SIMD for the 128 x 128 blocks (at the price of eleven spilled registers; left alone the compiler takes
-// registers for two): 1024-cube, r = 32, 770 -> 695 us, bf16 dWhat of 1024 x 1024 from four tile rows 57 -> 53.  With a sum into the
-// output it helps some sizes and costs others (r = 32 of the latter 123 -> 100, r = 8 31 -> 36) and stays at two.
-template <typename T, typename TO, bool ACC, int BT>
-__global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
+// Three wavefronts per SIMD (at the price of eleven spilled registers; left alone the compiler takes registers for two): 1024-cube,
+// r = 32, 770 -> 695 us, bf16 dWhat of 1024 x 1024 from four tile rows 57 -> 53.  With a sum into the output it helps some sizes and
+// costs others (r = 32 of the latter 123 -> 100, r = 8 31 -> 36) and stays at two.
+template <typename T, typename TO, bool ACC>
+__global__ __launch_bounds__(256, ACC ? 1 : 3) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                            TO *__restrict__ Out, int Mi, int Nj, int Kl, int a_km,
                                                            int b_km, int a_pg, int b_pg, int o_pg, int batch, int nb)
 {
-    constexpr int KC = BT == 64 ? 32 : 16, PAD = 4;    // contraction elements per stage
+    constexpr int BT = 128, KC = 16, PAD = 4;          // block, contraction elements per stage
     constexpr int F = BT / 64;                         // 32 x 32 products per wavefront and dimension
     constexpr int UNITS = BT * KC / 1024;              // 16-byte pieces per thread, operand and stage
     __shared__ __align__(16) float sA[2][KC][BT + PAD];    // [l][i]: a fragment read takes 32 consecutive i of one l
@@ -125,13 +123,108 @@ __global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_k
   }
 }
 
-template <typename T, typename TO, bool ACC, int BT>
-static hipError_t launch_bt(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+// A 32 x 32 block of one plane per workgroup, whose four wavefronts share the contraction, 16 of a stage's 64 elements each, and add
+// their sums up in LDS.  64 x 64 blocks gave 49 planes of 64 x 64 49 workgroups and a chain of two stages, these four times as many
+// and one stage of 16 KB in flight: 7.5 -> 4.0 us.  64 planes of 60 x 2000 x 60: 101 -> 40; bf16 Yhat of 7 x 1024 x 1024, r = 32: 81 -> 46.
+template <typename T, typename TO, bool ACC>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const T *__restrict__ A, const T *__restrict__ B, TO *__restrict__ Out, int Mi,
+                                                         int Nj, int Kl, int a_km, int b_km, int tiles_m, int tiles_n, int total,
+                                                         int batch, Div by_plane, Div by_row, Div by_batch, Lay la, Lay lb, Lay lo)
 {
+    constexpr int BT = 32, KC = 64, PITCH = BT + 4;
+    __shared__ __align__(16) float sA[KC][PITCH], sB[KC][PITCH];            // [l][i], [l][j]
+    __shared__ __align__(16) float red[4][BT][PITCH];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), fj = lane & 31, fh = lane >> 5;
+  for (int v = blockIdx.x; v < total; v += gridDim.x) {          // blocks beyond the grid
+    const int q = by_plane.of(v), rem = v - q * (tiles_m * tiles_n), bi = by_row.of(rem);
+    const int i0 = bi * BT, j0 = (rem - bi * tiles_n) * BT, pb = by_batch.of(q), p = q - pb * batch;
+    const T *Ap = A + (size_t)p * la.plane, *Bp = B + (size_t)p * lb.plane;
+
+    // four elements along the dimension that is contiguous in memory: unit u of 512 per operand and stage
+    auto fetch_one = [&](const T *X, const Lay &lay, int u, int l0, int c0, int total_c, int km, int r0) {
+        const int c = c0 + (km ? 4 * (u & 7) : u >> 4), l = l0 + (km ? u >> 3 : 4 * (u & 15));
+        const bool in = km ? l < Kl : c < total_c;
+        return load4<T>(X + (in ? lay.row(r0 + (km ? l : c)) + (km ? c : l) : 0), in ? (km ? total_c - c : Kl - l) : 0);
+    };
+    auto put = [&](float (*s)[PITCH], int u, int km, f32x4_t w) {
+        if (km) {
+            *reinterpret_cast<f32x4_t *>(&s[u >> 3][4 * (u & 7)]) = w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[4 * (u & 15) + e][u >> 4] = w[e];
+        }
+    };
+    f32x4_t ra[2], rb[2];
+    auto fetch = [&](int l0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            ra[k] = fetch_one(Ap, la, threadIdx.x + 256 * k, l0, i0, Mi, a_km, pb * (a_km ? Kl : Mi));
+            rb[k] = fetch_one(Bp, lb, threadIdx.x + 256 * k, l0, j0, Nj, b_km, pb * (b_km ? Kl : Nj));
+        }
+    };
+    f32x16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    fetch(0);
+    for (int l0 = 0; l0 < Kl; l0 += KC) {
+        __syncthreads();                               // the previous stage has been read
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            put(sA, threadIdx.x + 256 * k, a_km, ra[k]);
+            put(sB, threadIdx.x + 256 * k, b_km, rb[k]);
+        }
+        __syncthreads();
+        if (l0 + KC < Kl) fetch(l0 + KC);
+        // a product takes l and l + 8 (half the banks apart: 8 (BT + 4) = 32 mod 64 words)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int l = 16 * wave + s + 8 * fh;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sA[l][fj], sB[l][fj], acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[wave][8 * (e >> 2) + 4 * fh + (e & 3)][fj] = acc[e];
+    __syncthreads();
+    // thread: row i, columns j .. j + 3
+    const int i = threadIdx.x >> 3, j = 4 * (threadIdx.x & 7), gi = i0 + i, gj = j0 + j;
+    if (gi >= Mi) continue;
+    f32x4_t w = *reinterpret_cast<const f32x4_t *>(&red[0][i][j]);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) w += *reinterpret_cast<const f32x4_t *>(&red[k][i][j]);
+    TO *o = Out + (size_t)p * lo.plane + lo.row(pb * Mi + gi) + gj;
+    if constexpr (sizeof(TO) == 4) {
+        if (gj + 4 <= Nj) {
+            if (ACC) w += *reinterpret_cast<const f32x4_any_t *>(o);
+            *reinterpret_cast<f32x4_any_t *>(o) = w;
+            continue;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (gj + e < Nj) Elem<TO>::st(o + e, ACC ? Elem<TO>::ld(o + e) + w[e] : w[e]);
+  }
+}
+
+template <typename T, typename TO, bool ACC>
+static hipError_t launch_small(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+{
+    GemmLays l;
+    if (!l.set(g)) return hipErrorInvalidValue;
+    const int tiles_m = (g.Mi + 31) / 32, tiles_n = (g.Nj + 31) / 32, total = tiles_m * tiles_n * g.batch * g.nb;
+    hipLaunchKernelGGL((gemm_small_kernel<T, TO, ACC>), dim3(total > (1 << 22) ? 1 << 22 : total), dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out, g.Mi, g.Nj, g.Kl,
+                       (int)g.a_kmajor, (int)g.b_kmajor, tiles_m, tiles_n, total, g.batch, Div::by(tiles_m * tiles_n), Div::by(tiles_n),
+                       Div::by(g.batch), l.a, l.b, l.o);
+    return hipGetLastError();
+}
+
+template <typename T, typename TO, bool ACC>
+static hipError_t launch_large(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+{
+    constexpr int BT = 128;
     const long zs = (long)g.batch * g.nb;
     const int rows = (g.Mi + BT - 1) / BT;
     dim3 grid((g.Nj + BT - 1) / BT, (unsigned)(rows > 65535 ? 65535 : rows), (unsigned)(zs > 65535 ? 65535 : zs));   // the kernel strides over both
-    hipLaunchKernelGGL((gemm_generic_kernel<T, TO, ACC, BT>), grid, dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out,
+    hipLaunchKernelGGL((gemm_generic_kernel<T, TO, ACC>), grid, dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out,
                        g.Mi, g.Nj, g.Kl, (int)g.a_kmajor, (int)g.b_kmajor, g.a_rows_per_group(), g.b_rows_per_group(),
                        g.o_rows_per_group(), g.batch, g.nb);
     return hipGetLastError();
@@ -140,10 +233,12 @@ static hipError_t launch_bt(const GemmDesc &g, const void *A, const void *B, voi
 template <typename T, typename TO, bool ACC>
 static hipError_t launch_t(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    // 128 x 128 blocks (half the operand traffic) once they give every CU one
+    // 128 x 128 blocks (a quarter of the operand traffic) once every CU has two.  us at 128 / 32, fp32 products: 512 x 512 x 512, r = 32
+    // (512 blocks of 128) 103 / 129, 900 x 200 x 200, 32 (512) 51 / 60, 1024 x 64 x 1024, 8 (512) 27 / 27, 640 x 384 x 384, 24 (360) 81 / 73,
+    // 300 x 300 x 300, 32 (288) 67 / 41, 256 x 64 x 512, 32 (256) 19 / 15.  Contractions of one stage of the former store most of the
+    // time and take it at one per CU: bf16 dWhat (and the encode before it) of 512 x 512 from 4 tile rows, 16 (256) 16.8 / 18.9.
     const double blocks = (double)((g.Mi + 127) / 128) * ((g.Nj + 127) / 128) * g.batch * g.nb;
-    if (g.Mi > 64 && g.Nj > 64 && blocks >= 256) return launch_bt<T, TO, ACC, 128>(g, A, B, Out, s);
-    return launch_bt<T, TO, ACC, 64>(g, A, B, Out, s);
+    return g.Mi > 64 && g.Nj > 64 && blocks >= (g.Kl <= 16 ? 256 : 512) ? launch_large<T, TO, ACC>(g, A, B, Out, s) : launch_small<T, TO, ACC>(g, A, B, Out, s);
 }
 
 hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out,

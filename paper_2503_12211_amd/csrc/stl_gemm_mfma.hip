@@ -23,21 +23,6 @@ namespace staged {
 
 constexpr int BK = 64;      // contraction elements per LDS stage, in two pieces of pipe::BKS
 
-// Where the stored rows of one operand lie (see plane_row_base): row I of plane p begins at (I + (I >> shift) * skip) * ld + p * plane
-// elements.  Groups have a power of two of rows, or there is one group (shift 31).
-struct Lay {
-    int ld, shift, skip;
-    long plane;
-    __device__ __forceinline__ long row(int I) const { return (long)(I + (I >> shift) * skip) * ld; }
-};
-
-// n / d for 0 <= n < 2^31, as one multiplication: mul = ceil(2^(31 + s) / d) with 2^s >= d, so that the error n (mul d - 2^(31 + s)) / d
-// stays below 2^(31 + s) / d
-struct Div {
-    uint32_t mul, shift;
-    __device__ __forceinline__ int of(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
-};
-
 // eight elements moved h places towards the first, zeros behind them, any h >= 0
 __device__ __forceinline__ u32x4_t settle(u32x4_t v, int h) { return h <= 0 ? v : h >= 8 ? u32x4_t{0u, 0u, 0u, 0u} : shift_down(v, h); }
 
@@ -108,7 +93,7 @@ struct Piece {
 template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
 __global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 : KS == 1 ? 5 : 4) : 2) void gemm_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
                                                                           TO *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m, int tiles_n,
-                                                                          int total, int batch, Div by_plane, Div by_row, Div by_batch, Lay la,
+                                                                          int base, int total, int batch, Div by_plane, Div by_row, Div by_batch, Lay la,
                                                                           Lay lb, Lay lo)
 {
     using pipe::static_for;
@@ -120,8 +105,9 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 
     constexpr bool NARROW = BM == 64;
     extern __shared__ __align__(16) char smem[];
 
-    const int bid = pipe::first_block(total);                   // one block per workgroup; each XCD takes a contiguous eighth
+    int bid = pipe::first_block(total);                         // one block per workgroup; each XCD takes a contiguous eighth
     if (bid >= pipe::end_block(total)) return;
+    bid += base;
     const int q = by_plane.of(bid), rem = bid - q * (tiles_m * tiles_n);   // (stacked problem, plane)
     const int bi = by_row.of(rem), i0 = bi * BM, j0 = (rem - bi * tiles_n) * BN;
     const int pb = by_batch.of(q), p = q - pb * batch;
@@ -300,27 +286,6 @@ bool plane_gemm_mfma_eligible(const GemmDesc &g)
     return g.Mi >= 8 && g.Nj >= 8 && g.Kl >= 8;
 }
 
-// layout of an operand of `cols` columns in groups of pg rows (0: plane-major, `rows` stored rows per plane); false if the groups
-// have no power of two of rows
-static bool make_lay(staged::Lay &l, int pg, long rows, int cols, int batch)
-{
-    l.ld = cols;
-    l.plane = (pg > 0 ? pg : rows) * cols;
-    l.shift = 31;
-    l.skip = 0;
-    if (pg <= 0 || rows <= pg) return true;              // one group
-    l.skip = (batch - 1) * pg;
-    for (l.shift = 0; (1 << l.shift) < pg; ++l.shift) {}
-    return (1 << l.shift) == pg && (double)rows * batch < 2147483648.0;
-}
-
-static staged::Div make_div(int d)
-{
-    uint32_t s = 0;
-    while (((int64_t)1 << s) < d) ++s;
-    return {(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), 31 + s};
-}
-
 template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
 static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
@@ -330,17 +295,18 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
     const int smem = g.Kl > staged::BK ? most : stage;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
     if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, most, granted); e != hipSuccess) return e;
-    staged::Lay la, lb, lo;
-    if (!make_lay(la, g.a_pg, (long)g.nb * g.a_rows(), A_T ? g.Mi : g.Kl, g.batch) ||
-        !make_lay(lb, g.b_pg, (long)g.nb * g.b_rows(), B_T ? g.Nj : g.Kl, g.batch) ||
-        !make_lay(lo, g.o_pg, (long)g.nb * g.Mi, g.Nj, g.batch))
-        return hipErrorInvalidValue;
+    GemmLays l;
+    if (!l.set(g)) return hipErrorInvalidValue;
     const int tiles_m = (g.Mi + BM - 1) / BM, tiles_n = (g.Nj + BN - 1) / BN;
     const long total = (long)tiles_m * tiles_n * g.batch * g.nb;
-    if (total > 0x7ffffff0L) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WAVES_M * WAVES_N * KS * 64), smem, s, (const bf16_t *)A,
-                       (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, tiles_m, tiles_n, (int)total, g.batch,
-                       make_div(tiles_m * tiles_n), make_div(tiles_n), make_div(g.batch), la, lb, lo);
+    if (total > 0x7fffffffL) return hipErrorInvalidValue;
+    constexpr long kMost = 1 << 22;                        // blocks of a launch: its threads have to fit 32 bits
+    for (long base = 0; base < total; base += kMost) {
+        const long n = total - base < kMost ? total - base : kMost;
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n + 7) / 8 * 8)), dim3(WAVES_M * WAVES_N * KS * 64), smem, s, (const bf16_t *)A,
+                           (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, tiles_m, tiles_n, (int)base, (int)n, g.batch,
+                           Div::by(tiles_m * tiles_n), Div::by(tiles_n), Div::by(g.batch), l.a, l.b, l.o);
+    }
     return hipGetLastError();
 }
 

@@ -144,6 +144,49 @@ struct GemmDesc {
     int b_rows_per_group() const { return b_pg > 0 ? b_pg : nb * b_rows(); }
     int o_rows_per_group() const { return o_pg > 0 ? o_pg : nb * Mi; }
 };
+
+// Where the stored rows of one operand lie (see plane_row_base): row I of plane p begins at (I + (I >> shift) * skip) * ld + p * plane
+// elements.  Groups have a power of two of rows, or there is one group (shift 31).
+struct Lay {
+    int ld, shift, skip;
+    long plane;
+    __device__ __forceinline__ long row(int I) const { return (long)(I + (I >> shift) * skip) * ld; }
+    // an operand of `rows` stored rows per plane and `cols` columns in groups of pg rows (0: plane-major); false if it has more
+    // than one group and they are no power of two
+    bool set(int pg, long rows, int cols, int batch)
+    {
+        ld = cols;
+        plane = (pg > 0 ? pg : rows) * cols;
+        shift = 31;
+        skip = 0;
+        if (pg <= 0 || rows <= pg) return true;
+        skip = (batch - 1) * pg;
+        for (shift = 0; (1 << shift) < pg; ++shift) {}
+        return (1 << shift) == pg && (double)rows * batch < 2147483648.0;
+    }
+};
+struct GemmLays {
+    Lay a, b, o;
+    bool set(const GemmDesc &g)
+    {
+        return a.set(g.a_pg, (long)g.nb * g.a_rows(), g.a_kmajor ? g.Mi : g.Kl, g.batch) &&
+               b.set(g.b_pg, (long)g.nb * g.b_rows(), g.b_kmajor ? g.Nj : g.Kl, g.batch) && o.set(g.o_pg, (long)g.nb * g.Mi, g.Nj, g.batch);
+    }
+};
+
+// n / d for 0 <= n < 2^31, as one multiplication: mul = ceil(2^(31 + s) / d) with 2^s >= d, so that the error n (mul d - 2^(31 + s)) / d
+// stays below 2^(31 + s) / d
+struct Div {
+    uint32_t mul, shift;
+    __device__ __forceinline__ int of(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+    static Div by(int d)
+    {
+        uint32_t s = 0;
+        while (((int64_t)1 << s) < d) ++s;
+        return {(uint32_t)((((uint64_t)1 << (31 + s)) + d - 1) / d), 31 + s};
+    }
+};
+
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 // the kernel that launch_plane_gemm takes: stl_gemm_wide.hip, stl_gemm_pipe.hip, stl_gemm_mfma.hip, stl_gemm_generic.hip
 enum class GemmPath { wide, pipe, staged, generic };
