@@ -39,7 +39,7 @@ __global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restr
     extern __shared__ __align__(16) char smem[];
     const int ng = (r + 15) >> 4;                            // plane rows are staged in whole groups of 16, zeros beyond r
     float *sB = reinterpret_cast<float *>(smem);             // [r][16]
-    const int gt = threadIdx.x & 255, grp = threadIdx.x >> 8;
+    const int gt = threadIdx.x & 255, grp = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8));
     float *sP = sB + r * 16 + grp * ((PLANES ? ng * 16 * TP : 0) + (TILES ? 16 * TP : 0));     // [p][tile]
     float *sX = sP + (PLANES ? ng * 16 * TP : 0);            // [q][tile]
     if (ENC || DEC)
@@ -157,6 +157,116 @@ __global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restr
             part[(size_t)blockIdx.x * r * 16 + i] = tot;
         }
     }
+}
+
+// ---------------------------------------------------------------------------------------
+// The basis gradient of a small fp32 matrix, with the encode or the decode it is fused with.  One partial sum covers 256 tiles (four
+// items of 64, see above), which leaves a matrix of 64 x 64 tiles with 16 partials: as many workgroups of 1024 threads were bound by what one CU
+// issues (11.5 us at r = 49, 8 of them with every sum taken out).  Here four workgroups of 256 threads share a partial: workgroup y
+// sums planes 16 y .. 16 y + 15 over all its tiles (v_mfma_f32_32x32x2_f32, 64 tiles per wavefront on their own) and encodes those
+// planes, or decodes item y.  All loads are in flight at once.  64 x 64 tiles, r = 49: 11.3 -> 6.1 with the encode,
+// 12 -> 6.0 with the decode.
+// ---------------------------------------------------------------------------------------
+template <bool ENC, bool DEC>
+__global__ __launch_bounds__(256) void tile_grad_kernel(const float *__restrict__ V, const float *__restrict__ Pin, const float *__restrict__ B,
+                                                        float *__restrict__ Pout, float *__restrict__ Cmat, float *__restrict__ part, int R,
+                                                        int Cc, int r, int lw, int chunks, Div by_chunk, Lay lp, RowMap rm)
+{
+    constexpr int PT = 256 + 4, PD = kTilePitch;
+    __shared__ __align__(16) float sP[16][PT], sX[16][PT];   // [plane][tile], [entry][tile]; then the wavefronts' sums
+    __shared__ __align__(16) float sD[DEC ? 64 : 1][PD];     // DEC: all planes of item y
+    __shared__ __align__(16) float sB[ENC || DEC ? 64 * 16 : 4];
+    const int tid = threadIdx.x, y = blockIdx.y, p0 = 16 * y, item0 = 4 * blockIdx.x;
+    const int W = 1 << lw, rows = 64 >> lw;
+    const bool sums = p0 < r;
+    // tile t of the 256: its tile row among those of this launch, -1 beyond them, and its tile column
+    struct Pos { int I, J; };
+    auto locate = [&](int t) {
+        const int item = item0 + (t >> 6), rb = by_chunk.of(item), idx = rb * rows + ((t & 63) >> lw), J = ((item - rb * chunks) << lw) + (t & (W - 1));
+        return Pos{idx < R && J < Cc ? rm.tile_row(idx) : -1, J};
+    };
+    auto planes4 = [&](Pos at, int p) {                      // four neighbouring tiles of plane p
+        return at.I >= 0 && p < r ? load4<float>(Pin + (size_t)p * lp.plane + lp.row(at.I) + at.J, Cc - at.J) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+
+    const Pos own = locate(tid);                             // ENC and the tiles' entries: a tile per thread
+    const size_t ld = (size_t)Cc * 4;
+    f32x4_t x[4], pv[4], dv[DEC ? 4 : 1];
+    if (sums) {
+        const int nv = own.I >= 0 ? rm.valid(own.I) : 0;
+        const float *v = V + (own.I >= 0 ? rm.row0(own.I) * ld + (size_t)own.J * 4 : 0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) x[a] = a < nv ? load4<float>(v + a * ld, 4) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        const Pos at = locate(4 * (tid & 63));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pv[i] = planes4(at, p0 + (tid >> 6) + 4 * i);
+    }
+    if (DEC) {
+        const Pos at = locate(64 * y + 4 * (tid & 15));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) dv[i] = planes4(at, (tid >> 4) + 16 * i);
+    }
+    if (ENC || DEC)
+        for (int i = tid; i < r * 16; i += 256) sB[i] = B[i];
+    if (sums) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4_t *>(&sP[(tid >> 6) + 4 * i][4 * (tid & 63)]) = pv[i];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sX[q][tid] = x[q >> 2][q & 3];
+    }
+    if (DEC)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4_t *>(&sD[(tid >> 4) + 16 * i][4 * (tid & 15)]) = dv[i];
+    __syncthreads();
+
+    const int wave = tid >> 6, fj = tid & 31, fh = (tid >> 5) & 1;
+    f32x16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    if (sums) {
+        // rows = planes (16 of 32), columns = entries (16 of 32); a lane's four neighbouring tiles are the contraction index fh of
+        // four products
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int t0 = 64 * wave + 8 * u + 4 * fh;
+            const f32x4_t xv = *reinterpret_cast<const f32x4_t *>(&sX[fj & 15][t0]);
+            const f32x4_t yv = *reinterpret_cast<const f32x4_t *>(&sP[fj & 15][t0]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(yv[e], xv[e], acc, 0, 0, 0);
+        }
+    }
+    if (ENC && sums && own.I >= 0) {
+        float *out = Pout + lp.row(own.I) + own.J;
+        const int n = r - p0 < 16 ? r - p0 : 16;
+#pragma unroll 4
+        for (int p = 0; p < n; ++p) {
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) s = fmaf(sB[(p0 + p) * 16 + q], x[q >> 2][q & 3], s);
+            out[(size_t)(p0 + p) * lp.plane] = s;
+        }
+    }
+    if (DEC) {
+        const int t = tid & 63, a = tid >> 6;
+        const Pos at = locate(64 * y + t);
+        f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+        for (int p = 0; p < r; ++p) {
+            const f32x4_t d = *reinterpret_cast<const f32x4_t *>(sB + p * 16 + 4 * a);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[e] = fmaf(d[e], sD[p][t], c[e]);
+        }
+        if (at.I >= 0 && a < rm.valid(at.I)) store4(Cmat + (rm.row0(at.I) + a) * ld + (size_t)at.J * 4, c);
+    }
+    if (!sums) return;
+    __syncthreads();
+    float *red = &sP[0][0];                                  // [wavefront][plane][entry]
+#pragma unroll
+    for (int e = 0; e < 8; ++e)                              // element e: plane 8 (e / 4) + 4 fh + e % 4
+        if (fj < 16) red[(wave * 16 + 8 * (e >> 2) + 4 * fh + (e & 3)) * 16 + fj] = acc[e];
+    __syncthreads();
+    if (p0 * 16 + tid < r * 16)
+        part[(size_t)blockIdx.x * r * 16 + p0 * 16 + tid] = (red[tid] + red[256 + tid]) + (red[512 + tid] + red[768 + tid]);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -471,6 +581,20 @@ static hipError_t launch_tile_map(const void *V, const void *Pin, const void *B,
     return hipGetLastError();
 }
 
+// the same with a basis gradient in nb partials, see tile_grad_kernel: where one partial per 256 tiles leaves CUs without one
+template <bool ENC, bool DEC>
+static hipError_t launch_tile_grad(const void *V, const void *Pin, const void *B, void *Pout, void *Cmat, float *part, int R, int R_all, int Cc,
+                                   int r, int pg, const RowMap &rm, int nb, hipStream_t s)
+{
+    const int lw = tile_item_log2(Cc), chunks = (Cc + (1 << lw) - 1) >> lw;
+    Lay lp;
+    if (!lp.set(pg, R_all, Cc, r)) return hipErrorInvalidValue;
+    const dim3 grid(nb, DEC ? 4 : (r + 15) / 16);
+    hipLaunchKernelGGL((tile_grad_kernel<ENC, DEC>), grid, dim3(256), 0, s, (const float *)V, (const float *)Pin, (const float *)B, (float *)Pout,
+                       (float *)Cmat, part, R, Cc, r, lw, chunks, Div::by(chunks), lp, rm);
+    return hipGetLastError();
+}
+
 hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s,
                          RowMap rm, bool basis_f32)
 {
@@ -588,6 +712,11 @@ hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const
     return err != hipSuccess ? err : launch_outer_final(part, G, nb, r * 16, accumulate, s);
 }
 
+// tile_grad_kernel has no loop over items and reads the matrix once per 16 planes (from L2 while it is small).  us of a step, items of
+// tile_map_kernel / this: forward + backward of 128 x 256 x 256 tiles, r = 16 (128 partials) 71 / 46, 800 x 256 x 256, r = 16 (800) 177 / 162,
+// 900 x 200 x 200, r = 32 (900) 262 / 258, but 250 x 256 x 256, r = 64 (250) 178 / 184.
+static bool small_gradient(int nb, int r) { return nb < 1024 && (r <= 32 || nb <= 192); }
+
 // Cmat == nullptr: the basis gradient alone
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R_all,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm, bool final_sum)
@@ -603,6 +732,11 @@ hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *C
                            (const bf16_t *)V, part, pg, rm);
         e = hipGetLastError();
     } else {
+        if (dtype == 0 && small_gradient(nb, r)) {
+            e = Cmat ? launch_tile_grad<false, true>(V, P, Dm, nullptr, Cmat, part, R, R_all, Cc, r, pg, rm, nb, s)
+                     : launch_tile_grad<false, false>(V, P, Dm, nullptr, nullptr, part, R, R_all, Cc, r, pg, rm, nb, s);
+            return e != hipSuccess || !final_sum ? e : launch_outer_final(part, G, nb, r * 16, accumulate, s);
+        }
         auto run = dtype == 0 ? (Cmat ? launch_tile_map<float, float, false, true, true, false> : launch_tile_map<float, float, false, false, true, false>)
                               : (Cmat ? launch_tile_map<bf16_t, bf16_t, false, true, true, false> : launch_tile_map<bf16_t, bf16_t, false, false, true, false>);
         e = run(V, P, Dm, nullptr, Cmat, part, R, Cc, r, pg, rm, nb, s);
@@ -622,6 +756,10 @@ hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P,
     if (dtype == 1 && Cc >= 8) {
         e = launch_encode_outer_lines(A, E, P, Qp, part, R, Cc, r, pg, nb, s, rm);
     } else {
+        if (dtype == 0 && small_gradient(nb, r)) {
+            e = launch_tile_grad<true, false>(A, Qp, E, P, nullptr, part, R, R_all, Cc, r, pg, rm, nb, s);
+            return e != hipSuccess || !final_sum ? e : launch_outer_final(part, G, nb, r * 16, accumulate, s);
+        }
         auto run = dtype == 0 ? launch_tile_map<float, float, true, false, true, false> : launch_tile_map<bf16_t, bf16_t, true, false, true, false>;
         e = run(A, Qp, E, P, nullptr, part, R, Cc, r, pg, rm, nb, s);
     }
