@@ -538,17 +538,19 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
     if (any_misaligned(X, What, E_X, D, C, Xhat_save, Yhat_save))
         return fail(STL_ERR_INVALID_ARG, "stl_forward: pointer not 16-byte aligned");
     // Automatic choice.  The single launch decodes the fp32 sums, three launches round Yhat to the storage type in between.  It is taken
-    //  - up to about four million tile products per plane set, where the operator is bound by its launches (m = 128, k = n = 512, r = 8:
-    //    10.5 us against 13.2).  One block walks the whole contraction there, so that few rows and a long contraction take longer
-    //    than three launches would (m = 32, n = 512, r = 8: k = 1024 16.8 against 13.3, k = 2048 29.7 against 13.2); such calls keep
-    //    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other;
-    //  - at r <= 8 also wherever every CU has at most one block and the contraction is short: m = 1024 / 4096 / 8192, k = n = 512, r = 8
-    //    10.8 / 11.2 / 13.8 us against 13.1 / 13.2 / 17.6, and nowhere slower over m = 32 ... 8192, k = 64 ... 512, n = 128 ... 4096.
+    //  - wherever every CU has at most one block and the contraction is short: a block walks all of it, 0.65 us per 16 tile columns at
+    //    r <= 16 and 1.0 at r <= 32 behind 4 to 6 us, three launches take 13.1 us or more.  us of the single launch over 2 to 256
+    //    blocks: r <= 8 7.6 at K <= 64, 8.5 to 9.4 at 128 and 14 to 14.7 at 256; r <= 16 7.6 to 8.5, 9.7 to 10.9 and 16 to 17;
+    //    r <= 32 8.0 to 9.6 at K = 32, 10.4 to 11.7 at 64, 15 to 16 at 128.  The line is drawn where the gain is clear: of the 13.1 a
+    //    host that enqueues slowly is a part;
+    //  - up to about four million tile products per plane set whatever the contraction: few rows and a long contraction take longer
+    //    than three launches would (m = 32, n = 512, r = 8: k = 1024 14.2 against 13.1, k = 2048 25 against 13.2), but such calls keep
+    //    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other.
     // Three launches everywhere else.
     const FwdWs w_declared = fwd_layout(d, variant);     // the workspace is checked against what the caller asked for
     if (variant == STL_FLAG_AUTO && !Xhat_save && stl::block_forward_eligible(prob->dtype, d.M, d.K, d.N, d.r) &&
         ((double)d.M * d.K * d.N * d.r <= 4.2e6 ||
-         (d.r <= 8 && d.K <= 128 && (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) <= 256)))
+         (d.K <= (d.r <= 8 ? 128 : d.r <= 16 ? 112 : 48) && (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) <= 256)))
         variant = STL_FLAG_FUSED;
     if (variant == STL_FLAG_PIPELINED && !stl::forward_pipeline_eligible(prob->dtype, d.M, d.K, d.N, d.r))
         return fail(STL_ERR_UNSUPPORTED,
