@@ -265,6 +265,14 @@ AaWs aa_layout(const Dims &d, int64_t nb, bool backward)
     return w;
 }
 
+// Whether the backward runs its two decodes as one launch and its three sums as one.  Products then stand between a gradient's
+// planes and their decode, which finds them in the last-level cache while all of them are small beside its 256 MB; a partial sum of
+// 16 r floats per 256 tiles fits the area of the tiles' r planes from 8 tile columns on.
+bool aa_backward_paired(int dt, const Dims &d, int64_t RA, int64_t RB, int CB, bool everything)
+{
+    return everything && dt == STL_BF16 && d.K >= 8 && d.N >= 8 && (double)d.r * (RA * d.K + RB * CB) * d.es <= 64e6;
+}
+
 stl_status_t check_batch(const stl_problem_t *p, const Dims &d, int64_t nb)
 {
     if (nb < 1) return fail(STL_ERR_INVALID_ARG, "nbatch=%lld must be positive", (long long)nb);
@@ -671,10 +679,10 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
         STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, pair ? part2 : part, d.M, d.K, d.r, accumulate, PG, s,
                                          stl::RowMap(), !pair),
                 "backward/dX + dE_X");
-        if (pair)
-            STL_HIP(stl::launch_outer_final_pair(part, dD, stl::encode_outer_blocks(d.M, d.N), part2, dE_X,
-                                                 stl::decode_outer_blocks(d.M, d.K), d.r * 16, accumulate, s),
-                    "backward/dD and dE_X sums");
+        if (pair) {
+            const stl::OuterSum sums[2] = {{part, dD, stl::encode_outer_blocks(d.M, d.N), false}, {part2, dE_X, stl::decode_outer_blocks(d.M, d.K), false}};
+            STL_HIP(stl::launch_outer_finals(sums, 2, d.r * 16, accumulate, s), "backward/dD and dE_X sums");
+        }
     } else if (dX) {
         STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s), "backward/decode dX");
     }
@@ -784,16 +792,22 @@ stl_status_t stl_aa_forward(const stl_problem_t *prob, int64_t nbatch, const voi
     void *ahat = Ahat_save ? Ahat_save : (void *)(base + w.ahat);
     void *bhat = Bhat_save ? Bhat_save : (void *)(base + w.bhat);
     void *yhat = Yhat_save ? Yhat_save : (void *)(base + w.yhat);
-    // the stack of first operands is one tall matrix for the tile maps; so is the stack of second operands
-    STL_HIP(stl::launch_encode(dt, A, E_A, ahat, nb * d.M, d.K, d.r, PG, s), "aa_forward/encode A");
+    // the stack of first operands is one tall matrix for the tile maps; so is the stack of second operands.  Tile (L, J) of B^T is
+    // the transpose of tile (J, L) of B: with B stored transposed, B is encoded as it lies with the transposition folded into the
+    // basis; the planes come out as [p][J][L], the [j][l] operand form of the plane products
     const bool bt = (flags & STL_FLAG_B_TRANSPOSED) != 0;
-    if (bt) {
-        // tile (L, J) of B^T is the transpose of tile (J, L) of B: encode B as it lies with the transposition folded into
-        // the basis; the planes come out as [p][J][L], the [j][l] operand form of the plane products
-        STL_HIP(stl::launch_transpose_basis(dt, E_B, base + w.ebt, d.r, s), "aa_forward/transpose E_B");
-        STL_HIP(stl::launch_encode(dt, B, base + w.ebt, bhat, nb * d.N, d.K, d.r, PG, s), "aa_forward/encode B");
+    const stl::TileSide sides[2] = {{ahat, E_A, A, nb * d.M, d.K, false, nullptr, nullptr},
+                                    {bhat, E_B, B, bt ? nb * d.N : nb * d.K, bt ? d.K : d.N, bt, nullptr, nullptr}};
+    if (stl::encode_pair_eligible(dt, sides, d.r)) {
+        STL_HIP(stl::launch_encode_pair(sides, d.r, PG, s), "aa_forward/encode A and B");
     } else {
-        STL_HIP(stl::launch_encode(dt, B, E_B, bhat, nb * d.K, d.N, d.r, PG, s), "aa_forward/encode B");
+        STL_HIP(stl::launch_encode(dt, A, E_A, ahat, nb * d.M, d.K, d.r, PG, s), "aa_forward/encode A");
+        const void *e_b = E_B;
+        if (bt) {
+            STL_HIP(stl::launch_transpose_basis(dt, E_B, base + w.ebt, d.r, s), "aa_forward/transpose E_B");
+            e_b = base + w.ebt;
+        }
+        STL_HIP(stl::launch_encode(dt, B, e_b, bhat, sides[1].R, sides[1].Cc, d.r, PG, s), "aa_forward/encode B");
     }
     stl::GemmDesc g{d.M, d.N, d.K, d.r, false, !bt, false, false, PG, PG, PG, nb};
     STL_HIP(stl::launch_plane_gemm(dt, g, ahat, bhat, yhat, s), "aa_forward/plane products");
@@ -825,6 +839,25 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
     // stacked tile rows of A (and C) and of B, and B's tile columns, as B is stored
     const int RA = nb * d.M, RB = bt ? nb * d.N : nb * d.K, CB = bt ? d.K : d.N;
     char *base = (char *)ws;
+    if (aa_backward_paired(dt, d, RA, RB, CB, Ahat_saved && Bhat_saved && Yhat_saved && dA && dB && dE_A && dE_B && dD)) {
+        // nothing is recomputed, so that the workspace's areas for the planes are free for partial sums
+        float *part_d = (float *)(base + w.part), *part_a = (float *)(base + w.ahat), *part_b = (float *)(base + w.bhat);
+        void *dyhat = base + w.dyhat, *dahat = base + w.dahat, *dbhat = base + w.dbhat;
+        STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, Yhat_saved, dD, part_d, RA, d.N, d.r, accumulate, PG, s, stl::RowMap(), false),
+                "aa_backward/dYhat + dD");
+        const stl::GemmDesc ga{d.M, d.K, d.N, d.r, false, bt, false, false, PG, PG, PG, nb};
+        const stl::GemmDesc gb{bt ? d.N : d.K, bt ? d.K : d.N, d.M, d.r, true, true, false, false, PG, PG, PG, nb};
+        STL_HIP(stl::launch_plane_gemm(dt, ga, dyhat, Bhat_saved, dahat, s), "aa_backward/dAhat");
+        STL_HIP(bt ? stl::launch_plane_gemm(dt, gb, dyhat, Ahat_saved, dbhat, s) : stl::launch_plane_gemm(dt, gb, Ahat_saved, dyhat, dbhat, s),
+                "aa_backward/dBhat");
+        const stl::TileSide sides[2] = {{dahat, E_A, dA, RA, d.K, false, A, part_a}, {dbhat, E_B, dB, RB, CB, bt, B, part_b}};
+        STL_HIP(stl::launch_decode_outer_pair(sides, d.r, PG, s), "aa_backward/dA + dE_A and dB + dE_B");
+        const stl::OuterSum sums[3] = {{part_d, dD, stl::encode_outer_blocks(RA, d.N), false},
+                                       {part_a, dE_A, stl::decode_outer_blocks(RA, d.K), false},
+                                       {part_b, dE_B, stl::decode_outer_blocks(RB, CB), bt}};
+        STL_HIP(stl::launch_outer_finals(sums, 3, d.r * 16, accumulate, s), "aa_backward/dD, dE_A and dE_B sums");
+        return STL_OK;
+    }
     const void *e_b = E_B;                       // the basis that encodes B as it lies
     if (bt) {
         STL_HIP(stl::launch_transpose_basis(dt, E_B, base + w.ebt, d.r, s), "aa_backward/transpose E_B");

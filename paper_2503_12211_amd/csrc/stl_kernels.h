@@ -87,9 +87,15 @@ int outer_reduce_blocks(int64_t tiles);     // a further bound on the partials, 
 
 // G[i] (+)= sum over nb partials part[b][i], i < n_out, in block order (second stage of the basis-gradient sums)
 hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s);
-// two such sums in one launch (final_sum = false in the two fused passes leaves their partials for this)
-hipError_t launch_outer_final_pair(const float *part0, float *G0, int nb0, const float *part1, float *G1, int nb1, int n_out,
-                                   int accumulate, hipStream_t s);
+// up to three such sums in one launch (final_sum = false in the fused passes leaves their partials for this); turned: the partials
+// are of the basis for the tiles' transposes, G[p][4a + b] gets entry 4b + a
+struct OuterSum {
+    const float *part;
+    float *G;
+    int nb;
+    bool turned;
+};
+hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, int accumulate, hipStream_t s);
 
 // encode and basis gradient in one pass over the matrix: P <- encode(A, E), G (+)= Qp . tileview(A);
 // `part` holds encode_outer_blocks(R, Cc) * r * 16 floats
@@ -99,6 +105,19 @@ hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P,
 // its bf16 kernel (Cc >= 8); launch_encode_outer picks it
 hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
                                      int nb, hipStream_t s, RowMap rm);
+
+// Two matrices of one dtype (bf16) and rank in one launch: their encodes, or their decodes with a basis gradient each (partials only;
+// Cmat and V of R x Cc tiles, `part` holds decode_outer_blocks(R, Cc) * r * 16 floats).  turned: see encode_items.
+struct TileSide {
+    const void *planes, *basis, *matrix;          // the one that is written is cast
+    int R, Cc;
+    bool turned;
+    const void *V;
+    float *part;
+};
+bool encode_pair_eligible(int dtype, const TileSide *s, int r);
+hipError_t launch_encode_pair(const TileSide *s, int r, int pg, hipStream_t st);
+hipError_t launch_decode_outer_pair(const TileSide *s, int r, int pg, hipStream_t st);
 
 // fold of an image's last tile row (row counts not divisible by 4): composed decoder Dp (r x 16 fp32) from Dm and the
 // nrho x 4 fold coefficients; and the gradients that come from those tile rows, given Gt = Yhat (x) dC over them

@@ -21,10 +21,13 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 // 512 x 250 tiles, r = 32, took 10 + 285 us, now 8; dYhat + dD of 4800 x 50 tiles 13 + 577 us, now 14.
 // SHIFT (with ANY, without OUTER): an item's 64 tile columns begin where the plane rows' cache lines do, up to 63 columns to the
 // left of its multiple of 64; `chunks` then counts (Cc + 126) / 64 items per row (see encode_line_starts).
+// turned: the basis is meant for the transposes of the tiles (entry 4a + b is applied to entry 4b + a); the basis gradient is that
+// of the tiles as they lie.
 template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false>
 __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E, bf16_t *__restrict__ P,
                                              const bf16_t *__restrict__ Qp, int R, int Cc, int r, int chunks, int pg, const RowMap &rm,
-                                             long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane)
+                                             long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane,
+                                             bool turned = false)
 {
     constexpr int ROWB = 128;                               // bytes per plane row of the slab (64 tiles)
     // 16-byte chunk swizzle of a plane row: a fragment read takes chunk 4sx + kq of 16 rows; odd/even rows already
@@ -41,7 +44,13 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
     for (int g = 0; g < 4; ++g) {
         const int pl = 16 * g + j;
         u32x2_t ev = {0u, 0u};
-        if (pl < r) ev = *reinterpret_cast<const u32x2_t *>(E + pl * 16 + 4 * kq);
+        if (pl < r) {
+            const bf16_t *e = E + pl * 16;
+            if (turned)
+                ev = u32x2_t{e[kq] | ((uint32_t)e[4 + kq] << 16), e[8 + kq] | ((uint32_t)e[12 + kq] << 16)};
+            else
+                ev = *reinterpret_cast<const u32x2_t *>(e + 4 * kq);
+        }
         eb[g] = __builtin_bit_cast(bf16x8_t, u32x4_t{ev[0], ev[1], 0u, 0u});
     }
     // tile (relative to J0) of this lane in product u, and its row in the LDS slab: rows t and t^4 are swapped where
@@ -181,7 +190,8 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t>   // DEPTH, ANY as in encode_items
 __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
                                              int R, int Cc, int r, int chunks, const bf16_t *__restrict__ V, int pg, const RowMap &rm,
-                                             long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane)
+                                             long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane,
+                                             bool turned = false)                          // turned as in encode_items
 {
     constexpr int ROWB = 128;                               // bytes per LDS row (64 tiles)
     const int ngroups = (r + 15) >> 4;
@@ -198,7 +208,8 @@ __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf1
 #pragma unroll
         for (int e2 = 0; e2 < 4; ++e2) {
             const int p0 = 32 * g + 8 * kq + 2 * e2;
-            const uint32_t lo = p0 < r ? Dm[p0 * 16 + j] : 0u, hi = p0 + 1 < r ? Dm[(p0 + 1) * 16 + j] : 0u;
+            const int q = turned ? 4 * (j & 3) + (j >> 2) : j;
+            const uint32_t lo = p0 < r ? Dm[p0 * 16 + q] : 0u, hi = p0 + 1 < r ? Dm[(p0 + 1) * 16 + q] : 0u;
             w[e2] = lo | (hi << 16);
         }
         fa[g] = __builtin_bit_cast(bf16x8_t, u32x4_t{w[0], w[1], w[2], w[3]});

@@ -364,17 +364,17 @@ struct TileGrid {
     }
 };
 
-// second stage of the basis-gradient sums: the blocks' partials in block order
-__global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restrict__ part, float *__restrict__ G,
-                                                           int nblocks, int n_out, int accumulate,
-                                                           const float *__restrict__ part1 = nullptr,
-                                                           float *__restrict__ G1 = nullptr, int nblocks1 = 0)
+// second stage of the basis-gradient sums: the blocks' partials in block order; blockIdx.y picks the sum
+struct OuterSums {
+    OuterSum s[3];
+};
+
+__global__ __launch_bounds__(1024) void outer_final_kernel(OuterSums sums, int n_out, int accumulate)
 {
-    if (blockIdx.y == 1) {          // second sum of a launch that finishes two at once
-        part = part1;
-        G = G1;
-        nblocks = nblocks1;
-    }
+    const OuterSum m = blockIdx.y == 0 ? sums.s[0] : blockIdx.y == 1 ? sums.s[1] : sums.s[2];
+    const float *part = m.part;
+    float *G = m.G;
+    const int nblocks = m.nb;
     // 16 outputs per block of 1024 threads; 64 slices of the block range per output (up to 1024 partials: 16 loads per
     // thread, all in flight together), then a fixed-order sum over the slices.
     __shared__ float red[64][17];
@@ -390,7 +390,8 @@ __global__ __launch_bounds__(1024) void outer_final_kernel(const float *__restri
         float tot = 0.f;
 #pragma unroll
         for (int u = 0; u < 64; ++u) tot += red[u][o];
-        G[i] = accumulate ? G[i] + tot : tot;
+        const int to = m.turned ? (i & ~15) + 4 * (i & 3) + ((i >> 2) & 3) : i;
+        G[to] = accumulate ? G[to] + tot : tot;
     }
 }
 
@@ -436,6 +437,43 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(const TP *__restrict__
         for (int i = threadIdx.x; i < r * 16; i += 256)
             part[(size_t)blockIdx.x * r * 16 + i] = ((red[i] + red[1024 + i]) + red[2048 + i]) + red[3072 + i];
     }
+}
+
+// Two decodes with a basis gradient each in one launch, blockIdx.y picks the matrix (see encode_pair_kernel).  96 x (50 x 16) tiles
+// twice, r = 32: 7.7 + 8.0 -> 12.7 us.
+struct DecodeSide {
+    const bf16_t *P, *Dm, *V;
+    bf16_t *Cmat;
+    float *part;
+    int R, Cc, chunks, nb;
+    bool turned;
+};
+
+template <int KC, bool ANY>
+__global__ __launch_bounds__(256) void decode_outer_pair_kernel(DecodeSide s0, DecodeSide s1, int r, int pg)
+{
+    constexpr int ROWB = 128;
+    __shared__ __align__(16) char slab_all[4][KC * 32 * ROWB];
+    __shared__ __align__(16) char sT_all[4][64 * 32];
+    const DecodeSide s = blockIdx.y ? s1 : s0;
+    if ((int)blockIdx.x >= s.nb) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int j = lane & 15, kq = lane >> 4;
+    f32x4_t oacc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    decode_items<false, KC, true, 1, ANY>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, s.V, pg, RowMap(), (long)blockIdx.x * 4 + wave, (long)s.nb * 4,
+                                          (long)s.R * s.chunks, sT_all[wave], slab_all[wave], oacc, lane, s.turned);
+    // as in decode_mfma_kernel
+    __syncthreads();
+    float *red = reinterpret_cast<float *>(&slab_all[0][0]);
+#pragma unroll
+    for (int g = 0; g < 2 * KC; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[wave * (KC * 512) + (16 * g + 4 * kq + e) * 16 + j] = oacc[g][e];
+    __syncthreads();
+    for (int i = threadIdx.x; i < r * 16; i += 256)
+        s.part[(size_t)blockIdx.x * r * 16 + i] = ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -655,19 +693,18 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
     return run(nullptr, P, Dm, nullptr, Cmat, nullptr, R, Cc, r, pg, rm, 0, s);
 }
 
-hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s)
+hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, int accumulate, hipStream_t s)
 {
-    hipLaunchKernelGGL(outer_final_kernel, dim3((n_out + 15) / 16), dim3(1024), 0, s, part, G, nb, n_out, accumulate,
-                       (const float *)nullptr, (float *)nullptr, 0);
+    OuterSums all{};
+    for (int i = 0; i < n && i < 3; ++i) all.s[i] = sums[i];
+    hipLaunchKernelGGL(outer_final_kernel, dim3((n_out + 15) / 16, n), dim3(1024), 0, s, all, n_out, accumulate);
     return hipGetLastError();
 }
 
-hipError_t launch_outer_final_pair(const float *part0, float *G0, int nb0, const float *part1, float *G1, int nb1, int n_out,
-                                   int accumulate, hipStream_t s)
+hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s)
 {
-    hipLaunchKernelGGL(outer_final_kernel, dim3((n_out + 15) / 16, 2), dim3(1024), 0, s, part0, G0, nb0, n_out, accumulate, part1,
-                       G1, nb1);
-    return hipGetLastError();
+    const OuterSum one{part, G, nb, false};
+    return launch_outer_finals(&one, 1, n_out, accumulate, s);
 }
 
 int decode_outer_blocks(int R, int Cc)
@@ -716,6 +753,22 @@ hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const
 // tile_map_kernel / this: forward + backward of 128 x 256 x 256 tiles, r = 16 (128 partials) 71 / 46, 800 x 256 x 256, r = 16 (800) 177 / 162,
 // 900 x 200 x 200, r = 32 (900) 262 / 258, but 250 x 256 x 256, r = 64 (250) 178 / 184.
 static bool small_gradient(int nb, int r) { return nb < 1024 && (r <= 32 || nb <= 192); }
+
+hipError_t launch_decode_outer_pair(const TileSide *t, int r, int pg, hipStream_t st)
+{
+    DecodeSide s[2];
+    int nb = 1;
+    for (int i = 0; i < 2; ++i) {
+        s[i] = {(const bf16_t *)t[i].planes, (const bf16_t *)t[i].basis, (const bf16_t *)t[i].V, (bf16_t *)t[i].matrix, t[i].part, t[i].R, t[i].Cc,
+                (t[i].Cc + 63) / 64, decode_outer_blocks(t[i].R, t[i].Cc), t[i].turned};
+        nb = s[i].nb > nb ? s[i].nb : nb;
+    }
+    const bool any = s[0].Cc % 8 || s[1].Cc % 8;
+    auto kern = r <= 32 ? (any ? decode_outer_pair_kernel<1, true> : decode_outer_pair_kernel<1, false>)
+                        : (any ? decode_outer_pair_kernel<2, true> : decode_outer_pair_kernel<2, false>);
+    hipLaunchKernelGGL(kern, dim3(nb, 2), dim3(256), 0, st, s[0], s[1], r, pg);
+    return hipGetLastError();
+}
 
 // Cmat == nullptr: the basis gradient alone
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R_all,
