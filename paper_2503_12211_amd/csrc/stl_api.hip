@@ -680,7 +680,7 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
                                          stl::RowMap(), !pair),
                 "backward/dX + dE_X");
         if (pair) {
-            const stl::OuterSum sums[2] = {{part, dD, stl::encode_outer_blocks(d.M, d.N), false}, {part2, dE_X, stl::decode_outer_blocks(d.M, d.K), false}};
+            const stl::OuterSum sums[2] = {{part, dD, stl::gradient_blocks(dt, d.M, d.N, true), false}, {part2, dE_X, stl::gradient_blocks(dt, d.M, d.K, true), false}};
             STL_HIP(stl::launch_outer_finals(sums, 2, d.r * 16, accumulate, s), "backward/dD and dE_X sums");
         }
     } else if (dX) {
@@ -852,9 +852,9 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
                 "aa_backward/dBhat");
         const stl::TileSide sides[2] = {{dahat, E_A, dA, RA, d.K, false, A, part_a}, {dbhat, E_B, dB, RB, CB, bt, B, part_b}};
         STL_HIP(stl::launch_decode_outer_pair(sides, d.r, PG, s), "aa_backward/dA + dE_A and dB + dE_B");
-        const stl::OuterSum sums[3] = {{part_d, dD, stl::encode_outer_blocks(RA, d.N), false},
-                                       {part_a, dE_A, stl::decode_outer_blocks(RA, d.K), false},
-                                       {part_b, dE_B, stl::decode_outer_blocks(RB, CB), bt}};
+        const stl::OuterSum sums[3] = {{part_d, dD, stl::gradient_blocks(dt, RA, d.N, true), false},
+                                       {part_a, dE_A, stl::gradient_blocks(dt, RA, d.K, true), false},
+                                       {part_b, dE_B, stl::gradient_blocks(dt, RB, CB, true), bt}};
         STL_HIP(stl::launch_outer_finals(sums, 3, d.r * 16, accumulate, s), "aa_backward/dD, dE_A and dE_B sums");
         return STL_OK;
     }

@@ -20,6 +20,7 @@
 #include "stl_kernels.h"
 #include "stl_device.h"
 #include "stl_tile_items.h"
+#include <type_traits>
 
 namespace stl {
 
@@ -35,7 +36,6 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
     __shared__ __align__(16) char sT_all[OUTER ? 4 : 1][OUTER ? 64 * 32 : 16];   // per wavefront: [tile][16 entries] bf16
     __shared__ __align__(16) char slab_all[4][KC * 32 * ROWB];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = lane & 15, kq = lane >> 4;
     f32x4_t dacc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -44,17 +44,7 @@ __global__ __launch_bounds__(256) void encode_outer16_kernel(const bf16_t *__res
                             (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], dacc, lane);
 
     if (!OUTER) return;
-    // accumulator e of group g: plane 16g + 4kq + e, tile entry j; fixed-order sum over the four wavefronts
-    __syncthreads();                                        // every wavefront is done with its slab
-    float *red = reinterpret_cast<float *>(&slab_all[0][0]); // 4 x (32 KC x 16) floats = the slabs' size
-#pragma unroll
-    for (int g = 0; g < 2 * KC; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave * (KC * 512) + (16 * g + 4 * kq + e) * 16 + j] = dacc[g][e];
-    __syncthreads();
-    for (int i = threadIdx.x; i < r * 16; i += 256)
-        part[(size_t)blockIdx.x * r * 16 + i] =
-            ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
+    write_partial<KC>(dacc, reinterpret_cast<float *>(&slab_all[0][0]), part, r, wave, lane);
 }
 
 int encode_outer_blocks(int R, int Cc)
@@ -64,10 +54,115 @@ int encode_outer_blocks(int R, int Cc)
     return (int)(blocks > 1024 ? 1024 : blocks);
 }
 
+// A plane row of a width that is no multiple of 8 begins anywhere in a cache line, so that items of 64 columns counted from its
+// beginning write two incomplete lines per plane.  Once the planes no longer fit the caches beside the matrix that is most of the
+// time (8192 x 508 tiles, r = 32: 116 us; with 32-column fragments of 256 bytes per plane 90; lines written whole 84), and
+// narrower rows pay for an item more per row (16384 x 132, r = 49: 78 -> 95 us; 4096 x 252, r = 49: 25 both ways).  r R Cc = 3.3e7:
+// 4096 x 508, r = 16: 30 -> 24, 4096 x 1004, r = 8: 34 both ways; below, 1024 x 1004, r = 16: 12.6 -> 13.1.
+bool encode_line_starts(int R, int Cc, int r) { return Cc % 8 && Cc > 192 && (double)r * R * Cc >= 3.2e7; }
+
+// Two encodes in one launch, blockIdx.y picks the matrix: for matrices of a few microseconds, where half of each launch is its beginning
+// and its end.  The pair of 96 x (50 x 16) tiles, r = 32: 6.3 + 5.6 us and 1.2 for a transposed basis of the second -> 12.3, 6.9 in items of several tile rows.
+struct EncodeSide {
+    const bf16_t *A, *E;
+    bf16_t *P;
+    int R, Cc, chunks, lw;
+    Lay lay;
+    bool turned;
+    // false: a layout that Lay does not describe
+    bool set(const TileSide &t, int r, int pg, bool narrow)
+    {
+        A = (const bf16_t *)t.matrix;
+        E = (const bf16_t *)t.basis;
+        P = (bf16_t *)t.planes;
+        R = t.R;
+        Cc = t.Cc;
+        turned = t.turned;
+        const int l = narrow_log2(1, Cc, true);
+        lw = narrow && l ? l : 6;
+        chunks = (Cc + (1 << lw) - 1) >> lw;
+        return lay.set(pg, R, Cc, r);
+    }
+    long items() const { return (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks; }
+};
+
+template <int KC, bool ANY, bool NARROW>
+__global__ __launch_bounds__(256) void encode_pair_kernel(EncodeSide s0, EncodeSide s1, int r, int pg)
+{
+    __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const EncodeSide s = blockIdx.y ? s1 : s0;
+    const int rows = 64 >> s.lw;
+    f32x4_t none[4];
+    encode_items<KC, false, false, 1, ANY, false, NARROW>(s.A, s.E, s.P, nullptr, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                          (long)gridDim.x * 4, (long)((s.R + rows - 1) / rows) * s.chunks, nullptr,
+                                                          slab_all[wave], none, lane, s.turned, s.lw, s.lay);
+}
+
+// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns
+static hipError_t launch_encode_sides(const TileSide *t, int n, int r, int pg, hipStream_t st)
+{
+    EncodeSide s[2] = {};
+    bool any = false, narrow = false;
+    for (int i = 0; i < n; ++i) {
+        any = any || t[i].Cc % 8;
+        narrow = narrow || narrow_log2(1, t[i].Cc, true);
+    }
+    long blocks = 1;
+    for (int i = 0; i < n; ++i) {
+        if (!s[i].set(t[i], r, pg, narrow)) return hipErrorInvalidValue;
+        const long b = (s[i].items() + 3) / 4;
+        blocks = b > blocks ? b : blocks;
+    }
+    auto pick = [&](auto kc) {
+        constexpr int KC = decltype(kc)::value;
+        return narrow ? (any ? encode_pair_kernel<KC, true, true> : encode_pair_kernel<KC, false, true>)
+                      : (any ? encode_pair_kernel<KC, true, false> : encode_pair_kernel<KC, false, false>);
+    };
+    auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks), n), dim3(256), 0, st, s[0], s[1], r, pg);
+    return hipGetLastError();
+}
+
+bool encode_pair_eligible(int dtype, const TileSide *s, int r)
+{
+    return dtype == 1 && s[0].Cc >= 8 && s[1].Cc >= 8 && !encode_line_starts(s[0].R, s[0].Cc, r) && !encode_line_starts(s[1].R, s[1].Cc, r);
+}
+
+hipError_t launch_encode_pair(const TileSide *t, int r, int pg, hipStream_t st) { return launch_encode_sides(t, 2, r, pg, st); }
+
+// encode and basis gradient of a matrix of 8 to 32 tile columns, nb blocks that leave one partial each
+template <int KC, bool ANY>
+__global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, const bf16_t *__restrict__ Qp, float *__restrict__ part, int r, int pg)
+{
+    __shared__ __align__(16) char sT_all[4][64 * 32];
+    __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = 64 >> s.lw;
+    f32x4_t dacc[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    encode_items<KC, true, false, 1, ANY, false, true>(s.A, s.E, s.P, Qp, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                       (long)gridDim.x * 4, (long)((s.R + rows - 1) / rows) * s.chunks, sT_all[wave],
+                                                       slab_all[wave], dacc, lane, false, s.lw, s.lay);
+    write_partial<KC>(dacc, reinterpret_cast<float *>(&slab_all[0][0]), part, r, wave, lane);
+}
+
+static hipError_t launch_encode_outer_narrow(const TileSide &t, const void *Qp, float *part, int r, int pg, int nb, hipStream_t st)
+{
+    EncodeSide s;
+    if (!s.set(t, r, pg, true)) return hipErrorInvalidValue;
+    const bool any = t.Cc % 8;
+    auto kern = r <= 32 ? (any ? encode_outer_narrow_kernel<1, true> : encode_outer_narrow_kernel<1, false>)
+                        : (any ? encode_outer_narrow_kernel<2, true> : encode_outer_narrow_kernel<2, false>);
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, st, s, (const bf16_t *)Qp, part, r, pg);
+    return hipGetLastError();
+}
+
 // both maps on the matrix cores (bf16, Cc >= 8), nb blocks that leave one partial each; R counts the rows of this launch
 hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
                                      int nb, hipStream_t s, RowMap rm)
 {
+    if (narrow_log2(1, Cc, rm.Mt == 0)) return launch_encode_outer_narrow({P, E, A, R, Cc, false, nullptr, nullptr}, Qp, part, r, pg, nb, s);
     const bool any = Cc % 8 != 0;
     auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, true, true> : encode_outer16_kernel<1, true, false>)
                         : (any ? encode_outer16_kernel<2, true, true> : encode_outer16_kernel<2, true, false>);
@@ -76,19 +171,16 @@ hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, cons
     return hipGetLastError();
 }
 
-// A plane row of a width that is no multiple of 8 begins anywhere in a cache line, so that items of 64 columns counted from its
-// beginning write two incomplete lines per plane.  Once the planes no longer fit the caches beside the matrix that is most of the
-// time (8192 x 508 tiles, r = 32: 116 us; with 32-column fragments of 256 bytes per plane 90; lines written whole 84), and
-// narrower rows pay for an item more per row (16384 x 132, r = 49: 78 -> 95 us; 4096 x 252, r = 49: 25 both ways).  r R Cc = 3.3e7:
-// 4096 x 508, r = 16: 30 -> 24, 4096 x 1004, r = 8: 34 both ways; below, 1024 x 1004, r = 16: 12.6 -> 13.1.
-bool encode_line_starts(int R, int Cc, int r) { return Cc % 8 && Cc > 192 && (double)r * R * Cc >= 3.2e7; }
-
 // the encode alone through the same kernel (bf16, Cc >= 8): grid-stride over (tile row, 64-tile chunk) items
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm)
 {
     if (pg <= 0) pg = R;
     R = rm.count(R);
     if (R <= 0) return hipSuccess;
+    if (narrow_log2(1, Cc, rm.Mt == 0)) {
+        const TileSide one{P, E, A, R, Cc, false, nullptr, nullptr};
+        return launch_encode_sides(&one, 1, r, pg, s);
+    }
     const bool any = Cc % 8 != 0, starts = encode_line_starts(R, Cc, r);
     const int chunks = starts ? (Cc + 126) / 64 : (Cc + 63) / 64;
     const long items = (long)R * chunks;
@@ -99,47 +191,6 @@ hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int
                         : (any ? encode_outer16_kernel<2, false, true> : encode_outer16_kernel<2, false, false>);
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, (const bf16_t *)A, (const bf16_t *)E, (bf16_t *)P,
                        (const bf16_t *)nullptr, (float *)nullptr, R, Cc, r, chunks, pg, rm);
-    return hipGetLastError();
-}
-
-// Two encodes in one launch, blockIdx.y picks the matrix: for matrices of a few microseconds, where half of each launch is its beginning
-// and its end.  The pair of 96 x (50 x 16) tiles, r = 32: 6.3 + 5.6 us and 1.2 for a transposed basis of the second -> 12.3.
-struct EncodeSide {
-    const bf16_t *A, *E;
-    bf16_t *P;
-    int R, Cc, chunks;
-    bool turned;
-};
-
-template <int KC, bool ANY>
-__global__ __launch_bounds__(256) void encode_pair_kernel(EncodeSide s0, EncodeSide s1, int r, int pg)
-{
-    __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const EncodeSide s = blockIdx.y ? s1 : s0;
-    f32x4_t none[4];
-    encode_items<KC, false, false, 1, ANY, false>(s.A, s.E, s.P, nullptr, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
-                                                  (long)gridDim.x * 4, (long)s.R * s.chunks, nullptr, slab_all[wave], none, lane, s.turned);
-}
-
-bool encode_pair_eligible(int dtype, const TileSide *s, int r)
-{
-    return dtype == 1 && s[0].Cc >= 8 && s[1].Cc >= 8 && !encode_line_starts(s[0].R, s[0].Cc, r) && !encode_line_starts(s[1].R, s[1].Cc, r);
-}
-
-hipError_t launch_encode_pair(const TileSide *t, int r, int pg, hipStream_t st)
-{
-    EncodeSide s[2];
-    long blocks = 1;
-    for (int i = 0; i < 2; ++i) {
-        s[i] = {(const bf16_t *)t[i].matrix, (const bf16_t *)t[i].basis, (bf16_t *)t[i].planes, t[i].R, t[i].Cc, (t[i].Cc + 63) / 64, t[i].turned};
-        const long b = ((long)s[i].R * s[i].chunks + 3) / 4;
-        blocks = b > blocks ? b : blocks;
-    }
-    const bool any = s[0].Cc % 8 || s[1].Cc % 8;
-    auto kern = r <= 32 ? (any ? encode_pair_kernel<1, true> : encode_pair_kernel<1, false>)
-                        : (any ? encode_pair_kernel<2, true> : encode_pair_kernel<2, false>);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks), 2), dim3(256), 0, st, s[0], s[1], r, pg);
     return hipGetLastError();
 }
 

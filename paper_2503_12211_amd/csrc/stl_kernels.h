@@ -77,7 +77,10 @@ bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r);
 
 // Basis gradient G[p][q] (+)= sum_tiles P[p][tile] * tileview(V)[tile][q], in one pass with the decode of the same planes
 // (Cmat <- decode(P, Dm)), or alone when Cmat is NULL (Dm is not read then); `part` holds decode_outer_blocks(R, Cc) * r * 16 floats
-int decode_outer_blocks(int R, int Cc);
+int decode_outer_blocks(int R, int Cc);       // for the workspace; as many or fewer are used:
+int gradient_blocks(int dtype, int R, int Cc, bool plain_rows);
+// bf16 matrices of 8 to 32 tile columns (no row map) run in items of several tile rows, 1 << narrow_log2 columns each; 0: they do not
+int narrow_log2(int dtype, int Cc, bool plain_rows);
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
 // the same from fp32 planes into a bf16 matrix (plane-major, Cc >= 8); W or G may be NULL
@@ -98,7 +101,7 @@ struct OuterSum {
 hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, int accumulate, hipStream_t s);
 
 // encode and basis gradient in one pass over the matrix: P <- encode(A, E), G (+)= Qp . tileview(A);
-// `part` holds encode_outer_blocks(R, Cc) * r * 16 floats
+// `part` holds encode_outer_blocks(R, Cc) * r * 16 floats (gradient_blocks of them are used)
 int encode_outer_blocks(int R, int Cc);
 hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R, int Cc,
                                int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
@@ -109,7 +112,7 @@ hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, cons
 // Two matrices of one dtype (bf16) and rank in one launch: their encodes, or their decodes with a basis gradient each (partials only;
 // Cmat and V of R x Cc tiles, `part` holds decode_outer_blocks(R, Cc) * r * 16 floats).  turned: see encode_items.
 struct TileSide {
-    const void *planes, *basis, *matrix;          // the one that is written is cast
+    const void *planes, *basis, *matrix;          // of planes and matrix one is written
     int R, Cc;
     bool turned;
     const void *V;

@@ -23,11 +23,14 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 // left of its multiple of 64; `chunks` then counts (Cc + 126) / 64 items per row (see encode_line_starts).
 // turned: the basis is meant for the transposes of the tiles (entry 4a + b is applied to entry 4b + a); the basis gradient is that
 // of the tiles as they lie.
-template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false>
+// NARROW (no row map): an item is 64 >> lw tile rows of 1 << lw columns each, lw >= 3, and lay the planes' layout; `chunks` items to a row
+// group.  Items of a single row left a matrix of 16 tile columns with a quarter of each lane's work: two
+// encodes of 4800 x 16 tiles, r = 32, 12.3 -> 6.9 us, their two decodes with a basis gradient each 12.7 -> 7.6.
+template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false, bool NARROW = false>
 __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E, bf16_t *__restrict__ P,
                                              const bf16_t *__restrict__ Qp, int R, int Cc, int r, int chunks, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane,
-                                             bool turned = false)
+                                             bool turned = false, int lw = 6, Lay lay = Lay{})
 {
     constexpr int ROWB = 128;                               // bytes per plane row of the slab (64 tiles)
     // 16-byte chunk swizzle of a plane row: a fragment read takes chunk 4sx + kq of 16 rows; odd/even rows already
@@ -69,7 +72,32 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 
     u32x2_t xa[DEPTH][4];                   // this lane's tile rows, one per product
     u32x4_t qa[DEPTH][OUTER ? KC * 4 : 1];  // plane segments, loader role: plane 8*g8 + pr, tiles 8ch .. 8ch+7
+    // NARROW: tile row and column of tile t of an item, offset of the plane row that holds chunk ch (8 tiles) of it, elements left there
+    struct Pos { int I, J; };
+    auto locate = [&](long item, int t) {
+        const int rb = (int)(item / chunks), ck = (int)(item - (long)rb * chunks);
+        return Pos{(rb << (6 - lw)) + (t >> lw), (ck << lw) + (t & ((1 << lw) - 1))};
+    };
+    auto fetch_narrow = [&](int d, long item) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const Pos at = locate(item, trel[u]);
+            u32x2_t v = {0u, 0u};
+            if (at.I < R && at.J < Cc) v = *reinterpret_cast<const u32x2_t *>(A + ((size_t)at.I * 4 + kq) * ld + (size_t)at.J * 4);
+            xa[d][u] = v;
+        }
+        if (OUTER) {
+            const Pos at = locate(item, 8 * ch);
+            const size_t off = (size_t)lay.row(at.I) + at.J;
+#pragma unroll
+            for (int g8 = 0; g8 < KC * 4; ++g8) {
+                const int pl = 8 * g8 + pr;
+                qa[d][g8] = load8<ANY>(Qp + off + (size_t)pl * plane, at.I < R && pl < r ? Cc - at.J : 0);
+            }
+        }
+    };
     auto fetch = [&](int d, long item) {
+        if constexpr (NARROW) return fetch_narrow(d, item);
         const int Ii = (int)(item / chunks), cki = (int)(item - (long)Ii * chunks);
         const int Ia = Ii < R ? rm.tile_row(Ii) : 0;        // Ii counts the tile rows of this launch, Ia is the tile row itself
         const int J0 = cki * 64 - shift(Ia);
@@ -112,8 +140,8 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
             }
         }
         if (item0 + DEPTH * stride < end) fetch(d, item0 + DEPTH * stride);
-        if (Iidx >= R) continue;
-        const int I = rm.tile_row(Iidx), J0 = cki * 64 - shift(I);
+        if (!NARROW && Iidx >= R) continue;
+        const int I = NARROW ? 0 : rm.tile_row(Iidx), J0 = NARROW ? 0 : cki * 64 - shift(I);
 
         // tile rows -> second slab
         if (OUTER) {
@@ -167,6 +195,17 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
                 }
             }
         }
+        if constexpr (NARROW) {
+            const Pos at = locate(item0, 8 * ch);
+            bf16_t *o = P + lay.row(at.I) + at.J;
+#pragma unroll
+            for (int g8 = 0; g8 < KC * 4; ++g8) {
+                const int pl = 8 * g8 + pr;
+                if (pl < r && at.I < R && at.J < Cc)
+                    store8<ANY>(o + (size_t)pl * plane, Cc - at.J, *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4)));
+            }
+            continue;
+        }
         const size_t rowb_out = plane_row_base(I, pg, r, Cc);
 #pragma unroll
         for (int g8 = 0; g8 < KC * 4; ++g8) {
@@ -187,11 +226,11 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 // wavefront; sT: 64 x 32 bytes (OUTER only); oacc accumulates the basis gradient (OUTER).  No workgroup barrier inside.
 // DECODE = false: the basis gradient alone (Dm and Cmat unused).  TP: storage type of the planes; fp32 planes (the gradient of
 // an encoded weight) are rounded to bf16 on their way into LDS.
-template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t>   // DEPTH, ANY as in encode_items
+template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t, bool NARROW = false>   // DEPTH, ANY, NARROW as in encode_items
 __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
                                              int R, int Cc, int r, int chunks, const bf16_t *__restrict__ V, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane,
-                                             bool turned = false)                          // turned as in encode_items
+                                             bool turned = false, int lw = 6, Lay lay = Lay{})                          // as in encode_items
 {
     constexpr int ROWB = 128;                               // bytes per LDS row (64 tiles)
     const int ngroups = (r + 15) >> 4;
@@ -227,7 +266,31 @@ __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf1
     const int pr = lane >> 3, ch = lane & 7;
     Raw8<TP, ANY> pre[DEPTH][KC * 4];
     u32x2_t xpre[DEPTH][OUTER ? 4 : 1];
+    struct Pos { int I, J; };
+    auto locate = [&](long item, int t) {
+        const int rb = (int)(item / chunks), ck = (int)(item - (long)rb * chunks);
+        return Pos{(rb << (6 - lw)) + (t >> lw), (ck << lw) + (t & ((1 << lw) - 1))};
+    };
+    auto fetch_narrow = [&](int d, long item) {
+        const Pos at = locate(item, 8 * ch);
+        const size_t off = (size_t)lay.row(at.I) + at.J;
+#pragma unroll
+        for (int g8 = 0; g8 < KC * 4; ++g8) {
+            const int pl = 8 * g8 + pr;
+            pre[d][g8].load(P + off + (size_t)pl * plane, at.I < R && pl < r ? Cc - at.J : 0);
+        }
+        if (OUTER) {
+            const Pos v = locate(item, lane);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                u32x2_t xv = {0u, 0u};
+                if (v.I < R && v.J < Cc) xv = *reinterpret_cast<const u32x2_t *>(V + ((size_t)v.I * 4 + a) * ld + (size_t)v.J * 4);
+                xpre[d][a] = xv;
+            }
+        }
+    };
     auto fetch = [&](int d, long item) {
+        if constexpr (NARROW) return fetch_narrow(d, item);
         const int Ii = (int)(item / chunks), cki = (int)(item - (long)Ii * chunks);
         const int Jl = cki * 64 + 8 * ch;
         const int Ia = Ii < R ? rm.tile_row(Ii) : 0;        // Ii counts the tile rows of this launch, Ia is the tile row itself
@@ -259,8 +322,8 @@ __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf1
         const long item0 = base + d * stride;
         if (item0 >= end) break;
         const int In = (int)(item0 / chunks), J0 = (int)(item0 - (long)In * chunks) * 64;
-        const bool live = In < R;
-        const int I = live ? rm.tile_row(In) : 0;
+        const bool live = NARROW || In < R;
+        const int I = live && !NARROW ? rm.tile_row(In) : 0;
         // slab and sV belong to this wavefront alone and its LDS operations execute in order: the writes below land
         // after the previous round's fragment reads without a workgroup barrier (which would also make the wavefront
         // wait for the loads it is about to put in flight)
@@ -323,17 +386,40 @@ __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf1
                     struct { v4i16_t a, b; } both = {t[0], t[1]};
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[g], __builtin_bit_cast(bf16x8_t, both), acc, 0, 0, 0);
                 }
-                // lane holds row a = kq of tile J0 + 16u + j: entries acc[0..3]
-                const int J = J0 + 16 * u + j;
-                if (J < Cc && kq < nv_out) {
+                // lane holds row a = kq of tile 16u + j of the item: entries acc[0..3]
+                int J = J0 + 16 * u + j;
+                size_t row = r0_out + kq;
+                bool in = J < Cc && kq < nv_out;
+                if constexpr (NARROW) {
+                    const Pos at = locate(item0, 16 * u + j);
+                    J = at.J;
+                    row = (size_t)at.I * 4 + kq;
+                    in = at.I < R && at.J < Cc;
+                }
+                if (in) {
                     float c0 = acc[0], c1 = acc[1], c2 = acc[2], c3 = acc[3];
                     if (GELU) { c0 = gelu_erf(c0); c1 = gelu_erf(c1); c2 = gelu_erf(c2); c3 = gelu_erf(c3); }
                     const u32x2_t w = {pack_bf16x2(c0, c1), pack_bf16x2(c2, c3)};
-                    *reinterpret_cast<u32x2_t *>(Cmat + (r0_out + kq) * ld + (size_t)J * 4) = w;
+                    *reinterpret_cast<u32x2_t *>(Cmat + row * ld + (size_t)J * 4) = w;
                 }
             }
         }
     }
+}
+
+// A block's partial of a basis gradient: accumulator e of group g of a wavefront is plane 16g + 4 (lane / 16) + e, tile entry lane % 16;
+// fixed-order sum over the four wavefronts in `red`, 4 x (32 KC x 16) floats of LDS that they are done with otherwise.
+template <int KC>
+__device__ __forceinline__ void write_partial(const f32x4_t (&acc)[4], float *red, float *__restrict__ part, int r, int wave, int lane)
+{
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < 2 * KC; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) red[wave * (KC * 512) + (16 * g + 4 * (lane >> 4) + e) * 16 + (lane & 15)] = acc[g][e];
+    __syncthreads();
+    for (int i = threadIdx.x; i < r * 16; i += 256)
+        part[(size_t)blockIdx.x * r * 16 + i] = ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
 }
 
 }  // namespace stl

@@ -4,6 +4,7 @@
 #include "stl_kernels.h"
 #include "stl_device.h"
 #include "stl_tile_items.h"
+#include <type_traits>
 
 
 namespace stl {
@@ -418,38 +419,44 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(const TP *__restrict__
     // OUTER: per wavefront the 64 tiles of V, tile-major [tile][16 entries] (32 bytes per tile)
     __shared__ __align__(16) char sT_all[OUTER ? 4 : 1][OUTER ? 64 * 32 : 16];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = lane & 15, kq = lane >> 4;
     f32x4_t oacc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // wavefront w of block b takes items 4b + w, 4b + w + 4 * gridDim.x, ...
     decode_items<GELU, KC, OUTER, 1, ANY, DECODE, TP>(P, Dm, Cmat, R, Cc, r, chunks, V, pg, rm, (long)blockIdx.x * 4 + wave, (long)gridDim.x * 4,
                                   (long)R * chunks, sT_all[OUTER ? wave : 0], slab_all[wave], oacc, lane);
-    if (OUTER) {
-        // accumulator e of group g: plane 16g + 4*kq + e, tile entry j; fixed-order sum over the four wavefronts
-        __syncthreads();
-        float *red = reinterpret_cast<float *>(&slab_all[0][0]);      // 4 x (64 x 16) floats fit in the slabs
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) red[wave * 1024 + (16 * g + 4 * kq + e) * 16 + j] = oacc[g][e];
-        __syncthreads();
-        for (int i = threadIdx.x; i < r * 16; i += 256)
-            part[(size_t)blockIdx.x * r * 16 + i] = ((red[i] + red[1024 + i]) + red[2048 + i]) + red[3072 + i];
-    }
+    if (OUTER) write_partial<KC>(oacc, reinterpret_cast<float *>(&slab_all[0][0]), part, r, wave, lane);
 }
 
 // Two decodes with a basis gradient each in one launch, blockIdx.y picks the matrix (see encode_pair_kernel).  96 x (50 x 16) tiles
-// twice, r = 32: 7.7 + 8.0 -> 12.7 us.
+// twice, r = 32: 7.7 + 8.0 -> 12.7 us, 7.6 in items of several tile rows.
 struct DecodeSide {
     const bf16_t *P, *Dm, *V;
     bf16_t *Cmat;
     float *part;
-    int R, Cc, chunks, nb;
+    int R, Cc, chunks, nb, lw;
+    Lay lay;
     bool turned;
+    bool set(const TileSide &t, int r, int pg, bool narrow)
+    {
+        P = (const bf16_t *)t.planes;
+        Dm = (const bf16_t *)t.basis;
+        V = (const bf16_t *)t.V;
+        Cmat = (bf16_t *)t.matrix;
+        part = t.part;
+        R = t.R;
+        Cc = t.Cc;
+        turned = t.turned;
+        const int l = narrow_log2(1, Cc, true);
+        lw = narrow && l ? l : 6;
+        chunks = (Cc + (1 << lw) - 1) >> lw;
+        nb = gradient_blocks(1, R, Cc, true);
+        return lay.set(pg, R, Cc, r);
+    }
+    __host__ __device__ __forceinline__ long items() const { return (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks; }
 };
 
-template <int KC, bool ANY>
+template <int KC, bool ANY, bool NARROW, bool DECODE>
 __global__ __launch_bounds__(256) void decode_outer_pair_kernel(DecodeSide s0, DecodeSide s1, int r, int pg)
 {
     constexpr int ROWB = 128;
@@ -458,22 +465,25 @@ __global__ __launch_bounds__(256) void decode_outer_pair_kernel(DecodeSide s0, D
     const DecodeSide s = blockIdx.y ? s1 : s0;
     if ((int)blockIdx.x >= s.nb) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int j = lane & 15, kq = lane >> 4;
     f32x4_t oacc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    decode_items<false, KC, true, 1, ANY>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, s.V, pg, RowMap(), (long)blockIdx.x * 4 + wave, (long)s.nb * 4,
-                                          (long)s.R * s.chunks, sT_all[wave], slab_all[wave], oacc, lane, s.turned);
-    // as in decode_mfma_kernel
-    __syncthreads();
-    float *red = reinterpret_cast<float *>(&slab_all[0][0]);
-#pragma unroll
-    for (int g = 0; g < 2 * KC; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave * (KC * 512) + (16 * g + 4 * kq + e) * 16 + j] = oacc[g][e];
-    __syncthreads();
-    for (int i = threadIdx.x; i < r * 16; i += 256)
-        s.part[(size_t)blockIdx.x * r * 16 + i] = ((red[i] + red[KC * 512 + i]) + red[2 * KC * 512 + i]) + red[3 * KC * 512 + i];
+    decode_items<false, KC, true, 1, ANY, DECODE, bf16_t, NARROW>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, s.V, pg, RowMap(),
+                                                                  (long)blockIdx.x * 4 + wave, (long)s.nb * 4, s.items(), sT_all[wave],
+                                                                  slab_all[wave], oacc, lane, s.turned, s.lw, s.lay);
+    write_partial<KC>(oacc, reinterpret_cast<float *>(&slab_all[0][0]), s.part, r, wave, lane);
+}
+
+// decode of a matrix of 8 to 32 tile columns
+template <bool GELU, int KC, bool ANY>
+__global__ __launch_bounds__(256) void decode_narrow_kernel(DecodeSide s, int r, int pg)
+{
+    __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    f32x4_t none[4];
+    decode_items<GELU, KC, false, 1, ANY, true, bf16_t, true>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, nullptr, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                              (long)gridDim.x * 4, s.items(), nullptr, slab_all[wave], none, lane, false, s.lw,
+                                                              s.lay);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -677,6 +687,19 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
     if ((dtype == 0 || !basis_f32) && tile_per_thread(dtype, true, R, Cc, r))
         return dtype == 0 ? launch_decode_tiles<float>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm)
                           : launch_decode_tiles<bf16_t>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm);
+    if (dtype == 1 && !basis_f32 && narrow_log2(dtype, Cc, rm.Mt == 0)) {
+        DecodeSide d;
+        if (!d.set({P, Dm, Cmat, R, Cc, false, nullptr, nullptr}, r, pg, true)) return hipErrorInvalidValue;
+        const long blocks = (d.items() + 3) / 4;
+        auto pick = [&](auto kc) {
+            constexpr int KC = decltype(kc)::value;
+            return Cc % 8 ? (gelu ? decode_narrow_kernel<true, KC, true> : decode_narrow_kernel<false, KC, true>)
+                          : (gelu ? decode_narrow_kernel<true, KC, false> : decode_narrow_kernel<false, KC, false>);
+        };
+        auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
+        hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks)), dim3(256), 0, s, d, r, pg);
+        return hipGetLastError();
+    }
     if (dtype == 1 && Cc >= 8 && !basis_f32) {
         const int chunks = (Cc + 63) / 64;
         const long items = (long)R * chunks;
@@ -754,20 +777,45 @@ hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const
 // 900 x 200 x 200, r = 32 (900) 262 / 258, but 250 x 256 x 256, r = 64 (250) 178 / 184.
 static bool small_gradient(int nb, int r) { return nb < 1024 && (r <= 32 || nb <= 192); }
 
-hipError_t launch_decode_outer_pair(const TileSide *t, int r, int pg, hipStream_t st)
+// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns (its matrix may be NULL: the basis gradient alone)
+static hipError_t launch_decode_outer_sides(const TileSide *t, int n, int r, int pg, hipStream_t st)
 {
-    DecodeSide s[2];
+    DecodeSide s[2] = {};
+    bool any = false, narrow = false;
     int nb = 1;
-    for (int i = 0; i < 2; ++i) {
-        s[i] = {(const bf16_t *)t[i].planes, (const bf16_t *)t[i].basis, (const bf16_t *)t[i].V, (bf16_t *)t[i].matrix, t[i].part, t[i].R, t[i].Cc,
-                (t[i].Cc + 63) / 64, decode_outer_blocks(t[i].R, t[i].Cc), t[i].turned};
+    for (int i = 0; i < n; ++i) {
+        any = any || t[i].Cc % 8;
+        narrow = narrow || narrow_log2(1, t[i].Cc, true);
+    }
+    for (int i = 0; i < n; ++i) {
+        if (!s[i].set(t[i], r, pg, narrow)) return hipErrorInvalidValue;
         nb = s[i].nb > nb ? s[i].nb : nb;
     }
-    const bool any = s[0].Cc % 8 || s[1].Cc % 8;
-    auto kern = r <= 32 ? (any ? decode_outer_pair_kernel<1, true> : decode_outer_pair_kernel<1, false>)
-                        : (any ? decode_outer_pair_kernel<2, true> : decode_outer_pair_kernel<2, false>);
-    hipLaunchKernelGGL(kern, dim3(nb, 2), dim3(256), 0, st, s[0], s[1], r, pg);
+    auto pick = [&](auto kc) {
+        constexpr int KC = decltype(kc)::value;
+        if (!t[0].matrix) return any ? decode_outer_pair_kernel<KC, true, true, false> : decode_outer_pair_kernel<KC, false, true, false>;
+        return narrow ? (any ? decode_outer_pair_kernel<KC, true, true, true> : decode_outer_pair_kernel<KC, false, true, true>)
+                      : (any ? decode_outer_pair_kernel<KC, true, false, true> : decode_outer_pair_kernel<KC, false, false, true>);
+    };
+    auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
+    hipLaunchKernelGGL(kern, dim3(nb, n), dim3(256), 0, st, s[0], s[1], r, pg);
     return hipGetLastError();
+}
+
+hipError_t launch_decode_outer_pair(const TileSide *t, int r, int pg, hipStream_t st) { return launch_decode_outer_sides(t, 2, r, pg, st); }
+
+int narrow_log2(int dtype, int Cc, bool plain_rows)
+{
+    if (dtype != 1 || !plain_rows || Cc < 8 || Cc > 32) return 0;
+    return Cc <= 8 ? 3 : Cc <= 16 ? 4 : 5;
+}
+
+int gradient_blocks(int dtype, int R, int Cc, bool plain_rows)
+{
+    const int lw = narrow_log2(dtype, Cc, plain_rows);
+    if (!lw) return decode_outer_blocks(R, Cc);
+    const int rows = 64 >> lw, blocks = ((R + rows - 1) / rows + 3) / 4;
+    return blocks > 1024 ? 1024 : blocks;
 }
 
 // Cmat == nullptr: the basis gradient alone
@@ -777,9 +825,12 @@ hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *C
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);
     if (R <= 0) return hipErrorInvalidValue;
-    const int nb = decode_outer_blocks(R, Cc);
+    const int nb = gradient_blocks(dtype, R, Cc, rm.Mt == 0);
     hipError_t e;
-    if (dtype == 1 && Cc >= 8) {
+    if (narrow_log2(dtype, Cc, rm.Mt == 0)) {
+        const TileSide one{P, Dm, Cmat, R, Cc, false, V, part};
+        e = launch_decode_outer_sides(&one, 1, r, pg, s);
+    } else if (dtype == 1 && Cc >= 8) {
         auto kern = Cc % 8 ? pick_decode_outer<true>(r, Cmat) : pick_decode_outer<false>(r, Cmat);
         hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, (const bf16_t *)P, (const bf16_t *)Dm, (bf16_t *)Cmat, R, Cc, r, (Cc + 63) / 64,
                            (const bf16_t *)V, part, pg, rm);
@@ -804,7 +855,7 @@ hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P,
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);
     if (R <= 0) return hipErrorInvalidValue;
-    const int nb = encode_outer_blocks(R, Cc);
+    const int nb = gradient_blocks(dtype, R, Cc, rm.Mt == 0);
     hipError_t e;
     if (dtype == 1 && Cc >= 8) {
         e = launch_encode_outer_lines(A, E, P, Qp, part, R, Cc, r, pg, nb, s, rm);
