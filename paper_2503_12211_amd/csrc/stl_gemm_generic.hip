@@ -263,6 +263,7 @@ GemmPath plane_gemm_path(int dtype, const GemmDesc &g)
 
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
+    if (dtype == 1 && plane_gemm_rows_eligible(g)) return launch_plane_gemm_rows(g, A, B, Out, s);
     switch (plane_gemm_path(dtype, g)) {
         case GemmPath::wide: return launch_plane_gemm_wide(g, A, B, Out, s);
         case GemmPath::pipe: return launch_plane_gemm_pipe(g, A, B, Out, s);

@@ -220,6 +220,9 @@ hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A
 bool plane_gemm_mfma_eligible(const GemmDesc &g);
 int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes (thin products: 64 x 64 whatever this says)
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
+// bf16 products of up to 32 rows, any number of them (stl_gemm_rows.hip): taken before the path that plane_gemm_path names
+bool plane_gemm_rows_eligible(const GemmDesc &g);
+hipError_t launch_plane_gemm_rows(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 // bf16 MFMA path with LDS-DMA loads and a multi-stage LDS ring (contiguous dimensions a multiple of 8)
 enum class PipeBlock { b256, b128x256, b128, b64 };
 PipeBlock pipe_block(const GemmDesc &g);      // block of a plane that it takes
