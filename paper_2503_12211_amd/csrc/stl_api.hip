@@ -680,8 +680,9 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
                                          stl::RowMap(), !pair),
                 "backward/dX + dE_X");
         if (pair) {
-            const stl::OuterSum sums[2] = {{part, dD, stl::gradient_blocks(dt, d.M, d.N, true), false}, {part2, dE_X, stl::gradient_blocks(dt, d.M, d.K, true), false}};
-            STL_HIP(stl::launch_outer_finals(sums, 2, d.r * 16, accumulate, s), "backward/dD and dE_X sums");
+            const stl::OuterSum sums[2] = {{part, dD, stl::gradient_blocks(dt, d.M, d.N, true), false, accumulate},
+                                           {part2, dE_X, stl::gradient_blocks(dt, d.M, d.K, true), false, accumulate}};
+            STL_HIP(stl::launch_outer_finals(sums, 2, d.r * 16, s), "backward/dD and dE_X sums");
         }
     } else if (dX) {
         STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s), "backward/decode dX");
@@ -852,10 +853,10 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
                 "aa_backward/dBhat");
         const stl::TileSide sides[2] = {{dahat, E_A, dA, RA, d.K, false, A, part_a}, {dbhat, E_B, dB, RB, CB, bt, B, part_b}};
         STL_HIP(stl::launch_decode_outer_pair(sides, d.r, PG, s), "aa_backward/dA + dE_A and dB + dE_B");
-        const stl::OuterSum sums[3] = {{part_d, dD, stl::gradient_blocks(dt, RA, d.N, true), false},
-                                       {part_a, dE_A, stl::gradient_blocks(dt, RA, d.K, true), false},
-                                       {part_b, dE_B, stl::gradient_blocks(dt, RB, CB, true), bt}};
-        STL_HIP(stl::launch_outer_finals(sums, 3, d.r * 16, accumulate, s), "aa_backward/dD, dE_A and dE_B sums");
+        const stl::OuterSum sums[3] = {{part_d, dD, stl::gradient_blocks(dt, RA, d.N, true), false, accumulate},
+                                       {part_a, dE_A, stl::gradient_blocks(dt, RA, d.K, true), false, accumulate},
+                                       {part_b, dE_B, stl::gradient_blocks(dt, RB, CB, true), bt, accumulate}};
+        STL_HIP(stl::launch_outer_finals(sums, 3, d.r * 16, s), "aa_backward/dD, dE_A and dE_B sums");
         return STL_OK;
     }
     const void *e_b = E_B;                       // the basis that encodes B as it lies
@@ -957,9 +958,14 @@ stl_status_t stl_ragged_forward(const stl_problem_t *prob, int64_t rows, const v
         STL_HIP(stl::launch_decode(dt, yhat, D, C, d.M, d.N, d.r, false, PG, s), "ragged_forward/decode");
         return STL_OK;
     }
-    STL_HIP(stl::launch_fold_decoder(dt, D, fold, dprime, d.r, g.nrho, s), "ragged_forward/compose fold");
+    const stl::Fold fd{fold, g.nrho};
     STL_HIP(stl::launch_decode(dt, yhat, D, C, d.M, d.N, d.r, false, PG, s, g.map(1)), "ragged_forward/decode");
-    STL_HIP(stl::launch_decode(dt, yhat, dprime, C, d.M, d.N, d.r, false, PG, s, g.map(2), true), "ragged_forward/decode + fold");
+    if (dt == STL_BF16) {
+        STL_HIP(stl::launch_decode(dt, yhat, D, C, d.M, d.N, d.r, false, PG, s, g.map(2), fd), "ragged_forward/decode + fold");
+    } else {
+        STL_HIP(stl::launch_fold_decoder(D, fd, dprime, d.r, s), "ragged_forward/compose fold");
+        STL_HIP(stl::launch_decode(dt, yhat, dprime, C, d.M, d.N, d.r, false, PG, s, g.map(2)), "ragged_forward/decode + fold");
+    }
     return STL_OK;
 }
 
@@ -998,21 +1004,37 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
         yhat = base + w.yhat;
     }
     // dYhat and dD from the complete tile rows (all of them when nothing is ragged) ...
-    const stl::RowMap body = g.map(1);
-    if (dD)
+    const stl::RowMap body = g.map(1), tail = g.map(2);
+    const stl::Fold fd{fold, g.nrho};
+    // With everything saved and both basis gradients asked for (bf16), the last tile rows take one pass over dC and the three sums one
+    // launch at the end.  Nothing is recomputed then, so that the workspace's areas for the planes are free for partial sums: 64 r bytes per
+    // four items, 2 r per tile from 8 tile columns on.  64 images of 197 tokens, 768 -> 3072, r = 32, forward and backward: sixteen
+    // launches -> eleven, 362.8 -> 355.8 us; a smaller call, 120 -> 111.
+    const bool paired = dt == STL_BF16 && g.nrho && d.K >= 8 && d.N >= 8 && Xhat_saved && Yhat_saved && dD && dE_X;
+    float *part_x = paired ? (float *)(base + w.xhat) : part, *part_t = (float *)(base + w.yhat);
+    const int tail_blocks = g.nrho ? stl::gradient_blocks(dt, tail.count(d.M), d.N, false) : 0;
+    if (paired) {
+        STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, body, false), "ragged_backward/dYhat + dD");
+        STL_HIP(stl::launch_fold_encode_outer(dC, D, fd, dyhat, yhat, part_t, d.M, d.N, d.r, PG, s, tail), "ragged_backward/last tile rows");
+    } else if (dD)
         STL_HIP(stl::launch_encode_outer(dt, dC, D, dyhat, yhat, dD, part, d.M, d.N, d.r, accumulate, PG, s, body), "ragged_backward/dYhat + dD");
     else
         STL_HIP(stl::launch_encode(dt, dC, D, dyhat, d.M, d.N, d.r, PG, s, body), "ragged_backward/encode dC");
-    if (g.nrho) {
+    if (g.nrho && !paired) {
         // ... and from each image's last tile row through the fold: its adjoint is an encode with the composed decoder;
         // one product Yhat (x) dC over those tile rows feeds both dD and dfold
-        const stl::RowMap tail = g.map(2);
-        STL_HIP(stl::launch_fold_decoder(dt, D, fold, dprime, d.r, g.nrho, s), "ragged_backward/compose fold");
-        STL_HIP(stl::launch_encode(dt, dC, dprime, dyhat, d.M, d.N, d.r, PG, s, tail, true), "ragged_backward/encode folded dC");
-        if (dD || want_fold) {
-            STL_HIP(stl::launch_decode_outer(dt, yhat, nullptr, nullptr, dC, gtail, part, d.M, d.N, d.r, 0, PG, s, tail), "ragged_backward/last tile rows");
-            STL_HIP(stl::launch_fold_grads(dt, gtail, D, fold, dD, dfold, d.r, g.nrho, accumulate, s), "ragged_backward/dD + dfold");
+        if (dt == STL_BF16 && need_yhat) {
+            STL_HIP(stl::launch_fold_encode_outer(dC, D, fd, dyhat, yhat, part, d.M, d.N, d.r, PG, s, tail), "ragged_backward/last tile rows");
+            STL_HIP(stl::launch_outer_final(part, gtail, tail_blocks, d.r * 16, 0, s), "ragged_backward/last tile rows' sums");
+        } else if (dt == STL_BF16) {
+            STL_HIP(stl::launch_encode(dt, dC, D, dyhat, d.M, d.N, d.r, PG, s, tail, fd), "ragged_backward/encode folded dC");
+        } else {
+            STL_HIP(stl::launch_fold_decoder(D, fd, dprime, d.r, s), "ragged_backward/compose fold");
+            STL_HIP(stl::launch_encode(dt, dC, dprime, dyhat, d.M, d.N, d.r, PG, s, tail), "ragged_backward/encode folded dC");
+            if (need_yhat)
+                STL_HIP(stl::launch_decode_outer(dt, yhat, nullptr, nullptr, dC, gtail, part, d.M, d.N, d.r, 0, PG, s, tail), "ragged_backward/last tile rows");
         }
+        if (need_yhat) STL_HIP(stl::launch_fold_grads(dt, gtail, D, fold, dD, dfold, d.r, g.nrho, accumulate, s), "ragged_backward/dD + dfold");
     }
     if (dX || dE_X) {
         stl::GemmDesc gd{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG};
@@ -1025,9 +1047,16 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
     // gradients of null rows are dropped (never written); null rows of X count as zeros in dE_X
     const stl::RowMap all = g.map(0);
     if (dE_X)
-        STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, part, d.M, d.K, d.r, accumulate, PG, s, all), "ragged_backward/dX + dE_X");
+        STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, part_x, d.M, d.K, d.r, accumulate, PG, s, all, !paired), "ragged_backward/dX + dE_X");
     else if (dX)
         STL_HIP(stl::launch_decode(dt, dxhat, E_X, dX, d.M, d.K, d.r, false, PG, s, all), "ragged_backward/decode dX");
+    if (paired) {
+        const stl::OuterSum sums[3] = {{part, dD, stl::gradient_blocks(dt, body.count(d.M), d.N, false), false, accumulate},
+                                       {part_t, gtail, tail_blocks, false, 0},
+                                       {part_x, dE_X, stl::gradient_blocks(dt, all.count(d.M), d.K, false), false, accumulate}};
+        STL_HIP(stl::launch_outer_finals(sums, 3, d.r * 16, s), "ragged_backward/sums");
+        STL_HIP(stl::launch_fold_grads(dt, gtail, D, fold, dD, dfold, d.r, g.nrho, accumulate, s), "ragged_backward/dD + dfold");
+    }
     return STL_OK;
 }
 

@@ -63,14 +63,21 @@ struct RowMap {
     }
 };
 
+// Fold of an image's last tile row (row counts not divisible by 4): nrho real rows, each a combination (nrho x 4 coefficients) of the
+// four rows that its planes decode to; coef == NULL: none
+struct Fold {
+    const float *coef = nullptr;
+    int nrho = 0;
+};
+
 // planes P[p][R][Cc] <- encoder E (r x 16) applied to every 4x4 tile of A (4R x 4Cc)
 // rm: which matrix rows lie behind the tile rows, and which tile rows the launch walks over (R always counts ALL tile
-// rows of the plane tensor); basis_f32: E (or Dm) is stored as fp32 whatever the dtype
+// rows of the plane tensor); fold (bf16): E (or Dm) is composed with it
 hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s,
-                         RowMap rm = RowMap(), bool basis_f32 = false);
+                         RowMap rm = RowMap(), Fold fold = Fold());
 // matrix Cmat (4R x 4Cc) <- decoder Dm^T (r x 16 stored) applied to planes P[p][R][Cc]
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R, int Cc, int r, bool gelu, int pg,
-                         hipStream_t s, RowMap rm = RowMap(), bool basis_f32 = false);
+                         hipStream_t s, RowMap rm = RowMap(), Fold fold = Fold());
 
 // whether a plain encode or decode of R x Cc tiles goes one tile per thread (fp32 arithmetic)
 bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r);
@@ -97,8 +104,9 @@ struct OuterSum {
     float *G;
     int nb;
     bool turned;
+    int accumulate;
 };
-hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, int accumulate, hipStream_t s);
+hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, hipStream_t s);
 
 // encode and basis gradient in one pass over the matrix: P <- encode(A, E), G (+)= Qp . tileview(A);
 // `part` holds encode_outer_blocks(R, Cc) * r * 16 floats (gradient_blocks of them are used)
@@ -124,7 +132,9 @@ hipError_t launch_decode_outer_pair(const TileSide *s, int r, int pg, hipStream_
 
 // fold of an image's last tile row (row counts not divisible by 4): composed decoder Dp (r x 16 fp32) from Dm and the
 // nrho x 4 fold coefficients; and the gradients that come from those tile rows, given Gt = Yhat (x) dC over them
-hipError_t launch_fold_decoder(int dtype, const void *Dm, const float *fold, float *Dp, int r, int nrho, hipStream_t s);
+hipError_t launch_fold_decoder(const void *Dm, Fold fold, float *Dp, int r, hipStream_t s);        // fp32 storage; bf16 maps compose it themselves
+hipError_t launch_fold_encode_outer(const void *A, const void *Dm, Fold fold, void *P, const void *Qp, float *part, int R_all, int Cc, int r,
+                                    int pg, hipStream_t s, RowMap rm);
 hipError_t launch_fold_grads(int dtype, const float *Gt, const void *Dm, const float *fold, float *dD, float *dfold, int r,
                              int nrho, int accumulate, hipStream_t s);
 

@@ -9,6 +9,19 @@
 
 namespace stl {
 
+// Entry i = (p, rho, c) of the decoder of an image's last tile row: its real row rho is the fold of the four decoded ones.  Composed by
+// each workgroup that needs it: as a launch of its own it took 4.6 us, each way.
+template <typename T>
+__device__ __forceinline__ float fold_entry(const T *__restrict__ Dm, const Fold &fold, int i)
+{
+    const int p = i >> 4, rho = (i >> 2) & 3, c = i & 3;
+    float s = 0.f;
+    if (rho < fold.nrho)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) s = fmaf(fold.coef[rho * 4 + a], Elem<T>::ld(Dm + p * 16 + 4 * a + c), s);
+    return s;
+}
+
 // ---------------------------------------------------------------------------------------
 // The tile maps in fp32 arithmetic on the vector ALUs, for fp32 storage (plain encodes and decodes of large matrices: one tile
 // per thread, below), for bf16 rows of fewer than 8 tiles and for bases kept in fp32 (the folded decoder):
@@ -25,15 +38,15 @@ namespace stl {
 // OUTER blocks leave one partial each, added up in block order by outer_final_kernel: no floating-point atomics, so the
 // results are bitwise reproducible.
 // ---------------------------------------------------------------------------------------
-// T: storage type; TB: type the basis is stored in (the storage type, or fp32 for a basis composed on the device).
+// T: storage type; FOLD: the basis is B composed with the fold of an image's last tile row (see fold_entry).
 // R counts the tile rows this launch walks over (see RowMap).
 constexpr int kTilePitch = 64 + 4;          // floats per LDS row of 64 tiles
 
-template <typename T, typename TB, bool ENC, bool DEC, bool OUTER, bool GELU, int GROUPS>
+template <typename T, bool FOLD, bool ENC, bool DEC, bool OUTER, bool GELU, int GROUPS>
 __global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restrict__ V, const T *__restrict__ Pin,
-                                                                const TB *__restrict__ B, T *__restrict__ Pout,
+                                                                const T *__restrict__ B, T *__restrict__ Pout,
                                                                 T *__restrict__ Cmat, float *__restrict__ part, int R, int Cc, int r,
-                                                                int lw, int pg, RowMap rm)
+                                                                int lw, int pg, RowMap rm, Fold fold)
 {
     constexpr bool PLANES = DEC || OUTER, TILES = ENC || OUTER;
     constexpr int TP = kTilePitch;
@@ -44,7 +57,7 @@ __global__ __launch_bounds__(GROUPS * 256) void tile_map_kernel(const T *__restr
     float *sP = sB + r * 16 + grp * ((PLANES ? ng * 16 * TP : 0) + (TILES ? 16 * TP : 0));     // [p][tile]
     float *sX = sP + (PLANES ? ng * 16 * TP : 0);            // [q][tile]
     if (ENC || DEC)
-        for (int i = threadIdx.x; i < r * 16; i += GROUPS * 256) sB[i] = Elem<TB>::ld(B + i);
+        for (int i = threadIdx.x; i < r * 16; i += GROUPS * 256) sB[i] = FOLD ? fold_entry(B, fold, i) : Elem<T>::ld(B + i);
 
     const int W = 1 << lw, rows = 64 >> lw, chunks = (Cc + W - 1) >> lw;
     const long items = (long)((R + rows - 1) / rows) * chunks;
@@ -370,7 +383,7 @@ struct OuterSums {
     OuterSum s[3];
 };
 
-__global__ __launch_bounds__(1024) void outer_final_kernel(OuterSums sums, int n_out, int accumulate)
+__global__ __launch_bounds__(1024) void outer_final_kernel(OuterSums sums, int n_out)
 {
     const OuterSum m = blockIdx.y == 0 ? sums.s[0] : blockIdx.y == 1 ? sums.s[1] : sums.s[2];
     const float *part = m.part;
@@ -392,7 +405,7 @@ __global__ __launch_bounds__(1024) void outer_final_kernel(OuterSums sums, int n
 #pragma unroll
         for (int u = 0; u < 64; ++u) tot += red[u][o];
         const int to = m.turned ? (i & ~15) + 4 * (i & 3) + ((i >> 2) & 3) : i;
-        G[to] = accumulate ? G[to] + tot : tot;
+        G[to] = m.accumulate ? G[to] + tot : tot;
     }
 }
 
@@ -494,18 +507,9 @@ __global__ __launch_bounds__(256) void decode_narrow_kernel(DecodeSide s, int r,
 //     Dp[p][4 rho + c] = sum_a fold[rho][a] Dm[p][4a + c]      (zero for rho >= nrho),
 // and its adjoint an encode with the same Dp.  Dp is kept in fp32.
 // ---------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void fold_decoder_kernel(const T *__restrict__ Dm, const float *__restrict__ fold,
-                                                           float *__restrict__ Dp, int r, int nrho)
+__global__ __launch_bounds__(256) void fold_decoder_kernel(const float *__restrict__ Dm, Fold fold, float *__restrict__ Dp, int r)
 {
-    for (int i = threadIdx.x; i < r * 16; i += 256) {
-        const int p = i >> 4, rho = (i >> 2) & 3, c = i & 3;
-        float s = 0.f;
-        if (rho < nrho)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) s = fmaf(fold[rho * 4 + a], Elem<T>::ld(Dm + p * 16 + 4 * a + c), s);
-        Dp[i] = s;
-    }
+    for (int i = threadIdx.x; i < r * 16; i += 256) Dp[i] = fold_entry(Dm, fold, i);
 }
 
 // Gt[p][4 rho + c] = sum over the images' last tile rows of Yhat[p] * dC[rho][c] (rows rho >= nrho are zero) gives both
@@ -533,10 +537,9 @@ __global__ __launch_bounds__(256) void fold_grads_kernel(const float *__restrict
     }
 }
 
-hipError_t launch_fold_decoder(int dtype, const void *Dm, const float *fold, float *Dp, int r, int nrho, hipStream_t s)
+hipError_t launch_fold_decoder(const void *Dm, Fold fold, float *Dp, int r, hipStream_t s)
 {
-    if (dtype == 0) hipLaunchKernelGGL(fold_decoder_kernel<float>, dim3(1), dim3(256), 0, s, (const float *)Dm, fold, Dp, r, nrho);
-    else hipLaunchKernelGGL(fold_decoder_kernel<bf16_t>, dim3(1), dim3(256), 0, s, (const bf16_t *)Dm, fold, Dp, r, nrho);
+    hipLaunchKernelGGL(fold_decoder_kernel, dim3(1), dim3(256), 0, s, (const float *)Dm, fold, Dp, r);
     return hipGetLastError();
 }
 
@@ -610,12 +613,12 @@ static int tile_item_log2(int Cc)
 }
 
 // blocks > 0: exactly that many (one partial each); 0: as many as there are items, up to 8192
-template <typename T, typename TB, bool ENC, bool DEC, bool OUTER, bool GELU>
+template <typename T, bool FOLD, bool ENC, bool DEC, bool OUTER, bool GELU>
 static hipError_t launch_tile_map(const void *V, const void *Pin, const void *B, void *Pout, void *Cmat, float *part, int R, int Cc,
-                                  int r, int pg, const RowMap &rm, int blocks, hipStream_t s)
+                                  int r, int pg, const RowMap &rm, int blocks, hipStream_t s, Fold fold = Fold())
 {
     constexpr int GROUPS = OUTER ? 4 : 1;                   // a partial per four groups, as many blocks as the workspace has room for
-    auto kern = tile_map_kernel<T, TB, ENC, DEC, OUTER, GELU, GROUPS>;
+    auto kern = tile_map_kernel<T, FOLD, ENC, DEC, OUTER, GELU, GROUPS>;
     constexpr int most = 64 * 16 * 4 + GROUPS * (64 + 16) * kTilePitch * 4;
     static_assert(most <= 160 * 1024, "LDS budget");
     const int ng = (r + 15) / 16, lw = tile_item_log2(Cc), rows = 64 >> lw;
@@ -624,8 +627,8 @@ static hipError_t launch_tile_map(const void *V, const void *Pin, const void *B,
     if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, most, granted); e != hipSuccess) return e;
     const long items = (long)((R + rows - 1) / rows) * ((Cc + (1 << lw) - 1) >> lw);
     if (blocks <= 0) blocks = (int)(items > 8192 ? 8192 : items);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(GROUPS * 256), smem, s, (const T *)V, (const T *)Pin, (const TB *)B, (T *)Pout,
-                       (T *)Cmat, part, R, Cc, r, lw, pg, rm);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(GROUPS * 256), smem, s, (const T *)V, (const T *)Pin, (const T *)B, (T *)Pout,
+                       (T *)Cmat, part, R, Cc, r, lw, pg, rm, fold);
     return hipGetLastError();
 }
 
@@ -644,21 +647,21 @@ static hipError_t launch_tile_grad(const void *V, const void *Pin, const void *B
 }
 
 hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s,
-                         RowMap rm, bool basis_f32)
+                         RowMap rm, Fold fold)
 {
     if (pg <= 0) pg = R;
     const int Rs = rm.count(R);                             // tile rows this launch walks over
     if (Rs <= 0) return hipSuccess;
-    if (dtype == 1 && Cc >= 8 && !basis_f32) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
+    if (dtype == 1 && Cc >= 8 && !fold.coef) return launch_encode_lines(A, E, P, R, Cc, r, pg, s, rm);
     if (tile_per_thread(dtype, false, Rs, Cc, r)) {
         const TileGrid t(Rs, Cc);
         hipLaunchKernelGGL(encode_tiles_kernel, t.grid, t.block, 0, s, (const float *)A, (const float *)E, (float *)P, Rs, Cc, r, pg, rm);
         return hipGetLastError();
     }
-    auto run = dtype == 0     ? launch_tile_map<float, float, true, false, false, false>
-               : basis_f32 ? launch_tile_map<bf16_t, float, true, false, false, false>
-                           : launch_tile_map<bf16_t, bf16_t, true, false, false, false>;
-    return run(A, nullptr, E, P, nullptr, nullptr, Rs, Cc, r, pg, rm, 0, s);
+    auto run = dtype == 0     ? launch_tile_map<float, false, true, false, false, false>
+               : fold.coef ? launch_tile_map<bf16_t, true, true, false, false, false>
+                           : launch_tile_map<bf16_t, false, true, false, false, false>;
+    return run(A, nullptr, E, P, nullptr, nullptr, Rs, Cc, r, pg, rm, 0, s, fold);
 }
 
 template <typename T>
@@ -679,15 +682,15 @@ static auto pick_decode(int r, bool gelu)
 }
 
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R_all, int Cc, int r, bool gelu, int pg,
-                         hipStream_t s, RowMap rm, bool basis_f32)
+                         hipStream_t s, RowMap rm, Fold fold)
 {
     if (pg <= 0) pg = R_all;
     const int R = rm.count(R_all);                          // tile rows this launch walks over
     if (R <= 0) return hipSuccess;
-    if ((dtype == 0 || !basis_f32) && tile_per_thread(dtype, true, R, Cc, r))
+    if ((dtype == 0 || !fold.coef) && tile_per_thread(dtype, true, R, Cc, r))
         return dtype == 0 ? launch_decode_tiles<float>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm)
                           : launch_decode_tiles<bf16_t>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm);
-    if (dtype == 1 && !basis_f32 && narrow_log2(dtype, Cc, rm.Mt == 0)) {
+    if (dtype == 1 && !fold.coef && narrow_log2(dtype, Cc, rm.Mt == 0)) {
         DecodeSide d;
         if (!d.set({P, Dm, Cmat, R, Cc, false, nullptr, nullptr}, r, pg, true)) return hipErrorInvalidValue;
         const long blocks = (d.items() + 3) / 4;
@@ -700,7 +703,7 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
         hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks)), dim3(256), 0, s, d, r, pg);
         return hipGetLastError();
     }
-    if (dtype == 1 && Cc >= 8 && !basis_f32) {
+    if (dtype == 1 && Cc >= 8 && !fold.coef) {
         const int chunks = (Cc + 63) / 64;
         const long items = (long)R * chunks;
         long blocks = (items + 3) / 4;
@@ -710,24 +713,24 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
                            r, chunks, (const bf16_t *)nullptr, (float *)nullptr, pg, rm);
         return hipGetLastError();
     }
-    auto run = dtype == 0     ? (gelu ? launch_tile_map<float, float, false, true, false, true> : launch_tile_map<float, float, false, true, false, false>)
-               : basis_f32 ? (gelu ? launch_tile_map<bf16_t, float, false, true, false, true> : launch_tile_map<bf16_t, float, false, true, false, false>)
-                           : (gelu ? launch_tile_map<bf16_t, bf16_t, false, true, false, true> : launch_tile_map<bf16_t, bf16_t, false, true, false, false>);
-    return run(nullptr, P, Dm, nullptr, Cmat, nullptr, R, Cc, r, pg, rm, 0, s);
+    auto run = dtype == 0     ? (gelu ? launch_tile_map<float, false, false, true, false, true> : launch_tile_map<float, false, false, true, false, false>)
+               : fold.coef ? (gelu ? launch_tile_map<bf16_t, true, false, true, false, true> : launch_tile_map<bf16_t, true, false, true, false, false>)
+                           : (gelu ? launch_tile_map<bf16_t, false, false, true, false, true> : launch_tile_map<bf16_t, false, false, true, false, false>);
+    return run(nullptr, P, Dm, nullptr, Cmat, nullptr, R, Cc, r, pg, rm, 0, s, fold);
 }
 
-hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, int accumulate, hipStream_t s)
+hipError_t launch_outer_finals(const OuterSum *sums, int n, int n_out, hipStream_t s)
 {
     OuterSums all{};
     for (int i = 0; i < n && i < 3; ++i) all.s[i] = sums[i];
-    hipLaunchKernelGGL(outer_final_kernel, dim3((n_out + 15) / 16, n), dim3(1024), 0, s, all, n_out, accumulate);
+    hipLaunchKernelGGL(outer_final_kernel, dim3((n_out + 15) / 16, n), dim3(1024), 0, s, all, n_out);
     return hipGetLastError();
 }
 
 hipError_t launch_outer_final(const float *part, float *G, int nb, int n_out, int accumulate, hipStream_t s)
 {
-    const OuterSum one{part, G, nb, false};
-    return launch_outer_finals(&one, 1, n_out, accumulate, s);
+    const OuterSum one{part, G, nb, false, accumulate};
+    return launch_outer_finals(&one, 1, n_out, s);
 }
 
 int decode_outer_blocks(int R, int Cc)
@@ -841,12 +844,23 @@ hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *C
                      : launch_tile_grad<false, false>(V, P, Dm, nullptr, nullptr, part, R, R_all, Cc, r, pg, rm, nb, s);
             return e != hipSuccess || !final_sum ? e : launch_outer_final(part, G, nb, r * 16, accumulate, s);
         }
-        auto run = dtype == 0 ? (Cmat ? launch_tile_map<float, float, false, true, true, false> : launch_tile_map<float, float, false, false, true, false>)
-                              : (Cmat ? launch_tile_map<bf16_t, bf16_t, false, true, true, false> : launch_tile_map<bf16_t, bf16_t, false, false, true, false>);
-        e = run(V, P, Dm, nullptr, Cmat, part, R, Cc, r, pg, rm, nb, s);
+        auto run = dtype == 0 ? (Cmat ? launch_tile_map<float, false, false, true, true, false> : launch_tile_map<float, false, false, false, true, false>)
+                              : (Cmat ? launch_tile_map<bf16_t, false, false, true, true, false> : launch_tile_map<bf16_t, false, false, false, true, false>);
+        e = run(V, P, Dm, nullptr, Cmat, part, R, Cc, r, pg, rm, nb, s, Fold());
     }
     if (e != hipSuccess || !final_sum) return e;
     return launch_outer_final(part, G, nb, r * 16, accumulate, s);
+}
+
+// The last tile rows of a stack of ragged images (bf16) in one pass over dC: planes of the folded rows and the partials of Yhat (x) dC.
+// 64 images, 768 tile columns, r = 32: 5.8 us the planes and 4.9 the sums as launches of their own.
+hipError_t launch_fold_encode_outer(const void *A, const void *Dm, Fold fold, void *P, const void *Qp, float *part, int R_all, int Cc, int r,
+                                    int pg, hipStream_t s, RowMap rm)
+{
+    const int R = rm.count(R_all);
+    if (R <= 0) return hipErrorInvalidValue;
+    return launch_tile_map<bf16_t, true, true, false, true, false>(A, Qp, Dm, P, nullptr, part, R, Cc, r, pg, rm,
+                                                                   gradient_blocks(1, R, Cc, false), s, fold);
 }
 
 hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P, const void *Qp, float *G, float *part, int R_all, int Cc,
@@ -864,8 +878,8 @@ hipError_t launch_encode_outer(int dtype, const void *A, const void *E, void *P,
             e = launch_tile_grad<true, false>(A, Qp, E, P, nullptr, part, R, R_all, Cc, r, pg, rm, nb, s);
             return e != hipSuccess || !final_sum ? e : launch_outer_final(part, G, nb, r * 16, accumulate, s);
         }
-        auto run = dtype == 0 ? launch_tile_map<float, float, true, false, true, false> : launch_tile_map<bf16_t, bf16_t, true, false, true, false>;
-        e = run(A, Qp, E, P, nullptr, part, R, Cc, r, pg, rm, nb, s);
+        auto run = dtype == 0 ? launch_tile_map<float, false, true, false, true, false> : launch_tile_map<bf16_t, false, true, false, true, false>;
+        e = run(A, Qp, E, P, nullptr, part, R, Cc, r, pg, rm, nb, s, Fold());
     }
     if (e != hipSuccess || !final_sum) return e;
     return launch_outer_final(part, G, nb, r * 16, accumulate, s);

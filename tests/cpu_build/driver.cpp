@@ -126,10 +126,12 @@ int main(int argc, char **argv)
             float *g1 = (float *)exact(r * 64), *g2 = (float *)exact(r * 64), *g3 = (float *)exact(r * 64);
             CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, nullptr, nullptr, nullptr, dA, dB, g1, g2, g3, 0, exact(wb), wb, 0, nullptr));
             CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, Ah, Bh, Yh, dA, nullptr, nullptr, g2, nullptr, 1, exact(wb), wb, 0, nullptr));
+            CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, Ah, Bh, Yh, dA, dB, g1, g2, g3, 0, exact(wb), wb, 0, nullptr));
             // the second operand stored transposed: the same bytes read as (nb*n) x k
             void *Bt = exact(stl_plane_elems(nb * n / 4, k / 4, r) * es);
             CHECK(stl_aa_forward(&p, nb, A, B, Ea, Eb, D, C, Ah, Bt, Yh, exact(wf), wf, STL_FLAG_B_TRANSPOSED, nullptr));
             CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, nullptr, nullptr, nullptr, dA, dB, g1, g2, g3, 0, exact(wb), wb, STL_FLAG_B_TRANSPOSED, nullptr));
+            CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, Ah, Bt, Yh, dA, dB, g1, g2, g3, 1, exact(wb), wb, STL_FLAG_B_TRANSPOSED, nullptr));
             CHECK(stl_aa_backward(&p, nb, A, B, Ea, Eb, D, dC, Ah, Bt, Yh, nullptr, dB, nullptr, g2, nullptr, 1, exact(wb), wb, STL_FLAG_B_TRANSPOSED, nullptr));
         } else if (op == "ragged") {
             const long nimg = v[0], rows = v[1], k = v[2], n = v[3], m = nimg * rows;
@@ -145,6 +147,7 @@ int main(int argc, char **argv)
             CHECK(stl_ragged_forward(&p, rows, X, Wh, E, D, fold, C, Xh, Yh, exact(wf), wf, nullptr));
             float *dW = (float *)exact((size_t)r * (k / 4) * (n / 4) * 4), *g1 = (float *)exact(r * 64), *g2 = (float *)exact(r * 64);
             CHECK(stl_ragged_backward(&p, rows, X, Wh, E, D, fold, dC, nullptr, nullptr, dX, dW, g1, g2, df, 0, exact(wb), wb, nullptr));
+            CHECK(stl_ragged_backward(&p, rows, X, Wh, E, D, fold, dC, Xh, Yh, dX, dW, g1, g2, df, 1, exact(wb), wb, nullptr));
             CHECK(stl_ragged_backward(&p, rows, X, Wh, E, D, fold, dC, Xh, Yh, nullptr, nullptr, nullptr, nullptr, df, 1, exact(wb), wb, nullptr));
         } else {
             printf("unknown case %s\n", argv[a]);
