@@ -26,3 +26,11 @@ def test_few_rows(gu, M, K, N, r):
     C, Y = planes.forward(p["X"], p["What"], p["E_X"], p["D"], return_yhat=True)
     gu.check(got["Yhat"], Y, "bf16", "Yhat", slab=1)
     gu.check(got["C"], C, "bf16", "C")
+
+
+@pytest.mark.parametrize("M,K,N,r", [(16, 64, 72, 9), (5, 40, 264, 33), (16, 72, 64, 9)])
+def test_single_pair_of_activations(gu, M, K, N, r):
+    """A second operand in the grouped layout: one group of up to 64 tile rows is taken here, more are not."""
+    p = stl_synth.aa_problem(1, 4 * M, 4 * K, 4 * N, r, seed=1800 + M + K + N + r, dtype="bf16")
+    args = (p["A"], p["B"], p["E_A"], p["E_B"], p["D"])
+    gu.check(gu.aa_forward(*args, 1, "bf16"), planes.aa_forward(*args, nbatch=1), "bf16", "C")
