@@ -38,10 +38,9 @@ constexpr int SX_BYTES = 4 * BI * KC * 4 * 2;     // X sub-block: 128 rows x 64 
 constexpr int SD_BYTES = 32 * 16 * 4;             // decoder in fp32
 // per plane: Xhat stage 32 x 16 bf16 = 1 KB (encoded here: 32 bytes further apart, which spreads the planes of one write over the
 // banks), What stage 16 x 32 bf16 = 1 KB, exchanged accumulators 32 x 32 fp32 = 4 KB
-template <int RP, bool ENCODE>
+template <int RP, bool ENCODE, int NS>                                // NS: ring of stages (see block_forward_ring)
 struct Map {
-    static constexpr bool TWICE = ENCODE && RP <= 16;                 // two encoded stages (at 32 planes LDS holds one)
-    static constexpr int NS = RP == 8 ? 5 : RP == 32 ? 2 : ENCODE ? 3 : 4;     // ring of stages
+    static constexpr bool TWICE = ENCODE && RP <= 16 && NS > 2;       // two encoded stages (at 32 planes LDS holds one)
     static constexpr int PITCH = ENCODE ? 1024 + 32 : 1024;           // of a plane of Xhat
     static constexpr int A_STAGE = ENCODE ? SX_BYTES : RP * 1024, W_STAGE = RP * 1024;
     static constexpr int XH = NS * A_STAGE, XH_STAGE = ENCODE ? RP * PITCH : 0;
@@ -53,15 +52,15 @@ __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)"
 
 // ENCODE: true = FUSED (reads X), false = EPILOGUE (reads Xhat).  RP: planes padded to 8, 16 or 32 (sizes the LDS
 // stages and the accumulators; planes beyond r are zeros and cost less than leaving them out).
-template <int RP, bool ENCODE, bool GELU>
+template <int RP, bool ENCODE, bool GELU, int NS>
 __global__ __launch_bounds__(NW * 64) void stl_block_kernel(const bf16_t *__restrict__ Xin,   // X (m x k) or Xhat (r x M x K)
                                                         const bf16_t *__restrict__ What, const bf16_t *__restrict__ E,
                                                         const bf16_t *__restrict__ Dm, bf16_t *__restrict__ C,
                                                         bf16_t *__restrict__ Ysave, int M, int K, int N, int r,
                                                         int blocks_j, int pg)
 {
-    typedef Map<RP, ENCODE> L;
-    constexpr int PW = RP / NW, NS = L::NS, AW = ENCODE ? 2 : PW;      // planes, and DMA instructions of the A side, per wavefront
+    typedef Map<RP, ENCODE, NS> L;
+    constexpr int PW = RP / NW, AW = ENCODE ? 2 : PW;      // planes, and DMA instructions of the A side, per wavefront
     constexpr int LOADS = AW + PW;                                     // per wavefront and stage
     extern __shared__ __align__(16) char smem[];
     const char *sA = smem, *sW = smem + L::W;
@@ -266,21 +265,49 @@ bool block_forward_eligible(int dtype, int M, int K, int N, int r)
     return dtype == 1 && r >= 1 && r <= 32 && (K % fused::KC) == 0 && (N % 8) == 0 && N >= 8 && M >= 1;
 }
 
-template <int RP, bool ENCODE, bool GELU>
-static hipError_t launch_block_t(const void *Xin, const void *What, const void *E, const void *Dm, void *C, void *Ysave,
+// Stages of the ring, at RP = 8, 16 or 32 padded planes.  While every CU has at most one block, LDS holds as many as fit; beyond, two
+// where that gives a CU two blocks or more (all of it, at 9 to 16 planes with the encode and above 16, is one block's either
+// way).  us, deep ring / two stages: encode in the kernel, r = 8, 8192 x 64 -> 4096 (2048 blocks) 31.6 / 20.8, 4096 x 2048 -> 2048 (512)
+// 52.6 / 39.2, 4096 x 512 -> 1024 (256) 11.5 / 11.6; planes read, r = 8, 8192 x 64 -> 4096 34.3 / 18.7, r = 16 49.0 / 30.1;
+// encode in the kernel, r = 16, 4096 x 1024 -> 1152 (288) 36.4 / 44.0.
+constexpr int ring_stages(int RP, bool encode, bool shared)
+{
+    if (shared && (RP == 8 || (RP == 16 && !encode))) return 2;
+    return RP == 8 ? 5 : RP == 32 ? 2 : encode ? 3 : 4;
+}
+
+static long block_count(int M, int N) { return (long)((M + fused::BI - 1) / fused::BI) * ((N + fused::BJ - 1) / fused::BJ); }
+
+int block_forward_ring(bool encode, int M, int N, int r)
+{
+    return ring_stages(r <= 8 ? 8 : r <= 16 ? 16 : 32, encode, block_count(M, N) > pipe::cu_count());
+}
+
+template <int RP, bool ENCODE, bool GELU, int NS>
+static hipError_t launch_block_ring(const void *Xin, const void *What, const void *E, const void *Dm, void *C, void *Ysave,
                                  int M, int K, int N, int r, int pg, hipStream_t s)
 {
-    auto kern = fused::stl_block_kernel<RP, ENCODE, GELU>;
-    constexpr int smem = fused::Map<RP, ENCODE>::BYTES;
+    auto kern = fused::stl_block_kernel<RP, ENCODE, GELU, NS>;
+    constexpr int smem = fused::Map<RP, ENCODE, NS>::BYTES;
     static_assert(smem <= 160 * 1024, "LDS budget");
     static std::atomic<uint64_t> granted{0};               // of this instantiation
     if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted); e != hipSuccess) return e;
-    const int bi = (M + fused::BI - 1) / fused::BI, bj = (N + fused::BJ - 1) / fused::BJ;
-    const long total = (long)bi * bj;
+    const int bj = (N + fused::BJ - 1) / fused::BJ;
+    const long total = block_count(M, N);
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(fused::NW * 64), smem, s, (const bf16_t *)Xin, (const bf16_t *)What,
                        (const bf16_t *)E, (const bf16_t *)Dm, (bf16_t *)C, (bf16_t *)Ysave, M, K, N, r, bj, pg);
     return hipGetLastError();
+}
+
+template <int RP, bool ENCODE, bool GELU>
+static hipError_t launch_block_t(const void *Xin, const void *What, const void *E, const void *Dm, void *C, void *Ysave,
+                                 int M, int K, int N, int r, int pg, hipStream_t s)
+{
+    constexpr int ALONE = ring_stages(RP, ENCODE, false), SHARED = ring_stages(RP, ENCODE, true);
+    return block_forward_ring(ENCODE, M, N, r) == ALONE
+               ? launch_block_ring<RP, ENCODE, GELU, ALONE>(Xin, What, E, Dm, C, Ysave, M, K, N, r, pg, s)
+               : launch_block_ring<RP, ENCODE, GELU, SHARED>(Xin, What, E, Dm, C, Ysave, M, K, N, r, pg, s);
 }
 
 template <int RP>

@@ -254,6 +254,7 @@ hipError_t launch_plane_gemm_wide(const GemmDesc &g, const void *A, const void *
 // Forward on one output block with all planes resident (decode in the epilogue).  encode_in_kernel: Xin is X
 // (single-launch fused form); otherwise Xin is Xhat.  Ysave may be NULL.  bf16 storage only.
 bool block_forward_eligible(int dtype, int M, int K, int N, int r);
+int block_forward_ring(bool encode, int M, int N, int r);      // LDS stages that its kernel takes
 hipError_t launch_block_forward(bool encode_in_kernel, const void *Xin, const void *What, const void *E, const void *Dm,
                                 void *C, void *Ysave, int M, int K, int N, int r, bool gelu, int pg, hipStream_t s);
 

@@ -63,6 +63,17 @@ def test_wide_bf16_encodes_of_odd_widths_write_whole_lines(checker):  # noqa: F8
     checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "ragged:52:197:1000:32:64")
 
 
+def test_block_forward_shares_a_cu_where_there_are_more_blocks(checker):  # noqa: F811
+    """Up to a block per CU the ring of stages is as deep as LDS allows; beyond, two stages where several blocks then fit."""
+    cases = {"ring:1:1024:256:8": 5, "ring:1:1024:257:8": 2, "ring:1:2048:1024:3": 2, "ring:0:1024:256:8": 5, "ring:0:1025:256:8": 2,
+             "ring:0:1024:256:16": 4, "ring:0:2048:256:16": 2, "ring:1:1024:256:16": 3, "ring:1:2048:1024:16": 3, "ring:0:2048:256:17": 2,
+             "ring:1:64:64:32": 2}
+    _, text = checker(*cases)
+    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
+    # LDS and addresses of both rings, 256 and 288 blocks
+    checker(*(f"fwd:4096:128:{n}:{r}:{v}" for n in (1024, 1152) for r in (5, 13) for v in (2, 3)))
+
+
 def test_second_device_of_a_process(checker):  # noqa: F811
     """Dynamic LDS beyond 64 KB is granted per device and kernel: calls that ran on one device run on the next one too, and a kernel
     runs whether or not one of the same type ran before (the pipelined forward without and with GELU)."""

@@ -39,3 +39,18 @@ def test_automatic_choice(gu, M, K, N, r, single):
     p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=1200 + M + K, dtype="bf16")
     want = gu.forward(p, "bf16", flags=stl.STL_FLAG_FUSED if single else stl.STL_FLAG_UNFUSED)
     assert np.array_equal(gu.forward(p, "bf16", flags=stl.STL_FLAG_AUTO), want)
+
+
+@pytest.mark.parametrize("K,r", [(16, 8), (48, 3), (80, 16), (32, 9)])
+def test_more_blocks_than_cus(gu, K, r):
+    """288 blocks of 32 x 32 tiles, beyond one per CU: the oracle's values and, bit for bit, those of calls of 28 tile rows each, whose blocks
+    have a CU each and a deeper ring of stages."""
+    import paper_2503_12211_amd as stl
+    p = stl_synth.stl_problem(4 * 1020, 4 * K, 4 * 288, r, seed=1300 + K + r, dtype="bf16")
+    C = planes.forward(p["X"], p["What"], p["E_X"], p["D"])
+    for flag in (stl.STL_FLAG_FUSED, stl.STL_FLAG_EPILOGUE):
+        got = gu.forward(p, "bf16", flags=flag)
+        gu.check(got, C, "bf16", "C")
+        for row in (0, 512, 3968):
+            few = dict(p, X=np.ascontiguousarray(p["X"][row:row + 112]))
+            assert np.array_equal(gu.forward(few, "bf16", flags=flag), got[row:row + 112]), (flag, row)
