@@ -109,6 +109,29 @@ FwdWs fwd_layout(const Dims &d, int variant)
     return w;
 }
 
+// Automatic choice of stl_forward (bf16, no Xhat_save).  The single launch decodes the fp32 sums, three launches round Yhat to the
+// storage type in between.  It is taken
+//  - wherever every CU has at most one block and the contraction is short: a block walks all of it, 0.65 us per 16 tile columns at
+//    r <= 16 and 1.0 at r <= 32 behind 4 to 6 us, three launches take 13.1 us or more.  us of the single launch over 2 to 256
+//    blocks: r <= 8 7.6 at K <= 64, 8.5 to 9.4 at 128 and 14 to 14.7 at 256; r <= 16 7.6 to 8.5, 9.7 to 10.9 and 16 to 17;
+//    r <= 32 8.0 to 9.6 at K = 32, 10.4 to 11.7 at 64, 15 to 16 at 128.  The line is drawn where the gain is clear: of the 13.1 a
+//    host that enqueues slowly is a part (10 to 11 where it is quick);
+//  - at more than 24 planes not for fewer than 64 blocks where it also writes Yhat (2 bytes per thread and plane, up to 2.5 us): us of
+//    the three launches / the single one with Yhat_save, r = 32, K = 48, 4 / 16 / 32 / 64 / 256 blocks 10.8 / 12.0, 11.2 / 12.1, 11.7 / 12.5,
+//    14.1 / 12.9, 23.4 / 16.6, K = 32 10.2 / 10.9, 10.6 / 11.0, 11.1 / 11.3, 13.1 / 11.7, 22.1 / 14.8; K = 16 10.2 / 9.8 at 4; r = 24, K = 48
+//    10.6 / 10.8 at 4, 11.3 / 11.2 at 32; r = 16, K = 112 11.1 / 10.9 at 4;
+//  - up to about four million tile products per plane set whatever the contraction: few rows and a long contraction take longer
+//    than three launches would (m = 32, n = 512, r = 8: k = 1024 14.2 against 13.1, k = 2048 25 against 13.2), but such calls keep
+//    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other.
+// Three launches everywhere else.
+bool auto_single_launch(const Dims &d, bool yhat_save)
+{
+    if ((double)d.M * d.K * d.N * d.r <= 4.2e6) return true;
+    const int64_t blocks = (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32);
+    if (yhat_save && d.r > 24 && d.K > 16 && blocks < 64) return false;
+    return d.K <= (d.r <= 8 ? 128 : d.r <= 16 ? 112 : 48) && blocks <= 256;
+}
+
 struct BwdWs {
     size_t xhat, dyhat, dxhat, yhat, part, part2, total;
 };
@@ -545,20 +568,9 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
     if (!X || !What || !E_X || !D || !C) return fail(STL_ERR_INVALID_ARG, "stl_forward: NULL pointer");
     if (any_misaligned(X, What, E_X, D, C, Xhat_save, Yhat_save))
         return fail(STL_ERR_INVALID_ARG, "stl_forward: pointer not 16-byte aligned");
-    // Automatic choice.  The single launch decodes the fp32 sums, three launches round Yhat to the storage type in between.  It is taken
-    //  - wherever every CU has at most one block and the contraction is short: a block walks all of it, 0.65 us per 16 tile columns at
-    //    r <= 16 and 1.0 at r <= 32 behind 4 to 6 us, three launches take 13.1 us or more.  us of the single launch over 2 to 256
-    //    blocks: r <= 8 7.6 at K <= 64, 8.5 to 9.4 at 128 and 14 to 14.7 at 256; r <= 16 7.6 to 8.5, 9.7 to 10.9 and 16 to 17;
-    //    r <= 32 8.0 to 9.6 at K = 32, 10.4 to 11.7 at 64, 15 to 16 at 128.  The line is drawn where the gain is clear: of the 13.1 a
-    //    host that enqueues slowly is a part;
-    //  - up to about four million tile products per plane set whatever the contraction: few rows and a long contraction take longer
-    //    than three launches would (m = 32, n = 512, r = 8: k = 1024 14.2 against 13.1, k = 2048 25 against 13.2), but such calls keep
-    //    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other.
-    // Three launches everywhere else.
     const FwdWs w_declared = fwd_layout(d, variant);     // the workspace is checked against what the caller asked for
     if (variant == STL_FLAG_AUTO && !Xhat_save && stl::block_forward_eligible(prob->dtype, d.M, d.K, d.N, d.r) &&
-        ((double)d.M * d.K * d.N * d.r <= 4.2e6 ||
-         (d.K <= (d.r <= 8 ? 128 : d.r <= 16 ? 112 : 48) && (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) <= 256)))
+        auto_single_launch(d, Yhat_save != nullptr))
         variant = STL_FLAG_FUSED;
     if (variant == STL_FLAG_PIPELINED && !stl::forward_pipeline_eligible(prob->dtype, d.M, d.K, d.N, d.r))
         return fail(STL_ERR_UNSUPPORTED,

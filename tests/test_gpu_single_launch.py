@@ -41,6 +41,19 @@ def test_automatic_choice(gu, M, K, N, r, single):
     assert np.array_equal(gu.forward(p, "bf16", flags=stl.STL_FLAG_AUTO), want)
 
 
+@pytest.mark.parametrize("M,K,N,r,single", [(64, 48, 64, 32, False), (128, 48, 128, 32, False), (224, 32, 256, 25, False), (256, 48, 256, 32, True),
+                                            (128, 16, 160, 32, True), (128, 48, 128, 24, True), (32, 48, 64, 32, True)])
+def test_automatic_choice_that_saves_yhat(gu, M, K, N, r, single):
+    """The store of Yhat costs the single launch more than the three: few blocks of more than 24 planes stay with those."""
+    import paper_2503_12211_amd as stl
+    p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=1250 + M + K + r, dtype="bf16")
+    want = gu.forward(p, "bf16", flags=stl.STL_FLAG_FUSED if single else stl.STL_FLAG_UNFUSED, save_yhat=True)
+    other = gu.forward(p, "bf16", flags=stl.STL_FLAG_UNFUSED if single else stl.STL_FLAG_FUSED, save_yhat=True)
+    got = gu.forward(p, "bf16", flags=stl.STL_FLAG_AUTO, save_yhat=True)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert not np.array_equal(other[0], want[0])
+
+
 @pytest.mark.parametrize("K,r", [(16, 8), (48, 3), (80, 16), (32, 9)])
 def test_more_blocks_than_cus(gu, K, r):
     """288 blocks of 32 x 32 tiles, beyond one per CU: the oracle's values and, bit for bit, those of calls of 28 tile rows each, whose blocks
