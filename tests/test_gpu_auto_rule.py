@@ -1,6 +1,7 @@
 """Automatic choice of the forward variant: the single-launch variant's bits wherever the rule takes it, and right against the
-oracle on either side of the rule's edges (at r <= 8 128 tile columns of X and 256 blocks of 32 x 32 tiles; 4.2 million tile products at
-any contraction length and rank)."""
+oracle on either side of the rule's edges at r <= 8 (128 tile columns of X and 256 blocks of 32 x 32 tiles) and of 4.2 million tile
+products at any contraction length and rank.  The edges at r <= 16 (112 tile columns), r <= 32 (48) and with Yhat saved are in
+test_gpu_single_launch.py."""
 import numpy as np
 import pytest
 
