@@ -88,6 +88,7 @@ int decode_outer_blocks(int R, int Cc);       // for the workspace; as many or f
 int gradient_blocks(int dtype, int R, int Cc, bool plain_rows);
 // bf16 matrices of 8 to 32 tile columns (no row map) run in items of several tile rows, 1 << narrow_log2 columns each; 0: they do not
 int narrow_log2(int dtype, int Cc, bool plain_rows);
+bool encode_narrow(int R, int Cc, bool plain_rows);      // whether an encode alone does
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
 // the same from fp32 planes into a bf16 matrix (plane-major, Cc >= 8); W or G may be NULL

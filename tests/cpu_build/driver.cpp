@@ -4,6 +4,7 @@
 //   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (out_f32 = 2: added to it; prints which plane-product kernel and block a product takes)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   ring:encode:M:N:r   (tile counts: prints the LDS stages of the block-resident forward)
+//   narrow:R:Cc   (prints whether a bf16 encode of R x Cc tiles runs in items of several tile rows)
 //   lines:R:Cc:r   (prints whether a bf16 encode starts its items on cache lines)
 //   device:N   (the device that is current for the following cases)
 //   plant   (a planted mistake -- an output buffer 32 bytes short -- that the sanitizer must report)
@@ -62,6 +63,8 @@ int main(int argc, char **argv)
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "ring") {
             printf("  route %d\n", stl::block_forward_ring(v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
+        } else if (op == "narrow") {
+            printf("  route %d\n", (int)stl::encode_narrow((int)v[0], (int)v[1], true));
         } else if (op == "lines") {
             printf("  route %d\n", (int)stl::encode_line_starts((int)v[0], (int)v[1], (int)v[2]));
         } else if (op == "stages") {

@@ -63,6 +63,13 @@ def test_wide_bf16_encodes_of_odd_widths_write_whole_lines(checker):  # noqa: F8
     checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "ragged:52:197:1000:32:64")
 
 
+def test_encodes_of_few_narrow_rows_keep_items_of_a_row(checker):  # noqa: F811
+    cases = {"narrow:1024:15": 0, "narrow:1025:15": 1, "narrow:16:9": 0, "narrow:4096:32": 1, "narrow:4096:33": 0, "narrow:4096:7": 0}
+    _, text = checker(*cases)
+    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
+    checker("stages:1024:9:49", "stages:1025:9:49", "stages:1027:31:17", "stages:1600:15:64", "stages:1030:16:33")
+
+
 def test_block_forward_shares_a_cu_where_there_are_more_blocks(checker):  # noqa: F811
     """Up to a block per CU the ring of stages is as deep as LDS allows; beyond, two stages where several blocks then fit."""
     cases = {"ring:1:1024:256:8": 5, "ring:1:1024:257:8": 2, "ring:1:2048:1024:3": 2, "ring:0:1024:256:8": 5, "ring:0:1025:256:8": 2,

@@ -91,3 +91,25 @@ def test_encode_weight_backward_from_f32_planes(gu, K, N, r):
             assert gu.rel(gu.host(got[name]), ref[name]) <= gu.TOL["bf16"], (want, name)
         first = first or {n: t.clone() for n, t in got.items()}
         assert all(torch.equal(got[n], first[n]) for n in want)
+
+
+@pytest.mark.parametrize("M,Cc,r", [(1024, 15, 49), (1025, 15, 49), (1027, 9, 64), (1031, 31, 17), (1100, 16, 33), (1500, 8, 5)])
+def test_encode_of_narrow_matrices(gu, M, Cc, r):
+    """Items of one tile row up to 1024 rows, of several beyond: the oracle's planes and, bit for bit, those of the first 64 rows alone."""
+    import torch
+
+    import paper_2503_12211_amd as stl
+    rng = np.random.default_rng(M + Cc + r)
+    X = stl_synth.round_to(rng.standard_normal((4 * M, 4 * Cc)), "bf16")
+    E = stl_synth.round_to(rng.standard_normal((r, 16)) / 4, "bf16")
+
+    def encode(A):
+        rows = A.shape[0] // 4
+        gd = gu.Guard()
+        P = gd.alloc((stl.stl_plane_elems(rows, Cc, r),), torch.bfloat16)
+        stl.stl_encode_activation(stl.Problem(4 * rows, 4 * Cc, 4, r), gu.dev(A, "bf16"), gu.dev(E, "bf16"), P)
+        gd.check()
+        return gu.planes_to_host(P, r, rows, Cc)
+    P = encode(X)
+    gu.check(P, planes.encode(X, E), "bf16", "planes", slab=1)
+    assert np.array_equal(P[:, :64], encode(X[:256]))
