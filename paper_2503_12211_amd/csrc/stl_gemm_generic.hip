@@ -4,24 +4,26 @@
 //
 // Large planes are bound by the fp32 matrix cores (157 TFLOP/s): 128 x 128 blocks, operands in 16-byte pieces, the next stage in registers
 // while the current one is multiplied out of the other LDS buffer (one barrier per stage).  Small ones are bound by the latency
-// of a chain of stages and by idle CUs: 32 x 32 blocks with the contraction shared (gemm_small_kernel).
+// of a chain of stages and by idle CUs: 32 x 32 blocks with the contraction shared (gemm_small_kernel).  In between, mostly at
+// contractions of few stages, 64 x 64 blocks of the former kind.
 #include "stl_kernels.h"
 #include "stl_device.h"
-
+#include <algorithm>
+#include <cmath>
 
 namespace stl {
 
 // MFMA accumulator layout of v_mfma_f32_32x32x2_f32: lane (j = lane % 32, h = lane / 32) supplies A[row j][k = h] and
 // B[k = h][column j]; accumulator e of the lane is C[row 8 (e / 4) + 4 h + e % 4][column j].
-// Three wavefronts per SIMD (at the price of eleven spilled registers; left alone the compiler takes registers for two): 1024-cube,
+// Three wavefronts per SIMD for the 128 x 128 blocks (at the price of eleven spilled registers; left alone the compiler takes registers for two): 1024-cube,
 // r = 32, 770 -> 695 us, bf16 dWhat of 1024 x 1024 from four tile rows 57 -> 53.  With a sum into the output it helps some sizes and
 // costs others (r = 32 of the latter 123 -> 100, r = 8 31 -> 36) and stays at two.
-template <typename T, typename TO, bool ACC>
-__global__ __launch_bounds__(256, ACC ? 1 : 3) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
+template <typename T, typename TO, bool ACC, int BT>
+__global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                            TO *__restrict__ Out, int Mi, int Nj, int Kl, int a_km,
                                                            int b_km, int a_pg, int b_pg, int o_pg, int batch, int nb)
 {
-    constexpr int BT = 128, KC = 16, PAD = 4;          // block, contraction elements per stage
+    constexpr int KC = BT == 64 ? 32 : 16, PAD = 4;    // contraction elements per stage
     constexpr int F = BT / 64;                         // 32 x 32 products per wavefront and dimension
     constexpr int UNITS = BT * KC / 1024;              // 16-byte pieces per thread, operand and stage
     __shared__ __align__(16) float sA[2][KC][BT + PAD];    // [l][i]: a fragment read takes 32 consecutive i of one l
@@ -124,8 +126,8 @@ __global__ __launch_bounds__(256, ACC ? 1 : 3) void gemm_generic_kernel(const T 
 }
 
 // A 32 x 32 block of one plane per workgroup, whose four wavefronts share the contraction, 16 of a stage's 64 elements each, and add
-// their sums up in LDS.  64 x 64 blocks gave 49 planes of 64 x 64 49 workgroups and a chain of two stages, these four times as many
-// and one stage of 16 KB in flight: 7.5 -> 4.0 us.  64 planes of 60 x 2000 x 60: 101 -> 40; bf16 Yhat of 7 x 1024 x 1024, r = 32: 81 -> 46.
+// their sums up in LDS.  64 x 64 blocks give 49 planes of 64 x 64 49 workgroups and a chain of two stages, these four times as many
+// and one stage of 16 KB in flight: 7.5 / 4.0 us.  64 planes of 60 x 2000 x 60: 101 / 40.
 template <typename T, typename TO, bool ACC>
 __global__ __launch_bounds__(256) void gemm_small_kernel(const T *__restrict__ A, const T *__restrict__ B, TO *__restrict__ Out, int Mi,
                                                          int Nj, int Kl, int a_km, int b_km, int tiles_m, int tiles_n, int total,
@@ -210,6 +212,7 @@ static hipError_t launch_small(const GemmDesc &g, const void *A, const void *B, 
 {
     GemmLays l;
     if (!l.set(g)) return hipErrorInvalidValue;
+    // with at most 2^22 stacked tile rows and columns and 64 planes, what is not left to the large blocks stays far below 2^31 blocks
     const int tiles_m = (g.Mi + 31) / 32, tiles_n = (g.Nj + 31) / 32, total = tiles_m * tiles_n * g.batch * g.nb;
     hipLaunchKernelGGL((gemm_small_kernel<T, TO, ACC>), dim3(total > (1 << 22) ? 1 << 22 : total), dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out, g.Mi, g.Nj, g.Kl,
                        (int)g.a_kmajor, (int)g.b_kmajor, tiles_m, tiles_n, total, g.batch, Div::by(tiles_m * tiles_n), Div::by(tiles_n),
@@ -217,28 +220,44 @@ static hipError_t launch_small(const GemmDesc &g, const void *A, const void *B, 
     return hipGetLastError();
 }
 
-template <typename T, typename TO, bool ACC>
+template <typename T, typename TO, bool ACC, int BT>
 static hipError_t launch_large(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    constexpr int BT = 128;
     const long zs = (long)g.batch * g.nb;
     const int rows = (g.Mi + BT - 1) / BT;
     dim3 grid((g.Nj + BT - 1) / BT, (unsigned)(rows > 65535 ? 65535 : rows), (unsigned)(zs > 65535 ? 65535 : zs));   // the kernel strides over both
-    hipLaunchKernelGGL((gemm_generic_kernel<T, TO, ACC>), grid, dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out,
+    hipLaunchKernelGGL((gemm_generic_kernel<T, TO, ACC, BT>), grid, dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out,
                        g.Mi, g.Nj, g.Kl, (int)g.a_kmajor, (int)g.b_kmajor, g.a_rows_per_group(), g.b_rows_per_group(),
                        g.o_rows_per_group(), g.batch, g.nb);
     return hipGetLastError();
 }
 
+// Edge of the block: the one with the least predicted time, us, from the blocks per CU and the stages of a block, with what one stage
+// and the rest of a block take (fitted to 1515 products of 64 to 1500 tiles and 8 to 64 planes, timed in all three forms: the choice is
+// 0.3 % behind the fastest form on average; a block per CU hides less than two do).  Operands that both lie along the contraction
+// turn on their way to LDS, which costs the 32 x 32 blocks most.  us at 128 / 64 / 32, fp32 Yhat: 49 x (64 x 64 x 64) 16 / 6.9 / 4.1,
+// 32 x (300 x 300 x 300) 67 / 48 / 41, 32 x (256 x 16 x 256) 13.4 / 8.5 / 9.3, 24 x (512 x 96 x 256) 22 / 15.8 / 18.1, 56 x (384 x 384 x 384) 82 / 96 / 98,
+// 32 x (1024 x 128 x 128) 41 / 27 / 23; bf16 dX of 256 x 256 from 7 tile columns, r = 40, 24.4 / 21.6 / 28.4.  Furthest off: 64 x (128 x 300 x 300)
+// 48 / 34.5 / 42.7, taken at 32.
+int generic_block(const GemmDesc &g)
+{
+    auto blocks = [&](int bt) { return (double)((g.Mi + bt - 1) / bt) * ((g.Nj + bt - 1) / bt) * g.batch * g.nb / 256; };
+    auto stages = [&](int kc) { return (double)((g.Kl + kc - 1) / kc); };
+    const bool turns = !g.a_kmajor && !g.b_kmajor;
+    const double t32 = 1.9 + blocks(32) * stages(64) * (turns ? 0.68 : 0.59);
+    const double t64 = 0.84 + std::max(2.0, std::ceil(blocks(64))) * (0.98 + 1.19 * stages(32));
+    const double t128 = 2.0 + std::max(1.5, std::ceil(blocks(128))) * (3.0 + 1.77 * stages(16));
+    return t32 <= t64 && t32 <= t128 ? 32 : t64 <= t128 ? 64 : 128;
+}
+
 template <typename T, typename TO, bool ACC>
 static hipError_t launch_t(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    // 128 x 128 blocks (a quarter of the operand traffic) once every CU has two.  us at 128 / 32, fp32 products: 512 x 512 x 512, r = 32
-    // (512 blocks of 128) 103 / 129, 900 x 200 x 200, 32 (512) 51 / 60, 1024 x 64 x 1024, 8 (512) 27 / 27, 640 x 384 x 384, 24 (360) 81 / 73,
-    // 300 x 300 x 300, 32 (288) 67 / 41, 256 x 64 x 512, 32 (256) 19 / 15.  Contractions of one stage of the former store most of the
-    // time and take it at one per CU: bf16 dWhat (and the encode before it) of 512 x 512 from 4 tile rows, 16 (256) 16.8 / 18.9.
-    const double blocks = (double)((g.Mi + 127) / 128) * ((g.Nj + 127) / 128) * g.batch * g.nb;
-    return g.Mi > 64 && g.Nj > 64 && blocks >= (g.Kl <= 16 ? 256 : 512) ? launch_large<T, TO, ACC>(g, A, B, Out, s) : launch_small<T, TO, ACC>(g, A, B, Out, s);
+    switch (generic_block(g)) {
+        case 128: return launch_large<T, TO, ACC, 128>(g, A, B, Out, s);
+        case 64: return launch_large<T, TO, ACC, 64>(g, A, B, Out, s);
+    }
+    return launch_small<T, TO, ACC>(g, A, B, Out, s);
 }
 
 hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out,

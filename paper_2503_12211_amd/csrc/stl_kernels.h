@@ -225,6 +225,7 @@ hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const 
 enum class GemmPath { wide, pipe, staged, generic };
 GemmPath plane_gemm_path(int dtype, const GemmDesc &g);
 // the any-shape path (fp32 MFMA), also used directly for fp32 storage
+int generic_block(const GemmDesc &g);         // edge of the block of a plane that it takes
 hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out,
                                      hipStream_t s);
 // bf16 MFMA path, operands staged through registers (any width of at least 8)

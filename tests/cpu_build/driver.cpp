@@ -58,7 +58,8 @@ int main(int argc, char **argv)
             const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
             const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
             const char *staged = stl::staged_block(g) == 256 ? "256x256" : stl::staged_block(g) == 128 ? "128x128" : "64x64";
-            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::generic ? "-" : path == stl::GemmPath::staged ? staged : blocks[(int)stl::pipe_block(g)]);
+            const char *any = stl::generic_block(g) == 128 ? "128x128" : stl::generic_block(g) == 64 ? "64x64" : "32x32";
+            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::generic ? any : path == stl::GemmPath::staged ? staged : blocks[(int)stl::pipe_block(g)]);
         } else if (op == "tiles") {
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "ring") {
