@@ -123,9 +123,10 @@ def _ptr(x):
 def _stream(stream):
     if stream is None:
         # the handle that torch.cuda.current_stream().cuda_stream has, without the Stream object on the way to it (0.4 against 3.0 us,
-        # a fifth of the time in which a forward of three launches is enqueued)
+        # a fifth of the time in which a forward of three launches is enqueued); a torch without that private name gives the object
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

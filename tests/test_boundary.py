@@ -290,3 +290,14 @@ def test_dimension_cap_is_the_documented_one():
     with pytest.raises(stl.StlError) as e:
         stl.stl_forward(stl.Problem(4, cap + 4, 4, 1), FAKE, FAKE, FAKE, FAKE, FAKE, None, None, FAKE, 1 << 40, 0, stream=0)
     assert e.value.status == 1
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """A torch that lacks the private accessor of the current stream's handle: the handle of its stream object."""
+    import types
+
+    import torch
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    assert stl.binding._stream(None) == 1234
