@@ -275,6 +275,7 @@ hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A
 GemmPath plane_gemm_path(int dtype, const GemmDesc &g)
 {
     if (dtype != 1) return GemmPath::generic;
+    if (plane_gemm_rows_eligible(g)) return GemmPath::rows;
     if (plane_gemm_wide_eligible(g)) return GemmPath::wide;
     if (plane_gemm_pipe_eligible(g)) return GemmPath::pipe;
     return plane_gemm_mfma_eligible(g) ? GemmPath::staged : GemmPath::generic;
@@ -282,8 +283,8 @@ GemmPath plane_gemm_path(int dtype, const GemmDesc &g)
 
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    if (dtype == 1 && plane_gemm_rows_eligible(g)) return launch_plane_gemm_rows(g, A, B, Out, s);
     switch (plane_gemm_path(dtype, g)) {
+        case GemmPath::rows: return launch_plane_gemm_rows(g, A, B, Out, s);
         case GemmPath::wide: return launch_plane_gemm_wide(g, A, B, Out, s);
         case GemmPath::pipe: return launch_plane_gemm_pipe(g, A, B, Out, s);
         case GemmPath::staged: return launch_plane_gemm_mfma(g, A, B, Out, s);

@@ -312,9 +312,12 @@ static hipError_t launch_cfg(const GemmDesc &g, const void *A, const void *B, vo
 
 static bool any_width(const GemmDesc &g) { return g.Mi % 8 || g.Nj % 8 || g.Kl % 8; }
 
-// Edge of the (square) block.
+// Edge of the (square) block.  A product with a single stage, or an output that a 64 x 64 block covers in one dimension, takes 64 x 64
+// blocks however many there are (us at 64 / 128 / 256: Yhat 2048 x 50 x 513, r = 32 20 / 23 / 22; forward and backward of 96 x (64 x 64 x 20),
+// r = 32 96 / 136 / 242, of 96 x (128 x 16 x 128) 212 / 235 / 370).
 int staged_block(const GemmDesc &g)
 {
+    if (g.Mi <= 64 || g.Nj <= 64 || g.Kl <= staged::BK) return 64;
     // multiples of 8, stacked problems: 256 x 256 blocks, 8 wavefronts of 128 x 64, for large planes, 128 x 128, 4 of 64 x 64, for others
     if (!any_width(g)) return g.Mi > 128 && g.Nj > 128 ? 256 : 128;
     auto blocks = [&](int b) { return (double)((g.Mi + b - 1) / b) * ((g.Nj + b - 1) / b) * g.batch * g.nb; };
@@ -329,17 +332,13 @@ int staged_block(const GemmDesc &g)
     return g.Mi > 64 && g.Nj > 64 && blocks(128) >= (g.Kl > 640 ? 256 : 384) ? 128 : 64;
 }
 
-// A product with a single stage, or an output that a 64 x 64 block covers in one dimension, takes 64 x 64 blocks however many there
-// are (us at 64 / 128 / 256: Yhat 2048 x 50 x 513, r = 32 20 / 23 / 22; forward and backward of 96 x (64 x 64 x 20), r = 32 96 / 136 / 242,
-// of 96 x (128 x 16 x 128) 212 / 235 / 370).
-static bool thin(const GemmDesc &g) { return g.Mi <= 64 || g.Nj <= 64 || g.Kl <= staged::BK; }
-
 // Groups of wavefronts that share the contraction of a 64 x 64 block: where the blocks leave CUs idle and the chain of stages is
 // long, each group has loads of its own in flight.  us with 1 / 2 / 4 groups: Yhat 64 x 500 x 500, 32 (256 blocks, 8 stages) 10.0 / 7.5 / 8.0,
 // 512 x 192 x 250, 32 (1024 blocks, 3 stages) 8.5 / 10.4 / 14.8; dWhat and the encode before it 512 x 192 x 250, 32 (384, 8) 18.5 / 16.8 / 20.2,
-// 3000 x 100 x 100, 8 (32, 47) 56 / 35 / 27, 1023 x 257 x 513, 16 (720, 16) 32 / 32 / 38.
-static int staged_groups(const GemmDesc &g)
+// 3000 x 100 x 100, 8 (32, 47) 56 / 35 / 27, 1023 x 257 x 513, 16 (720, 16) 32 / 32 / 38.  0: one stage, one group.
+int staged_groups(const GemmDesc &g)
 {
+    if (g.Kl <= staged::BK) return 0;
     const double blocks = (double)((g.Mi + 63) / 64) * ((g.Nj + 63) / 64) * g.batch * g.nb;
     const int stages = (g.Kl + staged::BK - 1) / staged::BK;
     return blocks <= 256 && stages >= 12 ? 4 : blocks <= 512 && stages >= 4 ? 2 : 1;
@@ -348,12 +347,12 @@ static int staged_groups(const GemmDesc &g)
 template <bool A_T, bool B_T, typename TO, bool ACC>
 static hipError_t launch_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    switch (thin(g) ? 64 : staged_block(g)) {
+    switch (staged_block(g)) {
         case 256: return launch_cfg<256, 256, 2, 4, 1, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
         case 128: return launch_cfg<128, 128, 2, 2, 2, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
     }
-    if (g.Kl <= staged::BK) return launch_cfg<64, 64, 4, 1, 0, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
     switch (staged_groups(g)) {
+        case 0: return launch_cfg<64, 64, 4, 1, 0, 1, A_T, B_T, TO, ACC>(g, A, B, Out, s);
         case 4: return launch_cfg<64, 64, 4, 1, 2, 4, A_T, B_T, TO, ACC>(g, A, B, Out, s);
         case 2: return launch_cfg<64, 64, 4, 1, 2, 2, A_T, B_T, TO, ACC>(g, A, B, Out, s);
     }

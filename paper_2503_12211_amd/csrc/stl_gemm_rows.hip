@@ -161,6 +161,7 @@ __global__ __launch_bounds__(NW * 64, FM * DEPTH * CW <= 16 ? 4 : 2) void gemm_r
 // (256) 16.3 / 20.3; 192 x 768, r = 32 (384) 5.8 / 4.7, 1024 x 768, r = 32 (384) 13.7 / 12.2, 256 x 1024, r = 64 (1024) 10.5 / 8.7.
 static long blocks_of(const GemmDesc &g, int cw) { return (long)((g.Nj + 16 * cw - 1) / (16 * cw)) * g.batch; }
 static bool four_columns(const GemmDesc &g) { return blocks_of(g, 4) <= 256; }
+int rows_columns(const GemmDesc &g) { return four_columns(g) ? 64 : 128; }
 
 // Up to 16 rows it was nowhere slower than the LDS-DMA kernels over K = 8 ... 4096, N = 8 ... 4096, r = 1 ... 64 (64 x 64, r = 8
 // 3.75 -> 3.6; 512 x 2048, r = 32 17.3 both).  17 to 32 rows take two fragments per column and one workgroup per CU: us there / here

@@ -221,8 +221,8 @@ struct Div {
 };
 
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
-// the kernel that launch_plane_gemm takes: stl_gemm_wide.hip, stl_gemm_pipe.hip, stl_gemm_mfma.hip, stl_gemm_generic.hip
-enum class GemmPath { wide, pipe, staged, generic };
+// the kernel that launch_plane_gemm takes: stl_gemm_rows.hip, stl_gemm_wide.hip, stl_gemm_pipe.hip, stl_gemm_mfma.hip, stl_gemm_generic.hip
+enum class GemmPath { rows, wide, pipe, staged, generic };
 GemmPath plane_gemm_path(int dtype, const GemmDesc &g);
 // the any-shape path (fp32 MFMA), also used directly for fp32 storage
 int generic_block(const GemmDesc &g);         // edge of the block of a plane that it takes
@@ -230,10 +230,12 @@ hipError_t launch_plane_gemm_generic(int dtype, const GemmDesc &g, const void *A
                                      hipStream_t s);
 // bf16 MFMA path, operands staged through registers (any width of at least 8)
 bool plane_gemm_mfma_eligible(const GemmDesc &g);
-int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes (thin products: 64 x 64 whatever this says)
+int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes
+int staged_groups(const GemmDesc &g);         // and, of 64 x 64 blocks, the groups of wavefronts that share the contraction (0: it is one stage)
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
-// bf16 products of up to 32 rows, any number of them (stl_gemm_rows.hip): taken before the path that plane_gemm_path names
+// bf16 products of up to 32 rows
 bool plane_gemm_rows_eligible(const GemmDesc &g);
+int rows_columns(const GemmDesc &g);          // columns of the block of a plane that it takes
 hipError_t launch_plane_gemm_rows(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 // bf16 MFMA path with LDS-DMA loads and a multi-stage LDS ring (contiguous dimensions a multiple of 8)
 enum class PipeBlock { b256, b128x256, b128, b64 };

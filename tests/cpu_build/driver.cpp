@@ -1,7 +1,7 @@
 // Driver of the CPU address check (test infrastructure only): calls the C ABI entry points on host buffers whose end
 // coincides with the end of their allocation, under AddressSanitizer.  Each command-line argument is one case:
 //   fwd:m:k:n:r:flags   bwd:m:k:n:r   mlp:m:k:h:r   ewb:k:n:r   aa:nb:m:k:n:r   ragged:nimg:rows:k:n:r
-//   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (out_f32 = 2: added to it; prints which plane-product kernel and block a product takes)
+//   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (out_f32 = 2: added to it; prints which plane-product kernel and block a product takes; staged 64x64:G: G groups share the contraction, 0: one stage)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   ring:encode:M:N:r   (tile counts: prints the LDS stages of the block-resident forward)
 //   narrow:R:Cc   (prints whether a bf16 encode of R x Cc tiles runs in items of several tile rows)
@@ -55,11 +55,14 @@ int main(int argc, char **argv)
             (void)hipSetDevice((int)v[0]);
         } else if (op == "route") {
             stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, v[6] > 1, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
-            const char *paths[] = {"wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
+            const char *paths[] = {"rows", "wide", "pipe", "staged", "generic"}, *blocks[] = {"256x256", "128x256", "128x128", "64x64"};
             const stl::GemmPath path = stl::plane_gemm_path(dt == STL_BF16 ? 1 : 0, g);
-            const char *staged = stl::staged_block(g) == 256 ? "256x256" : stl::staged_block(g) == 128 ? "128x128" : "64x64";
-            const char *any = stl::generic_block(g) == 128 ? "128x128" : stl::generic_block(g) == 64 ? "64x64" : "32x32";
-            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::generic ? any : path == stl::GemmPath::staged ? staged : blocks[(int)stl::pipe_block(g)]);
+            char own[32];
+            const int edge = path == stl::GemmPath::staged ? stl::staged_block(g) : stl::generic_block(g);
+            snprintf(own, sizeof(own), "%dx%d", edge, edge);
+            if (path == stl::GemmPath::staged && edge == 64) snprintf(own, sizeof(own), "64x64:%d", stl::staged_groups(g));
+            if (path == stl::GemmPath::rows) snprintf(own, sizeof(own), "%dx%d", g.Mi > 16 ? 32 : 16, stl::rows_columns(g));
+            printf("  route %s %s\n", paths[(int)path], path == stl::GemmPath::wide || path == stl::GemmPath::pipe ? blocks[(int)stl::pipe_block(g)] : own);
         } else if (op == "tiles") {
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "ring") {

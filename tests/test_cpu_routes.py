@@ -90,38 +90,67 @@ def test_second_device_of_a_process(checker):  # noqa: F811
 
 
 def _covered(run, descs):
-    """{(operand forms, fp32 output, stacked, kernel, block, ends inside a stage or any width)} that these products reach."""
+    """{(operand forms, fp32 output, stacked, kernel, block, ends inside a stage or any width)} that these products reach; 64 x 64 blocks
+    staged through registers with the groups that share the contraction."""
     out = set()
     for d, (path, block) in zip(descs, routes(run, descs)):
         Mi, Nj, Kl, akm, bkm, f32, nb = d[0], d[1], d[2], d[4], d[5], d[6], d[10]
-        odd = bool(Kl % 32) if path in ("wide", "pipe") else bool(Mi % 8 or Nj % 8 or Kl % 8)
+        odd = bool(Kl % 32) if path in ("rows", "wide", "pipe") else bool(Mi % 8 or Nj % 8 or Kl % 8)
         out.add((akm, bkm, f32, nb > 1, path, block, odd))
     return out
 
 
+def _blocks(covered):
+    """Without the groups of wavefronts, and without products of few rows, which have no such block."""
+    return {k[:5] + (k[5].split(":")[0], k[6]) for k in covered if k[4] != "rows"}
+
+
 def test_gpu_shapes_reach_every_kernel_form_and_block(checker):  # noqa: F811
-    layer = _covered(checker, [desc(f, *s) for s in SHAPES for f in FORMS])
+    layer = _blocks(_covered(checker, [desc(f, *s) for s in SHAPES for f in FORMS]))
     forms = ((0, 1, 0), (0, 0, 0), (1, 1, 1), (1, 1, 2))
     want = {(a, b, f, False, "pipe", blk, tail) for a, b, f in forms for blk in BLOCKS for tail in (False, True)}
     want |= {(0, b, 0, False, "wide", "256x256", False) for b in (0, 1)}
     want |= {(a, b, f, False, "staged", blk, True) for a, b, f in forms for blk in ("64x64", "128x128", "256x256")}
     assert want - layer == set() and layer - want == set()
-    aa = _covered(checker, [d for s in AA_SHAPES for d in aa_descs(*s)])
+    aa = _blocks(_covered(checker, [d for s in AA_SHAPES for d in aa_descs(*s)]))
     want = {(1, 1, 0, False, "pipe", blk, tail) for blk in BLOCKS for tail in (False, True)}
     want |= {(1, 1, 0, False, "staged", blk, True) for blk in ("64x64", "128x128", "256x256")}
     for a, b in ((0, 1), (0, 0), (1, 1)):
         # stacked problems: the LDS-DMA kernel at one stage, otherwise staged
         want |= {(a, b, 0, True, "pipe", blk, False) for blk in BLOCKS}
-        want |= {(a, b, 0, True, "staged", blk, False) for blk in ("128x128", "256x256")}
-        want |= {(a, b, 0, True, "staged", blk, True) for blk in ("64x64", "128x128", "256x256")}
+        want |= {(a, b, 0, True, "staged", blk, odd) for blk in ("64x64", "128x128", "256x256") for odd in (False, True)}
     assert want - aa == set(), want - aa
     assert {k for k in aa if k[3]} - want == set()
+
+
+def test_gpu_shapes_reach_every_group_of_wavefronts(checker):  # noqa: F811
+    """64 x 64 blocks staged through registers: one stage, one group, two and four, for every operand form."""
+    from test_gpu_any_width import SHAPES as ANY
+    from test_gpu_staged import SHAPES as STAGED, STACKED
+    got = _covered(checker, [desc(f, *s) for s in ANY + SHAPES + STAGED for f in FORMS] + [d for s in AA_SHAPES + STACKED for d in aa_descs(*s)])
+    got = {k[:3] + (k[5],) for k in got if k[4] == "staged" and ":" in k[5]}
+    want = {form + (f"64x64:{g}",) for form in ((0, 1, 0), (0, 0, 0), (1, 1, 0), (1, 1, 1), (1, 1, 2)) for g in (0, 1, 2, 4)}
+    assert want - got == set() and got - want == set()
+
+
+def test_products_of_few_rows(checker):  # noqa: F811
+    """Where the few-row kernel begins and ends, and that the shapes of test_gpu_few_rows.py reach all its forms."""
+    from test_gpu_few_rows import OTHERS, SHAPES as FEW
+    got = _covered(checker, [desc("Yhat", *s) for s in FEW])
+    assert {k[4:] for k in got} == {("rows", f"{m}x{n}", tail) for m in (16, 32) for n in (64, 128) for tail in (False, True)}
+    cases = {(16, 1024, 1024, 49): ("rows", "16x128"), (16, 1024, 1024, 16): ("rows", "16x64"), (3, 8, 8, 1): ("rows", "16x64"),
+             (17, 128, 1024, 32): ("rows", "32x128"), (17, 120, 128, 5): ("pipe", "64x64"), (32, 512, 1024, 33): ("pipe", "64x64"),
+             (33, 128, 128, 5): ("pipe", "64x64"), (16, 100, 96, 8): ("staged", "64x64:1"), (7, 100, 96, 8): ("generic", "32x32"), **{s: ("pipe", "64x64") for s in OTHERS}}
+    assert routes(checker, [desc("Yhat", *s) for s in cases]) == list(cases.values())
+    # the other products of the same layers stay where they are, and so do several stacked problems
+    assert {p for p, _ in routes(checker, [desc(f, 16, 512, 512, 8) for f in FORMS[1:]])} == {"pipe"}
+    assert {p for p, _ in routes(checker, aa_descs(2, 16, 512, 512, 8, False))} == {"staged"}
 
 
 def test_blocks_that_were_measured_faster(checker):  # noqa: F811
     """Shapes on which the fastest block was at least 10 % ahead of the one taken by a rule without whole rounds and output types."""
     cases = {("Yhat", 1024, 256, 256, 49): "256x256", ("Yhat", 2048, 256, 256, 49): "256x256", ("Yhat", 1536, 512, 384, 16): "256x256",
-             ("Yhat", 3200, 192, 768, 16): "256x256", ("Yhat", 16, 1024, 1024, 49): "128x256", ("dWhat", 2048, 256, 256, 49): "128x128",
+             ("Yhat", 3200, 192, 768, 16): "256x256", ("dWhat", 2048, 256, 256, 49): "128x128",
              ("dWhat", 256, 512, 512, 49): "256x256", ("dWhat", 512, 768, 192, 49): "256x256", ("dWhat +=", 64, 256, 256, 8): "64x64"}
     got = routes(checker, [desc(*c) for c in cases])
     assert [block for _, block in got] == list(cases.values())

@@ -1,6 +1,6 @@
 """Register-staged plane products where their stages, groups and chunks end: contractions of one stage (64) and of one piece (32), of
 4, 5, 12 and 13 stages over two and four groups of wavefronts, rows whose last chunk has one element, stacked problems whose
-rows straddle the planes' groups of 64, thin outputs of widths that are multiples of 8.
+rows straddle the planes' groups of 64, thin outputs of widths that are multiples of 8.  test_cpu_routes.py asserts which groups they reach.
 
 Bars: gpu_util.check (see test_gpu_any_width.py).  Its bar for one entry takes an entry as the sum of many terms: with r planes and
 a contraction of K the entry's own scale has a relative spread of about sqrt(2 / (r K)), so that over 1e6 entries (4.9 sigma) the largest
@@ -24,8 +24,12 @@ def gu():
 
 
 # M, K, N, r: every dimension is the contraction of one of the three products
-@pytest.mark.parametrize("M,K,N,r", [(31, 32, 33, 3), (63, 64, 65, 2), (193, 257, 9, 5), (17, 705, 769, 4), (705, 9, 67, 3), (833, 65, 17, 8),
-                                     (70, 193, 129, 49)])
+SHAPES = [(31, 32, 33, 3), (63, 64, 65, 2), (193, 257, 9, 5), (17, 705, 769, 4), (705, 9, 67, 3), (833, 65, 17, 8), (70, 193, 129, 49)]
+STACKED = [(9, 50, 16, 50, 8, True), (5, 33, 9, 31, 49, False), (3, 64, 16, 64, 32, True), (3, 48, 64, 24, 5, False), (2, 257, 9, 321, 8, True),
+           (1, 705, 66, 67, 3, False), (1, 833, 67, 65, 3, True)]        # the last two: four groups store the gradient of the second operand
+
+
+@pytest.mark.parametrize("M,K,N,r", SHAPES)
 def test_step_staged(gu, M, K, N, r):
     p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=400 + M + K + N + r, dtype="bf16", with_dC=True)
     got = gu.step(p, "bf16")
@@ -39,8 +43,7 @@ def test_step_staged(gu, M, K, N, r):
     assert np.abs(acc["dWhat"] - 1.0 - got["dWhat"]).max() <= 2.0 ** -22 * max(1.0, np.abs(got["dWhat"]).max())
 
 
-@pytest.mark.parametrize("nb,M,K,N,r,bt", [(9, 50, 16, 50, 8, True), (5, 33, 9, 31, 49, False), (3, 64, 16, 64, 32, True),
-                                           (3, 48, 64, 24, 5, False), (2, 257, 9, 321, 8, True)])
+@pytest.mark.parametrize("nb,M,K,N,r,bt", STACKED)
 def test_stacked_staged(gu, nb, M, K, N, r, bt):
     import paper_2503_12211_amd as stl
     fl = stl.STL_FLAG_B_TRANSPOSED if bt else 0
