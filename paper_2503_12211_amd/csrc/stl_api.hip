@@ -289,8 +289,11 @@ AaWs aa_layout(const Dims &d, int64_t nb, bool backward)
 }
 
 // Whether the backward runs its two decodes as one launch and its three sums as one.  Products then stand between a gradient's
-// planes and their decode, which finds them in the last-level cache while all of them are small beside its 256 MB; a partial sum of
-// 16 r floats per 256 tiles fits the area of the tiles' r planes from 8 tile columns on.
+// planes and their decode, which finds them in the last-level cache while all of them are small beside its 256 MB.  us apart / paired by
+// the two gradients' planes, r = 32, second operand stored transposed: 10 MB 55 / 40 (96 x (50 x 16 x 50)), 34 MB 78 / 63 (8 x (256 x 128 x 256)),
+// 67 MB 134 / 119, 134 MB 237 / 227, 268 MB 324 / 323 (512 x (64 x 64 x 64)).
+// The partial sums lie in the workspace's areas for A's and B's planes: 64 r bytes per four items, and four items are at least 32 tiles
+// from 8 tile columns on, at 2 r bytes of planes each (the areas hold whole groups of 64 tile rows).
 bool aa_backward_paired(int dt, const Dims &d, int64_t RA, int64_t RB, int CB, bool everything)
 {
     return everything && dt == STL_BF16 && d.K >= 8 && d.N >= 8 && (double)d.r * (RA * d.K + RB * CB) * d.es <= 64e6;

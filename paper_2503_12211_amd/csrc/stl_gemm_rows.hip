@@ -9,10 +9,11 @@
 // added up in LDS in a fixed order.  A lane loads CW neighbouring columns (lane % 16) of eight stored rows (lane / 16) and turns
 // them in its registers, so that fragment c holds columns CW j + c of the block.  An operand stored [j][l] stays with the
 // LDS-DMA kernels: its fragments are rows far apart, 64 bytes of each (16 x 1024 x 1024, r = 8: 7.1 there, 7.3 this way).
-// Measured, us, 64 x 64 blocks of the LDS-DMA kernel -> here, 16 rows: 1024 x 1024, r = 32 19.3 -> 15.8 (4.3 TB/s), 1024 x 256, r = 32
-// 8.7 -> 5.7, 512 x 512, r = 32 6.9 -> 5.4, 256 x 1024, r = 32 7.8 -> 5.7, 128 x 128, r = 32 4.3 -> 3.5, 4096 x 1024, r = 32 59 -> 52.
-// Of fewer than 8 rows, which the fp32 matrix instructions took before, 4 rows: 1024 x 1024, r = 32 80 -> 12.7, 1024 x 256, r = 49 58 -> 6.4,
-// 128 x 128, r = 32 9.0 -> 3.3.
+// Measured, us, 64 x 64 blocks of the LDS-DMA kernel -> here, 16 rows, r = 32, weights in the last-level cache (and, in brackets,
+// from memory: a GB of them in turn): 1024 x 1024 15.3 -> 12.4, 5.4 TB/s (18.6 -> 15.6, 4.3 TB/s); 1024 x 256 8.5 -> 5.5 (9.1 -> 7.4);
+// 512 x 512 6.6 -> 4.4 (7.6 -> 6.5); 4096 x 1024 (57 -> 52, 5.2 TB/s); 128 x 128 4.3 -> 3.5.  32 rows: 1024 x 1024 15.5 -> 13.4 (18.7 -> 16.4).
+// Of fewer than 8 rows, which the fp32 matrix instructions took before, 4 rows: 1024 x 1024, r = 32 80 -> 12.0 (92 -> 15.1), 1024 x 256, r = 49
+// 58 -> 6.4, 128 x 128, r = 32 9.0 -> 3.3.
 #include "stl_gemm_pipe.h"
 
 namespace stl {

@@ -75,7 +75,7 @@ struct Fold {
 // rows of the plane tensor); fold (bf16): E (or Dm) is composed with it
 hipError_t launch_encode(int dtype, const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s,
                          RowMap rm = RowMap(), Fold fold = Fold());
-// matrix Cmat (4R x 4Cc) <- decoder Dm^T (r x 16 stored) applied to planes P[p][R][Cc]
+// matrix Cmat (4R x 4Cc) <- decoder Dm^T (r x 16 stored) applied to planes P[p][R][Cc]; gelu not with a fold
 hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, int R, int Cc, int r, bool gelu, int pg,
                          hipStream_t s, RowMap rm = RowMap(), Fold fold = Fold());
 
@@ -87,6 +87,7 @@ bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r);
 int decode_outer_blocks(int R, int Cc);       // for the workspace; as many or fewer are used:
 int gradient_blocks(int dtype, int R, int Cc, bool plain_rows);
 // bf16 matrices of 8 to 32 tile columns (no row map) run in items of several tile rows, 1 << narrow_log2 columns each; 0: they do not
+// (of more columns an item, 64 tiles of a power of two of columns, is a single row)
 int narrow_log2(int dtype, int Cc, bool plain_rows);
 bool encode_narrow(int R, int Cc, bool plain_rows);      // whether an encode alone does
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,

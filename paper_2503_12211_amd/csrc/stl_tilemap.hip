@@ -24,7 +24,7 @@ __device__ __forceinline__ float fold_entry(const T *__restrict__ Dm, const Fold
 
 // ---------------------------------------------------------------------------------------
 // The tile maps in fp32 arithmetic on the vector ALUs, for fp32 storage (plain encodes and decodes of large matrices: one tile
-// per thread, below), for bf16 rows of fewer than 8 tiles and for bases kept in fp32 (the folded decoder):
+// per thread, below; basis gradients of small ones: tile_grad_kernel), for bf16 rows of fewer than 8 tiles and for the folded decoder:
 //   ENC    Pout[p][I][J]  = sum_q B[p][q] V[4I + q/4][4J + q%4]                  (planes of encoded tiles)
 //   DEC    Cmat[4I + q/4][4J + q%4] = sum_p B[p][q] Pin[p][I][J]                 (+ optional GELU)
 //   OUTER  G[p][q] = sum_{I,J} Pin[p][I][J] V[4I + q/4][4J + q%4]                (basis gradient; with ENC or DEC or alone)
@@ -34,7 +34,7 @@ __device__ __forceinline__ float fold_entry(const T *__restrict__ Dm, const Fold
 // fourth plane), DEC (tile, tile row), OUTER (entry q, every 16th plane; the 64 tiles of an item are summed on their own
 // before they join the running sum).  Bound by HBM on large matrices and by latency on small ones, which is what the
 // grouping is for: with one thread per tile, planes one after the other, 64 x 64 tiles at r = 49 took 9 us to encode,
-// 19 to decode and 332 for a basis gradient (16 workgroups); now 5, 5 and 11 (with the decode).
+// 19 to decode and 332 for a basis gradient (16 workgroups); now 5 and 5, and the gradient, which tile_grad_kernel takes at this size, 6.
 // OUTER blocks leave one partial each, added up in block order by outer_final_kernel: no floating-point atomics, so the
 // results are bitwise reproducible.
 // ---------------------------------------------------------------------------------------
@@ -355,8 +355,10 @@ __global__ __launch_bounds__(256) void decode_tiles_kernel(const T *__restrict__
 
 // From 2^17 tiles on one tile per thread fills the chip (two wavefronts per SIMD; at 2^16 tiles and r = 64 the items are still ahead, 8.4
 // against 10.7 us).  Rows of fewer than 8 tiles stay with the items at any rank (100000 x 3, r = 49: 20 against 25 us to
-// encode), and so does the encode of bf16.  bf16 rows of 9 to 15 tiles fill a quarter of the matrix-core decode's chunk:
-// at small ranks one tile per thread decodes 16384 x 9 tiles, r = 8, in 7.7 us against 10.3 (at r = 32 of 65536 rows it takes 39 against 36).
+// encode), and so does the encode of bf16.  bf16 decodes of 9 to 15 columns: one tile per thread is ahead of items of several rows
+// (decode_narrow_kernel) at the smallest ranks and behind them at 8, where the line lies since items were of a single row (10.3 us
+// for 16384 x 9, r = 8).  us, one tile per thread / items of several rows: 16384 x 9 tiles, r = 1 / 3 / 8 3.9 / 4.5, 4.3 / 4.5, 5.0 / 4.5;
+// 65536 x 12 9.3 / 11.0, 10.2 / 11.1, 14.6 / 11.9; 8800 x 15 3.5 / 3.9, 3.7 / 4.0, 4.6 / 4.2.
 bool tile_per_thread(int dtype, bool decode, int R, int Cc, int r)
 {
     if ((int64_t)R * Cc < 131072) return false;
@@ -685,6 +687,7 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
                          hipStream_t s, RowMap rm, Fold fold)
 {
     if (pg <= 0) pg = R_all;
+    if (fold.coef && gelu) return hipErrorInvalidValue;
     const int R = rm.count(R_all);                          // tile rows this launch walks over
     if (R <= 0) return hipSuccess;
     if ((dtype == 0 || !fold.coef) && tile_per_thread(dtype, true, R, Cc, r))
@@ -714,7 +717,7 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
         return hipGetLastError();
     }
     auto run = dtype == 0     ? (gelu ? launch_tile_map<float, false, false, true, false, true> : launch_tile_map<float, false, false, true, false, false>)
-               : fold.coef ? (gelu ? launch_tile_map<bf16_t, true, false, true, false, true> : launch_tile_map<bf16_t, true, false, true, false, false>)
+               : fold.coef ? launch_tile_map<bf16_t, true, false, true, false, false>
                            : (gelu ? launch_tile_map<bf16_t, false, false, true, false, true> : launch_tile_map<bf16_t, false, false, true, false, false>);
     return run(nullptr, P, Dm, nullptr, Cmat, nullptr, R, Cc, r, pg, rm, 0, s, fold);
 }
