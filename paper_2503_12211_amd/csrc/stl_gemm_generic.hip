@@ -232,16 +232,19 @@ static hipError_t launch_large(const GemmDesc &g, const void *A, const void *B, 
     return hipGetLastError();
 }
 
-// Edge of the block: the one with the least predicted time, us, from the blocks per CU and the stages of a block, with what one stage
-// and the rest of a block take (fitted to 1515 products of 64 to 1500 tiles and 8 to 64 planes, timed in all three forms: the choice is
-// 0.3 % behind the fastest form on average; a block per CU hides less than two do).  Operands that both lie along the contraction
-// turn on their way to LDS, which costs the 32 x 32 blocks most.  us at 128 / 64 / 32, fp32 Yhat: 49 x (64 x 64 x 64) 16 / 6.9 / 4.1,
-// 32 x (300 x 300 x 300) 67 / 48 / 41, 32 x (256 x 16 x 256) 13.4 / 8.5 / 9.3, 24 x (512 x 96 x 256) 22 / 15.8 / 18.1, 56 x (384 x 384 x 384) 82 / 96 / 98,
-// 32 x (1024 x 128 x 128) 41 / 27 / 23; bf16 dX of 256 x 256 from 7 tile columns, r = 40, 24.4 / 21.6 / 28.4.  Furthest off: 64 x (128 x 300 x 300)
-// 48 / 34.5 / 42.7, taken at 32.
+// Edge of the block.  128 x 128 (a quarter of the operand traffic) once every CU has two, at contractions of one of its stages, which
+// store most of the time, one: bf16 dWhat (and the encode before it) of 512 x 512 from 4 tile rows, r = 16 (256 blocks), 16.8 us against 18.9 at 32;
+// the fp32 forward of 64 stacked problems of 82 x 32 x 82 tiles, r = 24 (1536 blocks), 80 against 87.
+// Below that the one with the least predicted time, us, from the blocks per CU and the stages of a block, with what one stage
+// and the rest of a block take (fitted to 1515 products of 64 to 1500 tiles and 8 to 64 planes, timed in all three forms; a block per CU
+// hides less than two do).  Operands that both lie along the contraction turn on their way to LDS, which costs the 32 x 32 blocks most.
+// us at 128 / 64 / 32, fp32 Yhat: 49 x (64 x 64 x 64) 16 / 6.9 / 4.1, 32 x (300 x 300 x 300) 67 / 48 / 41, 32 x (256 x 16 x 256) 13.4 / 8.5 / 9.3,
+// 24 x (512 x 96 x 256) 22 / 15.8 / 18.1, 56 x (384 x 384 x 384) 82 / 96 / 98, 32 x (1024 x 128 x 128) 41 / 27 / 23; bf16 dX of 256 x 256 from 7 tile
+// columns, r = 40, 24.4 / 21.6 / 28.4.  Furthest off: 64 x (128 x 300 x 300) 48 / 34.5 / 42.7, taken at 32.
 int generic_block(const GemmDesc &g)
 {
-    auto blocks = [&](int bt) { return (double)((g.Mi + bt - 1) / bt) * ((g.Nj + bt - 1) / bt) * g.batch * g.nb / 256; };
+    auto blocks = [&](int bt) { return (double)((g.Mi + bt - 1) / bt) * ((g.Nj + bt - 1) / bt) * g.batch * g.nb / 256; };    // per CU
+    if (g.Mi > 64 && g.Nj > 64 && blocks(128) >= (g.Kl <= 16 ? 1 : 2)) return 128;
     auto stages = [&](int kc) { return (double)((g.Kl + kc - 1) / kc); };
     const bool turns = !g.a_kmajor && !g.b_kmajor;
     const double t32 = 1.9 + blocks(32) * stages(64) * (turns ? 0.68 : 0.59);

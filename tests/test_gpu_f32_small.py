@@ -53,8 +53,8 @@ def check_products(gu, p, dtype):
     assert np.abs(acc["dWhat"] - 1.0 - got["dWhat"]).max() <= 2.0 ** -22 * max(1.0, np.abs(got["dWhat"]).max())
 
 
-@pytest.mark.parametrize("dtype,M,K,N,r", [("f32", 130, 9, 250, 64), ("f32", 250, 254, 9, 40), ("f32", 17, 260, 190, 64), ("bf16", 130, 7, 250, 64),
-                                           ("bf16", 250, 254, 7, 40), ("bf16", 5, 190, 260, 48)])
+@pytest.mark.parametrize("dtype,M,K,N,r", [("f32", 250, 9, 254, 40), ("f32", 250, 254, 9, 40), ("f32", 17, 260, 190, 64), ("bf16", 250, 7, 254, 40),
+                                           ("bf16", 250, 254, 7, 40), ("bf16", 5, 250, 254, 40)])
 def test_blocks_of_64(gu, dtype, M, K, N, r):
     """Contractions of one stage of 32 over incomplete blocks: the forward product, the input gradient's and the weight gradient's in turn."""
     check_products(gu, stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=640 + M + K + N + r, dtype=dtype, with_dC=True), dtype)
