@@ -4,8 +4,8 @@
 //
 // Large planes are bound by the fp32 matrix cores (157 TFLOP/s): 128 x 128 blocks, operands in 16-byte pieces, the next stage in registers
 // while the current one is multiplied out of the other LDS buffer (one barrier per stage).  Small ones are bound by the latency
-// of a chain of stages and by idle CUs: 32 x 32 blocks with the contraction shared (gemm_small_kernel).  In between, mostly at
-// contractions of few stages, 64 x 64 blocks of the former kind.
+// of a chain of stages and by idle CUs: 32 x 32 blocks with the contraction shared (gemm_small_kernel).  In between, at contractions
+// of one stage, 64 x 64 blocks of the former kind.
 #include "stl_kernels.h"
 #include "stl_device.h"
 #include <algorithm>
@@ -15,16 +15,17 @@ namespace stl {
 
 // MFMA accumulator layout of v_mfma_f32_32x32x2_f32: lane (j = lane % 32, h = lane / 32) supplies A[row j][k = h] and
 // B[k = h][column j]; accumulator e of the lane is C[row 8 (e / 4) + 4 h + e % 4][column j].
-// Three wavefronts per SIMD for the 128 x 128 blocks (at the price of eleven spilled registers; left alone the compiler takes registers for two): 1024-cube,
+// Three wavefronts per SIMD (for the 128 x 128 blocks at the price of eleven spilled registers; left alone the compiler takes registers for two): 1024-cube,
 // r = 32, 770 -> 695 us, bf16 dWhat of 1024 x 1024 from four tile rows 57 -> 53.  With a sum into the output it helps some sizes and
 // costs others (r = 32 of the latter 123 -> 100, r = 8 31 -> 36) and stays at two.
 template <typename T, typename TO, bool ACC, int BT>
-__global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
+__global__ __launch_bounds__(256, BT == 128 && ACC ? 1 : 3) void gemm_generic_kernel(const T *__restrict__ A, const T *__restrict__ B,
                                                            TO *__restrict__ Out, int Mi, int Nj, int Kl, int a_km,
                                                            int b_km, int a_pg, int b_pg, int o_pg, int batch, int nb)
 {
     constexpr int KC = BT == 64 ? 32 : 16, PAD = 4;    // contraction elements per stage
     constexpr int F = BT / 64;                         // 32 x 32 products per wavefront and dimension
+    constexpr int CH = BT == 64 ? 2 : 1;               // sums of 16 contraction elements of a stage each, added up at the end
     constexpr int UNITS = BT * KC / 1024;              // 16-byte pieces per thread, operand and stage
     __shared__ __align__(16) float sA[2][KC][BT + PAD];    // [l][i]: a fragment read takes 32 consecutive i of one l
     __shared__ __align__(16) float sB[2][KC][BT + PAD];    // [l][j]
@@ -39,13 +40,15 @@ __global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_k
     // element (row, col) of plane p of an operand stored [row][col] with `ld` columns, rows in groups of pg
     auto at = [&](int row, int col, int pg, int ld) { return plane_row_base(row, pg, batch, ld) + (size_t)p * pg * ld + col; };
     const int i0 = by * BT, j0 = blockIdx.x * BT;
-    f32x16_t acc[F][F];
+    f32x16_t acc[CH][F][F];
 #pragma unroll
-    for (int a = 0; a < F; ++a)
+    for (int c = 0; c < CH; ++c)
 #pragma unroll
-        for (int b = 0; b < F; ++b)
+        for (int a = 0; a < F; ++a)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[a][b][e] = 0.f;
+            for (int b = 0; b < F; ++b)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[c][a][b][e] = 0.f;
 
     // stage -> registers -> LDS, four elements at a time along the dimension that is contiguous in memory
     f32x4_t ra[UNITS], rb[UNITS];
@@ -102,13 +105,14 @@ __global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_k
 #pragma unroll
             for (int u = 0; u < F; ++u)
 #pragma unroll
-                for (int v = 0; v < F; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u], fb[v], acc[u][v], 0, 0, 0);
+                for (int v = 0; v < F; ++v) acc[CH == 2 ? s >> 3 : 0][u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u], fb[v], acc[CH == 2 ? s >> 3 : 0][u][v], 0, 0, 0);
         }
         if (st + 1 < nst) {
             stage_in(buf ^ 1);                         // its readers passed the barrier below one stage ago
             __syncthreads();
         }
     }
+    if constexpr (CH == 2) acc[0][0][0] += acc[1][0][0];
 #pragma unroll
     for (int u = 0; u < F; ++u)
 #pragma unroll
@@ -118,8 +122,8 @@ __global__ __launch_bounds__(256, BT == 128 && !ACC ? 3 : 1) void gemm_generic_k
                 const int gi = i0 + wi + 32 * u + 8 * (e >> 2) + 4 * fh + (e & 3), gj = j0 + wj + 32 * v + fj;
                 if (gi < Mi && gj < Nj) {
                     TO *o = Out + at(o_r0 + gi, gj, o_pg, Nj);
-                    if (ACC) Elem<TO>::st(o, Elem<TO>::ld(o) + acc[u][v][e]);
-                    else Elem<TO>::st(o, acc[u][v][e]);
+                    if (ACC) Elem<TO>::st(o, Elem<TO>::ld(o) + acc[0][u][v][e]);
+                    else Elem<TO>::st(o, acc[0][u][v][e]);
                 }
             }
   }
@@ -235,22 +239,22 @@ static hipError_t launch_large(const GemmDesc &g, const void *A, const void *B, 
 // Edge of the block.  128 x 128 (a quarter of the operand traffic) once every CU has two, at contractions of one of its stages, which
 // store most of the time, one: bf16 dWhat (and the encode before it) of 512 x 512 from 4 tile rows, r = 16 (256 blocks), 16.8 us against 18.9 at 32;
 // the fp32 forward of 64 stacked problems of 82 x 32 x 82 tiles, r = 24 (1536 blocks), 80 against 87.
-// Below that the one with the least predicted time, us, from the blocks per CU and the stages of a block, with what one stage
-// and the rest of a block take (fitted to 1515 products of 64 to 1500 tiles and 8 to 64 planes, timed in all three forms; a block per CU
-// hides less than two do).  Operands that both lie along the contraction turn on their way to LDS, which costs the 32 x 32 blocks most.
-// us at 128 / 64 / 32, fp32 Yhat: 49 x (64 x 64 x 64) 16 / 6.9 / 4.1, 32 x (300 x 300 x 300) 67 / 48 / 41, 32 x (256 x 16 x 256) 13.4 / 8.5 / 9.3,
-// 24 x (512 x 96 x 256) 22 / 15.8 / 18.1, 56 x (384 x 384 x 384) 82 / 96 / 98, 32 x (1024 x 128 x 128) 41 / 27 / 23; bf16 dX of 256 x 256 from 7 tile
-// columns, r = 40, 24.4 / 21.6 / 28.4.  Furthest off: 64 x (128 x 300 x 300) 48 / 34.5 / 42.7, taken at 32.
+// Below that 32 x 32; but at contractions of up to 32, where its four wavefronts have a stage of 64 for half of it or less, 64 x 64 where a
+// prediction of both times, us, from the blocks per CU says so (fitted to 264 products of 64 to 1500 tiles and 8 to 64 planes); the
+// sums are the same bit for bit.  Operands that both lie along the contraction turn on their way to LDS, which costs the 32 x 32
+// blocks more.  us at 128 / 64 / 32: fp32 Yhat
+// 32 x (256 x 16 x 256) 13.4 / 8.5 / 9.3, 64 x (256 x 32 x 256) 16.0 / 13.9 / 15.3, 8 x (96 x 16 x 96) 11.4 / 5.9 / 4.0; bf16 dX of 256 x 256 from
+// 7 tile columns, r = 40, 24.4 / 21.6 / 28.4, of 1000 x 64 from 6, r = 32, 21.4 / 18.2 / 21.8.
+// Longer contractions stay with the 32 x 32 blocks also where one of the others is ahead (56 x (384 x 384 x 384) 82 / 96 / 98, 64 x (128 x 300 x
+// 300) 48 / 34.5 / 42.7): those add a contraction up in one chain, these in four, with half the error against 64 bits (384 x 384 x 384 3.5e-7 / 1.8e-7).
 int generic_block(const GemmDesc &g)
 {
     auto blocks = [&](int bt) { return (double)((g.Mi + bt - 1) / bt) * ((g.Nj + bt - 1) / bt) * g.batch * g.nb / 256; };    // per CU
     if (g.Mi > 64 && g.Nj > 64 && blocks(128) >= (g.Kl <= 16 ? 1 : 2)) return 128;
-    auto stages = [&](int kc) { return (double)((g.Kl + kc - 1) / kc); };
+    if (g.Kl > 32) return 32;
     const bool turns = !g.a_kmajor && !g.b_kmajor;
-    const double t32 = 1.9 + blocks(32) * stages(64) * (turns ? 0.68 : 0.59);
-    const double t64 = 0.84 + std::max(2.0, std::ceil(blocks(64))) * (0.98 + 1.19 * stages(32));
-    const double t128 = 2.0 + std::max(1.5, std::ceil(blocks(128))) * (3.0 + 1.77 * stages(16));
-    return t32 <= t64 && t32 <= t128 ? 32 : t64 <= t128 ? 64 : 128;
+    const double t32 = 2.9 + blocks(32) * (turns ? 0.68 : 0.51), t64 = 1.4 + std::max(2.0, std::ceil(blocks(64))) * 2.13;
+    return t32 <= t64 ? 32 : 64;
 }
 
 template <typename T, typename TO, bool ACC>

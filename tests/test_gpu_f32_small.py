@@ -53,7 +53,7 @@ def check_products(gu, p, dtype):
     assert np.abs(acc["dWhat"] - 1.0 - got["dWhat"]).max() <= 2.0 ** -22 * max(1.0, np.abs(got["dWhat"]).max())
 
 
-@pytest.mark.parametrize("dtype,M,K,N,r", [("f32", 250, 9, 254, 40), ("f32", 250, 254, 9, 40), ("f32", 17, 260, 190, 64), ("bf16", 250, 7, 254, 40),
+@pytest.mark.parametrize("dtype,M,K,N,r", [("f32", 250, 9, 254, 40), ("f32", 250, 254, 9, 40), ("f32", 17, 254, 190, 64), ("bf16", 250, 7, 254, 40),
                                            ("bf16", 250, 254, 7, 40), ("bf16", 5, 250, 254, 40)])
 def test_blocks_of_64(gu, dtype, M, K, N, r):
     """Contractions of one stage of 32 over incomplete blocks: the forward product, the input gradient's and the weight gradient's in turn."""
@@ -68,3 +68,12 @@ def test_stacked_blocks_of_64(gu, nb, M, K, N, r):
     got = gu.aa_backward(*args, p["dC"], nb, "f32")
     for name, ref in zip(("dA", "dB", "dE_A", "dE_B", "dD"), planes.aa_backward(*args, p["dC"], nbatch=nb)):
         gu.check(got[name], ref, "f32", name)
+
+
+@pytest.mark.parametrize("dtype,M,K,N,r", [("f32", 250, 9, 254, 40), ("f32", 250, 32, 254, 40), ("bf16", 250, 7, 254, 40)])
+def test_blocks_of_64_add_up_as_blocks_of_32_do(gu, dtype, M, K, N, r):
+    """The same products with fewer planes, which take 32 x 32 blocks: bit for bit."""
+    p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=680 + K, dtype=dtype)
+    _, Y = gu.forward(p, dtype, flags=1, save_yhat=True)
+    few = dict(p, **{s: np.ascontiguousarray(p[s][:3]) for s in ("What", "E_X", "D")})
+    assert np.array_equal(Y[:3], gu.forward(few, dtype, flags=1, save_yhat=True)[1])
