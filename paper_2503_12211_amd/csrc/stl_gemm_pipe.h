@@ -16,6 +16,8 @@ constexpr int BKS = 32;                 // contraction elements per stage
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 #define STL_LDS(p) ((__attribute__((address_space(3))) char *)(p))
 
+typedef PlaneSplit Split;
+
 typedef float acc4_t __attribute__((ext_vector_type(4)));
 
 // Swizzles (16-byte chunk index XOR), chosen so that one access phase touches every bank once.  ds_read_b128 is served in
@@ -299,6 +301,12 @@ inline int cu_count()
 __device__ __forceinline__ int first_block(int total) { return (int)((long)(blockIdx.x & 7) * total / 8) + (int)(blockIdx.x >> 3); }
 __device__ __forceinline__ int end_block(int total) { return (int)((long)((blockIdx.x & 7) + 1) * total / 8); }
 __device__ __forceinline__ int block_step() { return (int)(gridDim.x >> 3); }
+// the end of the whole rounds of this XCD's share
+__device__ __forceinline__ int whole_end(int total)
+{
+    const int begin = (int)((long)(blockIdx.x & 7) * total / 8);
+    return begin + (end_block(total) - begin) / block_step() * block_step();
+}
 inline unsigned list_grid(long total, int workgroups)
 {
     const long wanted = total < workgroups ? (total + 7) / 8 * 8 : workgroups / 8 * 8;
@@ -484,6 +492,200 @@ struct WaveTile {
                 }
             });
         });
+    }
+};
+
+// Operands and output of a launch's plane products.
+template <typename TO>
+struct Products {
+    const bf16_t *A, *B;
+    TO *Out;
+    int Mi, Nj, Kl, a_pg, b_pg, o_pg, batch;
+};
+
+// One block of one plane at a time on a ring of NS LDS stages of 32 contraction elements, issued NS - 1 stages ahead of their use.
+// The ring's first LOW stages lie at the start of the workgroup's LDS, the others from byte HIGH on (LOW = NS: all of them side by side).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, int LOW = NS, int HIGH = 0>
+struct BlockRing {
+    static constexpr int NW = WAVES_M * WAVES_N, WM = BM / WAVES_M, WN = BN / WAVES_N, FM = WM / 16, FN = WN / 16;
+    static constexpr int OPER_BYTES = BM * BKS * 2, STAGE_BYTES = (BM + BN) * BKS * 2;
+    static constexpr int D = (BM + BN) / 16 / NW;          // DMA instructions per wavefront and stage
+    static constexpr int SLAB = slab_bytes<FM, FN, TO>();
+    static_assert(NS >= 3, "ring depth");
+    Frag<A_T, BM> fa;
+    Frag<B_T, BN> fb;
+    Src<A_T, BM, NW, KTAIL> sa;
+    Src<B_T, BN, NW, KTAIL> sb;
+    WaveTile<FM, FN> w;
+    static __device__ __forceinline__ int at(int s)        // LDS offset of stage s
+    {
+        const int i = s % NS;
+        return i < LOW ? i * STAGE_BYTES : HIGH + (i - LOW) * STAGE_BYTES;
+    }
+    __device__ __forceinline__ void init(int wave, int lane)
+    {
+        fa.init(wave / WAVES_N * WM, lane);
+        fb.init(wave % WAVES_N * WN, lane);
+    }
+    // point the DMA sources at block (i0, j0) of plane p of problem pb and put its first NS-1 stages in flight
+    __device__ __forceinline__ void start(const Products<TO> &g, int pb, int p, int i0, int j0, uint32_t smem_lds, int wave, int lane)
+    {
+        // the lane id as an opaque value: what the sources derive from it is computed per block and occupies no registers while
+        // the products run (spilled values would be reloaded between the loads issued here, and waited for with them)
+        int sl = lane;
+        asm volatile("" : "+v"(sl));
+        sa.init(g.A, A_T ? g.Mi : g.Kl, i0, g.Mi, wave, sl, p, g.batch, g.a_pg, pb * (A_T ? g.Kl : g.Mi), g.Kl);
+        sb.init(g.B, B_T ? g.Nj : g.Kl, j0, g.Nj, wave, sl, p, g.batch, g.b_pg, pb * (B_T ? g.Kl : g.Nj), g.Kl);
+        const int nks = (g.Kl + BKS - 1) / BKS;
+#pragma unroll
+        for (int s = 0; s < NS - 1; ++s) {
+            if (s < nks) {
+                sa.issue(smem_lds + at(s), wave, sl);
+                sb.issue(smem_lds + at(s) + OPER_BYTES, wave, sl);
+            }
+        }
+    }
+    // all stages of the block
+    __device__ __forceinline__ void multiply(int Kl, const char *smem, uint32_t smem_lds, int wave, int lane)
+    {
+        const int nks = (Kl + BKS - 1) / BKS;
+        w.clear();
+
+        // Stage s+NS-1 is issued in iteration s; stage s+1 must have landed at the top of iteration s (its fragments are
+        // fetched during stage s).  Stores of the previous epilogue may still be in flight: "at most N operations
+        // outstanding" then over-waits but never under-waits.
+        wait_stages<D, NS - 2>(nks - 1);
+        block_barrier();
+#pragma unroll
+        for (int a = 0; a < FM; ++a) w.va[a] = fa.read(smem + at(0), a);
+#pragma unroll
+        for (int b = 0; b < FN; ++b) w.vb[0][b] = fb.read(smem + at(0) + OPER_BYTES, b);
+
+        // One stage.  STEADY: there is a stage to refill -- known at compile time, so that the loop over these stages
+        // carries no test around the DMA instructions.  After the last stage the fragments of a stale ring slot are
+        // fetched and never used.
+        auto stage = [&](int s, auto par_c, auto steady_c) {
+            constexpr int PAR = decltype(par_c)::value;
+            constexpr bool STEADY = decltype(steady_c)::value;
+            const bool refill = STEADY || s + NS - 1 < nks;
+            if (STEADY) wait_vmcnt<D * (NS - 3)>();
+            else wait_stages<D, NS - 3>(nks - 2 - s < 0 ? 0 : nks - 2 - s);
+            block_barrier();   // stage s+1 visible to all; nobody reads stage s-1 any more
+            const uint32_t dst = smem_lds + at(s + NS - 1);
+            const char *nxt = smem + at(s + 1);
+            if (KTAIL && !STEADY && s == nks - 1) w.mask(PAR, Kl - s * BKS, lane);
+            w.template stage<PAR>([&](int f) { return fa.read(nxt, f); }, [&](int f) { return fb.read(nxt + OPER_BYTES, f); },
+                                  [&](auto a_c) {
+                                      // this wavefront's share of the refill, spread over the stage's products
+                                      constexpr int a = decltype(a_c)::value, NA = decltype(sa)::NI, NB = decltype(sb)::NI;
+                                      static_for<0, NA + NB>([&](auto j_c) {
+                                          constexpr int j = decltype(j_c)::value;
+                                          if constexpr (j * FM / (NA + NB) == a) {
+                                              if (refill) {
+                                                  if constexpr (j < NA) sa.issue_one(dst, wave, j);
+                                                  else sb.issue_one(dst + OPER_BYTES, wave, j - NA);
+                                              }
+                                          }
+                                      });
+                                  });
+            if (refill) {
+                sa.next_stage(wave, lane);
+                sb.next_stage(wave, lane);
+            }
+        };
+        using I0 = std::integral_constant<int, 0>;
+        using I1 = std::integral_constant<int, 1>;
+        const int n_refill = nks > NS - 1 ? nks - (NS - 1) : 0;
+        int s = 0;
+        for (; s + 1 < n_refill; s += 2) {
+            stage(s, I0{}, std::true_type{});
+            stage(s + 1, I1{}, std::true_type{});
+        }
+        for (; s < nks; s += 2) {
+            stage(s, I0{}, std::false_type{});
+            if (s + 1 < nks) stage(s + 1, I1{}, std::false_type{});
+        }
+    }
+    __device__ __forceinline__ void store(const Products<TO> &g, char *slab, int pb, int p, int i0, int j0, int wave, int lane) const
+    {
+        int el = lane;                                   // opaque, as above
+        asm volatile("" : "+v"(el));
+        w.template store<TO, ACC, false>(slab, g.Out + (size_t)p * g.o_pg * g.Nj, i0 + wave / WAVES_N * WM, j0 + wave % WAVES_N * WN, g.Mi, g.Nj,
+                                         pb * g.Mi, g.o_pg, g.batch, el);
+    }
+};
+
+// Parts of the blocks of a last round (Split in stl_kernels.h).
+template <Split S>
+struct Part {
+    static constexpr int N = S == Split::b128 ? 128 : 256;       // 128 rows by so many columns of a 256 x 256 block
+};
+
+// The parts of the blocks from `first` on of an XCD's share of the list (up to end_block), numbered block by block without those beyond
+// the output's edge, and dealt to its workgroups in turn.  A plane has PM x PN of them; two rows of parts lie in a row of blocks (one in the last
+// row, if the other does not exist), SN columns in a column of blocks.
+template <Split S>
+struct PartList {
+    static constexpr int N = Part<S>::N, SN = 256 / N;
+    int u, end, step, PM, PN;
+    __device__ __forceinline__ PartList(int first, int total, int tiles_m, int tiles_n, int Mi, int Nj)
+        : step(block_step()), PM((Mi + 127) / 128), PN((Nj + N - 1) / N)
+    {
+        auto before = [&](int v) {                       // parts of the blocks before block v
+            const int q = v / (tiles_m * tiles_n), rem = v - q * (tiles_m * tiles_n), bi = rem / tiles_n, bj = rem - bi * tiles_n;
+            return q * (PM * PN) + 2 * bi * PN + rows(bi) * SN * bj;
+        };
+        u = before(first) + (int)(blockIdx.x >> 3);
+        end = before(end_block(total));
+    }
+    __device__ __forceinline__ int rows(int bi) const { return PM - 2 * bi < 2 ? PM - 2 * bi : 2; }
+    // this workgroup's next part: false if there is none
+    __device__ __forceinline__ bool next(int batch, int &pb, int &p, int &i0, int &j0)
+    {
+        if (u >= end) return false;
+        const int q = u / (PM * PN);
+        int w = u - q * (PM * PN);
+        const int bi = w / (2 * PN);
+        w -= bi * (2 * PN);
+        const int bj = w / (rows(bi) * SN);
+        w -= bj * (rows(bi) * SN);
+        const int cols = PN - SN * bj < SN ? PN - SN * bj : SN, row = w / cols;
+        pb = q / batch;
+        p = q - pb * batch;
+        i0 = (2 * bi + row) * 128;
+        j0 = (SN * bj + w - row * cols) * N;
+        u += step;
+        return true;
+    }
+};
+
+// Parts of the last blocks, one after the other, on a ring of their own; the first part's loads are in flight when run begins.
+template <Split S, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, int LOW = NS, int HIGH = 0>
+struct PartWalk {
+    BlockRing<128, Part<S>::N, 2, 4, NS, A_T, B_T, TO, ACC, KTAIL, LOW, HIGH> ring;
+    PartList<S> list;
+    bool more;
+    int pb, p, i0, j0;
+    __device__ __forceinline__ PartWalk(const Products<TO> &g, int first, int total, int tiles_m, int tiles_n, uint32_t smem_lds, int wave, int lane)
+        : list(first, total, tiles_m, tiles_n, g.Mi, g.Nj)
+    {
+        more = list.next(g.batch, pb, p, i0, j0);
+        if (more) ring.start(g, pb, p, i0, j0, smem_lds, wave, lane);
+    }
+    __device__ __forceinline__ void run(const Products<TO> &g, char *smem, uint32_t smem_lds, char *slab, int wave, int lane)
+    {
+        int fl = lane;                                   // opaque, as above
+        asm volatile("" : "+v"(fl));
+        ring.init(wave, fl);
+        while (more) {
+            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
+            block_barrier();
+            int npb, np, ni0, nj0;
+            more = list.next(g.batch, npb, np, ni0, nj0);
+            if (more) ring.start(g, npb, np, ni0, nj0, smem_lds, wave, lane);
+            ring.store(g, slab, pb, p, i0, j0, wave, lane);
+            if (more) pb = npb, p = np, i0 = ni0, j0 = nj0;
+        }
     }
 };
 

@@ -26,135 +26,66 @@ namespace stl {
 // (plane, block) list.  When a block's MFMA loop ends, the first ring stages of the NEXT block are put in
 // flight before the epilogue starts, so the HBM/L2 latency of the refill and the store traffic of the
 // epilogue overlap instead of adding up.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
-                                                        TO *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m,
-                                                        int tiles_n, int total, int a_pg, int b_pg, int o_pg, int batch)
+//
+// SPLIT (256 x 256 only): the blocks of a last round that is not full are dealt to all workgroups in parts (see pipe_split).
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, pipe::Split SPLIT>
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const pipe::Products<TO> g, int tiles_m, int tiles_n, int total)
 {
     using namespace pipe;
-    constexpr int NW = WAVES_M * WAVES_N, WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int FM = WM / 16, FN = WN / 16;
-    constexpr int OPER_BYTES = BM * BKS * 2, STAGE_BYTES = (BM + BN) * BKS * 2;
-    constexpr int D = (BM + BN) / 16 / NW;                 // DMA instructions per wavefront and stage
-    constexpr int SLAB = slab_bytes<FM, FN, TO>();
-    static_assert(NS >= 3, "ring depth");
     extern __shared__ __align__(16) char smem[];
+    typedef BlockRing<BM, BN, WAVES_M, WAVES_N, NS, A_T, B_T, TO, ACC, KTAIL> Ring;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: LDS-DMA destinations stay in SGPRs
-    char *slab = smem + NS * STAGE_BYTES + wave * SLAB;
-    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    char *slab = smem + NS * Ring::STAGE_BYTES + wave * Ring::SLAB;
     const int per_plane = tiles_m * tiles_n;
-    const int nks = (Kl + BKS - 1) / BKS;
     const uint32_t smem_lds = (uint32_t)(uintptr_t)STL_LDS(smem);
-
-    Frag<A_T, BM> fa;
-    Frag<B_T, BN> fb;
-    fa.init(wm * WM, lane);
-    fb.init(wn * WN, lane);
 
     // block list, block v -> (stacked problem, plane, block row, block column); the blocks of a workgroup are first_block(),
     // + block_step() ... below end_block()
     auto locate = [&](int v, int &pb, int &p, int &i0, int &j0) {
         const int q = v / per_plane;                 // (stacked problem, plane)
         const int rem = v - q * per_plane;
-        pb = q / batch;
-        p = q - pb * batch;
+        pb = q / g.batch;
+        p = q - pb * g.batch;
         i0 = (rem / tiles_n) * BM;
         j0 = (rem % tiles_n) * BN;
     };
-
-    Src<A_T, BM, NW, KTAIL> sa;
-    Src<B_T, BN, NW, KTAIL> sb;
-    auto start_block = [&](int v) {      // point the DMA sources at block v and put its first NS-1 stages in flight
-        // the lane id as an opaque value: what the sources derive from it is computed per block and occupies no registers while
-        // the products run (spilled values would be reloaded between the loads issued here, and waited for with them)
-        int sl = lane;
-        asm volatile("" : "+v"(sl));
-        int pb, p, i0, j0;
-        locate(v, pb, p, i0, j0);
-        sa.init(A, A_T ? Mi : Kl, i0, Mi, wave, sl, p, batch, a_pg, pb * (A_T ? Kl : Mi), Kl);
-        sb.init(B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, b_pg, pb * (B_T ? Kl : Nj), Kl);
-#pragma unroll
-        for (int s = 0; s < NS - 1; ++s) {
-            if (s < nks) {
-                sa.issue(smem_lds + s * STAGE_BYTES, wave, sl);
-                sb.issue(smem_lds + s * STAGE_BYTES + OPER_BYTES, wave, sl);
-            }
-        }
+    Ring ring;
+    ring.init(wave, lane);
+    int pb, p, i0, j0;
+    auto start_block = [&](int v) {
+        int npb, np, ni0, nj0;
+        locate(v, npb, np, ni0, nj0);
+        ring.start(g, npb, np, ni0, nj0, smem_lds, wave, lane);
     };
 
-    const int step = block_step(), end = end_block(total);
+    const int step = block_step(), end = SPLIT == Split::none ? end_block(total) : whole_end(total);
     int v = first_block(total);
-    if (v < end) start_block(v);
-
-    WaveTile<FM, FN> w;
-    for (; v < end; v += step) {
-        int pb, p, i0, j0;
-        locate(v, pb, p, i0, j0);
-        w.clear();
-
-        // Stage s+NS-1 is issued in iteration s; stage s+1 must have landed at the top of iteration s (its fragments are
-        // fetched during stage s).  Stores of the previous epilogue may still be in flight: "at most N operations
-        // outstanding" then over-waits but never under-waits.
-        wait_stages<D, NS - 2>(nks - 1);
-        block_barrier();
-#pragma unroll
-        for (int a = 0; a < FM; ++a) w.va[a] = fa.read(smem, a);
-#pragma unroll
-        for (int b = 0; b < FN; ++b) w.vb[0][b] = fb.read(smem + OPER_BYTES, b);
-
-        // One stage.  STEADY: there is a stage to refill -- known at compile time, so that the loop over these stages
-        // carries no test around the DMA instructions.  After the last stage the fragments of a stale ring slot are
-        // fetched and never used.
-        auto stage = [&](int s, auto par_c, auto steady_c) {
-            constexpr int PAR = decltype(par_c)::value;
-            constexpr bool STEADY = decltype(steady_c)::value;
-            const bool refill = STEADY || s + NS - 1 < nks;
-            if (STEADY) wait_vmcnt<D * (NS - 3)>();
-            else wait_stages<D, NS - 3>(nks - 2 - s < 0 ? 0 : nks - 2 - s);
-            block_barrier();   // stage s+1 visible to all; nobody reads stage s-1 any more
-            const uint32_t dst = smem_lds + ((s + NS - 1) % NS) * STAGE_BYTES;
-            const char *nxt = smem + ((s + 1) % NS) * STAGE_BYTES;
-            if (KTAIL && !STEADY && s == nks - 1) w.mask(PAR, Kl - s * BKS, lane);
-            w.template stage<PAR>([&](int f) { return fa.read(nxt, f); }, [&](int f) { return fb.read(nxt + OPER_BYTES, f); },
-                                  [&](auto a_c) {
-                                      // this wavefront's share of the refill, spread over the stage's products
-                                      constexpr int a = decltype(a_c)::value, NA = decltype(sa)::NI, NB = decltype(sb)::NI;
-                                      static_for<0, NA + NB>([&](auto j_c) {
-                                          constexpr int j = decltype(j_c)::value;
-                                          if constexpr (j * FM / (NA + NB) == a) {
-                                              if (refill) {
-                                                  if constexpr (j < NA) sa.issue_one(dst, wave, j);
-                                                  else sb.issue_one(dst + OPER_BYTES, wave, j - NA);
-                                              }
-                                          }
-                                      });
-                                  });
-            if (refill) {
-                sa.next_stage(wave, lane);
-                sb.next_stage(wave, lane);
-            }
-        };
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        const int n_refill = nks > NS - 1 ? nks - (NS - 1) : 0;
-        int s = 0;
-        for (; s + 1 < n_refill; s += 2) {
-            stage(s, I0{}, std::true_type{});
-            stage(s + 1, I1{}, std::true_type{});
+    if constexpr (SPLIT == Split::none) {
+        if (v < end) start_block(v);
+        for (; v < end; v += step) {
+            locate(v, pb, p, i0, j0);
+            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
+            // every wavefront is done with the ring: refill it for the next block before storing this one
+            block_barrier();
+            if (v + step < end) start_block(v + step);
+            ring.store(g, slab, pb, p, i0, j0, wave, lane);
         }
-        for (; s < nks; s += 2) {
-            stage(s, I0{}, std::false_type{});
-            if (s + 1 < nks) stage(s + 1, I1{}, std::false_type{});
+    } else {
+        typedef PartWalk<SPLIT, SPLIT == Split::b128 ? 8 : 5, A_T, B_T, TO, ACC, KTAIL> Parts;
+        start_block(v);                                          // every workgroup has a whole block: total >= the grid
+        for (;;) {
+            locate(v, pb, p, i0, j0);
+            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
+            block_barrier();
+            if (v + step >= end) break;
+            start_block(v + step);
+            ring.store(g, slab, pb, p, i0, j0, wave, lane);
+            v += step;
         }
-
-        // every wavefront is done with the ring: refill it for the next block before storing this one
-        block_barrier();
-        if (v + step < end) start_block(v + step);
-        int el = lane;                                   // opaque, as above
-        asm volatile("" : "+v"(el));
-        w.template store<TO, ACC, false>(slab, Out + (size_t)p * o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, pb * Mi, o_pg, batch,
-                                             el);
+        Parts parts(g, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
+        ring.store(g, slab, pb, p, i0, j0, wave, lane);
+        parts.run(g, smem, smem_lds, slab, wave, lane);
     }
 }
 
@@ -187,28 +118,42 @@ bool plane_gemm_pipe_eligible(const GemmDesc &g)
 //   dXhat  208 x 128 x 624,  24: 17 / 13 / 12 / 7.8  3064 x 352 x 688, 12: 42 / 45 / 37 / 55
 //   dWhat 1024 x 1024 x 1024, 8: 30 / 26 / 26 / 45   1024 x 1024 x 1024, 32: 77 / 101 / 116 / 189  2048 x 256 x 256, 49: 49 / 38 / 35 / 40
 //   added to what is there  256 x 512 x 512, 49: 26 / 30 / 29 / 41   1024 x 1024 x 1024, 8: 39 / 31 / 31 / 50
+//
+// Split: what is left of the 256 x 256 blocks behind their last whole round (pipe_split) takes a time of the same form, in parts of 128 x 256 or
+// 128 x 128; so does whole + parts compare with the other blocks.  Coefficients: least squares over 320 shapes of 1 to 8 rounds that end in one
+// that is not full, 1.1 % slower than the fastest on average where taken at face value, but up to 19 % slower than without parts; taken where
+// 5 % ahead, on 1 of the 320 more than 2 % slower (3), and all of them 2.1 % faster in the mean.  us whole / 128 x 256 / 128 x 128:
+//   Yhat  1024 x 1024 x 1024, 49 (3.06 rounds): 111 / 104 / 103    4096 x 1024 x 256, 24 (1.5): 57 / 53 / 59    1500 x 1024 x 768, 16 (1.13): 51 / 42 / 40
+//   dXhat 1024 x 1024 x 1024, 20 (1.25): 50 / 43 / 41              3200 x 192 x 768, 32 (1.63): 43 / 49 / 50
+//   dWhat 3200 x 768 x 768, 32 (1.13): 161 / 139 / 129             added to what is there, 3072 x 768 x 1024, 32 (1.5): 195 / 171 / 190
 namespace {
 struct BlockCost {
     int m, n, workgroups;
     double round, round_stage, round_out;              // a full round: base, per stage of 32, per output size (2 bytes)
     double last, last_stage, last_out;                 // a last one that is not full
     double load_stage, load_out;                       // times the share of workgroups that it occupies
-    double time(const GemmDesc &g) const
+    double time(double full, double rem, const GemmDesc &g) const
     {
         const double st = (g.Kl + pipe::BKS - 1) / pipe::BKS, out = g.out_f32 ? (g.accumulate ? 4 : 2) : 1;
-        const double x = (double)((g.Mi + m - 1) / m) * ((g.Nj + n - 1) / n) * g.batch * g.nb / workgroups;
-        const double full = std::floor(x), rem = x - full;
         return full * (round + round_stage * st + round_out * out) +
                (rem > 0 ? last + last_stage * st + last_out * out + rem * (load_stage * st + load_out * out) : 0);
+    }
+    double blocks(const GemmDesc &g) const { return (double)((g.Mi + m - 1) / m) * ((g.Nj + n - 1) / n) * g.batch * g.nb; }
+    double time(const GemmDesc &g) const
+    {
+        const double x = blocks(g) / workgroups, full = std::floor(x);
+        return time(full, x - full, g);
     }
 };
 constexpr BlockCost kCost[] = {{256, 256, 256, 0.94, 0.80, 4.58, 4.18, 0.60, 1.44, 0.19, 2.10},        // in the order of PipeBlock
                                {128, 256, 256, 1.34, 0.52, 2.40, 3.94, 0.42, 1.11, 0.12, 1.02},
                                {128, 128, 512, 1.08, 0.60, 2.13, 3.32, 0.36, 0.57, 0.32, 1.84},
                                {64, 64, 512, 1.86, 0.26, 0.59, 3.19, 0.14, 0.18, 0.19, 1.23}};
-}  // namespace
+constexpr BlockCost kParts[] = {{128, 256, 256, 0.10, 0.37, 2.72, 4.15, 0.20, 1.58, 0.08, 1.00},       // behind whole rounds of 256 x 256
+                                {128, 128, 256, 1.56, 0.27, 1.31, 5.24, 0.08, 0.70, 0.16, 0.18}};
 
-PipeBlock pipe_block(const GemmDesc &g)
+// the choice of pipe_block and pipe_split
+void pipe_choice(const GemmDesc &g, PipeBlock *block, PlaneSplit *split)
 {
     int best = 0;
     double t = kCost[0].time(g);
@@ -216,15 +161,47 @@ PipeBlock pipe_block(const GemmDesc &g)
         const double ti = kCost[i].time(g);
         if (ti < t) t = ti, best = i;
     }
-    return (PipeBlock)best;
+    *block = (PipeBlock)best;
+    *split = PlaneSplit::none;
+    // in parts: the whole-line form and the fp32 outputs
+    if (g.nb > 1 || !(g.out_f32 || (!g.a_kmajor && g.Kl % 64 == 0))) return;
+    const double blocks = kCost[0].blocks(g), x = blocks / kCost[0].workgroups, full = std::floor(x);
+    if (full < 1 || x == full || blocks < pipe::cu_count()) return;      // every workgroup begins with a whole block
+    t *= 0.95;
+    for (int i = 0; i < 2; ++i) {
+        const double parts = (x - full) * kParts[i].blocks(g) / blocks, whole = std::floor(parts);
+        const double ti = kCost[0].time(full, 0, g) + kParts[i].time(whole, parts - whole, g);
+        if (ti < t) {
+            t = ti;
+            *block = PipeBlock::b256;
+            *split = i ? PlaneSplit::b128 : PlaneSplit::b128x256;
+        }
+    }
+}
+}  // namespace
+
+PipeBlock pipe_block(const GemmDesc &g)
+{
+    PipeBlock b;
+    PlaneSplit s;
+    pipe_choice(g, &b, &s);
+    return b;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL>
+PlaneSplit pipe_split(const GemmDesc &g)
+{
+    PipeBlock b;
+    PlaneSplit s;
+    pipe_choice(g, &b, &s);
+    return s;
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, pipe::Split SPLIT>
 static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    constexpr int NW = WAVES_M * WAVES_N;
-    auto kern = gemm_pipe_kernel<BM, BN, WAVES_M, WAVES_N, NS, A_T, B_T, TO, ACC, KTAIL>;
-    constexpr int smem = NS * (BM + BN) * pipe::BKS * 2 + NW * pipe::slab_bytes<BM / WAVES_M / 16, BN / WAVES_N / 16, TO>();
+    auto kern = gemm_pipe_kernel<BM, BN, WAVES_M, WAVES_N, NS, A_T, B_T, TO, ACC, KTAIL, SPLIT>;
+    typedef pipe::BlockRing<BM, BN, WAVES_M, WAVES_N, NS, A_T, B_T, TO, ACC, KTAIL> Ring;
+    constexpr int smem = NS * Ring::STAGE_BYTES + Ring::NW * Ring::SLAB;
     static_assert(smem <= 160 * 1024, "LDS budget");
     constexpr int per_cu = 160 * 1024 / smem > 2 ? 2 : 160 * 1024 / smem;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
@@ -234,19 +211,30 @@ static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
     const int wgs = pipe::cu_count() * per_cu;                   // they walk the block list
     const unsigned grid = pipe::list_grid(total, wgs);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), smem, s, (const bf16_t *)A, (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj,
-                       g.Kl, tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
+    if (SPLIT != pipe::Split::none && total < (long)grid) return hipErrorInvalidValue;      // every workgroup begins with a whole block
+    const pipe::Products<TO> pr{(const bf16_t *)A, (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, g.a_rows_per_group(), g.b_rows_per_group(),
+                                g.o_rows_per_group(), g.batch};
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Ring::NW * 64), smem, s, pr, tiles_m, tiles_n, (int)total);
     return hipGetLastError();
 }
 
 template <bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL>
 static hipError_t launch_pipe_block(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
+    using pipe::Split;
     switch (pipe_block(g)) {
-        case PipeBlock::b256: return launch_pipe_cfg<256, 256, 2, 4, 4, A_T, B_T, TO, ACC, KTAIL>(g, A, B, Out, s);
-        case PipeBlock::b128x256: return launch_pipe_cfg<128, 256, 2, 4, 5, A_T, B_T, TO, ACC, KTAIL>(g, A, B, Out, s);
-        case PipeBlock::b128: return launch_pipe_cfg<128, 128, 2, 2, 4, A_T, B_T, TO, ACC, KTAIL>(g, A, B, Out, s);
-        case PipeBlock::b64: return launch_pipe_cfg<64, 64, 2, 2, 8, A_T, B_T, TO, ACC, KTAIL>(g, A, B, Out, s);
+        case PipeBlock::b256:
+            if constexpr (sizeof(TO) == 4) {
+                switch (pipe_split(g)) {
+                    case Split::b128x256: return launch_pipe_cfg<256, 256, 2, 4, 4, A_T, B_T, TO, ACC, KTAIL, Split::b128x256>(g, A, B, Out, s);
+                    case Split::b128: return launch_pipe_cfg<256, 256, 2, 4, 4, A_T, B_T, TO, ACC, KTAIL, Split::b128>(g, A, B, Out, s);
+                    case Split::none: break;
+                }
+            }
+            return launch_pipe_cfg<256, 256, 2, 4, 4, A_T, B_T, TO, ACC, KTAIL, Split::none>(g, A, B, Out, s);
+        case PipeBlock::b128x256: return launch_pipe_cfg<128, 256, 2, 4, 5, A_T, B_T, TO, ACC, KTAIL, Split::none>(g, A, B, Out, s);
+        case PipeBlock::b128: return launch_pipe_cfg<128, 128, 2, 2, 4, A_T, B_T, TO, ACC, KTAIL, Split::none>(g, A, B, Out, s);
+        case PipeBlock::b64: return launch_pipe_cfg<64, 64, 2, 2, 8, A_T, B_T, TO, ACC, KTAIL, Split::none>(g, A, B, Out, s);
     }
     return hipErrorInvalidValue;
 }

@@ -14,12 +14,13 @@ namespace stl {
 
 // B_T: second operand stored [l][j]; otherwise [j][l] (32-element stages, half lines, as in gemm_pipe_kernel).
 // Requires Kl % 64 == 0.  One problem per launch (no stacking).
-template <bool B_T>
-__global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
-                                                             bf16_t *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m,
-                                                             int tiles_n, int total, int a_pg, int b_pg, int o_pg, int batch)
+// SPLIT: the blocks of a last round that is not full are dealt to all workgroups in parts (see pipe_split), whose rings lie
+// on both sides of the epilogue slabs.
+template <bool B_T, pipe::Split SPLIT>
+__global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Products<bf16_t> g, int tiles_m, int tiles_n, int total)
 {
     using namespace pipe;
+    const int Mi = g.Mi, Nj = g.Nj, Kl = g.Kl, batch = g.batch;
     constexpr int BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = WM / 16, FN = WN / 16, NSB = 4;
     constexpr int A_SLOT = BM * 128, B_STAGE = BN * BKS * 2, B_BASE = 3 * A_SLOT;
     constexpr int SLAB = slab_bytes<FM, FN, bf16_t>();
@@ -59,8 +60,8 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
         asm volatile("" : "+v"(sl));
         int p, i0, j0;
         locate(v, p, i0, j0);
-        sa.init(A, Kl, i0, Mi, wave, sl, p, batch, a_pg, 0);
-        sb.init(B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, b_pg, 0, Kl);
+        sa.init(g.A, Kl, i0, Mi, wave, sl, p, batch, g.a_pg, 0);
+        sb.init(g.B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, g.b_pg, 0, Kl);
         sa.template issue_half<0>(smem_lds + a_slot(0), wave);
         sb.issue(smem_lds + b_slot(0), wave, sl);
         sa.template issue_half<1>(smem_lds + a_slot(0), wave);
@@ -72,16 +73,9 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
         }
     };
 
-    const int step = block_step(), end = end_block(total);
-    int v = first_block(total);
-    if (v < end) start_block(v);
-
     WaveTile<FM, FN> w;
-    for (; v < end; v += step) {
-        int p, i0, j0;
-        locate(v, p, i0, j0);
+    auto multiply = [&]() {
         w.clear();
-
         // Loads complete in the order they were issued.  Before the first fragments are read H0, B0, H1 must have
         // landed: everything but the last eight instructions (B1 H2 B2 H3) when the contraction has more than one
         // pair, everything but B1 otherwise.  (Stores of the previous epilogue may still be in flight: "at most N
@@ -141,14 +135,40 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__res
         }
         stage(s, I0{}, F_{}, F_{}, W0{});        // s = nks - 2, nks - 1
         stage(s + 1, I1{}, F_{}, F_{}, WN_{});
-
-        // every wavefront is done with the ring: refill it for the next block before storing this one
-        block_barrier();
-        if (v + step < end) start_block(v + step);
+    };
+    auto store_block = [&](int v) {
         int el = lane;                                   // opaque, as above
         asm volatile("" : "+v"(el));
-        w.template store<bf16_t, false, false>(slab, Out + (size_t)p * o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, o_pg, batch,
-                                                   el);
+        int p, i0, j0;
+        locate(v, p, i0, j0);
+        w.template store<bf16_t, false, false>(slab, g.Out + (size_t)p * g.o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, g.o_pg, batch, el);
+    };
+
+    const int step = block_step(), end = SPLIT == Split::none ? end_block(total) : whole_end(total);
+    int v = first_block(total);
+    if constexpr (SPLIT == Split::none) {
+        if (v < end) start_block(v);
+        for (; v < end; v += step) {
+            multiply();
+            // every wavefront is done with the ring: refill it for the next block before storing this one
+            block_barrier();
+            if (v + step < end) start_block(v + step);
+            store_block(v);
+        }
+    } else {
+        start_block(v);                                          // every workgroup has a whole block: total >= the grid
+        for (;;) {
+            multiply();
+            block_barrier();
+            if (v + step >= end) break;
+            start_block(v + step);
+            store_block(v);
+            v += step;
+        }
+        constexpr int STAGE = (128 + Part<SPLIT>::N) * BKS * 2, LOW = 2 * A_SLOT / STAGE, HIGH = 3 * A_SLOT, N_UP = (160 * 1024 - HIGH) / STAGE;
+        PartWalk<SPLIT, LOW + N_UP, false, B_T, bf16_t, false, false, LOW, HIGH> parts(g, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
+        store_block(v);
+        parts.run(g, smem, smem_lds, slab, wave, lane);
     }
 }
 
@@ -157,10 +177,10 @@ bool plane_gemm_wide_eligible(const GemmDesc &g)
     return plane_gemm_pipe_eligible(g) && !g.a_kmajor && !g.out_f32 && !g.accumulate && g.nb == 1 && g.Kl % 64 == 0 && pipe_block(g) == PipeBlock::b256;
 }
 
-template <bool B_T>
-static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+template <bool B_T, pipe::Split SPLIT>
+static hipError_t launch_wide_cfg(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    auto kern = gemm_pipe_wide_kernel<B_T>;
+    auto kern = gemm_pipe_wide_kernel<B_T, SPLIT>;
     constexpr int smem = 160 * 1024;
     static std::atomic<uint64_t> granted{0};               // of this instantiation
     if (const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), smem, smem, granted); e != hipSuccess) return e;
@@ -168,9 +188,23 @@ static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, v
     const long total = (long)tiles_m * tiles_n * g.batch;
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
     const unsigned grid = pipe::list_grid(total, pipe::cu_count());
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, (const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl,
-                       tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
+    if (SPLIT != pipe::Split::none && total < (long)grid) return hipErrorInvalidValue;      // every workgroup begins with a whole block
+    const pipe::Products<bf16_t> pr{(const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl, g.a_rows_per_group(), g.b_rows_per_group(),
+                                    g.o_rows_per_group(), g.batch};
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, pr, tiles_m, tiles_n, (int)total);
     return hipGetLastError();
+}
+
+template <bool B_T>
+static hipError_t launch_wide(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
+{
+    using pipe::Split;
+    switch (pipe_split(g)) {
+        case Split::b128x256: return launch_wide_cfg<B_T, Split::b128x256>(g, A, B, Out, s);
+        case Split::b128: return launch_wide_cfg<B_T, Split::b128>(g, A, B, Out, s);
+        case Split::none: return launch_wide_cfg<B_T, Split::none>(g, A, B, Out, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_plane_gemm_wide(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)

@@ -241,6 +241,10 @@ hipError_t launch_plane_gemm_rows(const GemmDesc &g, const void *A, const void *
 // bf16 MFMA path with LDS-DMA loads and a multi-stage LDS ring (contiguous dimensions a multiple of 8)
 enum class PipeBlock { b256, b128x256, b128, b64 };
 PipeBlock pipe_block(const GemmDesc &g);      // block of a plane that it takes
+// What a persistent launch of 256 x 256 blocks does with those of its last round when they are fewer than its workgroups: whole
+// (one each, the other workgroups idle), or in parts that are dealt to all of them
+enum class PlaneSplit { none, b128x256, b128 };
+PlaneSplit pipe_split(const GemmDesc &g);
 bool plane_gemm_pipe_eligible(const GemmDesc &g);
 hipError_t launch_plane_gemm_pipe(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 
