@@ -80,10 +80,12 @@ enum { STL_OP_ENCODE_WEIGHT = 0, STL_OP_FORWARD = 1, STL_OP_BACKWARD = 2, STL_OP
 
 /* forward variants (low byte of `flags`) and modifiers */
 enum {
-    STL_FLAG_AUTO = 0,      /* the library's choice, FUSED or UNFUSED.  FUSED (C decoded from unrounded fp32 sums) in bf16, r <= 32, k a
-                               multiple of 64, n of 32, no Xhat_save: up to m k n r / 64 = 4.2e6, and up to 256 blocks of 128 x 128
-                               outputs where k <= 512 (r <= 8), 448 (r <= 16) or 192 (r <= 32); but with Yhat_save, r > 24 and
-                               k > 64 only from 64 such blocks on.  UNFUSED everywhere else */
+    STL_FLAG_AUTO = 0,      /* the library's choice, with the results of FUSED or UNFUSED.  FUSED (C decoded from unrounded fp32 sums) in
+                               bf16, r <= 32, k a multiple of 64, n of 32, no Xhat_save: up to m k n r / 64 = 4.2e6; up to 256 blocks of
+                               128 x 128 outputs where k <= 512 (r <= 8), 448 (r <= 16) or 192 (r <= 32), but with Yhat_save, r > 24 and
+                               k > 64 only from 64 such blocks on; up to 128 rows (where the plane products are those of few rows) and 256
+                               blocks of 64 x 64 outputs (512 for r <= 16) where k <= 1024 (r <= 16) or 512.  UNFUSED everywhere else,
+                               in one launch with the same bits where that takes less time */
     STL_FLAG_UNFUSED = 1,   /* Algorithm 1 as three launches: encode -> plane products -> decode   */
     STL_FLAG_EPILOGUE = 2,  /* encode launch, then plane products with D applied in the epilogue   */
     STL_FLAG_FUSED = 3,     /* one launch: encode -> MFMA -> decode, no plane ever written to HBM   */

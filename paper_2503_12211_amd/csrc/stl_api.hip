@@ -110,26 +110,45 @@ FwdWs fwd_layout(const Dims &d, int variant)
 }
 
 // Automatic choice of stl_forward (bf16, no Xhat_save).  The single launch decodes the fp32 sums, three launches round Yhat to the
-// storage type in between.  It is taken
-//  - wherever every CU has at most one block and the contraction is short: a block walks all of it, 0.65 us per 16 tile columns at
-//    r <= 16 and 1.0 at r <= 32 behind 4 to 6 us, three launches take 13.1 us or more.  us of the single launch over 2 to 256
-//    blocks: r <= 8 7.6 at K <= 64, 8.5 to 9.4 at 128 and 14 to 14.7 at 256; r <= 16 7.6 to 8.5, 9.7 to 10.9 and 16 to 17;
-//    r <= 32 8.0 to 9.6 at K = 32, 10.4 to 11.7 at 64, 15 to 16 at 128.  The line is drawn where the gain is clear: of the 13.1 a
-//    host that enqueues slowly is a part (10 to 11 where it is quick);
-//  - at more than 24 planes not for fewer than 64 blocks where it also writes Yhat (2 bytes per thread and plane, up to 2.5 us): us of
-//    the three launches / the single one with Yhat_save, r = 32, K = 48, 4 / 16 / 32 / 64 / 256 blocks 10.8 / 12.0, 11.2 / 12.1, 11.7 / 12.5,
-//    14.1 / 12.9, 23.4 / 16.6, K = 32 10.2 / 10.9, 10.6 / 11.0, 11.1 / 11.3, 13.1 / 11.7, 22.1 / 14.8; K = 16 10.2 / 9.8 at 4; r = 24, K = 48
-//    10.6 / 10.8 at 4, 11.3 / 11.2 at 32; r = 16, K = 112 11.1 / 10.9 at 4;
-//  - up to about four million tile products per plane set whatever the contraction: few rows and a long contraction take longer
-//    than three launches would (m = 32, n = 512, r = 8: k = 1024 14.2 against 13.1, k = 2048 25 against 13.2), but such calls keep
-//    the unrounded result they have always had, and STL_FLAG_UNFUSED is there for the other.
-// Three launches everywhere else.
-bool auto_single_launch(const Dims &d, bool yhat_save)
+// storage type in between.  The first is taken
+//  - wherever every CU has at most one block of 32 x 32 tiles and the contraction is short: us, single launch / three: 256 such blocks, r <= 8
+//    9.4 / 13 at K = 128, r <= 16 10.9 / 13 at 112, r <= 32 9.6 / 15 at 32; fewer blocks less (stl_fused_small.hip);
+//  - but at more than 24 planes not for fewer than 64 blocks where it also writes Yhat;
+//  - up to about four million tile products per plane set whatever the contraction (m = 32, k = 2048, n = 512, r = 8 8.5 / 11); few rows and
+//    a contraction of thousands of tile columns take longer than three launches would, but such calls keep the unrounded result they have always
+//    had, and STL_FLAG_UNFUSED is there for the other;
+//  - for up to 32 tile rows on up to 256 blocks of 16 x 16 tiles (512 at up to 16 planes), whose three launches add the contraction up in eight
+//    parts, while it is short: us, 1 to 32 tile rows, up to 4096 tile columns, single launch / three: r <= 8, K = 256 6.0 to 8.4 / 10.5 to 12.9, r <= 16
+//    6.8 to 13.5 / 10.5 to 15.6, r <= 32, K = 128 7.3 to 12.4 / 10.5 to 17.5.
+enum class AutoForward { unrounded, rounded, launches };
+
+// Where three launches would be taken, the single one that rounds like them takes less time on up to 256 blocks of 16 x 16 tiles (512 at up to 16
+// planes), and gives the same bits: its products add up in the same order (plane products of more than 32 tile rows do: `in_order`).  us, single
+// launch / three, 2 to 256 blocks: r <= 8, K = 384 7.2 to 10.2 / 10.5 to 14, K = 640 9.5 to 14.8 / 10.5 to 16.6, 768 10.8 to 17.1 / 10.5 to 16.9; r <= 16, K = 256
+// 6.5 to 10.2 / 10.5 to 15, 384 8.2 to 13.4 / 10.5 to 15.5, 512 9.7 to 16.9 / 10.5 to 16.8; r <= 32, K = 192 8.2 to 12.8 / 10.5 to 16.5, 256 9.9 to 15.5 / 10.4 to 16.8, 288 10.7
+// to 17.7 / 10.4 to 18, with Yhat_save 0.5 to 1 us more of the single launch alone.  384 and 512 blocks: r <= 8, K = 256 11.2 and 12.1 / 15; r <= 16, K = 192
+// 12.0 and 13.8 / 17.
+bool single_launch_rounded(const Dims &d, bool yhat_save)
 {
-    if ((double)d.M * d.K * d.N * d.r <= 4.2e6) return true;
+    if (!stl::small_forward(d.M, d.N, d.r)) return false;
+    const int64_t blocks = (int64_t)((d.M + 15) / 16) * ((d.N + 15) / 16);
+    if (blocks > 256) return d.K <= (d.r <= 8 ? 256 : 192);
+    return d.K <= (d.r <= 8 ? 640 : d.r <= 16 ? 384 : yhat_save ? 192 : 256);
+}
+
+AutoForward auto_forward(int dt, const Dims &d, bool yhat_save)
+{
+    if (!stl::block_forward_eligible(dt, d.M, d.K, d.N, d.r)) return AutoForward::launches;
+    if ((double)d.M * d.K * d.N * d.r <= 4.2e6) return AutoForward::unrounded;
     const int64_t blocks = (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32);
-    if (yhat_save && d.r > 24 && d.K > 16 && blocks < 64) return false;
-    return d.K <= (d.r <= 8 ? 128 : d.r <= 16 ? 112 : 48) && blocks <= 256;
+    const bool few_yhat = yhat_save && d.r > 24 && d.K > 16 && blocks < 64;
+    if (!few_yhat && d.K <= (d.r <= 8 ? 128 : d.r <= 16 ? 112 : 48) && blocks <= 256) return AutoForward::unrounded;
+    const stl::GemmDesc g{d.M, d.N, d.K, d.r, false, true, false, false, PG, 0, PG};
+    const stl::GemmPath path = stl::plane_gemm_path(dt, g);
+    if (path == stl::GemmPath::rows)
+        return stl::small_forward(d.M, d.N, d.r) && d.K <= (d.r <= 16 ? 256 : 128) ? AutoForward::unrounded : AutoForward::launches;
+    const bool in_order = path == stl::GemmPath::wide || path == stl::GemmPath::pipe;
+    return in_order && single_launch_rounded(d, yhat_save) ? AutoForward::rounded : AutoForward::launches;
 }
 
 struct BwdWs {
@@ -572,9 +591,8 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
     if (any_misaligned(X, What, E_X, D, C, Xhat_save, Yhat_save))
         return fail(STL_ERR_INVALID_ARG, "stl_forward: pointer not 16-byte aligned");
     const FwdWs w_declared = fwd_layout(d, variant);     // the workspace is checked against what the caller asked for
-    if (variant == STL_FLAG_AUTO && !Xhat_save && stl::block_forward_eligible(prob->dtype, d.M, d.K, d.N, d.r) &&
-        auto_single_launch(d, Yhat_save != nullptr))
-        variant = STL_FLAG_FUSED;
+    const AutoForward choice = variant == STL_FLAG_AUTO && !Xhat_save ? auto_forward(prob->dtype, d, Yhat_save != nullptr) : AutoForward::launches;
+    if (choice == AutoForward::unrounded) variant = STL_FLAG_FUSED;
     if (variant == STL_FLAG_PIPELINED && !stl::forward_pipeline_eligible(prob->dtype, d.M, d.K, d.N, d.r))
         return fail(STL_ERR_UNSUPPORTED,
                     "stl_forward: the pipelined variant needs bf16 storage, r <= 32, k and n multiples of 256, n >= 1024 and m >= 2048");
@@ -594,6 +612,10 @@ stl_status_t stl_forward(const stl_problem_t *prob, const void *X, const void *W
 
     if (variant == STL_FLAG_FUSED) {
         STL_HIP(stl::launch_block_forward(true, X, What, E_X, D, C, Yhat_save, d.M, d.K, d.N, d.r, gelu, PG, s), "forward/fused");
+        return STL_OK;
+    }
+    if (choice == AutoForward::rounded) {
+        STL_HIP(stl::launch_small_forward(X, What, E_X, D, C, Yhat_save, d.M, d.K, d.N, d.r, gelu, true, PG, s), "forward/fused, rounded");
         return STL_OK;
     }
     void *xhat = Xhat_save ? Xhat_save : (void *)(base + w.xhat);

@@ -326,6 +326,7 @@ hipError_t launch_block_forward(bool encode_in_kernel, const void *Xin, const vo
                                 void *C, void *Ysave, int M, int K, int N, int r, bool gelu, int pg, hipStream_t s)
 {
     if (pg <= 0) pg = M;
+    if (encode_in_kernel && small_forward(M, N, r)) return launch_small_forward(Xin, What, E, Dm, C, Ysave, M, K, N, r, gelu, false, pg, s);
     if (r <= 8) return launch_block_rp<8>(encode_in_kernel, Xin, What, E, Dm, C, Ysave, M, K, N, r, gelu, pg, s);
     if (r <= 16) return launch_block_rp<16>(encode_in_kernel, Xin, What, E, Dm, C, Ysave, M, K, N, r, gelu, pg, s);
     return launch_block_rp<32>(encode_in_kernel, Xin, What, E, Dm, C, Ysave, M, K, N, r, gelu, pg, s);

@@ -267,4 +267,10 @@ int block_forward_ring(bool encode, int M, int N, int r);      // LDS stages tha
 hipError_t launch_block_forward(bool encode_in_kernel, const void *Xin, const void *What, const void *E, const void *Dm,
                                 void *C, void *Ysave, int M, int K, int N, int r, bool gelu, int pg, hipStream_t s);
 
+// The single-launch form for few blocks, on 16 x 16 tiles each: whether it takes M x N output tiles (launch_block_forward picks it
+// then).  round: the sums are rounded to the storage type before they are decoded, as three launches do.
+bool small_forward(int M, int N, int r);
+hipError_t launch_small_forward(const void *X, const void *What, const void *E, const void *Dm, void *C, void *Ysave, int M, int K, int N,
+                                int r, bool gelu, bool round, int pg, hipStream_t s);
+
 }  // namespace stl
