@@ -516,9 +516,9 @@ struct BlockRing {
     Frag<B_T, BN> fb;
     Src<A_T, BM, NW, KTAIL> sa;
     Src<B_T, BN, NW, KTAIL> sb;
-    WaveTile<FM, FN> w;
     static __device__ __forceinline__ int at(int s)        // LDS offset of stage s
     {
+        if constexpr (LOW == NS) return s % NS * STAGE_BYTES;
         const int i = s % NS;
         return i < LOW ? i * STAGE_BYTES : HIGH + (i - LOW) * STAGE_BYTES;
     }
@@ -528,7 +528,7 @@ struct BlockRing {
         fb.init(wave % WAVES_N * WN, lane);
     }
     // point the DMA sources at block (i0, j0) of plane p of problem pb and put its first NS-1 stages in flight
-    __device__ __forceinline__ void start(const Products<TO> &g, int pb, int p, int i0, int j0, uint32_t smem_lds, int wave, int lane)
+    __device__ __forceinline__ void start(const Products<TO> &g, int nks, int pb, int p, int i0, int j0, uint32_t smem_lds, int wave, int lane)
     {
         // the lane id as an opaque value: what the sources derive from it is computed per block and occupies no registers while
         // the products run (spilled values would be reloaded between the loads issued here, and waited for with them)
@@ -536,7 +536,6 @@ struct BlockRing {
         asm volatile("" : "+v"(sl));
         sa.init(g.A, A_T ? g.Mi : g.Kl, i0, g.Mi, wave, sl, p, g.batch, g.a_pg, pb * (A_T ? g.Kl : g.Mi), g.Kl);
         sb.init(g.B, B_T ? g.Nj : g.Kl, j0, g.Nj, wave, sl, p, g.batch, g.b_pg, pb * (B_T ? g.Kl : g.Nj), g.Kl);
-        const int nks = (g.Kl + BKS - 1) / BKS;
 #pragma unroll
         for (int s = 0; s < NS - 1; ++s) {
             if (s < nks) {
@@ -545,10 +544,15 @@ struct BlockRing {
             }
         }
     }
-    // all stages of the block
-    __device__ __forceinline__ void multiply(int Kl, const char *smem, uint32_t smem_lds, int wave, int lane)
+    // Block (i0, j0) of plane p of problem pb, whose first loads are in flight: all its stages, next() (the loads of what follows) and its
+    // stores.  One function with its accumulators: in two, the compiler moves them from register to register in every stage (64 x 64
+    // blocks up to 10 % slower).
+    template <class F>
+    __device__ __forceinline__ void block(const Products<TO> &g, int nks, const char *smem, uint32_t smem_lds, char *slab, int pb, int p, int i0, int j0,
+                                          int wave, int lane, F &&next)
     {
-        const int nks = (Kl + BKS - 1) / BKS;
+        const int Kl = g.Kl;
+        WaveTile<FM, FN> w;
         w.clear();
 
         // Stage s+NS-1 is issued in iteration s; stage s+1 must have landed at the top of iteration s (its fragments are
@@ -605,9 +609,10 @@ struct BlockRing {
             stage(s, I0{}, std::false_type{});
             if (s + 1 < nks) stage(s + 1, I1{}, std::false_type{});
         }
-    }
-    __device__ __forceinline__ void store(const Products<TO> &g, char *slab, int pb, int p, int i0, int j0, int wave, int lane) const
-    {
+
+        // every wavefront is done with the ring: refill it for the next block before storing this one
+        block_barrier();
+        next();
         int el = lane;                                   // opaque, as above
         asm volatile("" : "+v"(el));
         w.template store<TO, ACC, false>(slab, g.Out + (size_t)p * g.o_pg * g.Nj, i0 + wave / WAVES_N * WM, j0 + wave % WAVES_N * WN, g.Mi, g.Nj,
@@ -628,9 +633,11 @@ template <Split S>
 struct PartList {
     static constexpr int N = Part<S>::N, SN = 256 / N;
     int u, end, step, PM, PN;
-    __device__ __forceinline__ PartList(int first, int total, int tiles_m, int tiles_n, int Mi, int Nj)
-        : step(block_step()), PM((Mi + 127) / 128), PN((Nj + N - 1) / N)
+    __device__ __forceinline__ void init(int first, int total, int tiles_m, int tiles_n, int Mi, int Nj)
     {
+        step = block_step();
+        PM = (Mi + 127) / 128;
+        PN = (Nj + N - 1) / N;
         auto before = [&](int v) {                       // parts of the blocks before block v
             const int q = v / (tiles_m * tiles_n), rem = v - q * (tiles_m * tiles_n), bi = rem / tiles_n, bj = rem - bi * tiles_n;
             return q * (PM * PN) + 2 * bi * PN + rows(bi) * SN * bj;
@@ -659,32 +666,30 @@ struct PartList {
     }
 };
 
-// Parts of the last blocks, one after the other, on a ring of their own; the first part's loads are in flight when run begins.
+// Parts of the last blocks, one after the other, on a ring of their own: begin() puts the first one's loads in flight, run() does the rest.
 template <Split S, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, int LOW = NS, int HIGH = 0>
 struct PartWalk {
     BlockRing<128, Part<S>::N, 2, 4, NS, A_T, B_T, TO, ACC, KTAIL, LOW, HIGH> ring;
     PartList<S> list;
     bool more;
     int pb, p, i0, j0;
-    __device__ __forceinline__ PartWalk(const Products<TO> &g, int first, int total, int tiles_m, int tiles_n, uint32_t smem_lds, int wave, int lane)
-        : list(first, total, tiles_m, tiles_n, g.Mi, g.Nj)
+    __device__ __forceinline__ void begin(const Products<TO> &g, int nks, int first, int total, int tiles_m, int tiles_n, uint32_t smem_lds, int wave, int lane)
     {
+        list.init(first, total, tiles_m, tiles_n, g.Mi, g.Nj);
         more = list.next(g.batch, pb, p, i0, j0);
-        if (more) ring.start(g, pb, p, i0, j0, smem_lds, wave, lane);
+        if (more) ring.start(g, nks, pb, p, i0, j0, smem_lds, wave, lane);
     }
-    __device__ __forceinline__ void run(const Products<TO> &g, char *smem, uint32_t smem_lds, char *slab, int wave, int lane)
+    __device__ __forceinline__ void run(const Products<TO> &g, int nks, const char *smem, uint32_t smem_lds, char *slab, int wave, int lane)
     {
         int fl = lane;                                   // opaque, as above
         asm volatile("" : "+v"(fl));
         ring.init(wave, fl);
         while (more) {
-            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
-            block_barrier();
-            int npb, np, ni0, nj0;
-            more = list.next(g.batch, npb, np, ni0, nj0);
-            if (more) ring.start(g, npb, np, ni0, nj0, smem_lds, wave, lane);
-            ring.store(g, slab, pb, p, i0, j0, wave, lane);
-            if (more) pb = npb, p = np, i0 = ni0, j0 = nj0;
+            const int cpb = pb, cp = p, ci0 = i0, cj0 = j0;
+            ring.block(g, nks, smem, smem_lds, slab, cpb, cp, ci0, cj0, wave, lane, [&]() {
+                more = list.next(g.batch, pb, p, i0, j0);
+                if (more) ring.start(g, nks, pb, p, i0, j0, smem_lds, wave, lane);
+            });
         }
     }
 };

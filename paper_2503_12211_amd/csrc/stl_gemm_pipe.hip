@@ -29,15 +29,18 @@ namespace stl {
 //
 // SPLIT (256 x 256 only): the blocks of a last round that is not full are dealt to all workgroups in parts (see pipe_split).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, pipe::Split SPLIT>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const pipe::Products<TO> g, int tiles_m, int tiles_n, int total)
+__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, TO *__restrict__ Out,
+                                                                      int Mi, int Nj, int Kl, int tiles_m, int tiles_n, int total, int a_pg, int b_pg,
+                                                                      int o_pg, int batch)
 {
     using namespace pipe;
+    const Products<TO> g{A, B, Out, Mi, Nj, Kl, a_pg, b_pg, o_pg, batch};
     extern __shared__ __align__(16) char smem[];
     typedef BlockRing<BM, BN, WAVES_M, WAVES_N, NS, A_T, B_T, TO, ACC, KTAIL> Ring;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: LDS-DMA destinations stay in SGPRs
     char *slab = smem + NS * Ring::STAGE_BYTES + wave * Ring::SLAB;
-    const int per_plane = tiles_m * tiles_n;
+    const int per_plane = tiles_m * tiles_n, nks = (g.Kl + BKS - 1) / BKS;
     const uint32_t smem_lds = (uint32_t)(uintptr_t)STL_LDS(smem);
 
     // block list, block v -> (stacked problem, plane, block row, block column); the blocks of a workgroup are first_block(),
@@ -52,11 +55,10 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const 
     };
     Ring ring;
     ring.init(wave, lane);
-    int pb, p, i0, j0;
     auto start_block = [&](int v) {
-        int npb, np, ni0, nj0;
-        locate(v, npb, np, ni0, nj0);
-        ring.start(g, npb, np, ni0, nj0, smem_lds, wave, lane);
+        int pb, p, i0, j0;
+        locate(v, pb, p, i0, j0);
+        ring.start(g, nks, pb, p, i0, j0, smem_lds, wave, lane);
     };
 
     const int step = block_step(), end = SPLIT == Split::none ? end_block(total) : whole_end(total);
@@ -64,28 +66,24 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const 
     if constexpr (SPLIT == Split::none) {
         if (v < end) start_block(v);
         for (; v < end; v += step) {
+            int pb, p, i0, j0;
             locate(v, pb, p, i0, j0);
-            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
-            // every wavefront is done with the ring: refill it for the next block before storing this one
-            block_barrier();
-            if (v + step < end) start_block(v + step);
-            ring.store(g, slab, pb, p, i0, j0, wave, lane);
+            ring.block(g, nks, smem, smem_lds, slab, pb, p, i0, j0, wave, lane, [&]() {
+                if (v + step < end) start_block(v + step);
+            });
         }
     } else {
-        typedef PartWalk<SPLIT, SPLIT == Split::b128 ? 8 : 5, A_T, B_T, TO, ACC, KTAIL> Parts;
+        PartWalk<SPLIT, SPLIT == Split::b128 ? 8 : 5, A_T, B_T, TO, ACC, KTAIL> parts;
         start_block(v);                                          // every workgroup has a whole block: total >= the grid
-        for (;;) {
+        for (; v < end; v += step) {
+            int pb, p, i0, j0;
             locate(v, pb, p, i0, j0);
-            ring.multiply(g.Kl, smem, smem_lds, wave, lane);
-            block_barrier();
-            if (v + step >= end) break;
-            start_block(v + step);
-            ring.store(g, slab, pb, p, i0, j0, wave, lane);
-            v += step;
+            ring.block(g, nks, smem, smem_lds, slab, pb, p, i0, j0, wave, lane, [&]() {
+                if (v + step < end) start_block(v + step);
+                else parts.begin(g, nks, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
+            });
         }
-        Parts parts(g, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
-        ring.store(g, slab, pb, p, i0, j0, wave, lane);
-        parts.run(g, smem, smem_lds, slab, wave, lane);
+        parts.run(g, nks, smem, smem_lds, slab, wave, lane);
     }
 }
 
@@ -212,9 +210,8 @@ static hipError_t launch_pipe_cfg(const GemmDesc &g, const void *A, const void *
     const int wgs = pipe::cu_count() * per_cu;                   // they walk the block list
     const unsigned grid = pipe::list_grid(total, wgs);
     if (SPLIT != pipe::Split::none && total < (long)grid) return hipErrorInvalidValue;      // every workgroup begins with a whole block
-    const pipe::Products<TO> pr{(const bf16_t *)A, (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj, g.Kl, g.a_rows_per_group(), g.b_rows_per_group(),
-                                g.o_rows_per_group(), g.batch};
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(Ring::NW * 64), smem, s, pr, tiles_m, tiles_n, (int)total);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(Ring::NW * 64), smem, s, (const bf16_t *)A, (const bf16_t *)B, (TO *)Out, g.Mi, g.Nj,
+                       g.Kl, tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
     return hipGetLastError();
 }
 

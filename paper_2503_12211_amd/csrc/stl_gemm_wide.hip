@@ -73,8 +73,11 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
         }
     };
 
-    WaveTile<FM, FN> w;
-    auto multiply = [&]() {
+    // block v, whose first loads are in flight: its stages, next() (the loads of what follows) and its stores
+    auto block = [&](int v, auto &&next) {
+        int p, i0, j0;
+        locate(v, p, i0, j0);
+        WaveTile<FM, FN> w;
         w.clear();
         // Loads complete in the order they were issued.  Before the first fragments are read H0, B0, H1 must have
         // landed: everything but the last eight instructions (B1 H2 B2 H3) when the contraction has more than one
@@ -135,12 +138,12 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
         }
         stage(s, I0{}, F_{}, F_{}, W0{});        // s = nks - 2, nks - 1
         stage(s + 1, I1{}, F_{}, F_{}, WN_{});
-    };
-    auto store_block = [&](int v) {
+
+        // every wavefront is done with the ring: refill it for the next block before storing this one
+        block_barrier();
+        next();
         int el = lane;                                   // opaque, as above
         asm volatile("" : "+v"(el));
-        int p, i0, j0;
-        locate(v, p, i0, j0);
         w.template store<bf16_t, false, false>(slab, g.Out + (size_t)p * g.o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, g.o_pg, batch, el);
     };
 
@@ -148,27 +151,20 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
     int v = first_block(total);
     if constexpr (SPLIT == Split::none) {
         if (v < end) start_block(v);
-        for (; v < end; v += step) {
-            multiply();
-            // every wavefront is done with the ring: refill it for the next block before storing this one
-            block_barrier();
-            if (v + step < end) start_block(v + step);
-            store_block(v);
-        }
+        for (; v < end; v += step)
+            block(v, [&]() {
+                if (v + step < end) start_block(v + step);
+            });
     } else {
-        start_block(v);                                          // every workgroup has a whole block: total >= the grid
-        for (;;) {
-            multiply();
-            block_barrier();
-            if (v + step >= end) break;
-            start_block(v + step);
-            store_block(v);
-            v += step;
-        }
         constexpr int STAGE = (128 + Part<SPLIT>::N) * BKS * 2, LOW = 2 * A_SLOT / STAGE, HIGH = 3 * A_SLOT, N_UP = (160 * 1024 - HIGH) / STAGE;
-        PartWalk<SPLIT, LOW + N_UP, false, B_T, bf16_t, false, false, LOW, HIGH> parts(g, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
-        store_block(v);
-        parts.run(g, smem, smem_lds, slab, wave, lane);
+        PartWalk<SPLIT, LOW + N_UP, false, B_T, bf16_t, false, false, LOW, HIGH> parts;
+        start_block(v);                                          // every workgroup has a whole block: total >= the grid
+        for (; v < end; v += step)
+            block(v, [&]() {
+                if (v + step < end) start_block(v + step);
+                else parts.begin(g, nks, end, total, tiles_m, tiles_n, smem_lds, wave, lane);
+            });
+        parts.run(g, nks, smem, smem_lds, slab, wave, lane);
     }
 }
 
