@@ -700,17 +700,17 @@ stl_status_t stl_backward(const stl_problem_t *prob, const void *X, const void *
     }
     // The weight gradient goes first: the pass that follows the second product (decode of dXhat) is bound by HBM and
     // finds the freshly written dXhat in the last-level cache, which a product in between would have flushed; the
-    // products themselves do not care which of them reads dYhat warm.
-    if (dWhat) {
-        // dWhat[p] = Xhat[p]^T * dYhat[p] : contraction over I, both operands stored [I][.]
-        stl::GemmDesc g{d.K, d.N, d.M, d.r, true, true, true, accumulate != 0, PG, PG, 0};
-        STL_HIP(stl::launch_plane_gemm(dt, g, xhat, dyhat, dWhat, s), "backward/dWhat");
-    }
-    if (dX || dE_X) {
-        // dXhat[p] = dYhat[p] * What[p]^T : contraction over J, What[p] is stored [L][J]
-        stl::GemmDesc g{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG};
-        STL_HIP(stl::launch_plane_gemm(dt, g, dyhat, What, dxhat, s), "backward/dXhat");
-    }
+    // products themselves do not care which of them reads dYhat warm.  Small ones run as one launch.
+    // dWhat[p] = Xhat[p]^T * dYhat[p] : contraction over I, both operands stored [I][.]
+    const stl::GemmDesc gw{d.K, d.N, d.M, d.r, true, true, true, accumulate != 0, PG, PG, 0};
+    // dXhat[p] = dYhat[p] * What[p]^T : contraction over J, What[p] is stored [L][J]
+    const stl::GemmDesc gx{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG};
+    if (dWhat && (dX || dE_X))
+        STL_HIP(stl::launch_plane_gemm_pair(dt, gw, xhat, dyhat, dWhat, gx, dyhat, What, dxhat, s), "backward/dWhat and dXhat");
+    else if (dWhat)
+        STL_HIP(stl::launch_plane_gemm(dt, gw, xhat, dyhat, dWhat, s), "backward/dWhat");
+    else if (dX || dE_X)
+        STL_HIP(stl::launch_plane_gemm(dt, gx, dyhat, What, dxhat, s), "backward/dXhat");
     if (dE_X) {
         // one pass over dXhat: dX = decode with E_X (if asked for), dE_X = sum over tiles of dXhat (x) x
         STL_HIP(stl::launch_decode_outer(dt, dxhat, E_X, dX, X, dE_X, pair ? part2 : part, d.M, d.K, d.r, accumulate, PG, s,
@@ -885,9 +885,8 @@ stl_status_t stl_aa_backward(const stl_problem_t *prob, int64_t nbatch, const vo
                 "aa_backward/dYhat + dD");
         const stl::GemmDesc ga{d.M, d.K, d.N, d.r, false, bt, false, false, PG, PG, PG, nb};
         const stl::GemmDesc gb{bt ? d.N : d.K, bt ? d.K : d.N, d.M, d.r, true, true, false, false, PG, PG, PG, nb};
-        STL_HIP(stl::launch_plane_gemm(dt, ga, dyhat, Bhat_saved, dahat, s), "aa_backward/dAhat");
-        STL_HIP(bt ? stl::launch_plane_gemm(dt, gb, dyhat, Ahat_saved, dbhat, s) : stl::launch_plane_gemm(dt, gb, Ahat_saved, dyhat, dbhat, s),
-                "aa_backward/dBhat");
+        STL_HIP(stl::launch_plane_gemm_pair(dt, ga, dyhat, Bhat_saved, dahat, gb, bt ? dyhat : Ahat_saved, bt ? Ahat_saved : dyhat, dbhat, s),
+                "aa_backward/dAhat and dBhat");
         const stl::TileSide sides[2] = {{dahat, E_A, dA, RA, d.K, false, A, part_a}, {dbhat, E_B, dB, RB, CB, bt, B, part_b}};
         STL_HIP(stl::launch_decode_outer_pair(sides, d.r, PG, s), "aa_backward/dA + dE_A and dB + dE_B");
         const stl::OuterSum sums[3] = {{part_d, dD, stl::gradient_blocks(dt, RA, d.N, true), false, accumulate},
@@ -1073,13 +1072,12 @@ stl_status_t stl_ragged_backward(const stl_problem_t *prob, int64_t rows, const 
         }
         if (need_yhat) STL_HIP(stl::launch_fold_grads(dt, gtail, D, fold, dD, dfold, d.r, g.nrho, accumulate, s), "ragged_backward/dD + dfold");
     }
-    if (dX || dE_X) {
-        stl::GemmDesc gd{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG};
-        STL_HIP(stl::launch_plane_gemm(dt, gd, dyhat, What, dxhat, s), "ragged_backward/dXhat");
-    }
-    if (dWhat) {
-        stl::GemmDesc gd{d.K, d.N, d.M, d.r, true, true, true, accumulate != 0, PG, PG, 0};
-        STL_HIP(stl::launch_plane_gemm(dt, gd, xhat, dyhat, dWhat, s), "ragged_backward/dWhat");
+    const stl::GemmDesc gx{d.M, d.K, d.N, d.r, false, false, false, false, PG, 0, PG}, gw{d.K, d.N, d.M, d.r, true, true, true, accumulate != 0, PG, PG, 0};
+    if (dWhat && (dX || dE_X) && stl::plane_gemm_paired(dt, gw, gx)) {
+        STL_HIP(stl::launch_plane_gemm_pair(dt, gw, xhat, dyhat, dWhat, gx, dyhat, What, dxhat, s), "ragged_backward/dWhat and dXhat");
+    } else {
+        if (dX || dE_X) STL_HIP(stl::launch_plane_gemm(dt, gx, dyhat, What, dxhat, s), "ragged_backward/dXhat");
+        if (dWhat) STL_HIP(stl::launch_plane_gemm(dt, gw, xhat, dyhat, dWhat, s), "ragged_backward/dWhat");
     }
     // gradients of null rows are dropped (never written); null rows of X count as zeros in dE_X
     const stl::RowMap all = g.map(0);

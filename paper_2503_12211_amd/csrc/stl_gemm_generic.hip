@@ -132,16 +132,29 @@ __global__ __launch_bounds__(256, BT == 128 && ACC ? 1 : 3) void gemm_generic_ke
 // A 32 x 32 block of one plane per workgroup, whose four wavefronts share the contraction, 16 of a stage's 64 elements each, and add
 // their sums up in LDS.  64 x 64 blocks give 49 planes of 64 x 64 49 workgroups and a chain of two stages, these four times as many
 // and one stage of 16 KB in flight: 7.5 / 4.0 us.  64 planes of 60 x 2000 x 60: 101 / 40.
+constexpr int kSmallBlock = 32, kSmallStage = 64, kSmallPitch = kSmallBlock + 4;
+struct SmallLds {
+    __align__(16) float a[kSmallStage][kSmallPitch];                         // [l][i]
+    __align__(16) float b[kSmallStage][kSmallPitch];                         // [l][j]
+    __align__(16) float red[4][kSmallBlock][kSmallPitch];
+};
+struct SmallProduct {
+    const void *A, *B;
+    void *Out;
+    int Mi, Nj, Kl, a_km, b_km, tiles_m, tiles_n, total, batch;
+    Div by_plane, by_row, by_batch;
+    Lay la, lb, lo;
+};
 template <typename T, typename TO, bool ACC>
-__global__ __launch_bounds__(256) void gemm_small_kernel(const T *__restrict__ A, const T *__restrict__ B, TO *__restrict__ Out, int Mi,
-                                                         int Nj, int Kl, int a_km, int b_km, int tiles_m, int tiles_n, int total,
-                                                         int batch, Div by_plane, Div by_row, Div by_batch, Lay la, Lay lb, Lay lo)
+__device__ __forceinline__ void small_product(const SmallProduct &g, int v, SmallLds &m)
 {
-    constexpr int BT = 32, KC = 64, PITCH = BT + 4;
-    __shared__ __align__(16) float sA[KC][PITCH], sB[KC][PITCH];            // [l][i], [l][j]
-    __shared__ __align__(16) float red[4][BT][PITCH];
+    constexpr int BT = kSmallBlock, KC = kSmallStage, PITCH = kSmallPitch;
+    const T *A = (const T *)g.A, *B = (const T *)g.B;
+    TO *Out = (TO *)g.Out;
+    const int Mi = g.Mi, Nj = g.Nj, Kl = g.Kl, a_km = g.a_km, b_km = g.b_km, tiles_m = g.tiles_m, tiles_n = g.tiles_n, batch = g.batch;
+    const Div &by_plane = g.by_plane, &by_row = g.by_row, &by_batch = g.by_batch;
+    const Lay &la = g.la, &lb = g.lb, &lo = g.lo;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), fj = lane & 31, fh = lane >> 5;
-  for (int v = blockIdx.x; v < total; v += gridDim.x) {          // blocks beyond the grid
     const int q = by_plane.of(v), rem = v - q * (tiles_m * tiles_n), bi = by_row.of(rem);
     const int i0 = bi * BT, j0 = (rem - bi * tiles_n) * BT, pb = by_batch.of(q), p = q - pb * batch;
     const T *Ap = A + (size_t)p * la.plane, *Bp = B + (size_t)p * lb.plane;
@@ -176,8 +189,8 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const T *__restrict__ A
         __syncthreads();                               // the previous stage has been read
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            put(sA, threadIdx.x + 256 * k, a_km, ra[k]);
-            put(sB, threadIdx.x + 256 * k, b_km, rb[k]);
+            put(m.a, threadIdx.x + 256 * k, a_km, ra[k]);
+            put(m.b, threadIdx.x + 256 * k, b_km, rb[k]);
         }
         __syncthreads();
         if (l0 + KC < Kl) fetch(l0 + KC);
@@ -185,42 +198,66 @@ __global__ __launch_bounds__(256) void gemm_small_kernel(const T *__restrict__ A
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int l = 16 * wave + s + 8 * fh;
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sA[l][fj], sB[l][fj], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(m.a[l][fj], m.b[l][fj], acc, 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) red[wave][8 * (e >> 2) + 4 * fh + (e & 3)][fj] = acc[e];
+    for (int e = 0; e < 16; ++e) m.red[wave][8 * (e >> 2) + 4 * fh + (e & 3)][fj] = acc[e];
     __syncthreads();
     // thread: row i, columns j .. j + 3
     const int i = threadIdx.x >> 3, j = 4 * (threadIdx.x & 7), gi = i0 + i, gj = j0 + j;
-    if (gi >= Mi) continue;
-    f32x4_t w = *reinterpret_cast<const f32x4_t *>(&red[0][i][j]);
+    if (gi >= Mi) return;
+    f32x4_t w = *reinterpret_cast<const f32x4_t *>(&m.red[0][i][j]);
 #pragma unroll
-    for (int k = 1; k < 4; ++k) w += *reinterpret_cast<const f32x4_t *>(&red[k][i][j]);
+    for (int k = 1; k < 4; ++k) w += *reinterpret_cast<const f32x4_t *>(&m.red[k][i][j]);
     TO *o = Out + (size_t)p * lo.plane + lo.row(pb * Mi + gi) + gj;
     if constexpr (sizeof(TO) == 4) {
         if (gj + 4 <= Nj) {
             if (ACC) w += *reinterpret_cast<const f32x4_any_t *>(o);
             *reinterpret_cast<f32x4_any_t *>(o) = w;
-            continue;
+            return;
         }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (gj + e < Nj) Elem<TO>::st(o + e, ACC ? Elem<TO>::ld(o + e) + w[e] : w[e]);
-  }
+}
+
+template <typename T, typename TO, bool ACC>
+__global__ __launch_bounds__(256) void gemm_small_kernel(const SmallProduct g)
+{
+    __shared__ SmallLds m;
+    for (int v = blockIdx.x; v < g.total; v += gridDim.x) small_product<T, TO, ACC>(g, v, m);          // blocks beyond the grid
+}
+
+// Two products of a layer's gradients that do not depend on each other in one launch, fp32: the weight's, which ACC may add to what is there, then
+// the input's.
+template <bool ACC>
+__global__ __launch_bounds__(256) void gemm_small_pair_kernel(const SmallProduct x, const SmallProduct y)
+{
+    __shared__ SmallLds m;
+    const int v = blockIdx.x;
+    if (v < x.total) small_product<float, float, ACC>(x, v, m);
+    else small_product<float, float, false>(y, v - x.total, m);
+}
+
+static bool small_args(const GemmDesc &g, const void *A, const void *B, void *Out, SmallProduct *x)
+{
+    GemmLays l;
+    if (!l.set(g)) return false;
+    // with at most 2^22 stacked tile rows and columns and 64 planes, what is not left to the large blocks stays far below 2^31 blocks
+    const int tm = (g.Mi + kSmallBlock - 1) / kSmallBlock, tn = (g.Nj + kSmallBlock - 1) / kSmallBlock;
+    *x = {A, B, Out, g.Mi, g.Nj, g.Kl, (int)g.a_kmajor, (int)g.b_kmajor, tm, tn, tm * tn * g.batch * g.nb, g.batch, Div::by(tm * tn), Div::by(tn),
+          Div::by(g.batch), l.a, l.b, l.o};
+    return true;
 }
 
 template <typename T, typename TO, bool ACC>
 static hipError_t launch_small(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s)
 {
-    GemmLays l;
-    if (!l.set(g)) return hipErrorInvalidValue;
-    // with at most 2^22 stacked tile rows and columns and 64 planes, what is not left to the large blocks stays far below 2^31 blocks
-    const int tiles_m = (g.Mi + 31) / 32, tiles_n = (g.Nj + 31) / 32, total = tiles_m * tiles_n * g.batch * g.nb;
-    hipLaunchKernelGGL((gemm_small_kernel<T, TO, ACC>), dim3(total > (1 << 22) ? 1 << 22 : total), dim3(256), 0, s, (const T *)A, (const T *)B, (TO *)Out, g.Mi, g.Nj, g.Kl,
-                       (int)g.a_kmajor, (int)g.b_kmajor, tiles_m, tiles_n, total, g.batch, Div::by(tiles_m * tiles_n), Div::by(tiles_n),
-                       Div::by(g.batch), l.a, l.b, l.o);
+    SmallProduct x;
+    if (!small_args(g, A, B, Out, &x)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((gemm_small_kernel<T, TO, ACC>), dim3(x.total > (1 << 22) ? 1 << 22 : x.total), dim3(256), 0, s, x);
     return hipGetLastError();
 }
 
@@ -298,6 +335,29 @@ hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const 
         case GemmPath::generic: break;
     }
     return launch_plane_gemm_generic(dtype, g, A, B, Out, s);
+}
+
+// Whether launch_plane_gemm_pair runs the two as one launch.
+bool plane_gemm_paired(int dtype, const GemmDesc &g1, const GemmDesc &g2)
+{
+    if (dtype != 0) return staged_pair_eligible(g1, g2);
+    auto blocks = [](const GemmDesc &g) { return (double)((g.Mi + 31) / 32) * ((g.Nj + 31) / 32) * g.batch * g.nb; };
+    return g1.Mi >= 1 && g1.out_f32 && !g2.out_f32 && !g2.accumulate && generic_block(g1) == 32 && generic_block(g2) == 32 && blocks(g1) + blocks(g2) < (1 << 22);
+}
+
+hipError_t launch_plane_gemm_pair(int dtype, const GemmDesc &g1, const void *A1, const void *B1, void *Out1, const GemmDesc &g2, const void *A2,
+                                  const void *B2, void *Out2, hipStream_t s)
+{
+    if (plane_gemm_paired(dtype, g1, g2)) {
+        if (dtype != 0) return launch_staged_pair(g1, A1, B1, Out1, g2, A2, B2, Out2, s);
+        SmallProduct x, y;
+        if (!small_args(g1, A1, B1, Out1, &x) || !small_args(g2, A2, B2, Out2, &y)) return hipErrorInvalidValue;
+        if (g1.accumulate) hipLaunchKernelGGL((gemm_small_pair_kernel<true>), dim3(x.total + y.total), dim3(256), 0, s, x, y);
+        else hipLaunchKernelGGL((gemm_small_pair_kernel<false>), dim3(x.total + y.total), dim3(256), 0, s, x, y);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_plane_gemm(dtype, g1, A1, B1, Out1, s);
+    return e != hipSuccess ? e : launch_plane_gemm(dtype, g2, A2, B2, Out2, s);
 }
 
 }  // namespace stl

@@ -90,11 +90,11 @@ struct Piece {
 // A_T: A stored [l][i];  B_T: B stored [l][j].  (false: stored [i][l] resp. [j][l].)
 // PF: stages on their way in registers (1 or 2); 0: the contraction is a single stage.  KS: groups of WAVES_M x WAVES_N wavefronts
 // that take every KS-th stage each, their sums added up in LDS at the end.
+// The block `bid` of the list of (stacked problem, plane, block row, block column).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
-__global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 : KS == 1 ? 5 : 4) : 2) void gemm_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
-                                                                          TO *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m, int tiles_n,
-                                                                          int base, int total, int batch, Div by_plane, Div by_row, Div by_batch, Lay la,
-                                                                          Lay lb, Lay lo)
+__device__ __forceinline__ void staged_product(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, TO *__restrict__ Out, int Mi, int Nj, int Kl,
+                                               int tiles_m, int tiles_n, int bid, int batch, Div by_plane, Div by_row, Div by_batch, const Lay &la,
+                                               const Lay &lb, const Lay &lo, char *smem)
 {
     using pipe::static_for;
     constexpr int NT = WAVES_M * WAVES_N * 64, WM = BM / WAVES_M, WN = BN / WAVES_N, FM = WM / 16, FN = WN / 16;
@@ -103,11 +103,6 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 
     constexpr int STAGE = 2 * (PA::BYTES + PB::BYTES);
     // blocks of narrow outputs: fragments that lie beyond the output take no part
     constexpr bool NARROW = BM == 64;
-    extern __shared__ __align__(16) char smem[];
-
-    int bid = pipe::first_block(total);                         // one block per workgroup; each XCD takes a contiguous eighth
-    if (bid >= pipe::end_block(total)) return;
-    bid += base;
     const int q = by_plane.of(bid), rem = bid - q * (tiles_m * tiles_n);   // (stacked problem, plane)
     const int bi = by_row.of(rem), i0 = bi * BM, j0 = (rem - bi * tiles_n) * BN;
     const int pb = by_batch.of(q), p = q - pb * batch;
@@ -272,6 +267,47 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 
     });
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int PF, int KS, bool A_T, bool B_T, typename TO, bool ACC>
+__global__ __launch_bounds__(WAVES_M *WAVES_N *KS * 64, BM == 64 ? (PF == 0 ? 8 : KS == 1 ? 5 : 4) : 2) void gemm_mfma_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
+                                                                          TO *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m, int tiles_n,
+                                                                          int base, int total, int batch, Div by_plane, Div by_row, Div by_batch, Lay la,
+                                                                          Lay lb, Lay lo)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int bid = pipe::first_block(total);                   // one block per workgroup; each XCD takes a contiguous eighth
+    if (bid >= pipe::end_block(total)) return;
+    staged_product<BM, BN, WAVES_M, WAVES_N, PF, KS, A_T, B_T, TO, ACC>(A, B, Out, Mi, Nj, Kl, tiles_m, tiles_n, base + bid, batch, by_plane, by_row, by_batch,
+                                                                        la, lb, lo, smem);
+}
+
+// Two products of 64 x 64 blocks in one launch: the blocks of the first, then those of the second.
+struct Product {
+    const bf16_t *A, *B;
+    void *Out;
+    int Mi, Nj, Kl, tiles_m, tiles_n, total, batch;
+    Div by_plane, by_row, by_batch;
+    Lay la, lb, lo;
+};
+template <int PF, bool A1, bool B1, typename T1, bool ACC1, bool A2, bool B2, typename T2>
+__global__ __launch_bounds__(256, PF == 0 ? 8 : 5) void gemm_pair_kernel(const Product x, const Product y)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int grid1 = (x.total + 7) / 8 * 8, bx = (int)blockIdx.x;
+    // each XCD takes a contiguous eighth of both lists
+    auto place = [](int b, int total) { return (b >> 3) < (int)((long)((b & 7) + 1) * total / 8 - (long)(b & 7) * total / 8) ? (int)((long)(b & 7) * total / 8) + (b >> 3) : -1; };
+    if (bx < grid1) {
+        const int bid = place(bx, x.total);
+        if (bid >= 0)
+            staged_product<64, 64, 4, 1, PF, 1, A1, B1, T1, ACC1>(x.A, x.B, (T1 *)x.Out, x.Mi, x.Nj, x.Kl, x.tiles_m, x.tiles_n, bid, x.batch, x.by_plane,
+                                                                  x.by_row, x.by_batch, x.la, x.lb, x.lo, smem);
+    } else {
+        const int bid = place(bx - grid1, y.total);
+        if (bid >= 0)
+            staged_product<64, 64, 4, 1, PF, 1, A2, B2, T2, false>(y.A, y.B, (T2 *)y.Out, y.Mi, y.Nj, y.Kl, y.tiles_m, y.tiles_n, bid, y.batch, y.by_plane,
+                                                                   y.by_row, y.by_batch, y.la, y.lb, y.lo, smem);
+    }
+}
+
 }  // namespace staged
 
 // ---- host side ---------------------------------------------------------------------------
@@ -367,6 +403,62 @@ hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *
                             : launch_block<true, true, float, false>(g, A, B, Out, s);
     if (g.a_kmajor) return launch_block<true, true, bf16_t, false>(g, A, B, Out, s);
     return g.b_kmajor ? launch_block<false, true, bf16_t, false>(g, A, B, Out, s) : launch_block<false, false, bf16_t, false>(g, A, B, Out, s);
+}
+
+// Pairs: a gradient of few blocks is the latency of its chain of stages, and two that read the same planes and write different ones
+// need not wait for each other.  us, two launches / one, r = 32: dWhat and dXhat of 512 x 192 x 250 18.0 / 14.0, of 64 x 128 x 96 8.6 / 5.7, dAhat
+// and dBhat of 96 x (50 x 16 x 50) 14.1 / 11.5; over 45 layers of odd widths 1.26 times as fast, over 25 pairs of activations 1.28.  A block has one
+// group of wavefronts, and where the contraction of one product alone is a single stage, the registers and LDS of two: many
+// blocks of that kind (96 x (256 x 256 x 8), 61440 blocks, 206 / 244; 48 x (145 x 145 x 32), 9216, 23.9 / 26.1; 2640 blocks 20.2 / 17.4, 3500 19.5 / 18.5) or one whose
+// contraction four groups would share (12 x 140 x 951, r = 40, 17.6 / 20.0) stay apart.
+bool staged_pair_eligible(const GemmDesc &g1, const GemmDesc &g2)
+{
+    if (plane_gemm_path(1, g1) != GemmPath::staged || plane_gemm_path(1, g2) != GemmPath::staged) return false;
+    if (staged_block(g1) != 64 || staged_block(g2) != 64) return false;
+    auto blocks = [](const GemmDesc &g) { return (double)((g.Mi + 63) / 64) * ((g.Nj + 63) / 64) * g.batch * g.nb; };
+    const double both = blocks(g1) + blocks(g2);
+    const bool one1 = g1.Kl <= staged::BK, one2 = g2.Kl <= staged::BK;
+    return one1 == one2 ? both < (1 << 22) : both <= 3072 && staged_groups(one1 ? g2 : g1) < 4;
+}
+
+template <int PF, bool A1, bool B1, typename T1, bool ACC1, bool A2, bool B2, typename T2>
+static hipError_t launch_pair_cfg(const staged::Product &x, const staged::Product &y, int smem, hipStream_t s)
+{
+    const unsigned grid = (unsigned)((x.total + 7) / 8 * 8 + (y.total + 7) / 8 * 8);
+    hipLaunchKernelGGL((staged::gemm_pair_kernel<PF, A1, B1, T1, ACC1, A2, B2, T2>), dim3(grid), dim3(256), smem, s, x, y);
+    return hipGetLastError();
+}
+
+hipError_t launch_staged_pair(const GemmDesc &g1, const void *A1, const void *B1, void *Out1, const GemmDesc &g2, const void *A2, const void *B2, void *Out2,
+                              hipStream_t s)
+{
+    if (!staged_pair_eligible(g1, g2)) return hipErrorInvalidValue;
+    staged::Product x[2];
+    const GemmDesc *g[2] = {&g1, &g2};
+    const void *ops[2][3] = {{A1, B1, Out1}, {A2, B2, Out2}};
+    for (int i = 0; i < 2; ++i) {
+        GemmLays l;
+        if (!l.set(*g[i])) return hipErrorInvalidValue;
+        const int tm = (g[i]->Mi + 63) / 64, tn = (g[i]->Nj + 63) / 64;
+        x[i] = {(const bf16_t *)ops[i][0], (const bf16_t *)ops[i][1], const_cast<void *>(ops[i][2]), g[i]->Mi, g[i]->Nj, g[i]->Kl, tm, tn,
+                tm * tn * g[i]->batch * g[i]->nb, g[i]->batch, Div::by(tm * tn), Div::by(tn), Div::by(g[i]->batch), l.a, l.b, l.o};
+    }
+    const bool one = g1.Kl <= staged::BK && g2.Kl <= staged::BK;
+    const int stage = 128 * staged::BK * 2, smem = one ? stage : 2 * stage;
+    auto launch = [&](auto pf_c) -> hipError_t {
+        constexpr int PF = decltype(pf_c)::value;
+        // the products of a layer: the weight gradient first, then the input gradient; of a pair of activations: the first operand's, which
+        // reads the second's planes as they were encoded ([l][j] if that was stored transposed), then the second's
+        if (g1.out_f32) {
+            if (!(g1.a_kmajor && g1.b_kmajor) || g2.a_kmajor || g2.b_kmajor || g2.out_f32) return hipErrorInvalidValue;
+            return g1.accumulate ? launch_pair_cfg<PF, true, true, float, true, false, false, bf16_t>(x[0], x[1], smem, s)
+                                 : launch_pair_cfg<PF, true, true, float, false, false, false, bf16_t>(x[0], x[1], smem, s);
+        }
+        if (g1.a_kmajor || !(g2.a_kmajor && g2.b_kmajor) || g2.out_f32 || g1.accumulate || g2.accumulate) return hipErrorInvalidValue;
+        return g1.b_kmajor ? launch_pair_cfg<PF, false, true, bf16_t, false, true, true, bf16_t>(x[0], x[1], smem, s)
+                           : launch_pair_cfg<PF, false, false, bf16_t, false, true, true, bf16_t>(x[0], x[1], smem, s);
+    };
+    return one ? launch(std::integral_constant<int, 0>{}) : launch(std::integral_constant<int, 2>{});
 }
 
 }  // namespace stl

@@ -222,6 +222,10 @@ struct Div {
 };
 
 hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
+// two products that do not depend on each other, in one launch where there is a kernel for that (plane_gemm_paired), else one after the other
+bool plane_gemm_paired(int dtype, const GemmDesc &g1, const GemmDesc &g2);
+hipError_t launch_plane_gemm_pair(int dtype, const GemmDesc &g1, const void *A1, const void *B1, void *Out1, const GemmDesc &g2, const void *A2,
+                                  const void *B2, void *Out2, hipStream_t s);
 // the kernel that launch_plane_gemm takes: stl_gemm_rows.hip, stl_gemm_wide.hip, stl_gemm_pipe.hip, stl_gemm_mfma.hip, stl_gemm_generic.hip
 enum class GemmPath { rows, wide, pipe, staged, generic };
 GemmPath plane_gemm_path(int dtype, const GemmDesc &g);
@@ -234,6 +238,9 @@ bool plane_gemm_mfma_eligible(const GemmDesc &g);
 int staged_block(const GemmDesc &g);          // edge of the block of a plane that it takes
 int staged_groups(const GemmDesc &g);         // and, of 64 x 64 blocks, the groups of wavefronts that share the contraction (0: it is one stage)
 hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
+bool staged_pair_eligible(const GemmDesc &g1, const GemmDesc &g2);
+hipError_t launch_staged_pair(const GemmDesc &g1, const void *A1, const void *B1, void *Out1, const GemmDesc &g2, const void *A2, const void *B2, void *Out2,
+                              hipStream_t s);
 // bf16 products of up to 32 rows
 bool plane_gemm_rows_eligible(const GemmDesc &g);
 int rows_columns(const GemmDesc &g);          // columns of the block of a plane that it takes

@@ -3,6 +3,7 @@
 //   fwd:m:k:n:r:flags   bwd:m:k:n:r   mlp:m:k:h:r   ewb:k:n:r   aa:nb:m:k:n:r   ragged:nimg:rows:k:n:r
 //   route:Mi:Nj:Kl:r:a_kmajor:b_kmajor:out_f32:a_pg:b_pg:o_pg:nb   (out_f32 = 2: added to it; prints which plane-product kernel and block a product takes; staged 64x64:G: G groups share the contraction, 0: one stage)
 //   split:...  (as route: what becomes of the 256 x 256 blocks of a last round that is not full)
+//   paired:...:...  (two products as in route: whether they run as one launch)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   ring:encode:M:N:r   (tile counts: prints the LDS stages of the block-resident forward)
 //   narrow:R:Cc   (prints whether a bf16 encode of R x Cc tiles runs in items of several tile rows)
@@ -68,6 +69,11 @@ int main(int argc, char **argv)
             stl::GemmDesc g{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, v[6] > 1, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
             const char *parts[] = {"whole", "128x256", "128x128"};
             printf("  route %s\n", parts[(int)stl::pipe_split(g)]);
+        } else if (op == "paired") {
+            auto desc = [&](const long *v) {
+                return stl::GemmDesc{(int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0, v[5] != 0, v[6] != 0, v[6] > 1, (int)v[7], (int)v[8], (int)v[9], (int)v[10]};
+            };
+            printf("  route %d\n", (int)stl::plane_gemm_paired(dt == STL_BF16 ? 1 : 0, desc(&v[0]), desc(&v[11])));
         } else if (op == "tiles") {
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "ring") {

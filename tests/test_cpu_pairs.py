@@ -1,0 +1,30 @@
+"""Gradients whose two plane products run as one launch: the rule, and addresses (see test_cpu_address_check.py)."""
+from test_cpu_address_check import checker, pytestmark  # noqa: F401
+from test_cpu_routes import PG, aa_descs, desc
+
+from test_gpu_pairs import AA_SHAPES, SHAPES
+
+
+def paired(run, cases):
+    _, text = run(*cases)
+    return [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")]
+
+
+def name(dtype, *descs):
+    return ("f32," if dtype == "f32" else "") + "paired:" + ":".join(str(int(x)) for d in descs for x in d)
+
+
+def test_what_runs_together(checker):  # noqa: F811
+    for form in ("dWhat", "dWhat +="):
+        cases = [name(dt, desc(form, *s), desc("dXhat", *s)) for dt, *s in SHAPES]
+        assert paired(checker, cases) == [int(x) for x in SHAPES.values()]
+    assert paired(checker, [name("bf16", *aa_descs(*s)[1:]) for s in AA_SHAPES]) == [int(x) for x in AA_SHAPES.values()]
+    # larger blocks, the LDS-DMA kernels, the fp32 matrix instructions in bf16 stay apart
+    apart = [("bf16", 2048, 513, 513, 32), ("bf16", 512, 192, 256, 32), ("bf16", 40, 6, 40, 8), ("f32", 512, 512, 512, 32)]
+    assert paired(checker, [name(dt, desc("dWhat", *s), desc("dXhat", *s)) for dt, *s in apart]) == [0] * 4
+
+
+def test_pair_addresses(checker):  # noqa: F811
+    checker(*(f"{'f32,' if dt == 'f32' else ''}bwd:{4 * M}:{4 * K}:{4 * N}:{r}" for dt, M, K, N, r in SHAPES),
+            *(f"aa:{nb}:{4 * M}:{4 * K}:{4 * N}:{r}" for nb, M, K, N, r, _ in AA_SHAPES), "ragged:5:39:300:164:49", "f32,ragged:3:13:24:20:11",
+            "ragged:9:50:44:1000:8")
