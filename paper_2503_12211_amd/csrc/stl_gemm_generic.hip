@@ -340,7 +340,7 @@ hipError_t launch_plane_gemm(int dtype, const GemmDesc &g, const void *A, const 
 // Whether launch_plane_gemm_pair runs the two as one launch.
 bool plane_gemm_paired(int dtype, const GemmDesc &g1, const GemmDesc &g2)
 {
-    if (dtype != 0) return staged_pair_eligible(g1, g2);
+    if (dtype != 0) return staged_pair_eligible(g1, g2) || pipe_pair_eligible(g1, g2);
     auto blocks = [](const GemmDesc &g) { return (double)((g.Mi + 31) / 32) * ((g.Nj + 31) / 32) * g.batch * g.nb; };
     return g1.Mi >= 1 && g1.out_f32 && !g2.out_f32 && !g2.accumulate && generic_block(g1) == 32 && generic_block(g2) == 32 && blocks(g1) + blocks(g2) < (1 << 22);
 }
@@ -349,7 +349,9 @@ hipError_t launch_plane_gemm_pair(int dtype, const GemmDesc &g1, const void *A1,
                                   const void *B2, void *Out2, hipStream_t s)
 {
     if (plane_gemm_paired(dtype, g1, g2)) {
-        if (dtype != 0) return launch_staged_pair(g1, A1, B1, Out1, g2, A2, B2, Out2, s);
+        if (dtype != 0)
+            return staged_pair_eligible(g1, g2) ? launch_staged_pair(g1, A1, B1, Out1, g2, A2, B2, Out2, s)
+                                                : launch_pipe_pair(g1, A1, B1, Out1, g2, A2, B2, Out2, s);
         SmallProduct x, y;
         if (!small_args(g1, A1, B1, Out1, &x) || !small_args(g2, A2, B2, Out2, &y)) return hipErrorInvalidValue;
         if (g1.accumulate) hipLaunchKernelGGL((gemm_small_pair_kernel<true>), dim3(x.total + y.total), dim3(256), 0, s, x, y);

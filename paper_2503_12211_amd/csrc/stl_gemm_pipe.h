@@ -507,6 +507,7 @@ struct Products {
 // The ring's first LOW stages lie at the start of the workgroup's LDS, the others from byte HIGH on (LOW = NS: all of them side by side).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int NS, bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, int LOW = NS, int HIGH = 0>
 struct BlockRing {
+    static constexpr int STAGES = NS;
     static constexpr int NW = WAVES_M * WAVES_N, WM = BM / WAVES_M, WN = BN / WAVES_N, FM = WM / 16, FN = WN / 16;
     static constexpr int OPER_BYTES = BM * BKS * 2, STAGE_BYTES = (BM + BN) * BKS * 2;
     static constexpr int D = (BM + BN) / 16 / NW;          // DMA instructions per wavefront and stage

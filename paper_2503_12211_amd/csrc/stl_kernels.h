@@ -253,6 +253,9 @@ PipeBlock pipe_block(const GemmDesc &g);      // block of a plane that it takes
 enum class PlaneSplit { none, b128x256, b128 };
 PlaneSplit pipe_split(const GemmDesc &g);
 bool plane_gemm_pipe_eligible(const GemmDesc &g);
+bool pipe_pair_eligible(const GemmDesc &g1, const GemmDesc &g2);
+hipError_t launch_pipe_pair(const GemmDesc &g1, const void *A1, const void *B1, void *Out1, const GemmDesc &g2, const void *A2, const void *B2, void *Out2,
+                            hipStream_t s);
 hipError_t launch_plane_gemm_pipe(const GemmDesc &g, const void *A, const void *B, void *Out, hipStream_t s);
 
 // The whole forward pass as one persistent launch: encode and decode items run on some CUs while the plane products

@@ -16,6 +16,11 @@ NAMES = ("dX", "dWhat", "dE_X", "dD")
 # dtype, M, K, N tile counts, r -> whether dWhat and dXhat run together
 SHAPES = {("bf16", 9, 10, 11, 3): True, ("bf16", 64, 61, 63, 8): True, ("bf16", 65, 66, 67, 5): True, ("bf16", 50, 33, 130, 32): True,
           ("bf16", 130, 129, 20, 9): True, ("bf16", 12, 140, 951, 40): False, ("bf16", 15, 601, 479, 49): False, ("bf16", 130, 264, 70, 3): True,
+          # widths that are multiples of 8: edges of 64 and 64, 64 and 128, 128 and 64, 128 and 128; contractions of part of a stage, of one, of as
+          # many as a ring holds and of more
+          ("bf16", 8, 16, 8, 3): True, ("bf16", 64, 64, 64, 5): True, ("bf16", 65, 136, 264, 9): True, ("bf16", 257, 72, 32, 33): True,
+          ("bf16", 200, 128, 1000, 24): True, ("bf16", 200, 520, 512, 48): True, ("bf16", 526, 576, 576, 16): True, ("bf16", 1100, 80, 616, 16): True,
+          ("bf16", 8, 1024, 264, 40): True, ("bf16", 1024, 1024, 1024, 32): False,
           ("f32", 1, 1, 1, 1): True, ("f32", 33, 31, 65, 7): True, ("f32", 64, 64, 64, 49): True, ("f32", 5, 130, 70, 16): True,
           ("f32", 100, 16, 30, 64): True}
 # nbatch, M, K, N, r, second operand stored transposed -> whether dAhat and dBhat do
@@ -78,3 +83,24 @@ def test_pair_of_activations(gu, nb, M, K, N, r, bt):
         x, y = both[name].double(), other[name].double()
         # the same products, whose sums may be added up in another order (and turn a rounding over here and there)
         assert ((x - y).norm() / y.norm()).item() <= 1e-3, name
+
+
+def _apart():
+    import test_gpu_blocks
+    import test_gpu_split
+    return list(test_gpu_blocks.SHAPES) + list(test_gpu_split.SHAPES)
+
+
+@pytest.mark.parametrize("M,K,N,r", _apart())
+def test_gradients_on_their_own(gu, M, K, N, r):
+    """The products of a call that asks for one gradient, over the shapes that reach every block and every last round in parts."""
+    p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=2100 + M + K + N + r, dtype="bf16", with_dC=True)
+    ref = dict(zip(NAMES, planes.backward(p["X"], p["What"], p["E_X"], p["D"], p["dC"])))
+    gu.check(gu.backward(p, "bf16", skip=("dWhat", "dE_X", "dD"))["dX"], ref["dX"], "bf16", "dX")
+    alone = ("dX", "dE_X", "dD")
+    dW = gu.backward(p, "bf16", skip=alone)["dWhat"]
+    gu.check(dW, ref["dWhat"], "bf16", "dWhat")
+    init = [np.ones_like(ref[nm], dtype=np.float32) for nm in NAMES[1:]]
+    acc = gu.backward(p, "bf16", accumulate=1, init=init, skip=alone)["dWhat"]
+    # one rounding of (1 + gradient) on top of the same sums
+    assert np.abs(acc - 1.0 - dW).max() <= 2.0 ** -22 * max(1.0, np.abs(dW).max())
