@@ -131,30 +131,40 @@ bool encode_pair_eligible(int dtype, const TileSide *s, int r)
 
 hipError_t launch_encode_pair(const TileSide *t, int r, int pg, hipStream_t st) { return launch_encode_sides(t, 2, r, pg, st); }
 
-// encode and basis gradient of a matrix of 8 to 32 tile columns, nb blocks that leave one partial each
-template <int KC, bool ANY>
-__global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, const bf16_t *__restrict__ Qp, float *__restrict__ part, int r, int pg)
+// encode and basis gradient of a matrix of 8 to 32 tile columns, or in items that follow the planes (FLAT), nb blocks that leave one partial each
+template <int KC, bool ANY, bool FLAT>
+__global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, const bf16_t *__restrict__ Qp, float *__restrict__ part, int r, int pg,
+                                                                  long items)
 {
     __shared__ __align__(16) char sT_all[4][64 * 32];
     __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), rows = 64 >> s.lw;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     f32x4_t dacc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    encode_items<KC, true, false, 1, ANY, false, true>(s.A, s.E, s.P, Qp, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
-                                                       (long)gridDim.x * 4, (long)((s.R + rows - 1) / rows) * s.chunks, sT_all[wave],
-                                                       slab_all[wave], dacc, lane, false, s.lw, s.lay);
+    encode_items<KC, true, false, 1, ANY, false, true, FLAT>(s.A, s.E, s.P, Qp, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                             (long)gridDim.x * 4, items, sT_all[wave], slab_all[wave], dacc, lane, false, s.lw,
+                                                             s.lay);
     write_partial<KC>(dacc, reinterpret_cast<float *>(&slab_all[0][0]), part, r, wave, lane);
 }
+
+// Whether the items of a matrix without a row map follow the planes rather than the rows: where rows are no whole items and planes lie in
+// groups of 64 of them.
+static bool flat_form(int Cc, int pg) { return pg == 64 && Cc > 32 && Cc % 64; }
 
 static hipError_t launch_encode_outer_narrow(const TileSide &t, const void *Qp, float *part, int r, int pg, int nb, hipStream_t st)
 {
     EncodeSide s;
     if (!s.set(t, r, pg, true)) return hipErrorInvalidValue;
-    const bool any = t.Cc % 8;
-    auto kern = r <= 32 ? (any ? encode_outer_narrow_kernel<1, true> : encode_outer_narrow_kernel<1, false>)
-                        : (any ? encode_outer_narrow_kernel<2, true> : encode_outer_narrow_kernel<2, false>);
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, st, s, (const bf16_t *)Qp, part, r, pg);
+    auto pick = [&](auto any_c, auto flat_c) {
+        constexpr bool ANY = decltype(any_c)::value, FLAT = decltype(flat_c)::value;
+        return r <= 32 ? encode_outer_narrow_kernel<1, ANY, FLAT> : encode_outer_narrow_kernel<2, ANY, FLAT>;
+    };
+    using T = std::true_type;
+    using F = std::false_type;
+    const bool any = t.Cc % 8, flat = flat_form(t.Cc, pg);
+    auto kern = any ? (flat ? pick(T{}, T{}) : pick(T{}, F{})) : (flat ? pick(F{}, T{}) : pick(F{}, F{}));
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, st, s, (const bf16_t *)Qp, part, r, pg, flat ? flat_items(t.R, t.Cc) : s.items());
     return hipGetLastError();
 }
 
@@ -162,7 +172,7 @@ static hipError_t launch_encode_outer_narrow(const TileSide &t, const void *Qp, 
 hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
                                      int nb, hipStream_t s, RowMap rm)
 {
-    if (narrow_log2(1, Cc, rm.Mt == 0)) return launch_encode_outer_narrow({P, E, A, R, Cc, false, nullptr, nullptr}, Qp, part, r, pg, nb, s);
+    if (rm.Mt == 0 && (narrow_log2(1, Cc, true) || flat_form(Cc, pg))) return launch_encode_outer_narrow({P, E, A, R, Cc, false, nullptr, nullptr}, Qp, part, r, pg, nb, s);
     const bool any = Cc % 8 != 0;
     auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, true, true> : encode_outer16_kernel<1, true, false>)
                         : (any ? encode_outer16_kernel<2, true, true> : encode_outer16_kernel<2, true, false>);

@@ -17,10 +17,11 @@ namespace stl {
 // SPLIT: the blocks of a last round that is not full are dealt to all workgroups in parts (see pipe_split), whose rings lie
 // on both sides of the epilogue slabs.
 template <bool B_T, pipe::Split SPLIT>
-__global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Products<bf16_t> g, int tiles_m, int tiles_n, int total)
+__global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B,
+                                                             bf16_t *__restrict__ Out, int Mi, int Nj, int Kl, int tiles_m,
+                                                             int tiles_n, int total, int a_pg, int b_pg, int o_pg, int batch)
 {
     using namespace pipe;
-    const int Mi = g.Mi, Nj = g.Nj, Kl = g.Kl, batch = g.batch;
     constexpr int BM = 256, BN = 256, NW = 8, WAVES_N = 4, WM = 128, WN = 64, FM = WM / 16, FN = WN / 16, NSB = 4;
     constexpr int A_SLOT = BM * 128, B_STAGE = BN * BKS * 2, B_BASE = 3 * A_SLOT;
     constexpr int SLAB = slab_bytes<FM, FN, bf16_t>();
@@ -60,8 +61,8 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
         asm volatile("" : "+v"(sl));
         int p, i0, j0;
         locate(v, p, i0, j0);
-        sa.init(g.A, Kl, i0, Mi, wave, sl, p, batch, g.a_pg, 0);
-        sb.init(g.B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, g.b_pg, 0, Kl);
+        sa.init(A, Kl, i0, Mi, wave, sl, p, batch, a_pg, 0);
+        sb.init(B, B_T ? Nj : Kl, j0, Nj, wave, sl, p, batch, b_pg, 0, Kl);
         sa.template issue_half<0>(smem_lds + a_slot(0), wave);
         sb.issue(smem_lds + b_slot(0), wave, sl);
         sa.template issue_half<1>(smem_lds + a_slot(0), wave);
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
         next();
         int el = lane;                                   // opaque, as above
         asm volatile("" : "+v"(el));
-        w.template store<bf16_t, false, false>(slab, g.Out + (size_t)p * g.o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, g.o_pg, batch, el);
+        w.template store<bf16_t, false, false>(slab, Out + (size_t)p * o_pg * Nj, i0 + wm * WM, j0 + wn * WN, Mi, Nj, 0, o_pg, batch, el);
     };
 
     const int step = block_step(), end = SPLIT == Split::none ? end_block(total) : whole_end(total);
@@ -156,6 +157,7 @@ __global__ __launch_bounds__(512) void gemm_pipe_wide_kernel(const pipe::Product
                 if (v + step < end) start_block(v + step);
             });
     } else {
+        const Products<bf16_t> g{A, B, Out, Mi, Nj, Kl, a_pg, b_pg, o_pg, batch};
         constexpr int STAGE = (128 + Part<SPLIT>::N) * BKS * 2, LOW = 2 * A_SLOT / STAGE, HIGH = 3 * A_SLOT, N_UP = (160 * 1024 - HIGH) / STAGE;
         PartWalk<SPLIT, LOW + N_UP, false, B_T, bf16_t, false, false, LOW, HIGH> parts;
         start_block(v);                                          // every workgroup has a whole block: total >= the grid
@@ -185,9 +187,8 @@ static hipError_t launch_wide_cfg(const GemmDesc &g, const void *A, const void *
     if (total > 0x7fffffffL) return hipErrorInvalidValue;
     const unsigned grid = pipe::list_grid(total, pipe::cu_count());
     if (SPLIT != pipe::Split::none && total < (long)grid) return hipErrorInvalidValue;      // every workgroup begins with a whole block
-    const pipe::Products<bf16_t> pr{(const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl, g.a_rows_per_group(), g.b_rows_per_group(),
-                                    g.o_rows_per_group(), g.batch};
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, pr, tiles_m, tiles_n, (int)total);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, (const bf16_t *)A, (const bf16_t *)B, (bf16_t *)Out, g.Mi, g.Nj, g.Kl,
+                       tiles_m, tiles_n, (int)total, g.a_rows_per_group(), g.b_rows_per_group(), g.o_rows_per_group(), g.batch);
     return hipGetLastError();
 }
 

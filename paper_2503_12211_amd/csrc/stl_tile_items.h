@@ -9,6 +9,32 @@ namespace stl {
 
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 
+// Items of 64 tiles that follow each other in a group of 64 tile rows (FLAT below): tile t of an item, for Cc >= 32 ...
+struct FlatTile {
+    int I, J;
+    template <class P>
+    __device__ __forceinline__ P as() const { return P{I, J}; }
+};
+__device__ __forceinline__ FlatTile flat_tile(long item, int t, int Cc)
+{
+    const int g = (int)(item / Cc), o = (int)(item - (long)g * Cc) * 64, row = o / Cc, x = o - row * Cc + t;     // x < Cc + 63
+    const int more = (x >= Cc ? 1 : 0) + (x >= 2 * Cc ? 1 : 0);
+    return {g * 64 + row + more, x - more * Cc};
+}
+// ... and where its tiles from t on lie in plane 0, and how many of the group's follow there
+struct FlatRun {
+    size_t off;
+    int left;
+};
+__device__ __forceinline__ FlatRun flat_run(long item, int t, int R, int Cc, int r)
+{
+    const int g = (int)(item / Cc), o = (int)(item - (long)g * Cc) * 64 + t, rows = R - g * 64;
+    // the last group's place is as long as the others'
+    return {(size_t)g * r * 64 * Cc + o, (rows < 64 ? rows : 64) * Cc - o};
+}
+
+inline long flat_items(int R, int Cc) { return (long)(R / 64) * Cc + ((long)(R % 64) * Cc + 63) / 64; }
+
 // The item loop of one wavefront: items `first`, `first + stride`, ... below `end`, an item being (tile row index of the
 // launch, 64-tile chunk) = item / chunks, item % chunks.  sT and slab are LDS areas private to the wavefront
 // (sT: 64 x 32 bytes, used with OUTER only; slab: KC * 32 * 128 bytes); dacc accumulates the basis gradient (OUTER).
@@ -26,7 +52,10 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 // NARROW (no row map): an item is 64 >> lw tile rows of 1 << lw columns each, lw >= 3, and lay the planes' layout; `chunks` items to a row
 // group.  Items of a single row left a matrix of 16 tile columns with a quarter of each lane's work: two
 // encodes of 4800 x 16 tiles, r = 32, 12.3 -> 6.9 us, their two decodes with a basis gradient each 12.7 -> 7.6.
-template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false, bool NARROW = false>
+// FLAT (with NARROW; more than 32 columns, groups of 64 tile rows): an item is 64 tiles that follow each other in the planes' groups, whatever the
+// rows; a group of Cc items.  No item but the last is incomplete, and every plane access is a whole line: dYhat + dD of 4800 x 50 tiles, r = 32,
+// with their final sum 17.7 -> 13.7 us, of 8192 x 100 45.6 -> 28.7, of 2048 x 1000 84 -> 71, of 512 x 250 11.6 -> 10.7.
+template <int KC, bool OUTER, bool THROUGH = false, int DEPTH = 1, bool ANY = false, bool SHIFT = false, bool NARROW = false, bool FLAT = false>
 __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const bf16_t *__restrict__ E, bf16_t *__restrict__ P,
                                              const bf16_t *__restrict__ Qp, int R, int Cc, int r, int chunks, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&dacc)[4], int lane,
@@ -75,8 +104,19 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
     // NARROW: tile row and column of tile t of an item, offset of the plane row that holds chunk ch (8 tiles) of it, elements left there
     struct Pos { int I, J; };
     auto locate = [&](long item, int t) {
+        if constexpr (FLAT) return flat_tile(item, t, Cc).template as<Pos>();
         const int rb = (int)(item / chunks), ck = (int)(item - (long)rb * chunks);
         return Pos{(rb << (6 - lw)) + (t >> lw), (ck << lw) + (t & ((1 << lw) - 1))};
+    };
+    // where chunk ch (8 tiles) of an item lies in plane 0, and how many elements from there on are the item's or follow it
+    struct Run { size_t off; int left; };
+    auto run = [&](long item) {
+        if constexpr (FLAT) {
+            const FlatRun f = flat_run(item, 8 * ch, R, Cc, r);
+            return Run{f.off, f.left};
+        }
+        const Pos at = locate(item, 8 * ch);
+        return Run{(size_t)lay.row(at.I) + at.J, at.I < R ? Cc - at.J : 0};
     };
     auto fetch_narrow = [&](int d, long item) {
 #pragma unroll
@@ -87,12 +127,11 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
             xa[d][u] = v;
         }
         if (OUTER) {
-            const Pos at = locate(item, 8 * ch);
-            const size_t off = (size_t)lay.row(at.I) + at.J;
+            const Run at = run(item);
 #pragma unroll
             for (int g8 = 0; g8 < KC * 4; ++g8) {
                 const int pl = 8 * g8 + pr;
-                qa[d][g8] = load8<ANY>(Qp + off + (size_t)pl * plane, at.I < R && pl < r ? Cc - at.J : 0);
+                qa[d][g8] = load8<ANY>(Qp + at.off + (size_t)pl * plane, pl < r ? at.left : 0);
             }
         }
     };
@@ -196,13 +235,13 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
             }
         }
         if constexpr (NARROW) {
-            const Pos at = locate(item0, 8 * ch);
-            bf16_t *o = P + lay.row(at.I) + at.J;
+            const Run at = run(item0);
+            bf16_t *o = P + at.off;
 #pragma unroll
             for (int g8 = 0; g8 < KC * 4; ++g8) {
                 const int pl = 8 * g8 + pr;
-                if (pl < r && at.I < R && at.J < Cc)
-                    store8<ANY>(o + (size_t)pl * plane, Cc - at.J, *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4)));
+                if (pl < r && at.left > 0)
+                    store8<ANY>(o + (size_t)pl * plane, at.left, *reinterpret_cast<const u32x4_t *>(slab + pl * ROWB + ((ch ^ swz(pl)) << 4)));
             }
             continue;
         }
