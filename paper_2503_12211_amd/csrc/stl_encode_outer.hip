@@ -67,10 +67,11 @@ struct EncodeSide {
     const bf16_t *A, *E;
     bf16_t *P;
     int R, Cc, chunks, lw;
+    long items;
     Lay lay;
     bool turned;
     // false: a layout that Lay does not describe
-    bool set(const TileSide &t, int r, int pg, bool narrow)
+    bool set(const TileSide &t, int r, int pg, bool narrow, bool flat)
     {
         A = (const bf16_t *)t.matrix;
         E = (const bf16_t *)t.basis;
@@ -81,43 +82,46 @@ struct EncodeSide {
         const int l = narrow_log2(1, Cc, true);
         lw = narrow && l ? l : 6;
         chunks = (Cc + (1 << lw) - 1) >> lw;
+        items = flat ? flat_items(R, Cc) : (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks;
         return lay.set(pg, R, Cc, r);
     }
-    long items() const { return (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks; }
 };
 
-template <int KC, bool ANY, bool NARROW>
+template <int KC, bool ANY, bool NARROW, bool FLAT>
 __global__ __launch_bounds__(256) void encode_pair_kernel(EncodeSide s0, EncodeSide s1, int r, int pg)
 {
     __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const EncodeSide s = blockIdx.y ? s1 : s0;
-    const int rows = 64 >> s.lw;
     f32x4_t none[4];
-    encode_items<KC, false, false, 1, ANY, false, NARROW>(s.A, s.E, s.P, nullptr, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
-                                                          (long)gridDim.x * 4, (long)((s.R + rows - 1) / rows) * s.chunks, nullptr,
-                                                          slab_all[wave], none, lane, s.turned, s.lw, s.lay);
+    encode_items<KC, false, false, 1, ANY, false, NARROW, FLAT>(s.A, s.E, s.P, nullptr, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                                (long)gridDim.x * 4, s.items, nullptr, slab_all[wave], none, lane, s.turned,
+                                                                s.lw, s.lay);
 }
 
-// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns
+// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns or in items that follow the planes
 static hipError_t launch_encode_sides(const TileSide *t, int n, int r, int pg, hipStream_t st)
 {
     EncodeSide s[2] = {};
-    bool any = false, narrow = false;
+    bool any = false, narrow = false, flat = true;
+    long items = 0;
+    for (int i = 0; i < n; ++i) items += row_items(t[i].R, t[i].Cc);
     for (int i = 0; i < n; ++i) {
         any = any || t[i].Cc % 8;
         narrow = narrow || narrow_log2(1, t[i].Cc, true);
+        flat = flat && flat_pays(t[i].R, t[i].Cc, pg, items);
     }
     long blocks = 1;
     for (int i = 0; i < n; ++i) {
-        if (!s[i].set(t[i], r, pg, narrow)) return hipErrorInvalidValue;
-        const long b = (s[i].items() + 3) / 4;
+        if (!s[i].set(t[i], r, pg, narrow, flat)) return hipErrorInvalidValue;
+        const long b = (s[i].items + 3) / 4;
         blocks = b > blocks ? b : blocks;
     }
     auto pick = [&](auto kc) {
         constexpr int KC = decltype(kc)::value;
-        return narrow ? (any ? encode_pair_kernel<KC, true, true> : encode_pair_kernel<KC, false, true>)
-                      : (any ? encode_pair_kernel<KC, true, false> : encode_pair_kernel<KC, false, false>);
+        if (flat) return any ? encode_pair_kernel<KC, true, true, true> : encode_pair_kernel<KC, false, true, true>;
+        return narrow ? (any ? encode_pair_kernel<KC, true, true, false> : encode_pair_kernel<KC, false, true, false>)
+                      : (any ? encode_pair_kernel<KC, true, false, false> : encode_pair_kernel<KC, false, false, false>);
     };
     auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
     hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks), n), dim3(256), 0, st, s[0], s[1], r, pg);
@@ -133,8 +137,7 @@ hipError_t launch_encode_pair(const TileSide *t, int r, int pg, hipStream_t st) 
 
 // encode and basis gradient of a matrix of 8 to 32 tile columns, or in items that follow the planes (FLAT), nb blocks that leave one partial each
 template <int KC, bool ANY, bool FLAT>
-__global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, const bf16_t *__restrict__ Qp, float *__restrict__ part, int r, int pg,
-                                                                  long items)
+__global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, const bf16_t *__restrict__ Qp, float *__restrict__ part, int r, int pg)
 {
     __shared__ __align__(16) char sT_all[4][64 * 32];
     __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
@@ -143,28 +146,24 @@ __global__ __launch_bounds__(256) void encode_outer_narrow_kernel(EncodeSide s, 
 #pragma unroll
     for (int g = 0; g < 4; ++g) dacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     encode_items<KC, true, false, 1, ANY, false, true, FLAT>(s.A, s.E, s.P, Qp, s.R, s.Cc, r, s.chunks, pg, RowMap(), (long)blockIdx.x * 4 + wave,
-                                                             (long)gridDim.x * 4, items, sT_all[wave], slab_all[wave], dacc, lane, false, s.lw,
+                                                             (long)gridDim.x * 4, s.items, sT_all[wave], slab_all[wave], dacc, lane, false, s.lw,
                                                              s.lay);
     write_partial<KC>(dacc, reinterpret_cast<float *>(&slab_all[0][0]), part, r, wave, lane);
 }
 
-// Whether the items of a matrix without a row map follow the planes rather than the rows: where rows are no whole items and planes lie in
-// groups of 64 of them.
-static bool flat_form(int Cc, int pg) { return pg == 64 && Cc > 32 && Cc % 64; }
-
 static hipError_t launch_encode_outer_narrow(const TileSide &t, const void *Qp, float *part, int r, int pg, int nb, hipStream_t st)
 {
+    const bool any = t.Cc % 8, flat = flat_form(t.R, t.Cc, pg);
     EncodeSide s;
-    if (!s.set(t, r, pg, true)) return hipErrorInvalidValue;
+    if (!s.set(t, r, pg, true, flat)) return hipErrorInvalidValue;
     auto pick = [&](auto any_c, auto flat_c) {
         constexpr bool ANY = decltype(any_c)::value, FLAT = decltype(flat_c)::value;
         return r <= 32 ? encode_outer_narrow_kernel<1, ANY, FLAT> : encode_outer_narrow_kernel<2, ANY, FLAT>;
     };
     using T = std::true_type;
     using F = std::false_type;
-    const bool any = t.Cc % 8, flat = flat_form(t.Cc, pg);
     auto kern = any ? (flat ? pick(T{}, T{}) : pick(T{}, F{})) : (flat ? pick(F{}, T{}) : pick(F{}, F{}));
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, st, s, (const bf16_t *)Qp, part, r, pg, flat ? flat_items(t.R, t.Cc) : s.items());
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, st, s, (const bf16_t *)Qp, part, r, pg);
     return hipGetLastError();
 }
 
@@ -172,7 +171,8 @@ static hipError_t launch_encode_outer_narrow(const TileSide &t, const void *Qp, 
 hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, const void *Qp, float *part, int R, int Cc, int r, int pg,
                                      int nb, hipStream_t s, RowMap rm)
 {
-    if (rm.Mt == 0 && (narrow_log2(1, Cc, true) || flat_form(Cc, pg))) return launch_encode_outer_narrow({P, E, A, R, Cc, false, nullptr, nullptr}, Qp, part, r, pg, nb, s);
+    if (rm.Mt == 0 && (narrow_log2(1, Cc, true) || flat_form(R, Cc, pg)))
+        return launch_encode_outer_narrow({P, E, A, R, Cc, false, nullptr, nullptr}, Qp, part, r, pg, nb, s);
     const bool any = Cc % 8 != 0;
     auto kern = r <= 32 ? (any ? encode_outer16_kernel<1, true, true> : encode_outer16_kernel<1, true, false>)
                         : (any ? encode_outer16_kernel<2, true, true> : encode_outer16_kernel<2, true, false>);
@@ -192,7 +192,7 @@ hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int
     if (pg <= 0) pg = R;
     R = rm.count(R);
     if (R <= 0) return hipSuccess;
-    if (encode_narrow(R, Cc, rm.Mt == 0)) {
+    if (encode_narrow(R, Cc, rm.Mt == 0) || (rm.Mt == 0 && flat_pays(R, Cc, pg, row_items(R, Cc)))) {
         const TileSide one{P, E, A, R, Cc, false, nullptr, nullptr};
         return launch_encode_sides(&one, 1, r, pg, s);
     }

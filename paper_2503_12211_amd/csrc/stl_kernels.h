@@ -89,6 +89,20 @@ int gradient_blocks(int dtype, int R, int Cc, bool plain_rows);
 // bf16 matrices of 8 to 32 tile columns (no row map) run in items of several tile rows, 1 << narrow_log2 columns each; 0: they do not
 // (of more columns an item, 64 tiles of a power of two of columns, is a single row)
 int narrow_log2(int dtype, int Cc, bool plain_rows);
+// Items of a bf16 matrix without a row map: 64 tile columns of one row, or 64 tiles in a row of the planes (FLAT in stl_tile_items.h), which is
+// possible where rows are no whole items and planes lie in groups of 64 tile rows.
+inline long row_items(int R, int Cc) { return (long)R * ((Cc + 63) / 64); }
+inline long flat_items(int R, int Cc) { return (long)(R / 64) * Cc + ((long)(R % 64) * Cc + 63) / 64; }
+inline bool flat_form(int R, int Cc, int pg) { return pg == 64 && Cc > 32 && Cc % 64 && R < 1 << 24; }   // (R: Lay::set takes it)
+// Whether that pays in a launch that has `items` of the first kind in all, other than the encode with a basis gradient.  An item that follows the
+// planes costs two divisions more before its first load, and a launch of half a round of items or less takes the 5 us of its start either
+// way.  Beyond that the planes' rows of 64 elements are whole cache lines if Cc is no multiple of 8 (2997 x 133 tiles, r = 64: encode
+// 15.9 -> 13.1 us, decode 22.7 -> 15.4, with its basis gradient 31.5 -> 23.6; two such decodes 44.9 -> 32.3), and if it is there only are fewer
+// items, which has to be felt: 3200 x 200, r = 32, 7/9 of them, decode 13.9 -> 11.6, but 2048 x 1000, 1/50 less, encode 35.6 -> 37.6.
+inline bool flat_pays(int R, int Cc, int pg, long items)
+{
+    return flat_form(R, Cc, pg) && (Cc % 8 ? items > 2048 : items > 4096 && 8 * flat_items(R, Cc) <= 7 * row_items(R, Cc));
+}
 bool encode_narrow(int R, int Cc, bool plain_rows);      // whether an encode alone does
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);

@@ -33,8 +33,6 @@ __device__ __forceinline__ FlatRun flat_run(long item, int t, int R, int Cc, int
     return {(size_t)g * r * 64 * Cc + o, (rows < 64 ? rows : 64) * Cc - o};
 }
 
-inline long flat_items(int R, int Cc) { return (long)(R / 64) * Cc + ((long)(R % 64) * Cc + 63) / 64; }
-
 // The item loop of one wavefront: items `first`, `first + stride`, ... below `end`, an item being (tile row index of the
 // launch, 64-tile chunk) = item / chunks, item % chunks.  sT and slab are LDS areas private to the wavefront
 // (sT: 64 x 32 bytes, used with OUTER only; slab: KC * 32 * 128 bytes); dacc accumulates the basis gradient (OUTER).
@@ -265,7 +263,7 @@ __device__ __forceinline__ void encode_items(const bf16_t *__restrict__ A, const
 // wavefront; sT: 64 x 32 bytes (OUTER only); oacc accumulates the basis gradient (OUTER).  No workgroup barrier inside.
 // DECODE = false: the basis gradient alone (Dm and Cmat unused).  TP: storage type of the planes; fp32 planes (the gradient of
 // an encoded weight) are rounded to bf16 on their way into LDS.
-template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t, bool NARROW = false>   // DEPTH, ANY, NARROW as in encode_items
+template <bool GELU, int KC, bool OUTER, int DEPTH = 1, bool ANY = false, bool DECODE = true, typename TP = bf16_t, bool NARROW = false, bool FLAT = false>   // DEPTH, ANY, NARROW, FLAT as in encode_items
 __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf16_t *__restrict__ Dm, bf16_t *__restrict__ Cmat,
                                              int R, int Cc, int r, int chunks, const bf16_t *__restrict__ V, int pg, const RowMap &rm,
                                              long first, long stride, long end, char *sT, char *slab, f32x4_t (&oacc)[4], int lane,
@@ -307,16 +305,26 @@ __device__ __forceinline__ void decode_items(const TP *__restrict__ P, const bf1
     u32x2_t xpre[DEPTH][OUTER ? 4 : 1];
     struct Pos { int I, J; };
     auto locate = [&](long item, int t) {
+        if constexpr (FLAT) return flat_tile(item, t, Cc).template as<Pos>();
         const int rb = (int)(item / chunks), ck = (int)(item - (long)rb * chunks);
         return Pos{(rb << (6 - lw)) + (t >> lw), (ck << lw) + (t & ((1 << lw) - 1))};
     };
     auto fetch_narrow = [&](int d, long item) {
-        const Pos at = locate(item, 8 * ch);
-        const size_t off = (size_t)lay.row(at.I) + at.J;
+        size_t off;
+        int left;                                           // elements from there on that are the item's or follow it
+        if constexpr (FLAT) {
+            const FlatRun f = flat_run(item, 8 * ch, R, Cc, r);
+            off = f.off;
+            left = f.left;
+        } else {
+            const Pos at = locate(item, 8 * ch);
+            off = (size_t)lay.row(at.I) + at.J;
+            left = at.I < R ? Cc - at.J : 0;
+        }
 #pragma unroll
         for (int g8 = 0; g8 < KC * 4; ++g8) {
             const int pl = 8 * g8 + pr;
-            pre[d][g8].load(P + off + (size_t)pl * plane, at.I < R && pl < r ? Cc - at.J : 0);
+            pre[d][g8].load(P + off + (size_t)pl * plane, pl < r ? left : 0);
         }
         if (OUTER) {
             const Pos v = locate(item, lane);

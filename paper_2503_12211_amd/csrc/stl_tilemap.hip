@@ -450,9 +450,10 @@ struct DecodeSide {
     bf16_t *Cmat;
     float *part;
     int R, Cc, chunks, nb, lw;
+    long items;
     Lay lay;
     bool turned;
-    bool set(const TileSide &t, int r, int pg, bool narrow)
+    bool set(const TileSide &t, int r, int pg, bool narrow, bool flat)
     {
         P = (const bf16_t *)t.planes;
         Dm = (const bf16_t *)t.basis;
@@ -465,13 +466,13 @@ struct DecodeSide {
         const int l = narrow_log2(1, Cc, true);
         lw = narrow && l ? l : 6;
         chunks = (Cc + (1 << lw) - 1) >> lw;
+        items = flat ? flat_items(R, Cc) : (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks;
         nb = gradient_blocks(1, R, Cc, true);
         return lay.set(pg, R, Cc, r);
     }
-    __host__ __device__ __forceinline__ long items() const { return (long)((R + (64 >> lw) - 1) / (64 >> lw)) * chunks; }
 };
 
-template <int KC, bool ANY, bool NARROW, bool DECODE>
+template <int KC, bool ANY, bool NARROW, bool DECODE, bool FLAT>
 __global__ __launch_bounds__(256) void decode_outer_pair_kernel(DecodeSide s0, DecodeSide s1, int r, int pg)
 {
     constexpr int ROWB = 128;
@@ -483,22 +484,22 @@ __global__ __launch_bounds__(256) void decode_outer_pair_kernel(DecodeSide s0, D
     f32x4_t oacc[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) oacc[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    decode_items<false, KC, true, 1, ANY, DECODE, bf16_t, NARROW>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, s.V, pg, RowMap(),
-                                                                  (long)blockIdx.x * 4 + wave, (long)s.nb * 4, s.items(), sT_all[wave],
-                                                                  slab_all[wave], oacc, lane, s.turned, s.lw, s.lay);
+    decode_items<false, KC, true, 1, ANY, DECODE, bf16_t, NARROW, FLAT>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, s.V, pg, RowMap(),
+                                                                        (long)blockIdx.x * 4 + wave, (long)s.nb * 4, s.items, sT_all[wave],
+                                                                        slab_all[wave], oacc, lane, s.turned, s.lw, s.lay);
     write_partial<KC>(oacc, reinterpret_cast<float *>(&slab_all[0][0]), s.part, r, wave, lane);
 }
 
-// decode of a matrix of 8 to 32 tile columns
-template <bool GELU, int KC, bool ANY>
+// decode of a matrix of 8 to 32 tile columns, or in items that follow the planes
+template <bool GELU, int KC, bool ANY, bool FLAT>
 __global__ __launch_bounds__(256) void decode_narrow_kernel(DecodeSide s, int r, int pg)
 {
     __shared__ __align__(16) char slab_all[4][KC * 32 * 128];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     f32x4_t none[4];
-    decode_items<GELU, KC, false, 1, ANY, true, bf16_t, true>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, nullptr, pg, RowMap(), (long)blockIdx.x * 4 + wave,
-                                                              (long)gridDim.x * 4, s.items(), nullptr, slab_all[wave], none, lane, false, s.lw,
-                                                              s.lay);
+    decode_items<GELU, KC, false, 1, ANY, true, bf16_t, true, FLAT>(s.P, s.Dm, s.Cmat, s.R, s.Cc, r, s.chunks, nullptr, pg, RowMap(), (long)blockIdx.x * 4 + wave,
+                                                                    (long)gridDim.x * 4, s.items, nullptr, slab_all[wave], none, lane, false,
+                                                                    s.lw, s.lay);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -708,16 +709,21 @@ hipError_t launch_decode(int dtype, const void *P, const void *Dm, void *Cmat, i
     if ((dtype == 0 || !fold.coef) && tile_per_thread(dtype, true, R, Cc, r))
         return dtype == 0 ? launch_decode_tiles<float>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm)
                           : launch_decode_tiles<bf16_t>(P, Dm, Cmat, R, Cc, r, gelu, pg, s, rm);
-    if (dtype == 1 && !fold.coef && narrow_log2(dtype, Cc, rm.Mt == 0)) {
+    const bool flat = dtype == 1 && rm.Mt == 0 && flat_pays(R, Cc, pg, row_items(R, Cc));
+    if (dtype == 1 && !fold.coef && (flat || narrow_log2(dtype, Cc, rm.Mt == 0))) {
         DecodeSide d;
-        if (!d.set({P, Dm, Cmat, R, Cc, false, nullptr, nullptr}, r, pg, true)) return hipErrorInvalidValue;
-        const long blocks = (d.items() + 3) / 4;
-        auto pick = [&](auto kc) {
+        if (!d.set({P, Dm, Cmat, R, Cc, false, nullptr, nullptr}, r, pg, true, flat)) return hipErrorInvalidValue;
+        const long blocks = (d.items + 3) / 4;
+        auto pick = [&](auto kc, auto flat_c) {
             constexpr int KC = decltype(kc)::value;
-            return Cc % 8 ? (gelu ? decode_narrow_kernel<true, KC, true> : decode_narrow_kernel<false, KC, true>)
-                          : (gelu ? decode_narrow_kernel<true, KC, false> : decode_narrow_kernel<false, KC, false>);
+            constexpr bool FLAT = decltype(flat_c)::value;
+            return Cc % 8 ? (gelu ? decode_narrow_kernel<true, KC, true, FLAT> : decode_narrow_kernel<false, KC, true, FLAT>)
+                          : (gelu ? decode_narrow_kernel<true, KC, false, FLAT> : decode_narrow_kernel<false, KC, false, FLAT>);
         };
-        auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
+        using One = std::integral_constant<int, 1>;
+        using Two = std::integral_constant<int, 2>;
+        auto kern = flat ? (r <= 32 ? pick(One{}, std::true_type{}) : pick(Two{}, std::true_type{}))
+                         : (r <= 32 ? pick(One{}, std::false_type{}) : pick(Two{}, std::false_type{}));
         hipLaunchKernelGGL(kern, dim3((unsigned)(blocks > 8192 ? 8192 : blocks)), dim3(256), 0, s, d, r, pg);
         return hipGetLastError();
     }
@@ -798,25 +804,31 @@ hipError_t launch_decode_outer_f32(const float *P, const void *E, void *W, const
 // 900 x 200 x 200, r = 32 (900) 262 / 258, but 250 x 256 x 256, r = 64 (250) 178 / 184.
 static bool small_gradient(int nb, int r) { return nb < 1024 && (r <= 32 || nb <= 192); }
 
-// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns (its matrix may be NULL: the basis gradient alone)
+// n = 2: as the name says; n = 1: one matrix of 8 to 32 tile columns or in items that follow the planes (its matrix may be NULL: the basis gradient alone)
 static hipError_t launch_decode_outer_sides(const TileSide *t, int n, int r, int pg, hipStream_t st)
 {
     DecodeSide s[2] = {};
-    bool any = false, narrow = false;
+    bool any = false, narrow = false, flat = true;
+    long items = 0;
+    for (int i = 0; i < n; ++i) items += row_items(t[i].R, t[i].Cc);
     int nb = 1;
     for (int i = 0; i < n; ++i) {
         any = any || t[i].Cc % 8;
         narrow = narrow || narrow_log2(1, t[i].Cc, true);
+        flat = flat && flat_pays(t[i].R, t[i].Cc, pg, items);
     }
     for (int i = 0; i < n; ++i) {
-        if (!s[i].set(t[i], r, pg, narrow)) return hipErrorInvalidValue;
+        if (!s[i].set(t[i], r, pg, narrow, flat)) return hipErrorInvalidValue;
         nb = s[i].nb > nb ? s[i].nb : nb;
     }
     auto pick = [&](auto kc) {
         constexpr int KC = decltype(kc)::value;
-        if (!t[0].matrix) return any ? decode_outer_pair_kernel<KC, true, true, false> : decode_outer_pair_kernel<KC, false, true, false>;
-        return narrow ? (any ? decode_outer_pair_kernel<KC, true, true, true> : decode_outer_pair_kernel<KC, false, true, true>)
-                      : (any ? decode_outer_pair_kernel<KC, true, false, true> : decode_outer_pair_kernel<KC, false, false, true>);
+        if (flat)
+            return t[0].matrix ? (any ? decode_outer_pair_kernel<KC, true, true, true, true> : decode_outer_pair_kernel<KC, false, true, true, true>)
+                               : (any ? decode_outer_pair_kernel<KC, true, true, false, true> : decode_outer_pair_kernel<KC, false, true, false, true>);
+        if (!t[0].matrix) return any ? decode_outer_pair_kernel<KC, true, true, false, false> : decode_outer_pair_kernel<KC, false, true, false, false>;
+        return narrow ? (any ? decode_outer_pair_kernel<KC, true, true, true, false> : decode_outer_pair_kernel<KC, false, true, true, false>)
+                      : (any ? decode_outer_pair_kernel<KC, true, false, true, false> : decode_outer_pair_kernel<KC, false, false, true, false>);
     };
     auto kern = r <= 32 ? pick(std::integral_constant<int, 1>{}) : pick(std::integral_constant<int, 2>{});
     hipLaunchKernelGGL(kern, dim3(nb, n), dim3(256), 0, st, s[0], s[1], r, pg);
@@ -848,7 +860,7 @@ hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *C
     if (R <= 0) return hipErrorInvalidValue;
     const int nb = gradient_blocks(dtype, R, Cc, rm.Mt == 0);
     hipError_t e;
-    if (narrow_log2(dtype, Cc, rm.Mt == 0)) {
+    if (dtype == 1 && rm.Mt == 0 && (narrow_log2(dtype, Cc, true) || flat_pays(R, Cc, pg, row_items(R, Cc)))) {
         const TileSide one{P, Dm, Cmat, R, Cc, false, V, part};
         e = launch_decode_outer_sides(&one, 1, r, pg, s);
     } else if (dtype == 1 && Cc >= 8) {

@@ -15,7 +15,10 @@ pytestmark = pytest.mark.gpu
 NAMES = ("dX", "dWhat", "dE_X", "dD")
 # M, K, N tile counts, r
 SHAPES = [(1, 33, 34, 5), (63, 36, 33, 3), (64, 63, 65, 8), (65, 100, 72, 33), (129, 127, 191, 49), (128, 40, 250, 16), (200, 200, 50, 32), (2, 130, 264, 64),
-          (67, 1000, 48, 8), (1100, 37, 41, 32)]
+          (67, 1000, 48, 8), (1100, 37, 41, 32),
+          # encodes and decodes without a basis gradient and pairs: from 2048 items of a row's 64 columns (4096 if the width is a multiple of 8) on
+          (2100, 37, 41, 5), (4100, 40, 72, 3), (690, 164, 133, 49)]
+PAIRS = [(28, 160, 148, 164, 8), (3, 2000, 1996, 140, 33)]
 
 
 @pytest.fixture(scope="module")
@@ -43,3 +46,19 @@ def test_step(gu, M, K, N, r):
     gu.check(one["dX"], ref["dX"], "bf16", "dX")
     for name in ("dE_X", "dD"):
         gu.check(two[name], ref[name], "bf16", name)
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("nb,m,k,n,r", PAIRS)
+def test_pairs(gu, nb, m, k, n, r, transposed):
+    p = stl_synth.aa_problem(nb, m, k, n, r, seed=2400 + m + r, dtype="bf16", with_dC=True)
+    args = (p["A"], p["B"], p["E_A"], p["E_B"], p["D"])
+    if transposed:
+        args = (p["A"], np.concatenate([b.T for b in np.split(p["B"], nb)]), p["E_A"], p["E_B"], p["D"])
+    ref = planes.aa_backward(*args, p["dC"], nbatch=nb, b_transposed=transposed)
+    C = planes.aa_forward(*args, nbatch=nb, b_transposed=transposed)
+    kw = {"flags": gu.stl.STL_FLAG_B_TRANSPOSED if transposed else 0}
+    gu.check(gu.aa_forward(*args, nb, "bf16", **kw), C, "bf16", "C")
+    got = gu.aa_backward(*args, p["dC"], nb, "bf16", **kw)
+    for name, want in zip(("dA", "dB", "dE_A", "dE_B", "dD"), ref):
+        gu.check(got[name], want, "bf16", name)
