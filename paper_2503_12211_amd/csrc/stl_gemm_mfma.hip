@@ -407,18 +407,19 @@ hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *
 
 // Pairs: a gradient of few blocks is the latency of its chain of stages, and two that read the same planes and write different ones
 // need not wait for each other.  us, two launches / one, r = 32: dWhat and dXhat of 512 x 192 x 250 18.0 / 14.0, of 64 x 128 x 96 8.6 / 5.7, dAhat
-// and dBhat of 96 x (50 x 16 x 50) 14.1 / 11.5; over 45 layers of odd widths 1.26 times as fast, over 25 pairs of activations 1.28.  A block has one
-// group of wavefronts, and where the contraction of one product alone is a single stage, the registers and LDS of two: many
-// blocks of that kind (96 x (256 x 256 x 8), 61440 blocks, 206 / 244; 48 x (145 x 145 x 32), 9216, 23.9 / 26.1; 2640 blocks 20.2 / 17.4, 3500 19.5 / 18.5) or one whose
-// contraction four groups would share (12 x 140 x 951, r = 40, 17.6 / 20.0) stay apart.
+// and dBhat of 96 x (50 x 16 x 50) 14.1 / 11.5; whole backward passes over 228 layers of odd widths 1.16 times as fast in the mean (5 % slower
+// at worst), over 259 pairs of activations 1.15 (4 %).  A block has one group of wavefronts.  Where two groups would share a contraction that is
+// little lost (of up to 7 stages 1.00 to 1.33, of 8 to 11 0.95 to 1.24); one that four would share is a chain longer than all the rest: whole
+// backward passes of 5886 x 15 x 82, r = 3 59.7 / 104, 7037 x 9 x 69, r = 32 85 / 121, 750 x 12 x 159, r = 3 19.9 / 21.6, 837 x 52 x 126, r = 64
+// 34.8 / 36.6, in the mean of 45 1.2 times as long (at best 1.06 times as fast): such products stay apart.  Where the contraction of
+// one product alone is a single stage, a block has the registers and LDS of two: many blocks of that kind stay apart too (96 x (256 x 256 x 8), 61440
+// blocks, 206 / 244; 48 x (145 x 145 x 32), 9216, 23.9 / 26.1; 2640 blocks 20.2 / 17.4, 3500 19.5 / 18.5).
 bool staged_pair_eligible(const GemmDesc &g1, const GemmDesc &g2)
 {
     if (plane_gemm_path(1, g1) != GemmPath::staged || plane_gemm_path(1, g2) != GemmPath::staged) return false;
-    if (staged_block(g1) != 64 || staged_block(g2) != 64) return false;
+    if (staged_block(g1) != 64 || staged_block(g2) != 64 || staged_groups(g1) == 4 || staged_groups(g2) == 4) return false;
     auto blocks = [](const GemmDesc &g) { return (double)((g.Mi + 63) / 64) * ((g.Nj + 63) / 64) * g.batch * g.nb; };
-    const double both = blocks(g1) + blocks(g2);
-    const bool one1 = g1.Kl <= staged::BK, one2 = g2.Kl <= staged::BK;
-    return one1 == one2 ? both < (1 << 22) : both <= 3072 && staged_groups(one1 ? g2 : g1) < 4;
+    return blocks(g1) + blocks(g2) <= ((g1.Kl <= staged::BK) == (g2.Kl <= staged::BK) ? (1 << 22) - 1 : 3072);
 }
 
 template <int PF, bool A1, bool B1, typename T1, bool ACC1, bool A2, bool B2, typename T2>

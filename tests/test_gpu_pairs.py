@@ -16,6 +16,8 @@ NAMES = ("dX", "dWhat", "dE_X", "dD")
 # dtype, M, K, N tile counts, r -> whether dWhat and dXhat run together
 SHAPES = {("bf16", 9, 10, 11, 3): True, ("bf16", 64, 61, 63, 8): True, ("bf16", 65, 66, 67, 5): True, ("bf16", 50, 33, 130, 32): True,
           ("bf16", 130, 129, 20, 9): True, ("bf16", 12, 140, 951, 40): False, ("bf16", 15, 601, 479, 49): False, ("bf16", 130, 264, 70, 3): True,
+          # contractions that two and four groups of wavefronts share where a product runs by itself
+          ("bf16", 704, 67, 70, 3): True, ("bf16", 705, 67, 70, 3): False, ("bf16", 2899, 9, 195, 3): False, ("bf16", 70, 67, 706, 3): False,
           # widths that are multiples of 8: edges of 64 and 64, 64 and 128, 128 and 64, 128 and 128; contractions of part of a stage, of one, of as
           # many as a ring holds and of more
           ("bf16", 8, 16, 8, 3): True, ("bf16", 64, 64, 64, 5): True, ("bf16", 65, 136, 264, 9): True, ("bf16", 257, 72, 32, 33): True,
@@ -25,7 +27,8 @@ SHAPES = {("bf16", 9, 10, 11, 3): True, ("bf16", 64, 61, 63, 8): True, ("bf16", 
           ("f32", 100, 16, 30, 64): True}
 # nbatch, M, K, N, r, second operand stored transposed -> whether dAhat and dBhat do
 AA_SHAPES = {(3, 9, 11, 13, 4, False): True, (3, 9, 11, 13, 4, True): True, (8, 50, 16, 50, 32, True): True, (8, 50, 50, 16, 32, False): True,
-             (5, 70, 33, 66, 8, True): True, (5, 70, 66, 33, 8, False): True, (17, 100, 70, 20, 32, False): False}
+             (5, 70, 33, 66, 8, True): True, (5, 70, 66, 33, 8, False): True, (17, 100, 70, 20, 32, False): False,
+             (2, 704, 67, 66, 3, False): True, (2, 705, 67, 66, 3, False): False, (1, 70, 66, 705, 5, True): False}
 
 
 @pytest.fixture(scope="module")
