@@ -83,12 +83,12 @@ def host(t):
 PG = stl.STL_PLANE_GROUP
 
 
-def group_planes(a):
-    """Plane-major (r, R, Cc) numpy -> the library's activation-side layout (groups of PG tile rows), flat."""
+def group_planes(a, behind=0.0):
+    """Plane-major (r, R, Cc) numpy -> the library's activation-side layout (groups of PG tile rows), flat; `behind`: the rows behind R."""
     a = np.asarray(a)
     r, R, Cc = a.shape
     Rp = (R + PG - 1) // PG * PG
-    pad = np.zeros((r, Rp, Cc), dtype=a.dtype)
+    pad = np.full((r, Rp, Cc), behind, dtype=a.dtype)
     pad[:, :R] = a
     return np.ascontiguousarray(pad.reshape(r, Rp // PG, PG, Cc).transpose(1, 0, 2, 3)).reshape(-1)
 
@@ -104,9 +104,9 @@ def planes_buffer(r, R, Cc, dtype, fill=float("nan")):
     return torch.full((stl.stl_plane_elems(R, Cc, r),), fill, dtype=TORCH_DT[dtype], device="cuda")
 
 
-def planes_to_dev(a, dtype):
+def planes_to_dev(a, dtype, behind=0.0):
     """plane-major numpy (r, R, Cc) -> device tensor in the grouped layout"""
-    return dev(group_planes(np.asarray(a, dtype=np.float32)), dtype)
+    return dev(group_planes(np.asarray(a, dtype=np.float32), behind), dtype)
 
 
 def planes_to_host(t, r, R, Cc):
@@ -163,14 +163,16 @@ def forward(p, dtype, flags=0, save_yhat=False, save_xhat=False):
     return (host(C), planes_to_host(Y, r, m // 4, N)) if save_yhat else host(C)
 
 
-def backward(p, dtype, yhat=None, accumulate=0, init=None, skip=(), xhat=None):
+def backward(p, dtype, yhat=None, accumulate=0, init=None, skip=(), xhat=None, poison=False):
+    """poison: the planes' rows behind the last tile row, and the workspace before the call, are not numbers."""
     m, k = p["X"].shape
     r, K, N = p["What"].shape
     n = 4 * N
     prob = stl.Problem(m, k, n, r, STL_DT[dtype])
     X, What, E_X, D, dC = (dev(p[s], dtype) for s in ("X", "What", "E_X", "D", "dC"))
-    Y = planes_to_dev(yhat, dtype) if yhat is not None else None
-    Xh = planes_to_dev(xhat, dtype) if xhat is not None else None
+    behind = np.nan if poison else 0.0
+    Y = planes_to_dev(yhat, dtype, behind) if yhat is not None else None
+    Xh = planes_to_dev(xhat, dtype, behind) if xhat is not None else None
     gd = Guard()
     outs = {"dX": gd.alloc((m, k), TORCH_DT[dtype]), "dWhat": gd.alloc((r, K, N), torch.float32),
             "dE_X": gd.alloc((r, 16), torch.float32), "dD": gd.alloc((r, 16), torch.float32)}
@@ -179,7 +181,7 @@ def backward(p, dtype, yhat=None, accumulate=0, init=None, skip=(), xhat=None):
             outs[name].copy_(torch.from_numpy(np.asarray(a, dtype=np.float32)))
     args = {k_: (None if k_ in skip else v) for k_, v in outs.items()}
     nbytes = stl.stl_workspace_bytes(prob, stl.STL_OP_BACKWARD)
-    ws = gd.alloc((max(nbytes, 16),), torch.uint8, fill=None)
+    ws = gd.alloc((max(nbytes, 16),), torch.uint8, fill=0xFF if poison else None)      # all ones: not a number in both types
     stl.stl_backward(prob, X, What, E_X, D, dC, Xh, Y, args["dX"], args["dWhat"], args["dE_X"], args["dD"],
                      accumulate, ws, nbytes)
     gd.check()
