@@ -55,11 +55,23 @@ int encode_outer_blocks(int R, int Cc)
 }
 
 // A plane row of a width that is no multiple of 8 begins anywhere in a cache line, so that items of 64 columns counted from its
-// beginning write two incomplete lines per plane.  Once the planes no longer fit the caches beside the matrix that is most of the
-// time (8192 x 508 tiles, r = 32: 116 us; with 32-column fragments of 256 bytes per plane 90; lines written whole 84), and
-// narrower rows pay for an item more per row (16384 x 132, r = 49: 78 -> 95 us; 4096 x 252, r = 49: 25 both ways).  r R Cc = 3.3e7:
-// 4096 x 508, r = 16: 30 -> 24, 4096 x 1004, r = 8: 34 both ways; below, 1024 x 1004, r = 16: 12.6 -> 13.1.
-bool encode_line_starts(int R, int Cc, int r) { return Cc % 8 && Cc > 192 && (double)r * R * Cc >= 3.2e7; }
+// beginning write two incomplete lines per plane.  Items that follow the planes (flat_pays) write whole ones in the grouped layout; a weight's
+// plane-major planes and rows behind a row map get items that begin where the lines do, once the planes no longer fit the caches beside the
+// matrix.  us, weights in items of a row / from a cache line on: 8192 x 508 tiles, r = 32 144 / 96, 4096 x 508, r = 16 32 / 25, r = 49 74 / 59; where the planes
+// are that large only just 4096 x 1004, r = 8 34 both ways, 4096 x 252, r = 49 25 / 24; below, 1024 x 1004, r = 16 12.6 both ways.  Ragged forward of 64
+// images of 197 rows, 508 columns, r = 32 73 / 66, of 256, 252 columns, r = 16 72 / 76.  Narrower rows pay for an item more per row (16384 x 132, r = 49,
+// grouped 78 / 95).
+static bool line_starts(int R, int Cc, int r) { return Cc % 8 && Cc > 192 && (double)r * R * Cc >= 3.2e7; }
+
+// Several rows to an item: up to 1024 tile rows every CU has at most one block of four items of a single row, and fuller items only make the longest one longer:
+// 512 x 15 tiles, r = 64, 4.3 us in items of a row, 5.3 in items of four; 1024 x 15, r = 49, 8 % behind, 1152 x 15 7 % ahead, 1152 x 23,
+// r = 64, 14 %, 4096 x 15, r = 64, 10.1 / 7.2; at r <= 16 all the same up to 2048.
+EncodeItems encode_items_of(int R, int Cc, int r, int pg, bool plain_rows)
+{
+    if (R > 1024 && narrow_log2(1, Cc, plain_rows)) return EncodeItems::several_rows;
+    if (plain_rows && flat_pays(R, Cc, pg, row_items(R, Cc))) return EncodeItems::flat;
+    return line_starts(R, Cc, r) ? EncodeItems::line_starts : EncodeItems::row;
+}
 
 // Two encodes in one launch, blockIdx.y picks the matrix: for matrices of a few microseconds, where half of each launch is its beginning
 // and its end.  The pair of 96 x (50 x 16) tiles, r = 32: 6.3 + 5.6 us and 1.2 for a transposed basis of the second -> 12.3, 6.9 in items of several tile rows.
@@ -128,9 +140,11 @@ static hipError_t launch_encode_sides(const TileSide *t, int n, int r, int pg, h
     return hipGetLastError();
 }
 
+// One form of items serves both matrices: one this large, which takes 1.3 to 1.6 times as long in items of a row as in items that follow the planes
+// (flat_pays), stays apart from any other.
 bool encode_pair_eligible(int dtype, const TileSide *s, int r)
 {
-    return dtype == 1 && s[0].Cc >= 8 && s[1].Cc >= 8 && !encode_line_starts(s[0].R, s[0].Cc, r) && !encode_line_starts(s[1].R, s[1].Cc, r);
+    return dtype == 1 && s[0].Cc >= 8 && s[1].Cc >= 8 && !line_starts(s[0].R, s[0].Cc, r) && !line_starts(s[1].R, s[1].Cc, r);
 }
 
 hipError_t launch_encode_pair(const TileSide *t, int r, int pg, hipStream_t st) { return launch_encode_sides(t, 2, r, pg, st); }
@@ -181,22 +195,18 @@ hipError_t launch_encode_outer_lines(const void *A, const void *E, void *P, cons
     return hipGetLastError();
 }
 
-// Up to 1024 tile rows every CU has at most one block of four items of a single row, and fuller items only make the longest one longer:
-// 512 x 15 tiles, r = 64, 4.3 us in items of a row, 5.3 in items of four; 1024 x 15, r = 49, 8 % behind, 1152 x 15 7 % ahead, 1152 x 23,
-// r = 64, 14 %, 4096 x 15, r = 64, 10.1 / 7.2; at r <= 16 all the same up to 2048.
-bool encode_narrow(int R, int Cc, bool plain_rows) { return R > 1024 && narrow_log2(1, Cc, plain_rows); }
-
 // the encode alone through the same kernel (bf16, Cc >= 8): grid-stride over (tile row, 64-tile chunk) items
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm)
 {
     if (pg <= 0) pg = R;
     R = rm.count(R);
     if (R <= 0) return hipSuccess;
-    if (encode_narrow(R, Cc, rm.Mt == 0) || (rm.Mt == 0 && flat_pays(R, Cc, pg, row_items(R, Cc)))) {
+    const EncodeItems form = encode_items_of(R, Cc, r, pg, rm.Mt == 0);
+    if (form == EncodeItems::several_rows || form == EncodeItems::flat) {
         const TileSide one{P, E, A, R, Cc, false, nullptr, nullptr};
         return launch_encode_sides(&one, 1, r, pg, s);
     }
-    const bool any = Cc % 8 != 0, starts = encode_line_starts(R, Cc, r);
+    const bool any = Cc % 8 != 0, starts = form == EncodeItems::line_starts;
     const int chunks = starts ? (Cc + 126) / 64 : (Cc + 63) / 64;
     const long items = (long)R * chunks;
     long blocks = (items + 3) / 4;

@@ -97,13 +97,14 @@ inline bool flat_form(int R, int Cc, int pg) { return pg == 64 && Cc > 32 && Cc 
 // Whether that pays in a launch that has `items` of the first kind in all, other than the encode with a basis gradient.  An item that follows the
 // planes costs two divisions more before its first load, and a launch of half a round of items or less takes the 5 us of its start either
 // way.  Beyond that the planes' rows of 64 elements are whole cache lines if Cc is no multiple of 8 (2997 x 133 tiles, r = 64: encode
-// 15.9 -> 13.1 us, decode 22.7 -> 15.4, with its basis gradient 31.5 -> 23.6; two such decodes 44.9 -> 32.3), and if it is there only are fewer
-// items, which has to be felt: 3200 x 200, r = 32, 7/9 of them, decode 13.9 -> 11.6, but 2048 x 1000, 1/50 less, encode 35.6 -> 37.6.
+// 15.7 -> 12.7 us, decode 23.1 -> 15.3, with its basis gradient 31.5 -> 23.6; two such decodes 44.9 -> 32.3; large encodes, in items of a row / from a
+// cache line on / this: 8192 x 508, r = 32 118 / 84 / 78, 16384 x 196, r = 32 94 / 85 / 65, 4096 x 252, r = 64 in the second and third 28.2 / 27.3, 4096 x 508,
+// r = 64 71.6 / 71.5, 65536 x 201, r = 8 155 / 145 / 115; over 18 shapes of that size 1.00 to 1.30 times as fast as the second), and if it is there
+// only are fewer items, which has to be felt: 3200 x 200, r = 32, 7/9 of them, decode 13.8 -> 11.5, but 2048 x 1000, 1/50 less, encode 35.6 -> 37.6.
 inline bool flat_pays(int R, int Cc, int pg, long items)
 {
     return flat_form(R, Cc, pg) && (Cc % 8 ? items > 2048 : items > 4096 && 8 * flat_items(R, Cc) <= 7 * row_items(R, Cc));
 }
-bool encode_narrow(int R, int Cc, bool plain_rows);      // whether an encode alone does
 hipError_t launch_decode_outer(int dtype, const void *P, const void *Dm, void *Cmat, const void *V, float *G, float *part, int R,
                                int Cc, int r, int accumulate, int pg, hipStream_t s, RowMap rm = RowMap(), bool final_sum = true);
 // the same from fp32 planes into a bf16 matrix (plane-major, Cc >= 8); W or G may be NULL
@@ -160,7 +161,9 @@ hipError_t launch_transpose_basis(int dtype, const void *E, void *Et, int r, hip
 hipError_t launch_transpose_basis_grad(const float *Gt, float *G, int r, int accumulate, hipStream_t s);
 
 // bf16 encode with whole-line plane stores (Cc >= 8); launch_encode picks it
-bool encode_line_starts(int R, int Cc, int r);      // whether its items begin on cache lines
+// Its items: 64 columns of a row, of several rows, 64 tiles that follow each other in the planes, 64 columns from a cache line on
+enum class EncodeItems { row, several_rows, flat, line_starts };
+EncodeItems encode_items_of(int R, int Cc, int r, int pg, bool plain_rows);
 hipError_t launch_encode_lines(const void *A, const void *E, void *P, int R, int Cc, int r, int pg, hipStream_t s, RowMap rm);
 
 // out[i] = bf16(in[i]), round to nearest even

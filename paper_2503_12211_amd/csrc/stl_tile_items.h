@@ -44,7 +44,7 @@ __device__ __forceinline__ FlatRun flat_run(long item, int t, int R, int Cc, int
 // launch; one pass over a row's planes whatever the width: with one thread per tile and a separate scalar sum, dYhat + dD of
 // 512 x 250 tiles, r = 32, took 10 + 285 us, now 8; dYhat + dD of 4800 x 50 tiles 13 + 577 us, now 14.
 // SHIFT (with ANY, without OUTER): an item's 64 tile columns begin where the plane rows' cache lines do, up to 63 columns to the
-// left of its multiple of 64; `chunks` then counts (Cc + 126) / 64 items per row (see encode_line_starts).
+// left of its multiple of 64; `chunks` then counts (Cc + 126) / 64 items per row (see line_starts).
 // turned: the basis is meant for the transposes of the tiles (entry 4a + b is applied to entry 4b + a); the basis gradient is that
 // of the tiles as they lie.
 // NARROW (no row map): an item is 64 >> lw tile rows of 1 << lw columns each, lw >= 3, and lay the planes' layout; `chunks` items to a row

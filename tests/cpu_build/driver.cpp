@@ -6,8 +6,7 @@
 //   paired:...:...  (two products as in route: whether they run as one launch)
 //   stages:M:N:r   (tile counts: encode, decode)   tiles:decode:R:Cc:r   (prints whether those go one tile per thread)
 //   ring:encode:M:N:r   (tile counts: prints the LDS stages of the block-resident forward)
-//   narrow:R:Cc   (prints whether a bf16 encode of R x Cc tiles runs in items of several tile rows)
-//   lines:R:Cc:r   (prints whether a bf16 encode starts its items on cache lines)
+//   items:R:Cc:r:pg:plain   (prints what the items of a bf16 encode are: 64 columns of a row, of several rows, 64 tiles in the planes' order, 64 columns from a cache line on)
 //   device:N   (the device that is current for the following cases)
 //   plant   (a planted mistake -- an output buffer 32 bytes short -- that the sanitizer must report)
 // A leading "f32," selects fp32 storage (default bf16).
@@ -78,10 +77,9 @@ int main(int argc, char **argv)
             printf("  route %d\n", (int)stl::tile_per_thread(dt == STL_BF16 ? 1 : 0, v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
         } else if (op == "ring") {
             printf("  route %d\n", stl::block_forward_ring(v[0] != 0, (int)v[1], (int)v[2], (int)v[3]));
-        } else if (op == "narrow") {
-            printf("  route %d\n", (int)stl::encode_narrow((int)v[0], (int)v[1], true));
-        } else if (op == "lines") {
-            printf("  route %d\n", (int)stl::encode_line_starts((int)v[0], (int)v[1], (int)v[2]));
+        } else if (op == "items") {
+            const char *items[] = {"row", "several_rows", "flat", "line_starts"};
+            printf("  route %s\n", items[(int)stl::encode_items_of((int)v[0], (int)v[1], (int)v[2], (int)v[3], v[4] != 0)]);
         } else if (op == "stages") {
             const long m = 4 * v[0], n = 4 * v[1];
             const int r = (int)v[2];

@@ -56,17 +56,31 @@ def test_large_fp32_tile_maps_addresses(checker):  # noqa: F811
             "stages:8740:15:3", "f32,ragged:2800:197:32:36:5", "f32,ewb:520:4096:9")
 
 
-def test_wide_bf16_encodes_of_odd_widths_write_whole_lines(checker):  # noqa: F811
-    cases = {"lines:8192:508:32": 1, "lines:4096:1001:49": 1, "lines:8192:512:32": 0, "lines:16384:132:49": 0, "lines:1024:1004:16": 0}
-    _, text = checker(*cases)
-    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
-    checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "ragged:52:197:1000:32:64")
+def items(run, cases):
+    """What the items of these encodes are: tile rows, tile columns, planes, rows of a group (activations 64, a weight all its rows),
+    whether no row map lies between."""
+    _, text = run(*("items:" + ":".join(map(str, c)) for c in cases))
+    return [ln.split()[1] for ln in text.splitlines() if ln.startswith("  route")]
+
+
+def test_items_of_bf16_encodes(checker):  # noqa: F811
+    cases = {  # activations follow the planes where there are enough items, or few enough of them
+             (8192, 508, 32, PG, 1): "flat", (4096, 1001, 49, PG, 1): "flat", (16384, 132, 49, PG, 1): "flat", (1024, 1004, 16, PG, 1): "flat",
+             (3200, 200, 32, PG, 1): "flat", (2048, 1000, 32, PG, 1): "row", (8192, 512, 32, PG, 1): "row", (2049, 33, 8, PG, 1): "flat",
+             (2048, 33, 8, PG, 1): "row",
+             # a weight, and rows behind a row map: large planes of odd widths from a cache line on
+             (8192, 508, 32, 8192, 1): "line_starts", (2001, 255, 64, 2001, 1): "line_starts", (8192, 508, 32, PG, 0): "line_starts",
+             (2600, 250, 64, PG, 0): "line_starts", (8192, 512, 32, 8192, 1): "row", (16384, 132, 49, 16384, 1): "row", (1024, 1004, 16, 1024, 1): "row",
+             # a weight of 64 tile rows is one group
+             (64, 2100, 8, 64, 1): "flat", (63, 2100, 8, 63, 1): "row"}
+    assert items(checker, cases) == list(cases.values())
+    checker("stages:3401:193:49", "stages:2620:250:49", "stages:4001:252:33", "stages:1000:1001:32", "stages:527:2044:32", "stages:64:2100:8",
+            "ragged:52:197:1000:32:64")
 
 
 def test_encodes_of_few_narrow_rows_keep_items_of_a_row(checker):  # noqa: F811
-    cases = {"narrow:1024:15": 0, "narrow:1025:15": 1, "narrow:16:9": 0, "narrow:4096:32": 1, "narrow:4096:33": 0, "narrow:4096:7": 0}
-    _, text = checker(*cases)
-    assert [int(ln.split()[1]) for ln in text.splitlines() if ln.startswith("  route")] == list(cases.values())
+    cases = {(1024, 15): "row", (1025, 15): "several_rows", (16, 9): "row", (4096, 32): "several_rows", (4096, 33): "flat", (4096, 7): "row"}
+    assert items(checker, [(R, Cc, 16, PG, 1) for R, Cc in cases]) == list(cases.values())
     checker("stages:1024:9:49", "stages:1025:9:49", "stages:1027:31:17", "stages:1600:15:64", "stages:1030:16:33")
 
 
