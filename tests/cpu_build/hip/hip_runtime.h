@@ -94,7 +94,6 @@ inline float __uint_as_float(uint32_t u) { float f; memcpy(&f, &u, 4); return f;
 #define __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, x, y, z) (c)
-#define __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, x, y, z) (c)
 #define __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, x, y, z) (c)
 typedef short cpu_v4i16 __attribute__((ext_vector_type(4)));
 #define __builtin_amdgcn_ds_read_tr16_b64_v4i16(p) (cpu_v4i16{0, 0, 0, 0})

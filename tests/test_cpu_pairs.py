@@ -2,7 +2,7 @@
 from test_cpu_address_check import checker, pytestmark  # noqa: F401
 from test_cpu_routes import aa_descs, desc, routes
 
-from test_gpu_pairs import AA_SHAPES, SHAPES
+from test_gpu_pairs import AA_SHAPES, AA_SHARED, SHAPES, SHARED
 
 
 def paired(run, cases):
@@ -23,6 +23,15 @@ def test_what_runs_together(checker):  # noqa: F811
     apart = [("bf16", 2048, 513, 513, 32), ("bf16", 512, 192, 250, 32), ("bf16", 40, 6, 40, 8), ("f32", 512, 512, 512, 32)]
     assert paired(checker, [name(dt, desc("dWhat", *s), desc("dXhat", *s)) for dt, *s in apart]) == [0, 1, 0, 0]
     assert paired(checker, [name("bf16", desc("dWhat", 512, 192, 250, 32), desc("dXhat", 512, 192, 256, 32))]) == [0]
+
+
+def test_contractions_that_groups_share(checker):  # noqa: F811
+    """Of the products that run together, those that would be added up in another order by themselves."""
+    def shared(descs):
+        return any(path == "staged" and block.split(":")[1:] not in (["0"], ["1"]) for path, block in routes(checker, descs))
+    layers = {s for s, together in SHAPES.items() if together and s[0] == "bf16" and shared([desc(f, *s[1:]) for f in ("dWhat", "dXhat")])}
+    assert layers == SHARED
+    assert {s for s, together in AA_SHAPES.items() if together and shared(aa_descs(*s)[1:])} == AA_SHARED
 
 
 def test_edges_of_the_blocks(checker):  # noqa: F811

@@ -138,9 +138,12 @@ def test_gpu_shapes_reach_every_kernel_form_and_block(checker):  # noqa: F811
 
 
 def test_gpu_shapes_reach_every_group_of_wavefronts(checker):  # noqa: F811
-    """64 x 64 blocks staged through registers: one stage, one group, two and four, for every operand form."""
+    """64 x 64 blocks staged through registers: one stage, one group, two and four, for every operand form.  Two gradients of a layer may run as one
+    launch, of one group: these shapes are also run one gradient at a time."""
     from test_gpu_any_width import SHAPES as ANY
+    from test_gpu_pairs import ALONE
     from test_gpu_staged import SHAPES as STAGED, STACKED
+    assert set(ANY + SHAPES + STAGED) <= set(ALONE)
     got = _covered(checker, [desc(f, *s) for s in ANY + SHAPES + STAGED for f in FORMS] + [d for s in AA_SHAPES + STACKED for d in aa_descs(*s)])
     got = {k[:3] + (k[5],) for k in got if k[4] == "staged" and ":" in k[5]}
     want = {form + (f"64x64:{g}",) for form in ((0, 1, 0), (0, 0, 0), (1, 1, 0), (1, 1, 1), (1, 1, 2)) for g in (0, 1, 2, 4)}

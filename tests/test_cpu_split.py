@@ -2,7 +2,7 @@
 from test_cpu_address_check import checker, pytestmark  # noqa: F401
 from test_cpu_routes import FORMS, desc, routes
 
-from test_gpu_split import SHAPES
+from test_gpu_split import FEW, SHAPES
 
 
 def split(run, descs):
@@ -16,6 +16,9 @@ def test_parts_of_the_last_round(checker):  # noqa: F811
         assert tuple(split(checker, descs)) == want, s
         for parts, (path, block) in zip(want, routes(checker, descs)):
             assert parts == "whole" or (path in ("wide", "pipe") and block == "256x256"), s
+        # the same planes a few at a time are not cut, and stay with the kernels that add up in that order
+        few = [desc(f, *s[:3], n) for f, parts in zip(FORMS, want) if parts != "whole" for n in {FEW, s[3] % FEW or FEW}]
+        assert set(split(checker, few)) == {"whole"} and {path for path, _ in routes(checker, few)} <= {"wide", "pipe"}, s
     # whole rounds, less than one, a last one that is nearly full, contractions without whole lines, stacked problems: as they are
     stacked = list(desc("Yhat", 640, 64, 264, 64))
     stacked[-1] = 2

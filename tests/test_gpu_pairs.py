@@ -1,12 +1,16 @@
 """Gradients whose two plane products run as one launch, at sizes where one product has a single block, a single stage or an incomplete one,
-or many more blocks than the other: against the oracle, and against calls that ask for one gradient at a time and so launch them apart.
-test_cpu_pairs.py asserts which run together.
+or many more blocks than the other: against the oracle, and against calls that ask for one gradient at a time and so launch them apart,
+bit for bit unless groups of wavefronts share a contraction there.  test_cpu_pairs.py asserts which run together, and which those are.
 
 Bars: gpu_util.check (see test_gpu_any_width.py)."""
 import numpy as np
 import pytest
 
 import stl_synth
+import test_gpu_any_width
+import test_gpu_blocks
+import test_gpu_split
+import test_gpu_staged
 from oracle import planes
 
 pytestmark = pytest.mark.gpu
@@ -25,10 +29,13 @@ SHAPES = {("bf16", 9, 10, 11, 3): True, ("bf16", 64, 61, 63, 8): True, ("bf16", 
           ("bf16", 8, 1024, 264, 40): True, ("bf16", 1024, 1024, 1024, 32): False,
           ("f32", 1, 1, 1, 1): True, ("f32", 33, 31, 65, 7): True, ("f32", 64, 64, 64, 49): True, ("f32", 5, 130, 70, 16): True,
           ("f32", 100, 16, 30, 64): True}
+# those of which a product's contraction is shared by groups of wavefronts where it runs by itself: sums in another order
+SHARED = {("bf16", 704, 67, 70, 3)}
 # nbatch, M, K, N, r, second operand stored transposed -> whether dAhat and dBhat do
 AA_SHAPES = {(3, 9, 11, 13, 4, False): True, (3, 9, 11, 13, 4, True): True, (8, 50, 16, 50, 32, True): True, (8, 50, 50, 16, 32, False): True,
              (5, 70, 33, 66, 8, True): True, (5, 70, 66, 33, 8, False): True, (17, 100, 70, 20, 32, False): False,
              (2, 704, 67, 66, 3, False): True, (2, 705, 67, 66, 3, False): False, (1, 70, 66, 705, 5, True): False}
+AA_SHARED = {(2, 704, 67, 66, 3, False)}
 
 
 @pytest.fixture(scope="module")
@@ -48,6 +55,15 @@ def test_layer(gu, dtype, M, K, N, r):
     acc = gu.backward(p, dtype, accumulate=1, init=init)
     # one rounding of (1 + gradient) on top of the same sums
     assert np.abs(acc["dWhat"] - 1.0 - got["dWhat"]).max() <= 2.0 ** -22 * max(1.0, np.abs(got["dWhat"]).max())
+    if (dtype, M, K, N, r) in SHARED:
+        return
+    # the same planes, dWhat without dXhat and dXhat without dWhat
+    saved = {"xhat": got["Xhat"], "yhat": got["Yhat"]}
+    alone = gu.backward(p, dtype, skip=("dWhat",), **saved)
+    assert all(np.array_equal(alone[name], got[name]) for name in ("dX", "dE_X"))
+    for kw in ({}, {"accumulate": 1, "init": init}):
+        both, alone = (gu.backward(p, dtype, skip=skip, **saved, **kw)["dWhat"] for skip in ((), ("dX", "dE_X")))
+        assert np.array_equal(both, alone)
 
 
 @pytest.mark.parametrize("nb,M,K,N,r,bt", AA_SHAPES)
@@ -84,19 +100,18 @@ def test_pair_of_activations(gu, nb, M, K, N, r, bt):
     both, only_a, only_b = backward(True, True), backward(True, False), backward(False, True)
     for name, other in (("dA", only_a), ("dE_A", only_a), ("dB", only_b), ("dE_B", only_b)):
         x, y = both[name].double(), other[name].double()
-        # the same products, whose sums may be added up in another order (and turn a rounding over here and there)
+        # basis gradients are added up in another order; so are the products if groups share a contraction (a rounding is turned over here and there)
         assert ((x - y).norm() / y.norm()).item() <= 1e-3, name
+        assert name.startswith("dE") or (nb, M, K, N, r, bt) in AA_SHARED or torch.equal(x, y), name
 
 
-def _apart():
-    import test_gpu_blocks
-    import test_gpu_split
-    return list(test_gpu_blocks.SHAPES) + list(test_gpu_split.SHAPES)
+ALONE = [*test_gpu_blocks.SHAPES, *test_gpu_split.SHAPES, *test_gpu_staged.SHAPES, *test_gpu_any_width.SHAPES]
 
 
-@pytest.mark.parametrize("M,K,N,r", _apart())
+@pytest.mark.parametrize("M,K,N,r", ALONE)
 def test_gradients_on_their_own(gu, M, K, N, r):
-    """The products of a call that asks for one gradient, over the shapes that reach every block and every last round in parts."""
+    """The products of a call that asks for one gradient, over the shapes that reach every block, every last round in parts and every group of
+    wavefronts."""
     p = stl_synth.stl_problem(4 * M, 4 * K, 4 * N, r, seed=2100 + M + K + N + r, dtype="bf16", with_dC=True)
     ref = dict(zip(NAMES, planes.backward(p["X"], p["What"], p["E_X"], p["D"], p["dC"])))
     gu.check(gu.backward(p, "bf16", skip=("dWhat", "dE_X", "dD"))["dX"], ref["dX"], "bf16", "dX")

@@ -1,6 +1,7 @@
 """The single-launch forward on 16 x 16 tiles: incomplete blocks in both directions, contractions of fewer steps than are in flight, of
 exactly as many and of more, ending in half a step, ranks on either side of 8, 16 and 32 planes and of the four- and eight-plane groups of
-its decodes; what it rounds equals three launches bit for bit, on either side of the automatic choice's lines.
+its decodes; what it does not round equals the 32 x 32 blocks bit for bit (the decode-in-epilogue variant runs them, on the same rounded
+Xhat), what it rounds three launches, on either side of the automatic choice's lines.
 
 Bars: gpu_util.check (see test_gpu_any_width.py)."""
 import numpy as np
@@ -31,6 +32,8 @@ def test_fused(gu, M, K, N, r):
     got, yhat = gu.forward(p, "bf16", flags=stl.STL_FLAG_FUSED, save_yhat=True)
     assert gu.rel(got, C) <= gu.TOL["bf16"] and gu.rel(yhat, Y) <= gu.TOL["bf16"]
     assert np.array_equal(gu.forward(p, "bf16", flags=stl.STL_FLAG_FUSED), got)
+    blocks = gu.forward(p, "bf16", flags=stl.STL_FLAG_EPILOGUE, save_yhat=True)
+    assert np.array_equal(got, blocks[0]) and np.array_equal(yhat, blocks[1])
     out = gu.forward(p, "bf16", flags=stl.STL_FLAG_FUSED | stl.STL_FLAG_GELU)
     assert gu.rel(out, planes.gelu(C)) <= gu.TOL["bf16"]
 
