@@ -113,7 +113,9 @@ FwdWs fwd_layout(const Dims &d, int variant)
 // storage type in between.  The first is taken
 //  - wherever every CU has at most one block of 32 x 32 tiles and the contraction is short: us, single launch / three: 256 such blocks, r <= 8
 //    9.4 / 13 at K = 128, r <= 16 10.9 / 13 at 112, r <= 32 9.6 / 15 at 32; fewer blocks less (stl_fused_small.hip);
-//  - but at more than 24 planes not for fewer than 64 blocks where it also writes Yhat;
+//  - but at more than 24 planes not for fewer than 64 blocks where it also writes Yhat: such calls have the rounding that they always had, and of the
+//    two forms of the single launch the one that rounds takes no longer: us, rounded / unrounded / three launches, with Yhat_save, r = 32, K = 48, 4 / 16 / 32
+//    blocks 5.7 / 6.0 / 10.9, 5.9 / 6.3 / 11.3, 6.4 / 6.8 / 11.9, K = 32, 16 blocks 5.3 / 5.6 / 10.7; of up to 32 tile rows see below;
 //  - up to about four million tile products per plane set whatever the contraction (m = 32, k = 2048, n = 512, r = 8 8.5 / 11); few rows and
 //    a contraction of thousands of tile columns take longer than three launches would, but such calls keep the unrounded result they have always
 //    had, and STL_FLAG_UNFUSED is there for the other;

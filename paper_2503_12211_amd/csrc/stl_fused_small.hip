@@ -14,9 +14,9 @@
 // row of a tile: from fp32 (16x16x4, as the other single-launch form bit for bit), or rounded to bf16 first, which is what three
 // launches do, bit for bit.
 //
-// us, 32 x 32 blocks / this / three launches: 128 x 512 -> 512, r = 8 8.8 / 5.4 / 10.9 (what a host takes to enqueue one launch, or three);
-// 1024 x 512 -> 1024, r = 8 9.1 / 6.0 / 11.1, r = 32 16.4 / 8.7 / 14.8; 256 x 2048 -> 512, r = 8 24.9 / 8.4 / 13.0;
-// 1024 x 1024 -> 1024, r = 16 18.2 / 9.8 / 13.6, r = 32 32.0 / 15.0 / 16.2.
+// us a call among others, 32 x 32 blocks / this / three launches: 128 x 512 -> 512, r = 8 8.8 / 5.2 / 11.4 (replayed from a graph, without what a host
+// takes to enqueue a launch, 9.1 / 4.5 / 10.5); 1024 x 512 -> 1024, r = 8 9.1 / 5.3 / 11.5, r = 32 16.4 / 9.1 / 15.1; 256 x 2048 -> 512, r = 8 24.8 / 8.4 /
+// 12.9; 1024 x 1024 -> 1024, r = 16 17.2 / 8.7 / 13.7, r = 32 25.4 / 13.8 / 17.1 (13.1 rounded: one product decodes what takes eight of fp32).
 #include "stl_gemm_pipe.h"
 
 namespace stl {

@@ -545,8 +545,8 @@ struct BlockRing {
             }
         }
     }
-    // Block (i0, j0) of plane p of problem pb, whose first loads are in flight: all its stages, next() (the loads of what follows) and its
-    // stores.  One function with its accumulators: in two, the compiler moves them from register to register in every stage (64 x 64
+    // Block (i0, j0) of plane p of problem pb, whose first loads are in flight: all its stages (as in gemm_pipe_kernel), next() (the loads of what
+    // follows) and its stores.  One function with its accumulators: in two, the compiler moves them from register to register in every stage (64 x 64
     // blocks up to 10 % slower).
     template <class F>
     __device__ __forceinline__ void block(const Products<TO> &g, int nks, const char *smem, uint32_t smem_lds, char *slab, int pb, int p, int i0, int j0,

@@ -159,8 +159,10 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_pipe_kernel(const 
     }
 }
 
-// The same for 256 x 256 blocks, of which those of a last round that is not full are dealt to all workgroups in parts (see pipe_split).  (A
-// kernel of its own: with its blocks in BlockRing the one above has a few scalar instructions more per stage, 1 % of a small layer.)
+// The same for 256 x 256 blocks, of which those of a last round that is not full are dealt to all workgroups in parts (see pipe_split).  A
+// kernel of its own: with its blocks in BlockRing the one above has a few scalar instructions more per stage, 1 % of a small layer.  So the
+// stages of a block, their waits and their order, are written down there, in BlockRing::block and (whole lines) in gemm_pipe_wide_kernel: what is
+// changed in one belongs in all three.
 template <bool A_T, bool B_T, typename TO, bool ACC, bool KTAIL, pipe::Split SPLIT>
 __global__ __launch_bounds__(512) void gemm_pipe_split_kernel(const pipe::Products<TO> g, int tiles_m, int tiles_n, int total)
 {
