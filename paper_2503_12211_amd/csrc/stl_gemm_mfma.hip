@@ -407,9 +407,9 @@ hipError_t launch_plane_gemm_mfma(const GemmDesc &g, const void *A, const void *
 
 // Pairs: a gradient of few blocks is the latency of its chain of stages, and two that read the same planes and write different ones
 // need not wait for each other.  us, two launches / one, r = 32: dWhat and dXhat of 512 x 192 x 250 18.0 / 14.0, of 64 x 128 x 96 8.6 / 5.7, dAhat
-// and dBhat of 96 x (50 x 16 x 50) 14.1 / 11.5; whole backward passes over 228 layers of odd widths 1.16 times as fast in the mean (5 % slower
-// at worst), over 259 pairs of activations 1.15 (4 %).  A block has one group of wavefronts.  Where two groups would share a contraction that is
-// little lost (of up to 7 stages 1.00 to 1.33, of 8 to 11 0.95 to 1.24); one that four would share is a chain longer than all the rest: whole
+// and dBhat of 96 x (50 x 16 x 50) 14.1 / 11.5; whole backward passes over 228 layers of odd widths 1.16 times as fast in the mean, over
+// 259 pairs of activations 1.15.  A block has one group of wavefronts.  Where two groups would share a contraction that is
+// little lost (of up to 7 stages 0.99 to 1.33, of 8 to 11 0.93 to 1.30, 1.07 in the mean of 174); one that four would share is a chain longer than all the rest: whole
 // backward passes of 5886 x 15 x 82, r = 3 59.7 / 104, 7037 x 9 x 69, r = 32 85 / 121, 750 x 12 x 159, r = 3 19.9 / 21.6, 837 x 52 x 126, r = 64
 // 34.8 / 36.6, in the mean of 45 1.2 times as long (at best 1.06 times as fast): such products stay apart.  Where the contraction of
 // one product alone is a single stage, a block has the registers and LDS of two: many blocks of that kind stay apart too (96 x (256 x 256 x 8), 61440
